@@ -1,0 +1,325 @@
+"""The work that users of this library have it do, as cases that can be prepared, run and counted one by one.
+
+Four kinds of pass, all through ``paper_2509_22622_amd.binding``:
+
+``stream``   a video chunk by chunk: rotary + cache write of the chunk, then sink+window attention, layer by layer.  With
+             ``video_chunks`` == 0 one denoising pass over a chunk of a video in steady state (the chunk is staged again
+             and again, as the denoising steps of one chunk do); otherwise a whole video of that many chunks from its
+             first frame on (warm-up, growing window, first evictions).
+``prefill``  KV-recache at a prompt switch: the cache rebuilt from the retained frames under the chunk-causal rule.
+``prompt``   cross-attention of the video tokens over the prompt, with or without the block's output projection; with
+             ``switch`` the layer's prompt keys and values are replaced first.
+``clip``     one training step of a layer: attention of a supervised clip and the gradients of its q, k and v.
+
+Inputs are i.i.d. normal numbers in bfloat16, the recipe of the benchmark; ``q_std`` spreads the attention logits
+(1: logits of standard deviation 1; a trained model's heads are mixed, some flat and some peaky).
+"""
+import math
+
+import torch
+
+from paper_2509_22622_amd import binding as B
+
+WAN = {"heads": 12, "head_dim": 128, "grid_h": 30, "grid_w": 52}      # Wan-1.3B shape: 832 x 480, 1560 tokens per frame
+
+
+def _stream(name, **kw):
+    case = {"name": name, "kind": "stream", "cache": "bf16", "form": "unrotated", "layers": 1, **WAN, "chunk": 3, "sink": 3,
+            "window": 9, "frames": 3, "first_frame": 45, "video_chunks": 0, "sink_relative": False, "q_std": 1.0}
+    return {**case, **kw}
+
+
+def _prefill(name, **kw):
+    case = {"name": name, "kind": "prefill", "cache": "bf16", "layers": 1, **WAN, "chunk": 3, "sink": 3, "window": 9,
+            "win_start": 33, "n_win": 12, "q_std": 1.0}
+    return {**case, **kw}
+
+
+def _prompt(name, **kw):
+    case = {"name": name, "kind": "prompt", "layers": 1, "heads": 12, "head_dim": 128, "queries": 4680, "tokens": 512,
+            "projection": False, "switch": False, "q_std": 1.0}
+    return {**case, **kw}
+
+
+def _clip(name, **kw):
+    case = {"name": name, "kind": "clip", **WAN, "chunk": 3, "sink": 3, "window": 9, "ctx_start": 40, "n_ctx": 9,
+            "clip_frames": 21, "q_std": 1.0}
+    return {**case, **kw}
+
+
+def listed():
+    return [
+        # the tiny configuration of the benchmark: eight chunks from the first frame on; latency and launches
+        _stream("tiny_video", form="two_call", heads=4, head_dim=64, grid_h=6, grid_w=10, window=6, video_chunks=8),
+        # a small preview: ragged frames of 135 tokens, head_dim 64, two layers, a denoising pass
+        _stream("preview_pass", form="two_call", layers=2, heads=6, head_dim=64, grid_h=9, grid_w=15, chunk=2, sink=2,
+                window=6, frames=2, first_frame=31),
+        # quarter resolution (416 x 240): four layers of a denoising pass
+        _stream("quarter_pass", layers=4, grid_h=15, grid_w=26),
+        # frame by frame generation at full resolution: one new frame against sink and window
+        _stream("frame_pass", layers=2, chunk=1, frames=1, first_frame=47, q_std=2.0),
+        # the headline: one denoising pass of a three-frame chunk through all 30 layers
+        _stream("wan_pass", layers=30),
+        # the long-window comparison configuration: no sink, window 21
+        _stream("long_window_pass", form="two_call", sink=0, window=21, first_frame=60),
+        # the 8-bit cache at the Wan shape
+        _stream("wan_pass_fp8", cache="fp8_e4m3", form="two_call", layers=6),
+        # KV-recache of 15 frames at the Wan shape, four layers
+        _prefill("wan_recache", layers=4),
+        # KV-recache of an 8-bit cache with ragged frames and a sink that is no whole chunk
+        _prefill("small_recache_fp8", cache="fp8_e4m3", heads=5, grid_h=13, grid_w=23, sink=2, window=7, win_start=20,
+                 n_win=8),
+        # the cross-attention block of a chunk's pass: attention over a 512-token prompt and the output projection
+        _prompt("chunk_cross_attn", layers=4, projection=True),
+        # a prompt switch during recache: new prompt keys, then the cross-attention of all 15 retained frames
+        _prompt("recache_cross_attn", layers=2, queries=23400, tokens=226, switch=True),
+        # one training step of a layer: a 21-frame clip at the Wan shape, forward and backward
+        _clip("wan_clip"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return min(hi, max(lo, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi + 0.49)))))))
+
+
+DRAW_FLOPS = 3e12           # a drawn case costs at most this (the largest listed one 2e13)
+
+
+def draw(rng):
+    """One more case: any geometry the library takes, from a hundred tokens to the Wan shape."""
+    while True:
+        case = _draw_any(rng)
+        if work(case)["flops"] <= DRAW_FLOPS:
+            return case
+
+
+def _draw_any(rng):
+    kind = rng.choice(["stream", "stream", "stream", "prefill", "prompt", "prompt", "clip"])
+    dims = {"heads": _log_int(rng, 1, 24), "head_dim": rng.choice([64, 128, 128])}
+    q_std = rng.choice([1.0, 1.0, 2.0, 3.0])
+    if kind == "prompt":
+        case = _prompt("", layers=rng.randint(1, 4), queries=_log_int(rng, 60, 23400), tokens=_log_int(rng, 16, 512),
+                       projection=rng.random() < 0.5, switch=rng.random() < 0.3, q_std=q_std, **dims)
+    else:
+        dims.update(grid_h=_log_int(rng, 5, 30), grid_w=_log_int(rng, 8, 52), chunk=rng.randint(1, 4), sink=rng.randint(0, 4))
+        window = rng.randint(3, 21) if kind == "stream" else rng.randint(3, 12)
+        first = dims["sink"] + rng.randint(0, 60)
+        if kind == "stream":
+            fp8 = rng.random() < 0.3
+            form = "two_call" if fp8 else rng.choice(["two_call", "unrotated"])
+            frames = dims["chunk"] if rng.random() < 0.8 else rng.randint(1, dims["chunk"])
+            case = _stream("", cache="fp8_e4m3" if fp8 else "bf16", form=form, layers=rng.randint(1, 4), window=window,
+                           frames=frames, first_frame=first + window, q_std=q_std,
+                           sink_relative=form == "two_call" and not fp8 and rng.random() < 0.2, **dims)
+        elif kind == "prefill":
+            case = _prefill("", cache=rng.choice(["bf16", "bf16", "fp8_e4m3"]), layers=rng.randint(1, 3), window=window,
+                            win_start=first, n_win=rng.randint(max(1, window // 2), window + dims["chunk"]), q_std=q_std, **dims)
+        else:
+            case = _clip("", window=window, ctx_start=first, n_ctx=window, clip_frames=rng.randint(3, 21), q_std=q_std, **dims)
+    del case["name"]
+    return case
+
+
+# ---------------------------------------------------------------------------------------------------------------------
+def _normal(g, shape, std=1.0):
+    x = torch.empty(shape, dtype=torch.bfloat16, device="cuda")
+    return x.normal_(0.0, std, generator=g)
+
+
+def prepare(case, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return _PREPARE[case["kind"]](case, g)
+
+
+def run(state):
+    return _RUN[state["case"]["kind"]](state)
+
+
+def _cache(case):
+    cache = B.Cache(case["layers"], case["heads"], case["head_dim"], case["grid_h"], case["grid_w"], case["chunk"],
+                    case["sink"], case["window"], kv_format=case["cache"])
+    if case.get("sink_relative"):
+        cache.set_sink_relative(True)
+    return cache
+
+
+def _prepare_stream(case, g):
+    cache = _cache(case)
+    hd = (case["heads"], case["head_dim"])
+    P = case["grid_h"] * case["grid_w"]
+    f0, n = case["first_frame"], case["frames"]
+    if not case["video_chunks"]:
+        # what the video so far has left in the cache: the sink and the window before the chunk
+        rows = (case["sink"] + case["window"]) * P
+        scratch = torch.empty((rows, *hd), dtype=torch.bfloat16, device="cuda")
+        for layer in range(case["layers"]):
+            k, v = _normal(g, (rows, *hd)), _normal(g, (rows, *hd))
+            cache.recache_prefill(layer, True, f0 - case["window"], case["window"], k, k, v, scratch)
+    passes = []                     # one entry per (chunk, layer): what the model hands over, and where the result goes
+    starts = [i * case["chunk"] for i in range(case["video_chunks"])] or [f0]
+    for start in starts:
+        for layer in range(case["layers"]):
+            q, k, v = _normal(g, (n * P, *hd), case["q_std"]), _normal(g, (n * P, *hd)), _normal(g, (n * P, *hd))
+            q_out = None
+            if case["form"] == "two_call":
+                q_out = torch.empty(q.shape, dtype=torch.uint8 if case["cache"] != "bf16" else torch.bfloat16, device="cuda")
+            passes.append((layer, start, q, k, v, q_out, torch.empty_like(q)))
+    return {"case": case, "cache": cache, "passes": passes}
+
+
+def _run_stream(state):
+    case, cache = state["case"], state["cache"]
+    n = case["frames"]
+    if case["video_chunks"]:
+        cache.reset()
+    if case["form"] == "two_call":
+        for layer, start, q, k, v, q_out, out in state["passes"]:
+            cache.chunk_append(layer, start, n, q, k, v, q_out)
+            cache.sink_window_attn(layer, q_out, out)
+    else:
+        for layer, start, q, k, v, _, out in state["passes"]:
+            cache.chunk_append(layer, start, n, None, k, v, None)
+            cache.sink_window_attn_unrotated(layer, q, out)
+    return [p[-1] for p in state["passes"]]
+
+
+def _prepare_prefill(case, g):
+    cache = _cache(case)
+    shape = ((case["sink"] + case["n_win"]) * case["grid_h"] * case["grid_w"], case["heads"], case["head_dim"])
+    layers = []
+    for _ in range(case["layers"]):
+        q, k, v = _normal(g, shape, case["q_std"]), _normal(g, shape), _normal(g, shape)
+        layers.append((q, k, v, torch.empty_like(q)))
+    return {"case": case, "cache": cache, "layers": layers}
+
+
+def _run_prefill(state):
+    case, cache = state["case"], state["cache"]
+    for layer, (q, k, v, out) in enumerate(state["layers"]):
+        cache.recache_prefill(layer, True, case["win_start"], case["n_win"], q, k, v, out)
+    return [x[-1] for x in state["layers"]]
+
+
+def _prepare_prompt(case, g):
+    prompt = B.Prompt(case["layers"], case["heads"], case["head_dim"], 512)
+    hd = (case["heads"], case["head_dim"])
+    n = case["heads"] * case["head_dim"]
+    workspace = None
+    if case["projection"]:
+        workspace = torch.empty(prompt.cross_attn_out_workspace_bytes(case["queries"]), dtype=torch.uint8, device="cuda")
+    layers = []
+    for layer in range(case["layers"]):
+        k, v = _normal(g, (case["tokens"], *hd)), _normal(g, (case["tokens"], *hd))
+        q = _normal(g, (case["queries"], *hd), case["q_std"])
+        packed = None
+        if case["projection"]:
+            w = _normal(g, (n, n), n ** -0.5)
+            packed = torch.empty_like(w)
+            prompt.pack_out_weight(w, packed)
+        if not case["switch"]:
+            prompt.recache(layer, k, v)
+        layers.append((k, v, q, packed, torch.empty((case["queries"], n) if case["projection"] else q.shape,
+                                                    dtype=torch.bfloat16, device="cuda")))
+    return {"case": case, "prompt": prompt, "workspace": workspace, "layers": layers}
+
+
+def _run_prompt(state):
+    case, prompt = state["case"], state["prompt"]
+    for layer, (k, v, q, packed, out) in enumerate(state["layers"]):
+        if case["switch"]:
+            prompt.recache(layer, k, v)
+        if packed is not None:
+            prompt.cross_attn_out(layer, q, packed, state["workspace"], out)
+        else:
+            prompt.cross_attn(layer, q, out)
+    return [x[-1] for x in state["layers"]]
+
+
+def _prepare_clip(case, g):
+    P = case["grid_h"] * case["grid_w"]
+    hd = (case["heads"], case["head_dim"])
+    clip = B.Clip(case["heads"], case["head_dim"], case["grid_h"], case["grid_w"], case["chunk"], case["sink"], case["window"],
+                  case["clip_frames"])
+    rows, resident = case["clip_frames"] * P, (case["sink"] + case["n_ctx"] + case["clip_frames"]) * P
+    q, dout = _normal(g, (rows, *hd), case["q_std"]), _normal(g, (rows, *hd))
+    k, v = _normal(g, (resident, *hd)), _normal(g, (resident, *hd))
+    return {"case": case, "clip": clip, "in": (q, k, v, dout), "out": tuple(torch.empty_like(q) for _ in range(4))}
+
+
+def _run_clip(state):
+    case, clip = state["case"], state["clip"]
+    q, k, v, dout = state["in"]
+    out, dq, dk, dv = state["out"]
+    clip.forward(case["ctx_start"], case["n_ctx"], case["clip_frames"], q, k, v, out)
+    clip.backward(dout, dq, dk, dv)
+    return state["out"]
+
+
+_PREPARE = {"stream": _prepare_stream, "prefill": _prepare_prefill, "prompt": _prepare_prompt, "clip": _prepare_clip}
+_RUN = {"stream": _run_stream, "prefill": _run_prefill, "prompt": _run_prompt, "clip": _run_clip}
+
+
+# ---------------------------------------------------------------------------------------------------------------------
+def _live(case, f0, n, oldest=0):
+    """Frames the chunk [f0, f0 + n) attends to, with the non-sink frames before `oldest` gone."""
+    sink, lo = min(case["sink"], f0 + n), max(case["sink"], f0 - case["window"], oldest)
+    return sink + max(0, f0 + n - lo)
+
+
+def _chunks(start, n, size):
+    return [(f, min(size, start + n - f)) for f in range(start, start + n, size)]
+
+
+def work(case):
+    H, D = case["heads"], case["head_dim"]
+    if case["kind"] == "prompt":
+        n, t = case["queries"], case["tokens"]
+        flops, elems = 4 * n * t * D * H, (2 * n + 2 * t) * H * D
+        if case["switch"]:
+            elems += 2 * t * H * D                              # the new keys and values in, besides the layer's own copy
+        if case["projection"]:
+            flops += 2 * n * (H * D) ** 2
+            elems += (H * D) ** 2
+        return {"bytes": 2 * elems * case["layers"], "flops": flops * case["layers"]}
+    P = case["grid_h"] * case["grid_w"]
+    frame = P * H * D                                           # elements of one frame of one tensor
+    pair = 4 * P * P * D * H                                    # flops of one frame of queries over one frame of keys
+    if case["kind"] == "clip":
+        start = case["ctx_start"] + case["n_ctx"]
+        clip, all_pairs, clip_pairs = case["clip_frames"], 0, 0
+        for f0, n in _chunks(start, clip, case["chunk"]):
+            all_pairs += n * _live(case, f0, n, case["ctx_start"])
+            clip_pairs += n * (f0 + n - max(start, f0 - case["window"]))
+        resident = case["sink"] + case["n_ctx"] + clip
+        # forward 2 products; backward the scores again, dP and dQ over all pairs, dK and dV over those of clip keys
+        return {"bytes": 2 * frame * (6 * clip + 2 * resident), "flops": pair * (2.5 * all_pairs + clip_pairs)}
+    kv = 2 if case["cache"] == "bf16" else 1                    # bytes per cached element
+    if case["kind"] == "prefill":
+        n_all, pairs = case["sink"] + case["n_win"], 0
+        for f0, n in _chunks(0, case["sink"], case["chunk"]):
+            pairs += n * _live(case, f0, n)
+        for f0, n in _chunks(case["win_start"], case["n_win"], case["chunk"]):
+            pairs += n * _live(case, f0, n, case["win_start"])
+        return {"bytes": case["layers"] * frame * n_all * (2 * 4 + 2 * kv), "flops": case["layers"] * pair * pairs}
+    n, total_bytes, pairs = case["frames"], 0, 0
+    for f0 in [i * case["chunk"] for i in range(case["video_chunks"])] or [case["first_frame"]]:
+        live = _live(case, f0, n)
+        pairs += n * live
+        # q, k, v in, out out, the chunk's keys and values into the cache, the other live frames read from it
+        total_bytes += frame * (2 * 4 * n + 2 * kv * live)
+    return {"bytes": case["layers"] * total_bytes, "flops": case["layers"] * pair * pairs}
+
+
+def tolerance(case):
+    """Largest difference between two correct implementations, about four times what was measured between the library's
+    own kernel variants (other matrix instruction shapes, other softmax references, scores scaled instead of queries:
+    relative 2-norm up to 5e-3, largest difference up to 5e-2 of max(rms, value)) and against 64-bit arithmetic."""
+    if case["kind"] == "clip":
+        # five bf16 roundings on a gradient's way: 3.8e-3 against 64 bits, 6.2e-3 at q_std 3
+        return {"rel": 1.5e-2, "max": 0.3}
+    if case.get("cache") == "fp8_e4m3":
+        # weights rounded to 3 mantissa bits relative to a running reference, 2.6 % rms each: another reference gives
+        # other roundings, sqrt(2) x 2.6 % = 3.7e-2 apart
+        return {"rel": 5e-2, "max": 0.4}
+    return {"rel": 1.2e-2, "max": 0.2}
