@@ -144,27 +144,32 @@ def _cache(case):
     return cache
 
 
-def _prepare_stream(case, g):
-    cache = _cache(case)
+def _stream_inputs(case, g):
+    """What the video so far left behind, per layer (keys and values of the sink and of the window before the chunk;
+    nothing for a whole video), and what the model hands over: (layer, first frame, q, k, v)."""
     hd = (case["heads"], case["head_dim"])
     P = case["grid_h"] * case["grid_w"]
-    f0, n = case["first_frame"], case["frames"]
+    n = case["frames"]
+    past = []
     if not case["video_chunks"]:
-        # what the video so far has left in the cache: the sink and the window before the chunk
         rows = (case["sink"] + case["window"]) * P
-        scratch = torch.empty((rows, *hd), dtype=torch.bfloat16, device="cuda")
-        for layer in range(case["layers"]):
-            k, v = _normal(g, (rows, *hd)), _normal(g, (rows, *hd))
-            cache.recache_prefill(layer, True, f0 - case["window"], case["window"], k, k, v, scratch)
+        past = [(_normal(g, (rows, *hd)), _normal(g, (rows, *hd))) for _ in range(case["layers"])]
+    starts = [i * case["chunk"] for i in range(case["video_chunks"])] or [case["first_frame"]]
+    return past, [(layer, start, _normal(g, (n * P, *hd), case["q_std"]), _normal(g, (n * P, *hd)), _normal(g, (n * P, *hd)))
+                  for start in starts for layer in range(case["layers"])]
+
+
+def _prepare_stream(case, g):
+    cache = _cache(case)
+    past, given = _stream_inputs(case, g)
+    for layer, (k, v) in enumerate(past):
+        cache.recache_prefill(layer, True, case["first_frame"] - case["window"], case["window"], k, k, v, torch.empty_like(k))
     passes = []                     # one entry per (chunk, layer): what the model hands over, and where the result goes
-    starts = [i * case["chunk"] for i in range(case["video_chunks"])] or [f0]
-    for start in starts:
-        for layer in range(case["layers"]):
-            q, k, v = _normal(g, (n * P, *hd), case["q_std"]), _normal(g, (n * P, *hd)), _normal(g, (n * P, *hd))
-            q_out = None
-            if case["form"] == "two_call":
-                q_out = torch.empty(q.shape, dtype=torch.uint8 if case["cache"] != "bf16" else torch.bfloat16, device="cuda")
-            passes.append((layer, start, q, k, v, q_out, torch.empty_like(q)))
+    for layer, start, q, k, v in given:
+        q_out = None
+        if case["form"] == "two_call":
+            q_out = torch.empty(q.shape, dtype=torch.uint8 if case["cache"] != "bf16" else torch.bfloat16, device="cuda")
+        passes.append((layer, start, q, k, v, q_out, torch.empty_like(q)))
     return {"case": case, "cache": cache, "passes": passes}
 
 
@@ -184,14 +189,14 @@ def _run_stream(state):
     return [p[-1] for p in state["passes"]]
 
 
+def _prefill_inputs(case, g):
+    shape = ((case["sink"] + case["n_win"]) * case["grid_h"] * case["grid_w"], case["heads"], case["head_dim"])
+    return [(_normal(g, shape, case["q_std"]), _normal(g, shape), _normal(g, shape)) for _ in range(case["layers"])]
+
+
 def _prepare_prefill(case, g):
     cache = _cache(case)
-    shape = ((case["sink"] + case["n_win"]) * case["grid_h"] * case["grid_w"], case["heads"], case["head_dim"])
-    layers = []
-    for _ in range(case["layers"]):
-        q, k, v = _normal(g, shape, case["q_std"]), _normal(g, shape), _normal(g, shape)
-        layers.append((q, k, v, torch.empty_like(q)))
-    return {"case": case, "cache": cache, "layers": layers}
+    return {"case": case, "cache": cache, "layers": [(q, k, v, torch.empty_like(q)) for q, k, v in _prefill_inputs(case, g)]}
 
 
 def _run_prefill(state):
@@ -201,26 +206,33 @@ def _run_prefill(state):
     return [x[-1] for x in state["layers"]]
 
 
-def _prepare_prompt(case, g):
-    prompt = B.Prompt(case["layers"], case["heads"], case["head_dim"], 512)
+def _prompt_inputs(case, g):
+    """Per layer the prompt's keys and values, the queries and (or None) the weight of the output projection."""
     hd = (case["heads"], case["head_dim"])
     n = case["heads"] * case["head_dim"]
+    layers = []
+    for _ in range(case["layers"]):
+        k, v = _normal(g, (case["tokens"], *hd)), _normal(g, (case["tokens"], *hd))
+        q = _normal(g, (case["queries"], *hd), case["q_std"])
+        layers.append((k, v, q, _normal(g, (n, n), n ** -0.5) if case["projection"] else None))
+    return layers
+
+
+def _prepare_prompt(case, g):
+    prompt = B.Prompt(case["layers"], case["heads"], case["head_dim"], 512)
     workspace = None
     if case["projection"]:
         workspace = torch.empty(prompt.cross_attn_out_workspace_bytes(case["queries"]), dtype=torch.uint8, device="cuda")
     layers = []
-    for layer in range(case["layers"]):
-        k, v = _normal(g, (case["tokens"], *hd)), _normal(g, (case["tokens"], *hd))
-        q = _normal(g, (case["queries"], *hd), case["q_std"])
+    for layer, (k, v, q, w) in enumerate(_prompt_inputs(case, g)):
         packed = None
-        if case["projection"]:
-            w = _normal(g, (n, n), n ** -0.5)
+        if w is not None:
             packed = torch.empty_like(w)
             prompt.pack_out_weight(w, packed)
         if not case["switch"]:
             prompt.recache(layer, k, v)
-        layers.append((k, v, q, packed, torch.empty((case["queries"], n) if case["projection"] else q.shape,
-                                                    dtype=torch.bfloat16, device="cuda")))
+        out = torch.empty(q.shape if w is None else (case["queries"], w.shape[0]), dtype=torch.bfloat16, device="cuda")
+        layers.append((k, v, q, packed, out))
     return {"case": case, "prompt": prompt, "workspace": workspace, "layers": layers}
 
 
@@ -236,15 +248,20 @@ def _run_prompt(state):
     return [x[-1] for x in state["layers"]]
 
 
-def _prepare_clip(case, g):
+def _clip_inputs(case, g):
+    """(q, k, v, dout): queries and the loss's gradient for the clip, keys and values of sink, context and clip."""
     P = case["grid_h"] * case["grid_w"]
     hd = (case["heads"], case["head_dim"])
-    clip = B.Clip(case["heads"], case["head_dim"], case["grid_h"], case["grid_w"], case["chunk"], case["sink"], case["window"],
-                  case["clip_frames"])
     rows, resident = case["clip_frames"] * P, (case["sink"] + case["n_ctx"] + case["clip_frames"]) * P
     q, dout = _normal(g, (rows, *hd), case["q_std"]), _normal(g, (rows, *hd))
-    k, v = _normal(g, (resident, *hd)), _normal(g, (resident, *hd))
-    return {"case": case, "clip": clip, "in": (q, k, v, dout), "out": tuple(torch.empty_like(q) for _ in range(4))}
+    return q, _normal(g, (resident, *hd)), _normal(g, (resident, *hd)), dout
+
+
+def _prepare_clip(case, g):
+    clip = B.Clip(case["heads"], case["head_dim"], case["grid_h"], case["grid_w"], case["chunk"], case["sink"], case["window"],
+                  case["clip_frames"])
+    given = _clip_inputs(case, g)
+    return {"case": case, "clip": clip, "in": given, "out": tuple(torch.empty_like(given[0]) for _ in range(4))}
 
 
 def _run_clip(state):
@@ -323,3 +340,146 @@ def tolerance(case):
         # other roundings, sqrt(2) x 2.6 % = 3.7e-2 apart
         return {"rel": 5e-2, "max": 0.4}
     return {"rel": 1.2e-2, "max": 0.2}
+
+
+# ---------------------------------------------------------------------------------------------------------------------
+# The same passes written out in 64 bits with plain torch.
+def _pairs(case):
+    """Rotary pairs of the frame, row and column axes."""
+    n = case["head_dim"] // 6
+    return case["head_dim"] // 2 - 2 * n, n, n
+
+
+def _rotate(case, x, frames, back=False):
+    """x [len(frames) * P, H, D] (64 bits) turned by the factorised (frame, row, column) rotary embedding, or turned back."""
+    w, P = case["grid_w"], case["grid_h"] * case["grid_w"]
+    tok = torch.arange(P, device=x.device).repeat(len(frames))
+    pos = (torch.tensor(frames, device=x.device).repeat_interleave(P), tok // w, tok % w)
+    freq = [10000.0 ** (-torch.arange(n, dtype=torch.float64, device=x.device) / n) for n in _pairs(case)]
+    angle = torch.cat([p.double()[:, None] * f for p, f in zip(pos, freq)], 1)[:, None, :]
+    turn = torch.polar(torch.ones_like(angle), -angle if back else angle)
+    return torch.view_as_real(torch.view_as_complex(x.unflatten(-1, (-1, 2)).contiguous()) * turn).flatten(-2)
+
+
+def _weights(q_k, scale):
+    """Softmax over the keys of all (q, k) blocks, one head."""
+    return torch.softmax(torch.cat([q @ k.T for q, k in q_k], 1) * scale, 1)
+
+
+def _attend(q_k, v):
+    """[(q, k), ...] with [rows, H, D] each, and the values of all those keys."""
+    out = torch.empty_like(q_k[0][0])
+    for h in range(v.shape[1]):
+        out[:, h] = _weights([(q[:, h], k[:, h]) for q, k in q_k], v.shape[2] ** -0.5) @ v[:, h]
+    return out
+
+
+def _e4m3(x):
+    return x.clamp(-448, 448).to(torch.float8_e4m3fn).double()
+
+
+def _cached(case, q, k, v):
+    """Turned queries, turned keys and values as the cache's format holds them (8 bits: the queries with their factor)."""
+    if case["cache"] == "bf16":
+        return q, k, v
+    c = math.log2(math.e) * case["head_dim"] ** -0.5
+    return _e4m3(q * c) / c, _e4m3(k), _e4m3(v)
+
+
+def _live_list(case, f0, n, oldest=0):
+    return list(range(min(case["sink"], f0 + n))) + list(range(max(case["sink"], f0 - case["window"], oldest), f0 + n))
+
+
+def _per_frame(case, x, frames):
+    P = case["grid_h"] * case["grid_w"]
+    return {f: x[i * P:(i + 1) * P] for i, f in enumerate(frames)}
+
+
+def _exact_chunk(case, raw_q, f0, n, keys, values, oldest=0):
+    q = _rotate(case, raw_q, range(f0, f0 + n))
+    q, _, _ = _cached(case, q, q, q)
+    live = _live_list(case, f0, n, oldest)
+    parts = [(q, torch.cat([keys[f] for f in live]))]
+    shift = f0 - case["window"] - case["sink"]
+    if case.get("sink_relative") and shift > 0 and case["sink"]:
+        q_sink = _rotate(case, raw_q, range(f0 - shift, f0 - shift + n))
+        parts = [(q_sink, torch.cat([keys[f] for f in live if f < case["sink"]])),
+                 (q, torch.cat([keys[f] for f in live if f >= case["sink"]]))]
+    return _attend(parts, torch.cat([values[f] for f in live]))
+
+
+def _exact_stream(case, g):
+    past, given = _stream_inputs(case, g)
+    keys, values = [{} for _ in range(case["layers"])], [{} for _ in range(case["layers"])]
+
+    def store(layer, frames, k, v):
+        _, k, v = _cached(case, k.double(), _rotate(case, k.double(), frames), v.double())
+        keys[layer].update(_per_frame(case, k, frames))
+        values[layer].update(_per_frame(case, v, frames))
+
+    f0, n = case["first_frame"], case["frames"]
+    for layer, (k, v) in enumerate(past):
+        store(layer, list(range(case["sink"])) + list(range(f0 - case["window"], f0)), k, v)
+    outs = []
+    for layer, start, q, k, v in given:
+        store(layer, list(range(start, start + n)), k, v)
+        outs.append(_exact_chunk(case, q.double(), start, n, keys[layer], values[layer]))
+        if not case["video_chunks"]:
+            keys[layer] = values[layer] = None
+    return outs
+
+
+def _exact_prefill(case, g):
+    sink, start, P = case["sink"], case["win_start"], case["grid_h"] * case["grid_w"]
+    frames = list(range(sink)) + list(range(start, start + case["n_win"]))
+    outs = []
+    for q, k, v in _prefill_inputs(case, g):
+        _, k, v = _cached(case, k.double(), _rotate(case, k.double(), frames), v.double())
+        keys, values = _per_frame(case, k, frames), _per_frame(case, v, frames)
+        out, row = [], 0
+        for f0, n, oldest in [(f, n, 0) for f, n in _chunks(0, sink, case["chunk"])] + \
+                             [(f, n, start) for f, n in _chunks(start, case["n_win"], case["chunk"])]:
+            out.append(_exact_chunk(case, q[row:row + n * P].double(), f0, n, keys, values, oldest))
+            row += n * P
+        outs.append(torch.cat(out))
+    return outs
+
+
+def _exact_prompt(case, g):
+    outs = []
+    for k, v, q, w in _prompt_inputs(case, g):
+        out = _attend([(q.double(), k.double())], v.double())
+        outs.append(out if w is None else out.flatten(1) @ w.double().T)
+    return outs
+
+
+def _exact_clip(case, g):
+    q, k, v, dout = (x.double() for x in _clip_inputs(case, g))
+    sink, P, scale = case["sink"], case["grid_h"] * case["grid_w"], case["head_dim"] ** -0.5
+    ctx, start, clip = case["ctx_start"], case["ctx_start"] + case["n_ctx"], case["clip_frames"]
+    frames = list(range(sink)) + list(range(ctx, start + clip))
+    at = {f: i * P for i, f in enumerate(frames)}
+    q, k = _rotate(case, q, range(start, start + clip)), _rotate(case, k, frames)
+    out, dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.zeros_like(k), torch.zeros_like(v)
+    for f0, n in _chunks(start, clip, case["chunk"]):
+        rows = slice((f0 - start) * P, (f0 - start + n) * P)
+        live = torch.cat([torch.arange(at[f], at[f] + P, device=q.device) for f in _live_list(case, f0, n, ctx)])
+        for h in range(case["heads"]):
+            qh, kh, vh, do = q[rows, h], k[live, h], v[live, h], dout[rows, h]
+            p = _weights([(qh, kh)], scale)
+            out[rows, h] = p @ vh
+            dz = p * (do @ vh.T - (do * out[rows, h]).sum(1, keepdim=True))
+            dq[rows, h] = dz @ kh * scale
+            dk[live, h] += dz.T @ qh * scale
+            dv[live, h] += p.T @ do
+    own = -clip * P
+    return out, _rotate(case, dq, range(start, start + clip), True), _rotate(case, dk, frames, True)[own:], dv[own:]
+
+
+_EXACT = {"stream": _exact_stream, "prefill": _exact_prefill, "prompt": _exact_prompt, "clip": _exact_clip}
+
+
+def exact(case, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return _EXACT[case["kind"]](case, g)
