@@ -501,7 +501,7 @@ def main():
         "pct_of_bf16_mfma_peak": round(100 * tflops / PEAK_BF16_TFLOPS, 2),
         "attn_ms_per_layer": round(attn_ms, 4), "append_ms_per_layer": round(append_ms, 4),
         "append_GBps": round(append_bytes / (append_ms * 1e-3) / 1e9, 1),
-        "roofline": {"bound": "mfma", "kernel": "ll_attn_stream16_kernel<128, false, false, %d>" % (9 if args.two_call_step else 25), "achieved": round(attn_tflops, 2), "peak": PEAK_BF16_TFLOPS,
+        "roofline": {"bound": "mfma", "kernel": "ll_attn_stream16_kernel<128, false, false, %d, 1>" % (9 if args.two_call_step else 25), "achieved": round(attn_tflops, 2), "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(attn_tflops / PEAK_BF16_TFLOPS, 4), "traffic": ATTN_HBM_TRAFFIC_BYTES,
                      "traffic_source": ATTN_HBM_TRAFFIC_SOURCE,
                      "flops_per_launch": fl_layer, "avg_launch_ms": round(attn_ms, 4),

@@ -314,7 +314,6 @@ static bool can_turn_queries(const ll_cache* c, const std::vector<ChunkWork>& wo
 static ll_status build_attn(const ll_cache* c, int layer, const std::vector<ChunkWork>& work, const void* q, void* out,
                             AttnLaunches& L, bool raw_q = false) {
     const int variant = raw_q ? attn_variant_qrope(c->D) : pick_variant(c);
-    const int qt = attn_variant_qtile(variant);
     L.variant = variant;
     L.params.clear();
     for (size_t base = 0; base < work.size(); base += MAX_ATTN_CHUNKS) {
@@ -345,7 +344,6 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
         auto keys = [&](int i) { int64_t t = 0; for (auto& r : work[i].ranges) t += r.end - r.begin; return t; };
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return keys(a) > keys(b); });
         p.inv_freq_t = c->rope.inv_freq_t; p.n_t = c->rope.n_t;
-        int tiles = 0;
         for (int i = 0; i < m; ++i) {
             ChunkWork w = work[order[i]];
             const int64_t shift = sink_shift_of(c, w.f0);
@@ -364,14 +362,13 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
             if (w.ranges.empty() || w.ranges.size() > size_t(MAX_RANGES))
                 return fail(LL_ERR_STATE, "key set has %zu ranges", w.ranges.size());
             AttnChunk& ch = p.chunk[i];
-            ch.q_begin = w.q_begin; ch.q_end = w.q_end; ch.tile_begin = tiles;
+            ch.q_begin = w.q_begin; ch.q_end = w.q_end;
             ch.sink_shift = int(shift);
             ch.t_row = w.t_row;
             ch.n_ranges = int(w.ranges.size());
             for (int r = 0; r < ch.n_ranges; ++r) { ch.rs[r] = int(w.ranges[r].begin); ch.re[r] = int(w.ranges[r].end); }
-            tiles += (w.q_end - w.q_begin + qt - 1) / qt;
         }
-        p.n_chunks = m; p.n_tiles = tiles;
+        p.n_chunks = m;
         L.params.push_back(p);
     }
     return LL_OK;

@@ -255,7 +255,6 @@ ll_status ll_clip_forward(ll_clip* clip, int64_t ctx_start, int n_ctx, int n_cli
     }
     // 3. attention of the clip's chunks, each over its own key set, with the row sums kept for the backward pass
     const int variant = attn_variant_lse(c->D);
-    const int qt = attn_variant_qtile(variant);
     const int n_chunks = (n_clip + c->C - 1) / c->C;
     for (int base = 0; base < n_chunks; base += MAX_ATTN_CHUNKS) {
         AttnParams p{};
@@ -267,19 +266,17 @@ ll_status ll_clip_forward(ll_clip* clip, int64_t ctx_start, int n_ctx, int n_cli
         p.lse = clip_f32(c, c->o_lse); p.lse_stride = c->row_stride;
         p.out32 = clip_f32(c, c->o_o32);
         const int m = std::min(MAX_ATTN_CHUNKS, n_chunks - base);
-        int tiles = 0;
         for (int i = 0; i < m; ++i) {
             const int ci = base + m - 1 - i;                      // longest key sets (the latest chunks) first
             const int64_t f0 = clip_start + int64_t(ci) * c->C;
             const int n = int(std::min<int64_t>(c->C, clip_start + n_clip - f0));
             const std::vector<SlotRange> ranges = clip_key_ranges(c, f0, n);
             AttnChunk& ch = p.chunk[i];
-            ch.q_begin = ci * c->C * c->P; ch.q_end = ch.q_begin + n * c->P; ch.tile_begin = tiles;
+            ch.q_begin = ci * c->C * c->P; ch.q_end = ch.q_begin + n * c->P;
             ch.n_ranges = int(ranges.size());
             for (int r = 0; r < ch.n_ranges; ++r) { ch.rs[r] = int(ranges[r].begin); ch.re[r] = int(ranges[r].end); }
-            tiles += (ch.q_end - ch.q_begin + qt - 1) / qt;
         }
-        p.n_chunks = m; p.n_tiles = tiles;
+        p.n_chunks = m;
         hipError_t e = launch_attn(p, variant, s);
         if (e != hipSuccess) return hip_fail(e, "clip attention kernel launch");
     }

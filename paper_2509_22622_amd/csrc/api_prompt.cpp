@@ -194,10 +194,8 @@ static ll_status cross_attn(const ll_prompt* prompt, int layer, const void* q, i
     p.scale_log2e = float(1.4426950408889634 / std::sqrt(double(prompt->D)));
     p.n_chunks = 1;
     AttnChunk& ch = p.chunk[0];
-    ch.q_begin = 0; ch.q_end = n_q; ch.tile_begin = 0;
+    ch.q_begin = 0; ch.q_end = n_q;
     ch.n_ranges = 1; ch.rs[0] = 0; ch.re[0] = prompt->tokens[layer];
-    const int qt = attn_variant_qtile(variant);
-    p.n_tiles = (n_q + qt - 1) / qt;
     hipError_t e = launch_attn(p, variant, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "cross-attention kernel launch");
     return LL_OK;

@@ -330,19 +330,64 @@ bool attn_variant_applies_scale(int v) {
     return (v >= 1 && v <= kNumSimple) || v == kNumSimple + 3 || v == kNumSimple + 4 || v == first_stream16() + 2 || v == first_stream16() + 3;
 }
 
+// Into how many key groups (as a power of two) the workgroups of a launch deal their tiles' keys.  The chip holds one
+// workgroup per CU.  With whole-key tiles of 256 rows a launch of few rows and heads leaves most of the 256 CUs idle
+// while the others walk all its keys; G groups give G times as many workgroups of 1 / G of the steps each.  What the
+// groups cost is LDS and L2 traffic: a kblock that goes into LDS serves 256 / G rows, so a step takes longer, the more
+// so the more workgroups run.  A step's length relative to one group's, with n workgroups at work, as measured at
+// 4 to 24 heads and 180 to 1560 rows over 2 to 634 kblocks (us per step with one group: 0.56 at head_dim 128, 0.41
+// at 64):  a_G + n / b_G.  At 1170 rows x 183 kblocks x 12 heads x 128: 114 us with one group, 71 with two, 54 with four.
+static int key_groups_log2(const AttnVariant& v, const AttnParams& p) {
+    constexpr int CUS = 256;
+    struct Step { double a, b; };
+    static constexpr Step steps128[4] = {{1.0, 1300}, {1.1, 900}, {1.35, 650}, {0, 1}};
+    static constexpr Step steps64[4] = {{1.0, 1300}, {1.05, 1300}, {1.2, 1500}, {1.6, 800}};
+    int best = 0;
+    double best_cost = 0;
+    for (int lg = 0; lg < 4; ++lg) {
+        if (lg > 0 && v.grouped[lg - 1] == nullptr) continue;
+        const int qtile = v.qtile >> lg;
+        int64_t tiles = 0, work = 0, longest = 0;
+        for (int c = 0; c < p.n_chunks; ++c) {
+            const int64_t t = (p.chunk[c].q_end - p.chunk[c].q_begin + qtile - 1) / qtile * int64_t(p.H);
+            const int64_t len = (p.chunk[c].n_kblocks + (1 << lg) - 1) >> lg;
+            tiles += t;
+            work += t * len;
+            longest = std::max(longest, len);
+        }
+        // equal workgroups run in whole rounds; of unequal ones the last to finish is half a workgroup behind the mean
+        double n_steps = double(longest);
+        if (tiles > CUS) n_steps = p.n_chunks == 1 ? double((tiles + CUS - 1) / CUS) * longest : double(work) / CUS + 0.5 * longest;
+        const Step& s = (v.D == 128 ? steps128 : steps64)[lg];
+        const double cost = n_steps * (s.a + double(std::min<int64_t>(tiles, CUS)) / s.b);
+        if (lg == 0 || cost < best_cost) {
+            best = lg;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+constexpr int GROUPED_LDS_BYTES = 128 * 1024;    // GroupRing: 128 KB / G at most per group; the groups' results fit too
+
 hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     if (!attn_variant_supports(variant, p_in.D, p_in.kblock)) return hipErrorInvalidValue;
     AttnParams p = p_in;
-    const int KB = p.kblock;
     const AttnVariant& v = *ll::variant(variant);
-    const int total = p.n_tiles * p.H;
-    if (total <= 0) return hipSuccess;
+    const int KB = p.kblock;
     for (int c = 0; c < p.n_chunks; ++c) {
         AttnChunk& ch = p.chunk[c];
         ch.n_kblocks = 0;
         for (int r = 0; r < ch.n_ranges; ++r) ch.n_kblocks += (ch.re[r] + KB - 1) / KB - ch.rs[r] / KB;
         if (ch.n_kblocks < 1) return hipErrorInvalidValue;
     }
+    const int log_g = key_groups_log2(v, p), qtile = v.qtile >> log_g;
+    p.n_tiles = 0;
+    for (int c = 0; c < p.n_chunks; ++c) {
+        p.chunk[c].tile_begin = p.n_tiles;
+        p.n_tiles += (p.chunk[c].q_end - p.chunk[c].q_begin + qtile - 1) / qtile;
+    }
+    const int total = p.n_tiles * p.H;
+    if (total <= 0) return hipSuccess;
     int grid = ((total + 7) / 8) * 8;           // the kernels spread their workgroups over the 8 XCDs
     p.n_groups = 0;
     const int groups = p.H * p.n_chunks;
@@ -382,15 +427,17 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         p.n_groups = n;
         grid = 8 * most_tiles;
     }
-    static bool attr_set[64] = {};
+    static bool attr_set[64][4] = {};
     if (variant > 64) return hipErrorInvalidValue;
-    if (!attr_set[variant - 1]) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(v.kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, v.lds_bytes);
+    void (*const kernel)(const AttnParams) = log_g == 0 ? v.kernel : v.grouped[log_g - 1];
+    const int lds_bytes = log_g == 0 ? v.lds_bytes : GROUPED_LDS_BYTES;
+    if (!attr_set[variant - 1][log_g]) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (e != hipSuccess) return e;
-        attr_set[variant - 1] = true;
+        attr_set[variant - 1][log_g] = true;
     }
-    hipLaunchKernelGGL(v.kernel, dim3(grid), dim3(v.threads), v.lds_bytes, s, p);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(v.threads), lds_bytes, s, p);
     return hipGetLastError();
 }
 

@@ -27,6 +27,15 @@
 // weights of query block 0 are needed when the O^T slots begin and those of block 1 half way through them, as the
 // two key halves were in the 32x32x16 form.  Exponentials, packing, row sums, the running maximum, fragment reads,
 // direct-to-LDS loads, waits and barriers sit in the same slots (lds_plan.h: LdsPlan16, RingPlan).
+//
+// A launch of few rows and heads has fewer 256-row tiles than the chip has CUs, and every workgroup of it walks all
+// keys.  Such a launch deals a tile's keys to G = 2, 4 or 8 groups of the workgroup's waves (template parameter G; the rule is
+// key_groups_log2 in attn_kernel.hip): a tile is 256 / G rows, a group of 8 / G waves walks its share through a ring
+// of its own (lds_plan.h: GroupRing), and the groups' results meet in LDS, so no memory outside the workgroup is
+// needed.  What bounds it: with 256 / G rows per kblock the LDS (fragment reads and ring writes, 144, 160 and 192 KB
+// per step at G = 1, 2, 4 and head_dim 128) and, with all CUs at work, L2 (12.5 TB/s at G = 4).  Measured, us: 270 rows x 43 kblocks x
+// 6 heads x 64: 25 -> 10 (G = 8); 1170 x 183 x 12 x 128: 121 -> 57 (G = 4); 1560 x 634 x 12 x 128: 361 -> 231 (G = 2).  One barrier per step with
+// loads three steps ahead instead of one per two steps and one period ahead was slower (head_dim 64, G = 2: 55 against 48).
 #include "kernels.h"
 #include "lds_plan.h"
 
@@ -88,9 +97,10 @@ __device__ __forceinline__ void s16_lds_arrived(u32x4& x) { asm volatile("" : "+
 __device__ __forceinline__ int s16_pick(int v, int n0, int n01, int a0, int a1, int a2) {
     return v < n0 ? a0 : (v < n01 ? a1 : a2);
 }
-__device__ __forceinline__ int s16_next_edge(int v, int n0, int n01, int T) {
+// (`dead`: first step of a share past its last kblock, 0x7FFFFFFF where there is none)
+__device__ __forceinline__ int s16_next_edge(int v, int n0, int n01, int T, int dead) {
     const int cand[6] = {0, n0 - 1, n0, n01 - 1, n01, T - 1};
-    int best = 0x7FFFFFFF;
+    int best = dead > v ? dead : 0x7FFFFFFF;
 #pragma unroll
     for (int c = 0; c < 6; ++c)
         if (cand[c] > v && cand[c] < best) best = cand[c];
@@ -129,9 +139,12 @@ __device__ __forceinline__ unsigned s16_k_load_offset(int lane) {
 // vote, no rescaling), the reference stays at the first kblock's maximum, and the caller must look at the row sums
 // afterwards: a sum beyond S16_FIXED_REF_LIMIT (or not a number) means some score rose far above the reference, and
 // the tile has to be computed again with the reference followed.
-template <int D, bool QSCALE, int SCHED>
+// G: key groups of the workgroup (lds_plan.h: GroupRing).  G == 1: all eight waves walk the chunk's kblocks [vb, ve)
+// through one ring.  G > 1: this wave's group of 8 / G waves walks its own share [vb, ve) through its own ring and runs
+// n_steps >= ve - vb steps, as many as the longest share has (a step past ve has no live key).
+template <int D, bool QSCALE, int SCHED, int G>
 __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk& ch, int head, int q0, int vb, int ve,
-                                            char* lds, S16State<D>& st, const float2* shift_cs) {
+                                            int n_steps, char* lds, S16State<D>& st, const float2* shift_cs) {
     using Plan = LdsPlan16<D, (SCHED & 2) != 0>;
     constexpr bool TRACK = !(SCHED & 8);
     constexpr int KS = Plan::KS;                // K fragments per kblock = S^T slots (two MFMAs each)
@@ -142,16 +155,20 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     constexpr int STAGE_BYTES = 2 * KB_BYTES;   // [K kblock | V kblock]
     constexpr int NS = RingPlan::STAGES;
     constexpr int NF = KS + NV;                 // 1 KB fragments per stage
-    constexpr int NW = 8;                       // waves per workgroup
-    constexpr int LPW = NF / NW;                // direct-to-LDS loads per wave per kblock
+    using GR = GroupRing<D, G>;
+    constexpr int NW = 8 / G;                   // waves that share a ring
+    constexpr int PERIOD = G == 1 ? 2 : GR::PERIOD;             // steps per barrier
+    constexpr int LPW = G == 1 ? NF / NW : PERIOD * NF / NW;    // direct-to-LDS loads per wave, per kblock (per period)
     constexpr int PF = RingPlan::AHEAD;
     constexpr int LAND = RingPlan::LANDED;
-    static_assert(NF % NW == 0, "fragments must split over the waves");
+    static_assert(NF % NW == 0 && (G == 1 || KS % NW == 0), "fragments must split over the waves");
     static_assert(PF >= LAND && PF + 2 <= NS, "ring too short for the prefetch distance");
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave_wg % NW;              // among the waves that share this ring
     const int n = lane & 15, g = lane >> 4;
+    if (G > 1) lds += (wave_wg / NW) * GR::BYTES;
 
     const int n_ranges = ch.n_ranges;
     const int rs0 = ch.rs[0], re0 = ch.re[0];
@@ -165,7 +182,10 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     const int T = (ke0 - kb0) + (ke1 - kb1) + (ke2 - kb2);
     const int n0 = ke0 - kb0, n01 = n0 + (ke1 - kb1);
 #define S16_PHYS_KB(v) ((v) + s16_pick((v), n0, n01, kb0, kb1 - n0, kb2 - n01))
-#define S16_LIVE(v) s16_live_mask(S16_PHYS_KB(v) * KBLOCK, s16_pick((v), n0, n01, rs0, rs1, rs2), s16_pick((v), n0, n01, re0, re1, re2), g)
+#define S16_LIVE(v) (G > 1 && (v) >= ve ? 0u : \
+    s16_live_mask(S16_PHYS_KB(v) * KBLOCK, s16_pick((v), n0, n01, rs0, rs1, rs2), s16_pick((v), n0, n01, re0, re1, re2), g))
+    const int v_end = G == 1 ? ve : vb + n_steps;
+    const int dead = G > 1 && v_end > ve ? ve : 0x7FFFFFFF;
 
     const char* kbase = reinterpret_cast<const char*>(p.k_cache + head * p.head_stride);
     const char* vbase = reinterpret_cast<const char*>(p.v_cache + head * p.head_stride);
@@ -184,12 +204,50 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
                                          (__attribute__((address_space(3))) void*)(dst), 16, 0, 0);
     };
 
+    // G > 1: load l of the period that begins with step `first` (relative to vb): V of its kblocks, K two kblocks on
+    auto issue_group = [&](int first, int l) {
+        constexpr int DEPTH = GR::DEPTH;
+        const int j = (NW * l) / NF, part = (NW * l) % NF;          // compile-time where l is
+        const bool is_k = part < KS;
+        const int rel = first + j + (is_k ? 2 : 0);
+        const int v = min(vb + rel, ve - 1);
+        const int fr = (is_k ? part : part - KS) + wave;
+        const char* src = (is_k ? kbase + k_load_off : vbase + lane_off) + int64_t(S16_PHYS_KB(v)) * KB_BYTES + fr * 1024;
+        char* dst = lds + ((is_k ? 0 : DEPTH) + (rel & (DEPTH - 1))) * KB_BYTES + fr * 1024;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
+                                         (__attribute__((address_space(3))) void*)(dst), 16, 0, 0);
+    };
+    // end of a period of a group's ring: what this wave loaded for the next one has landed, and its K fragment reads,
+    // whose stages the loads issued next overwrite, have returned; then every wave's have
+    auto group_handover = [&](u32x4 (&kf)[KS]) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) s16_lds_wait<0>(kf[k]);
+        s16_wait_vmcnt<0>();
+        if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
+    };
+
     // the ring's first loads go out before the queries are fetched: one memory latency for both
+    u32x4 kfr[KS];                               // K fragments of kblock i + 1
+    u32x4 kfirst[G == 1 ? 1 : KS];               // G > 1: those of kblock vb; the ring begins with kblock vb + 2
+    if constexpr (G == 1) {
 #pragma unroll
-    for (int j = 0; j < PF; ++j) {
-        const int v = min(vb + j, ve - 1);
+        for (int j = 0; j < PF; ++j) {
+            const int v = min(vb + j, ve - 1);
 #pragma unroll
-        for (int l = 0; l < LPW; ++l) issue_load(S16_PHYS_KB(v), (vb + j) & (NS - 1), l);
+            for (int l = 0; l < LPW; ++l) issue_load(S16_PHYS_KB(v), (vb + j) & (NS - 1), l);
+        }
+    } else {
+#pragma unroll
+        for (int l = 0; l < LPW; ++l) issue_group(0, l);
+        // the same 16 bytes per lane as the reads of the permuted fragments below, straight from memory
+        const unsigned k_lane = (g >> 1) * 1024 + ((g & 1) * 32 + (n & 7) + 16 * (n >> 3)) * 16;
+        const char* k0 = kbase + int64_t(S16_PHYS_KB(vb)) * KB_BYTES + k_lane;
+        const char* k1 = kbase + int64_t(S16_PHYS_KB(min(vb + 1, ve - 1))) * KB_BYTES + k_lane;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            kfirst[k] = *reinterpret_cast<const u32x4*>(k0 + (k >> 1) * 2048 + (k & 1) * 128);
+            kfr[k] = *reinterpret_cast<const u32x4*>(k1 + (k >> 1) * 2048 + (k & 1) * 128);
+        }
     }
 
     // Q^T fragments (pre-scaled by log2(e)/sqrt(D)): fragment (qb, s) holds features 32 s + 8 g + 0..7 of query q0 + 16 qb + n
@@ -238,7 +296,8 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     }
     // Sink at a fixed rotary distance (see attn_stream.hip): range 0 is the sink, scored with the queries turned back
     // by sink_shift frames on the frame axis; the unturned queries are loaded again in step n0 - 1.
-    const int sink_shift = ch.sink_shift;
+    // (a share that begins behind the sink has nothing to turn)
+    const int sink_shift = G > 1 && vb >= n0 ? 0 : ch.sink_shift;
     if (sink_shift != 0) {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
@@ -256,8 +315,13 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
                 }
     }
 
-    s16_wait_vmcnt<(PF - LAND) * LPW>();
-    __builtin_amdgcn_s_barrier();
+    if constexpr (G == 1) {
+        s16_wait_vmcnt<(PF - LAND) * LPW>();
+        __builtin_amdgcn_s_barrier();
+    } else {
+        s16_wait_vmcnt<0>();
+        if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
+    }
 
     // dead slots may hold anything, even NaN: zero the V elements of keys outside the range
     auto mask_v = [&](u32x4 (&av)[NV], unsigned live) {
@@ -296,11 +360,10 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     f32x4 negm[2];                               // every element = -mref[qb]: the score accumulators start from it
     float mx[2];                                 // largest score of kblock i among this lane's keys, per query block
     f32x4 sA[2][2], sB[2][2];                    // scores [m][qb] (log2 domain) of kblocks i and i + 1
-    u32x4 kfr[KS];                               // K fragments of kblock i + 1
     u32x4 vfr[NV];                               // V^T fragments of kblock i
 
     // ---- prologue: scores of kblock vb, the first reference, K fragments of kblock vb + 1
-    {
+    if constexpr (G == 1) {
         const char* kt = lds + (vb & (NS - 1)) * STAGE_BYTES + g * 512 + n * 16;
 #pragma unroll
         for (int k = 0; k < KS; ++k) kfr[k] = *reinterpret_cast<const u32x4*>(kt + S16_FRAG(k));
@@ -317,7 +380,8 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     for (int k = 0; k < KS; ++k)
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
-            sA[k & 1][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kfr[k]), qf[qb][k >> 1], sA[k & 1][qb], 0, 0, 0);
+            sA[k & 1][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, G == 1 ? kfr[k] : kfirst[G == 1 ? 0 : k]),
+                                                                    qf[qb][k >> 1], sA[k & 1][qb], 0, 0, 0);
     mask_s(sA, S16_LIVE(vb));
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
@@ -328,8 +392,10 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
         mx[qb] = -INFINITY;
         lsum[qb][0] = lsum[qb][1] = 0.f;
     }
+    if constexpr (G == 1) {
 #pragma unroll
-    for (int k = 0; k < KS; ++k) s16_lds_read(kfr[k], lds_a + ((vb + 1) & (NS - 1)) * STAGE_BYTES, S16_FRAG(k));
+        for (int k = 0; k < KS; ++k) s16_lds_read(kfr[k], lds_a + ((vb + 1) & (NS - 1)) * STAGE_BYTES, S16_FRAG(k));
+    }
 
     // ---- main loop: see attn_stream.hip for the plan; every slot here opens with two MFMAs
     constexpr int NSLOT = KS + NV;
@@ -338,14 +404,14 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     constexpr int SPAN = KS + HV - 2;
     static_assert((3 * SPAN) / NPAIR + 1 <= KS - 1, "a packed pair would be late for its MFMA");
     static_assert(MAX_FIRST >= KS, "the running maximum would read scores still being accumulated");
-    constexpr int DMA_STEP = NSLOT / LPW, DMA_FIRST = DMA_STEP - 1;
+    constexpr int DMA_STEP = G == 1 ? NSLOT / LPW : 1, DMA_FIRST = DMA_STEP - 1;
 #define S16_PIN(x) asm volatile("" ::"v"(x))
 #define S16_STEP(I, S_CUR, S_NEXT, EDGE, BAR)                                                                       \
     {                                                                                                               \
         const bool edge = EDGE && (I) == next_edge;                                                                 \
         if (__builtin_expect(edge || vote, 0)) {                                                                    \
             if (edge) {                                                                                             \
-                next_edge = s16_next_edge((I), n0, n01, T);                                                         \
+                next_edge = s16_next_edge((I), n0, n01, T, dead);                                                   \
                 mask_s(S_CUR, S16_LIVE(I));                                                                         \
                 if (TRACK) {                                                                                        \
                     mx[0] = max_s(S_CUR, 0);                                                                        \
@@ -369,8 +435,10 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
                 S_CUR[1][qb] -= delta;                                                                              \
             }                                                                                                       \
         }                                                                                                           \
-        const unsigned vt_a = lds_a + (((I)) & (NS - 1)) * STAGE_BYTES + KB_BYTES;                                  \
-        const unsigned kt_a = lds_a + (((I) + 2) & (NS - 1)) * STAGE_BYTES;                                         \
+        const unsigned vt_a = lds_a + (G == 1 ? ((I) & (NS - 1)) * STAGE_BYTES + KB_BYTES                           \
+                                              : (GR::DEPTH + (((I) - vb) & (GR::DEPTH - 1))) * KB_BYTES);           \
+        const unsigned kt_a = lds_a + (G == 1 ? (((I) + 2) & (NS - 1)) * STAGE_BYTES                                \
+                                              : (((I) + 2 - vb) & (GR::DEPTH - 1)) * KB_BYTES);                     \
         float d0[NPAIR], d1[NPAIR];                                                                                 \
         unsigned pb[2][4];                                                                                          \
         float m_run[2] = {-INFINITY, -INFINITY};                                                                    \
@@ -396,7 +464,12 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
                 st.o[2 * j + 1][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vfr[2 * j + 1]), \
                                           __builtin_bit_cast(bf16x8, bv), st.o[2 * j + 1][qb], 0, 0, 0);            \
             }                                                                                                       \
-            if (k >= DMA_FIRST && (k - DMA_FIRST) % DMA_STEP == 0 && (k - DMA_FIRST) / DMA_STEP < LPW) {            \
+            if (G > 1) {                                                                                            \
+                /* the next period's loads, in the period's first step */                                           \
+                if (PERIOD == 1 || (BAR) == 0 || ((BAR) == 2 && !(((I) - vb) & 1)))                                 \
+                    _Pragma("unroll") for (int l = 0; l < LPW; ++l)                                                 \
+                        if (GR::dma_slot(l, LPW, NSLOT) == k) issue_group((I) - vb + PERIOD, l);                    \
+            } else if (k >= DMA_FIRST && (k - DMA_FIRST) % DMA_STEP == 0 && (k - DMA_FIRST) / DMA_STEP < LPW) {     \
                 const int v = min((I) + PF, ve - 1);                                                                \
                 issue_load(S16_PHYS_KB(v), ((I) + PF) & (NS - 1), (k - DMA_FIRST) / DMA_STEP);                      \
             }                                                                                                       \
@@ -439,17 +512,21 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
             mx[1] = m_run[1];                                                                                       \
             vote = __any(fmaxf(mx[0], mx[1]) > S16_RESCALE_SLACK);                                                  \
         }                                                                                                           \
-        if (BAR == 1 || (BAR == 2 && RingPlan::barrier_after((I) - vb))) {                                          \
-            s16_wait_vmcnt<(PF - LAND) * LPW>();                                                                    \
-            __builtin_amdgcn_s_barrier();                                                                           \
+        if (PERIOD == 1 || BAR == 1 || (BAR == 2 && RingPlan::barrier_after((I) - vb))) {                           \
+            if constexpr (G == 1) {                                                                                 \
+                s16_wait_vmcnt<(PF - LAND) * LPW>();                                                                \
+                __builtin_amdgcn_s_barrier();                                                                       \
+            } else {                                                                                                \
+                group_handover(kfr);                                                                                \
+            }                                                                                                       \
         }                                                                                                           \
     }
 
-    int next_edge = s16_next_edge(vb - 1, n0, n01, T);
+    int next_edge = s16_next_edge(vb - 1, n0, n01, T, dead);
     bool vote = false;
     int i = vb;
-    while (i < ve) {
-        while (i < ve && (((i - vb) & 1) || i + 1 >= ve || i == next_edge || i + 1 == next_edge)) {
+    while (i < v_end) {
+        while (i < v_end && (((i - vb) & 1) || i + 1 >= v_end || i == next_edge || i + 1 == next_edge)) {
             S16_STEP(i, sA, sB, 1, 2)
 #pragma unroll
             for (int m = 0; m < 2; ++m)
@@ -457,7 +534,7 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
                 for (int qb = 0; qb < 2; ++qb) sA[m][qb] = sB[m][qb];
             ++i;
         }
-        for (int cnt = (min(ve, next_edge) - i) >> 1; cnt > 0; --cnt) {
+        for (int cnt = (min(v_end, next_edge) - i) >> 1; cnt > 0; --cnt) {
             S16_STEP(i, sA, sB, 0, 0)
             S16_STEP(i + 1, sB, sA, 0, 1)
             i += 2;
@@ -522,12 +599,143 @@ __device__ __forceinline__ void s16_segment_loads_only(const AttnParams& p, cons
     __builtin_amdgcn_s_waitcnt(0);
 }
 
-// ---- one workgroup per (head, query tile): placement on the XCDs as in attn_stream.hip
-template <int D, bool QSCALE, bool LSE, int SCHED = 0>
+// The same for a wave of a key group (G > 1) that has no queries, or whose group has no kblocks (loads nothing then).
+template <int D, int G>
+__device__ __forceinline__ void s16_group_idle(const AttnParams& p, const AttnChunk& ch, int head, int vb, int ve, int n_steps, char* lds) {
+    using GR = GroupRing<D, G>;
+    constexpr int KS = D / 16, NF = 2 * KS, NW = 8 / G, PERIOD = GR::PERIOD, DEPTH = GR::DEPTH, LPW = PERIOD * NF / NW;
+    constexpr int KB_BYTES = KBLOCK * D * 2;
+    if constexpr (NW == 1) return;               // a ring of its own: nobody waits for this wave
+    const int lane = threadIdx.x & 63;
+    const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_wg % NW;
+    lds += (wave_wg / NW) * GR::BYTES;
+    const int n_ranges = ch.n_ranges;
+    const int rs0 = ch.rs[0], re0 = ch.re[0];
+    int rs1 = ch.rs[1], re1 = ch.re[1], rs2 = ch.rs[2];
+    if (n_ranges < 2) rs1 = re1 = 0;
+    if (n_ranges < 3) rs2 = 0;
+    const int kb0 = rs0 / KBLOCK, ke0 = (re0 + KBLOCK - 1) / KBLOCK;
+    const int kb1 = rs1 / KBLOCK, ke1 = (re1 + KBLOCK - 1) / KBLOCK;
+    const int kb2 = rs2 / KBLOCK;
+    const int n0 = ke0 - kb0, n01 = n0 + (ke1 - kb1);
+    const char* kbase = reinterpret_cast<const char*>(p.k_cache + head * p.head_stride);
+    const char* vbase = reinterpret_cast<const char*>(p.v_cache + head * p.head_stride);
+    const unsigned lane_off = lane * 16, k_load_off = s16_k_load_offset(lane);
+    auto issue_period = [&](int first) {
+        if (ve <= vb) return;
+#pragma unroll
+        for (int l = 0; l < LPW; ++l) {
+            const int j = (NW * l) / NF, part = (NW * l) % NF;
+            const bool is_k = part < KS;
+            const int rel = first + j + (is_k ? 2 : 0);
+            const int v = min(vb + rel, ve - 1), kb = v + s16_pick(v, n0, n01, kb0, kb1 - n0, kb2 - n01);
+            const int fr = (is_k ? part : part - KS) + wave;
+            const char* src = (is_k ? kbase + k_load_off : vbase + lane_off) + int64_t(kb) * KB_BYTES + fr * 1024;
+            char* dst = lds + ((is_k ? 0 : DEPTH) + (rel & (DEPTH - 1))) * KB_BYTES + fr * 1024;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
+                                             (__attribute__((address_space(3))) void*)(dst), 16, 0, 0);
+        }
+    };
+    issue_period(0);
+    s16_wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    for (int r = 0; r + PERIOD <= n_steps; r += PERIOD) {
+        issue_period(r + PERIOD);
+        s16_wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+    }
+    if (n_steps % PERIOD != 0) issue_period(n_steps / PERIOD * PERIOD + PERIOD);
+    __builtin_amdgcn_s_waitcnt(0);
+}
+
+// One query tile of 256 / G rows, its keys dealt to G groups of 8 / G waves: kblocks [T j / G, T (j + 1) / G) to group j.
+// Each group's result is relative to its own reference; they meet in LDS (the rings' memory), where every wave adds up
+// its part of the features over the groups: weights 2^(m_j - max m), one division by the weighted sum of the row sums.
+template <int D, bool QSCALE, bool LSE, int SCHED, int G>
+__device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnChunk& ch, int head, int tile, char* lds,
+                                               const float2* shift_cs, float2 (*ml)[2][16]) {
+    constexpr int NW = 8 / G, UNITS = D / 16 * 2;                // (dq, qb) blocks of a wave's O^T
+    static_assert(UNITS % G == 0, "the O^T blocks must split over the groups");
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int group = wave / NW, rb = wave % NW;
+    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+    const int q0 = ch.q_begin + (tile - ch.tile_begin) * (256 / G) + rb * 32;
+    const bool has_rows = q0 < ch.q_end;
+    const int T = ch.n_kblocks, vb = T * group / G, ve = T * (group + 1) / G, n_steps = (T + G - 1) / G;
+    const bool works = has_rows && ve > vb;
+    S16State<D> st;
+    if (works) s16_segment<D, QSCALE, SCHED, G>(p, ch, head, q0, vb, ve, n_steps, lds, st, shift_cs);
+    else s16_group_idle<D, G>(p, ch, head, vb, ve, n_steps, lds);
+    if constexpr ((SCHED & 8) != 0) {
+        const bool ran_away = works && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
+        if (__syncthreads_or(ran_away)) {
+            if (works) s16_segment<D, QSCALE, SCHED & ~8, G>(p, ch, head, q0, vb, ve, n_steps, lds, st, shift_cs);
+            else s16_group_idle<D, G>(p, ch, head, vb, ve, n_steps, lds);
+        }
+    }
+    if (!works) {
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            st.l[qb] = 0.f;
+            st.m[qb] = -INFINITY;
+#pragma unroll
+            for (int dq = 0; dq < D / 16; ++dq) st.o[dq][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    __syncthreads();                             // every group has left its ring
+    f32x4* part = reinterpret_cast<f32x4*>(lds);                 // [wave][unit][lane]
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        float l = st.l[qb];
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
+        if (g == 0) ml[wave][qb][n] = make_float2(st.m[qb], l);
+#pragma unroll
+        for (int dq = 0; dq < D / 16; ++dq) part[(wave * UNITS + dq * 2 + qb) * 64 + lane] = st.o[dq][qb];
+    }
+    __syncthreads();
+    if (!has_rows) return;
+#pragma unroll
+    for (int i = 0; i < UNITS / G; ++i) {
+        const int u = group * (UNITS / G) + i, dq = u >> 1, qb = u & 1;
+        const int row = q0 + 16 * qb + n;
+        float m = -INFINITY, l = 0.f;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + rb][qb][n].x);      // finite: some group has a kblock
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const float2 s = ml[j * NW + rb][qb][n];
+            const float a = __builtin_amdgcn_exp2f(s.x - m);
+            l += s.y * a;
+            o += part[((j * NW + rb) * UNITS + u) * 64 + lane] * a;
+        }
+        if (row >= ch.q_end) continue;
+        const float inv = 1.0f / l;
+        const u32x2 w = {s16_pack_bf16(o[0] * inv, o[1] * inv), s16_pack_bf16(o[2] * inv, o[3] * inv)};
+        uint16_t* dst = p.out_frag != nullptr        // uniform
+            ? p.out_frag + op_frag_offset(row, head * (D / 32) + (dq >> 1), g, p.H * (D / 32)) + (dq & 1) * 4
+            : p.out + (int64_t(row) * p.H + head) * D + dq * 16 + g * 4;
+        *reinterpret_cast<u32x2*>(dst) = w;
+        if constexpr (LSE) {
+            if (p.lse != nullptr && dq == 0 && g == 0) p.lse[int64_t(head) * p.lse_stride + row] = m + __builtin_amdgcn_logf(l);
+            if (p.out32 != nullptr) *reinterpret_cast<f32x4*>(p.out32 + (int64_t(row) * p.H + head) * D + dq * 16 + g * 4) = o * inv;
+        }
+    }
+}
+
+// ---- one workgroup per (head, query tile): placement on the XCDs as in attn_stream.hip.  G: key groups
+template <int D, bool QSCALE, bool LSE, int SCHED, int G>
 __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_stream16_kernel(const AttnParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ float2 shift_cs[64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // The arguments lie in several cache lines; where a launch has one chunk, all that a workgroup needs of them is
+    // fetched here in one go instead of one cold scalar load after another.
+    AttnChunk ch = p.chunk[0];
+    asm volatile("" ::"s"(ch.q_begin), "s"(ch.q_end), "s"(ch.tile_begin), "s"(ch.n_ranges), "s"(ch.rs[0]), "s"(ch.rs[1]), "s"(ch.rs[2]),
+                 "s"(ch.re[0]), "s"(ch.re[1]), "s"(ch.re[2]), "s"(ch.n_kblocks), "s"(ch.sink_shift), "s"(ch.t_row));
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_frag), "s"(p.t_table), "s"(p.row_cs), "s"(p.col_cs));
     const int xcd = blockIdx.x & 7;
     int idx = blockIdx.x >> 3, head = -1, tile = 0;
     if (p.n_groups == 0) {
@@ -550,9 +758,11 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         }
     }
     if (head < 0) return;                        // uniform over the workgroup
-    int ci = 0;
-    while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
-    const AttnChunk& ch = p.chunk[ci];
+    if (p.n_chunks > 1) {
+        int ci = 0;
+        while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
+        ch = p.chunk[ci];
+    }
     if (ch.sink_shift != 0) {                    // uniform over the workgroup
         if ((int)threadIdx.x < p.n_t) {
             double sn, cs;
@@ -561,12 +771,17 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         }
         __syncthreads();
     }
+    if constexpr (G > 1) {
+        __shared__ float2 ml[8][2][16];          // (reference, row sum) per wave, query block and column
+        s16_split_tile<D, QSCALE, LSE, SCHED, G>(p, ch, head, tile, lds, shift_cs, ml);
+        return;
+    }
     const int row_block = ((wave & 3) << 1) | (wave >> 2);      // waves w and w + 4 (one SIMD) take neighbouring blocks
     const int q0 = ch.q_begin + (tile - ch.tile_begin) * 256 + row_block * 32;
     // wave-uniform: a wave without rows in the chunk's last tile only takes its share of the loads and barriers
     const bool has_rows = q0 < ch.q_end;
     S16State<D> st;
-    if (has_rows) s16_segment<D, QSCALE, SCHED>(p, ch, head, q0, 0, ch.n_kblocks, lds, st, shift_cs);
+    if (has_rows) s16_segment<D, QSCALE, SCHED, 1>(p, ch, head, q0, 0, ch.n_kblocks, ch.n_kblocks, lds, st, shift_cs);
     else s16_segment_loads_only<D>(p, ch, head, 0, ch.n_kblocks, lds);
     if constexpr ((SCHED & 8) != 0) {
         // the pass above kept its first reference: fine unless some row's sum ran away (a score far above the first
@@ -574,7 +789,7 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         // with the reference followed.  The barrier inside the vote also ends every wave's reads of the first pass.
         const bool ran_away = has_rows && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
         if (__syncthreads_or(ran_away)) {
-            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8>(p, ch, head, q0, 0, ch.n_kblocks, lds, st, shift_cs);
+            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1>(p, ch, head, q0, 0, ch.n_kblocks, ch.n_kblocks, lds, st, shift_cs);
             else s16_segment_loads_only<D>(p, ch, head, 0, ch.n_kblocks, lds);
         }
     }
@@ -625,8 +840,14 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
 // the second, maximum-following pass as the fallback (SCHED 9).  The *_tracked variants follow the maximum throughout;
 // the *_qrope variants (SCHED bit 4) take unrotated queries and turn them on load.
 constexpr int S16_DEFAULT = 9, S16_TRACKED = 1;
-#define S16_ENTRY(name, D, QS, LSE, SCHED) \
-    {name, D, 256, 8 * 2 * KBLOCK * D * 2, ll_attn_stream16_kernel<D, QS, LSE, SCHED>, S16_THREADS, KBLOCK}
+#define S16_KERNEL(D, QS, LSE, SCHED, G) ll_attn_stream16_kernel<D, QS, LSE, SCHED, G>
+#define S16_ENTRY(name, D, QS, LSE, SCHED)                                                                            \
+    {name, D, 256, 8 * 2 * KBLOCK * D * 2, S16_KERNEL(D, QS, LSE, SCHED, 1), S16_THREADS, KBLOCK,                     \
+     {S16_KERNEL(D, QS, LSE, SCHED, 2), S16_KERNEL(D, QS, LSE, SCHED, 4),                                             \
+      D == 64 ? S16_KERNEL(D, QS, LSE, SCHED, (D == 64 ? 8 : 4)) : nullptr}}
+// (the tracked variants are there to be compared with, one key group)
+#define S16_ENTRY_WHOLE(name, D, QS, LSE, SCHED) \
+    {name, D, 256, 8 * 2 * KBLOCK * D * 2, S16_KERNEL(D, QS, LSE, SCHED, 1), S16_THREADS, KBLOCK, {}}
 const AttnVariant kStream16Variants[] = {
     S16_ENTRY("d128_stream16", 128, false, false, S16_DEFAULT),
     S16_ENTRY("d64_stream16", 64, false, false, S16_DEFAULT),
@@ -634,12 +855,14 @@ const AttnVariant kStream16Variants[] = {
     S16_ENTRY("d64_stream16_qscale", 64, true, false, S16_DEFAULT),
     S16_ENTRY("d128_stream16_lse", 128, false, true, S16_DEFAULT),
     S16_ENTRY("d64_stream16_lse", 64, false, true, S16_DEFAULT),
-    S16_ENTRY("d128_stream16_tracked", 128, false, false, S16_TRACKED),
-    S16_ENTRY("d64_stream16_tracked", 64, false, false, S16_TRACKED),
+    S16_ENTRY_WHOLE("d128_stream16_tracked", 128, false, false, S16_TRACKED),
+    S16_ENTRY_WHOLE("d64_stream16_tracked", 64, false, false, S16_TRACKED),
     S16_ENTRY("d128_stream16_qrope", 128, false, false, S16_DEFAULT | 16),
     S16_ENTRY("d64_stream16_qrope", 64, false, false, S16_DEFAULT | 16),
 };
 #undef S16_ENTRY
+#undef S16_ENTRY_WHOLE
+#undef S16_KERNEL
 const int kNumStream16Variants = sizeof(kStream16Variants) / sizeof(kStream16Variants[0]);
 
 }  // namespace ll

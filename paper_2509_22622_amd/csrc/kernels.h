@@ -111,7 +111,7 @@ __device__ __forceinline__ void rope_turn_scaled(float re, float im, float2 w, f
 
 struct AttnChunk {
     int q_begin, q_end;          // query rows [q_begin, q_end) of the q tensor
-    int tile_begin;              // first query tile of this chunk in the launch
+    int tile_begin;              // first query tile of this chunk in the launch  (filled in by launch_attn)
     int n_ranges;
     int rs[MAX_RANGES], re[MAX_RANGES];   // key token-slot ranges
     int n_kblocks;               // kblocks the ranges touch        (filled in by launch_attn)
@@ -134,7 +134,7 @@ struct AttnParams {
     int H, D;
     float scale_log2e;           // factor still to apply to q.k in the log2 domain (1 when q is pre-scaled); only
                                  // the simple kernels and the *_qscale kernels apply it
-    int n_chunks, n_tiles;       // n_tiles = query tiles over all chunks
+    int n_chunks, n_tiles;       // n_tiles = query tiles over all chunks (filled in by launch_attn)
     // Placement on the 8 XCDs (filled in by launch_attn; workgroup b runs on XCD b % 8).  n_groups == 0: the
     // (head, tile) items are split into 8 contiguous runs.  Otherwise (launches of several chunks, whose tiles
     // differ in length) XCD x runs the (head, chunk) groups xcd_group[xcd_first[x] .. xcd_first[x + 1]) in that
@@ -213,6 +213,9 @@ struct AttnVariant {
     void (*kernel)(const AttnParams);
     int threads;
     int kblock;                  // 32: bf16 cache, 64: 8-bit cache
+    // The same work with the keys of a tile dealt to G = 2, 4, 8 groups of the workgroup's waves (qtile / G rows per
+    // workgroup); null where there is no such kernel.
+    void (*grouped[3])(const AttnParams);
 };
 extern const AttnVariant kStreamVariants[];
 extern const int kNumStreamVariants;
@@ -225,7 +228,7 @@ extern const int kNumStream16Variants;
 int attn_variant_count();
 const char* attn_variant_name(int v);
 int attn_variant_default(int D, int kblock);
-int attn_variant_qtile(int v);                 // query rows per workgroup
+int attn_variant_qtile(int v);                 // query rows per workgroup (of one key group)
 bool attn_variant_supports(int v, int D, int kblock);
 bool attn_variant_sink_shift(int v);          // the variant honours AttnChunk::sink_shift
 int attn_variant_lse(int D);                   // the variant that also writes AttnParams::lse

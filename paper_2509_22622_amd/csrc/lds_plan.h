@@ -103,4 +103,22 @@ struct RingPlan {
     static constexpr bool barrier_after(int step) { return step & 1; }
 };
 
+// The rings of a workgroup whose waves are dealt into G key groups (G = 2, 4, 8; attn_stream16.hip): a group's 8 / G
+// waves walk their own share of the kblocks through a ring of their own, 128 KB / G at most.  Keys and values have
+// separate rings of DEPTH half stages (kblock v in half stage v % DEPTH), because the step for kblock i reads V^T of i
+// but K of i + 2.  Loads, waits and barriers come in periods of PERIOD steps: in its first step a period issues the
+// loads of the next one (V of its kblocks, K two kblocks further on), at its end a wave waits for all it has issued,
+// LDS reads included, and meets the group's other waves at a barrier.  The K of a share's first two kblocks goes straight
+// to registers, so the ring starts with the third.
+template <int D, int G>
+struct GroupRing {
+    static constexpr int PERIOD = G * D <= 256 ? 2 : 1;
+    static constexpr int DEPTH = 2 * PERIOD;
+    static constexpr int BYTES = 2 * DEPTH * 32 * D * 2;
+    static_assert(G * BYTES <= 128 * 1024, "the rings of a workgroup");
+    // slot of a period's first step behind whose MFMAs load l of n is issued: spread over the step, or, where that step
+    // is the whole period, over its first half (they have to land within it)
+    static constexpr int dma_slot(int l, int n, int slots) { return l * slots / n / (PERIOD == 1 ? 2 : 1); }
+};
+
 }  // namespace ll
