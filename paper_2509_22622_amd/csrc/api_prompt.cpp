@@ -175,8 +175,10 @@ static ll_status cross_attn(const ll_prompt* prompt, int layer, const void* q, i
     if (!q || !out) return fail(LL_ERR_INVALID_ARG, "null tensor");
     if (!aligned16(q, out)) return fail(LL_ERR_INVALID_ARG, "tensors must be 16-byte aligned");
     // these queries carry no factor yet: only kernels that apply AttnParams::scale_log2e themselves qualify
-    // A workgroup meets few kblocks here, and most of its life is the load of its queries and the store of its
-    // outputs.  With one round of workgroups on the chip (a chunk's queries) the pipelined kernel is the quicker one;
+    // A prompt that fits into LDS whole (256 tokens at head_dim 128, 512 at 64) goes to the kernel made for that
+    // (attn_resident.hip: faster or level at every size measured, 3 to 24 heads, 60 to 23400 rows), unless a variant is forced.
+    // Beyond that a workgroup streams the keys, and most of its life is still the load of its queries and the store of
+    // its outputs.  With one round of workgroups on the chip (a chunk's queries) the pipelined kernel is the quicker one;
     // with several rounds (a re-prefill's queries) small workgroups, three to a CU in different phases, are.
     int variant = attn_variant_qscale(prompt->D);
     if ((int64_t(n_q) + 255) / 256 * prompt->H > 512) variant = attn_variant_short_keys(prompt->D);
@@ -192,6 +194,7 @@ static ll_status cross_attn(const ll_prompt* prompt, int layer, const void* q, i
     p.H = prompt->H; p.D = prompt->D;
     p.kblock = KBLOCK;
     p.scale_log2e = float(1.4426950408889634 / std::sqrt(double(prompt->D)));
+    p.keys_reside = g_variant == 0;
     p.n_chunks = 1;
     AttnChunk& ch = p.chunk[0];
     ch.q_begin = 0; ch.q_end = n_q;

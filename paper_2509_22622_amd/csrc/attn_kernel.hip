@@ -380,6 +380,14 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         for (int r = 0; r < ch.n_ranges; ++r) ch.n_kblocks += (ch.re[r] + KB - 1) / KB - ch.rs[r] / KB;
         if (ch.n_kblocks < 1) return hipErrorInvalidValue;
     }
+    if (p.keys_reside && attn_resident_fits(p.D, p.chunk[0].n_kblocks)) {
+        ResidentParams r{};
+        r.q = p.q; r.out = p.out; r.out_frag = p.out_frag;
+        r.k_cache = p.k_cache; r.v_cache = p.v_cache; r.head_stride = p.head_stride;
+        r.H = p.H; r.n_rows = p.chunk[0].q_end; r.n_keys = p.chunk[0].re[0];
+        r.scale_log2e = p.scale_log2e;
+        return launch_attn_resident(r, p.D, s);
+    }
     const int log_g = key_groups_log2(v, p), qtile = v.qtile >> log_g;
     p.n_tiles = 0;
     for (int c = 0; c < p.n_chunks; ++c) {

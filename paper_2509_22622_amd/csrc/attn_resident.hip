@@ -1,0 +1,255 @@
+// Attention of many query rows over a key set that fits into a CU's LDS whole (cross-attention over a prompt of up to
+// 256 tokens at head_dim 128, 512 at 64): the same 16x16x32 MFMA formulation, fragments and cache layout as
+// attn_stream16.hip.
+//
+// What bounds it: the queries in and the outputs out.  At 226 tokens x 23400 rows x 12 heads x 128 these are 144 MB
+// (29 us at a copy's rate) next to some 16 us of matrix time.  A kernel that streams the keys through a ring for every
+// tile of 256 rows spends most of a tile's life loading queries, filling the ring and storing outputs, one after the
+// other.  Here a workgroup brings the keys and values of one head into LDS once and its eight waves then go through
+// their rows on their own: blocks of 32 rows, no barrier, no ring, the next block's queries on their way while this
+// block is computed, and the waves of a CU in different phases.  Measured against the streaming kernels, us:
+// 226 tokens x 23400 rows x 12 x 128 75 -> 55 (16 tokens, all memory: 47 -> 36, 4.0 TB/s), x 24 heads 137 -> 101;
+// 1200 rows x 77 tokens x 24 x 64 10 -> 7.  Rows that went to memory in the lanes' own order (64-byte loads, 32-byte stores) took
+// 46 us at 16 tokens; fragments read a phase ahead of their MFMAs spill and are no faster.
+#include "kernels.h"
+
+#include <algorithm>
+
+namespace ll {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int RES_WAVES = 8, RES_THREADS = 64 * RES_WAVES;
+constexpr int RES_KEY_BYTES = 128 * 1024;        // keys and values; 16 rows per wave come on top: 160 KB at head_dim 128
+constexpr float RES_SLACK = 6.0f;                // log2 units: weights stay below 2^6 between rescales
+
+__device__ __forceinline__ unsigned res_pack_bf16(float a, float b) {
+    f32x2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+
+// FRAG: the output goes out in the output projection's fragment order (AttnParams::out_frag)
+template <int D, bool FRAG>
+__global__ __launch_bounds__(RES_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_resident_kernel(const ResidentParams p) {
+    constexpr int KS = D / 16, NV = D / 16, NQ = D / 32, NF = KS + NV;
+    constexpr int KB_BYTES = KBLOCK * D * 2, STAGE_BYTES = 2 * KB_BYTES;      // [K kblock | V kblock]
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int head = blockIdx.x % p.H, part = blockIdx.x / p.H;               // workgroups of all heads walk the same rows
+    const int T = p.n_kblocks, tail = p.n_keys - (T - 1) * KBLOCK;            // keys in the last kblock
+    const int n_blocks = (p.n_rows + 31) >> 5;
+    const int lo = int(int64_t(n_blocks) * part / p.parts), hi = int(int64_t(n_blocks) * (part + 1) / p.parts);
+
+    {
+        const char* kbase = reinterpret_cast<const char*>(p.k_cache + head * p.head_stride);
+        const char* vbase = reinterpret_cast<const char*>(p.v_cache + head * p.head_stride);
+        // K fragments are permuted on the way, as in attn_stream16.hip: lane (c, m, r) fetches stored row
+        // (r & 7) + 8 m + 16 (r >> 3) of 16-byte chunk c
+        const int hc = lane >> 5, m = (lane >> 4) & 1, r = lane & 15;
+        const unsigned k_off = unsigned(hc * 32 + (r & 7) + 8 * m + 16 * (r >> 3)) * 16u, v_off = lane * 16u;
+        for (int f = wave; f < T * NF; f += RES_WAVES) {
+            const int kb = f / NF, fr = f % NF;
+            const char* src = (fr < KS ? kbase + fr * 1024 + k_off : vbase + (fr - KS) * 1024 + v_off) + int64_t(kb) * KB_BYTES;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
+                                             (__attribute__((address_space(3))) void*)(lds + kb * STAGE_BYTES + fr * 1024), 16, 0, 0);
+        }
+    }
+    // Rows come and go as whole rows (a load or store instruction covers 64 / CH of them), so that memory sees full
+    // lines; between that order and the lanes' own (row n, features 32 s + 8 g ..) they pass through 16 rows of LDS of the
+    // wave's own, chunk c of row r at place c ^ r (no bank conflicts).
+    constexpr int CH = D / 8, RPI = 64 / CH;     // 16-byte chunks per row, rows per instruction
+    char* turn = lds + T * STAGE_BYTES + wave * (16 * D * 2);
+    const int line_row = lane / CH, line_c = lane % CH;
+    auto place = [&](int row, int c) { return turn + row * (D * 2) + ((c ^ row) & (CH - 1)) * 16; };
+    u32x4 q_next[2][NQ];
+    auto fetch = [&](int b) {
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) {
+                const int row = min(32 * b + 16 * qb + i * RPI + line_row, p.n_rows - 1);
+                q_next[qb][i] = *reinterpret_cast<const u32x4*>(p.q + (int64_t(row) * p.H + head) * D + line_c * 8);
+            }
+    };
+    fetch(min(lo + wave, n_blocks - 1));
+    __syncthreads();
+    if (tail < KBLOCK) {                         // slots past the last key may hold anything, even NaN
+        uint16_t* v_last = reinterpret_cast<uint16_t*>(lds + (T - 1) * STAGE_BYTES + KB_BYTES);
+        for (int i = tid; i < KBLOCK * D; i += RES_THREADS)
+            if (i / D >= tail) v_last[v_elem_offset(i / D, i % D)] = 0;
+        __syncthreads();
+    }
+
+    const char* lane_lds = lds + g * 512 + n * 16;
+    auto frag = [&](int kb, int kind, int f) {   // as attn_stream16.hip reads them
+        return *reinterpret_cast<const bf16x8*>(lane_lds + kb * STAGE_BYTES + kind * KB_BYTES + (f >> 1) * 2048 + (f & 1) * 256);
+    };
+    auto col_max = [&](float x) {
+        x = fmaxf(x, __shfl_xor(x, 16));
+        return fmaxf(x, __shfl_xor(x, 32));
+    };
+
+    const float c = p.scale_log2e;               // applied to the scores in fp32: the queries are not rounded again
+    bf16x8 qf[2][NQ];
+    auto take_queries = [&]() {
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) *reinterpret_cast<u32x4*>(place(i * RPI + line_row, line_c)) = q_next[qb][i];
+#pragma unroll
+            for (int s = 0; s < NQ; ++s) qf[qb][s] = *reinterpret_cast<const bf16x8*>(place(n, 4 * s + g));
+        }
+    };
+    take_queries();
+    for (int b = lo + wave; b < hi; b += RES_WAVES) {
+        fetch(min(b + RES_WAVES, n_blocks - 1));
+
+        f32x4 o[NV][2];
+        float lsum[2] = {0.f, 0.f}, mref[2] = {0.f, 0.f};        // row sums, references (log2 domain)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+            for (int f = 0; f < NV; ++f) o[f][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        auto scores = [&](int kb, f32x4 (&s)[2][2]) {
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                const bf16x8 a = frag(kb, 0, k);
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) {
+                    if (k < 2) s[k & 1][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    s[k & 1][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[qb][k >> 1], s[k & 1][qb], 0, 0, 0);
+                }
+            }
+        };
+        // kblock kb, whose scores are `cur`; those of kb + 1 go to `nxt` under its vector work
+        f32x4 cur[2][2], nxt[2][2] = {};
+        scores(0, cur);
+        for (int kb = 0; kb < T; ++kb) {
+            if (kb + 1 < T) scores(kb + 1, nxt);
+            if (kb == T - 1 && tail < KBLOCK) {  // register j of group m is key 8 g + 4 m + j
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb) {
+                        const f32x4 x = cur[m][qb];
+                        const int left = tail - 8 * g - 4 * m;
+                        cur[m][qb] = f32x4{left > 0 ? x[0] : -INFINITY, left > 1 ? x[1] : -INFINITY,
+                                           left > 2 ? x[2] : -INFINITY, left > 3 ? x[3] : -INFINITY};
+                    }
+            }
+            float mx[2];
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                mx[qb] = fmaxf(fmaxf(cur[0][qb][0], cur[0][qb][1]), cur[0][qb][2]);
+                mx[qb] = fmaxf(fmaxf(mx[qb], cur[0][qb][3]), cur[1][qb][0]);
+                mx[qb] = fmaxf(fmaxf(mx[qb], cur[1][qb][1]), cur[1][qb][2]);
+                mx[qb] = fmaxf(mx[qb], cur[1][qb][3]);
+            }
+            if (kb == 0 || __any(mx[0] * c > mref[0] + RES_SLACK || mx[1] * c > mref[1] + RES_SLACK)) {
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) {
+                    const float top = col_max(mx[qb]) * c;       // the first kblock holds a live key: finite there
+                    const float m = kb == 0 ? top : fmaxf(mref[qb], top);
+                    const float alpha = kb == 0 ? 0.f : __builtin_amdgcn_exp2f(mref[qb] - m);
+                    mref[qb] = m;
+                    lsum[qb] *= alpha;
+                    if (kb != 0)
+#pragma unroll
+                        for (int f = 0; f < NV; ++f) o[f][qb] *= alpha;
+                }
+            }
+            u32x4 pb[2];
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[w >> 1][qb][2 * (w & 1)], c, -mref[qb]));
+                    const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[w >> 1][qb][2 * (w & 1) + 1], c, -mref[qb]));
+                    lsum[qb] += e0;
+                    lsum[qb] += e1;
+                    pb[qb][w] = res_pack_bf16(e0, e1);
+                }
+#pragma unroll
+            for (int f = 0; f < NV; ++f) {
+                const bf16x8 a = frag(kb, 1, f);
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb)
+                    o[f][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, pb[qb]), o[f][qb], 0, 0, 0);
+            }
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) cur[m][qb] = nxt[m][qb];
+        }
+
+        // the next block's queries are waited for before the stores are issued: one counter counts both, in order
+        take_queries();
+        __builtin_amdgcn_sched_barrier(0);
+
+        // out[row][head][16 dq + 4 g + j] = O^T block (dq, qb) register j, divided by the row sum
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            float l = lsum[qb];
+            l += __shfl_xor(l, 16);
+            l += __shfl_xor(l, 32);
+            const float inv = 1.0f / l;
+            if constexpr (FRAG) {                // 1 KB per store instruction as it is
+                const int row = 32 * b + 16 * qb + n;
+                if (row >= p.n_rows) continue;
+#pragma unroll
+                for (int t = 0; t < D / 32; ++t) {
+                    const f32x4 x = o[2 * t][qb] * inv, y = o[2 * t + 1][qb] * inv;
+                    const u32x4 w = {res_pack_bf16(x[0], x[1]), res_pack_bf16(x[2], x[3]), res_pack_bf16(y[0], y[1]), res_pack_bf16(y[2], y[3])};
+                    *reinterpret_cast<u32x4*>(p.out_frag + op_frag_offset(row, head * (D / 32) + t, g, p.H * (D / 32))) = w;
+                }
+            } else {
+#pragma unroll
+                for (int dq = 0; dq < NV; ++dq) {
+                    const f32x4 x = o[dq][qb] * inv;
+                    const u32x2 w = {res_pack_bf16(x[0], x[1]), res_pack_bf16(x[2], x[3])};
+                    *reinterpret_cast<u32x2*>(place(n, 2 * dq + (g >> 1)) + (g & 1) * 8) = w;
+                }
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) {
+                    const u32x4 w = *reinterpret_cast<const u32x4*>(place(i * RPI + line_row, line_c));
+                    const int row = 32 * b + 16 * qb + i * RPI + line_row;
+                    if (row < p.n_rows) *reinterpret_cast<u32x4*>(p.out + (int64_t(row) * p.H + head) * D + line_c * 8) = w;
+                }
+            }
+        }
+    }
+}
+
+bool attn_resident_fits(int D, int n_kblocks) { return n_kblocks * 2 * KBLOCK * D * 2 <= RES_KEY_BYTES; }
+
+hipError_t launch_attn_resident(const ResidentParams& p_in, int D, hipStream_t s) {
+    ResidentParams p = p_in;
+    p.n_kblocks = (p.n_keys + KBLOCK - 1) / KBLOCK;
+    if (p.n_keys < 1 || p.n_rows < 1 || (D != 64 && D != 128) || !attn_resident_fits(D, p.n_kblocks)) return hipErrorInvalidValue;
+    // one workgroup per CU, every head the same number of them, at least one block of rows each
+    const int blocks = (p.n_rows + 31) / 32;
+    p.parts = std::max(1, std::min(256 / p.H, blocks));
+    const int lds = p.n_kblocks * 2 * KBLOCK * D * 2 + RES_WAVES * 16 * D * 2;
+    static bool attr_set[2][2] = {};
+    void (*const kernel)(const ResidentParams) = p.out_frag != nullptr
+        ? (D == 128 ? ll_attn_resident_kernel<128, true> : ll_attn_resident_kernel<64, true>)
+        : (D == 128 ? ll_attn_resident_kernel<128, false> : ll_attn_resident_kernel<64, false>);
+    bool& set = attr_set[D == 128][p.out_frag != nullptr];
+    if (!set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           RES_KEY_BYTES + RES_WAVES * 16 * D * 2);
+        if (e != hipSuccess) return e;
+        set = true;
+    }
+    hipLaunchKernelGGL(kernel, dim3(unsigned(p.H) * unsigned(p.parts)), dim3(RES_THREADS), lds, s, p);
+    return hipGetLastError();
+}
+
+}  // namespace ll

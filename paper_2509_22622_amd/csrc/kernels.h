@@ -134,6 +134,7 @@ struct AttnParams {
     int H, D;
     float scale_log2e;           // factor still to apply to q.k in the log2 domain (1 when q is pre-scaled); only
                                  // the simple kernels and the *_qscale kernels apply it
+    bool keys_reside;            // the one key range may be brought into LDS whole where it fits (attn_resident.hip)
     int n_chunks, n_tiles;       // n_tiles = query tiles over all chunks (filled in by launch_attn)
     // Placement on the 8 XCDs (filled in by launch_attn; workgroup b runs on XCD b % 8).  n_groups == 0: the
     // (head, tile) items are split into 8 contiguous runs.  Otherwise (launches of several chunks, whose tiles
@@ -251,6 +252,18 @@ struct OutProjParams { const uint16_t* x_frag; const uint16_t* w_frag; uint16_t*
 hipError_t launch_out_proj(const OutProjParams& p, hipStream_t s);
 // w [N, K] bf16 row-major ([output feature][input feature]) -> fragment order, same size
 hipError_t launch_pack_out_weight(const uint16_t* w, uint16_t* w_frag, int N, int K, hipStream_t s);
+
+// Attention over one key range that starts at slot 0 and fits into LDS whole (attn_resident.hip).
+struct ResidentParams {
+    const uint16_t* q; uint16_t* out; uint16_t* out_frag;        // as in AttnParams; rows [0, n_rows)
+    const uint16_t* k_cache; const uint16_t* v_cache;
+    int64_t head_stride;
+    int H, n_rows, n_keys;
+    float scale_log2e;           // factor to apply to the scores
+    int n_kblocks, parts;        // workgroups per head (filled in by launch_attn_resident)
+};
+bool attn_resident_fits(int D, int n_kblocks);
+hipError_t launch_attn_resident(const ResidentParams& p, int D, hipStream_t s);
 
 hipError_t launch_append(const AppendParams& p, hipStream_t s);
 hipError_t launch_append8(const AppendParams& p, hipStream_t s);

@@ -1,7 +1,11 @@
-"""Launches of few rows and heads deal a tile's keys to 2, 4 or 8 groups of the workgroup's waves (attn_stream16.hip);
+"""Kernels that a launch's size selects, at the edges of what they take.
+
+Launches of few rows and heads deal a tile's keys to 2, 4 or 8 groups of the workgroup's waves (attn_stream16.hip);
 the groups' results meet in LDS.  Where that can go wrong: shares of unequal length, fewer kblocks than groups, a last
 kblock of one key, a last tile of one row, a score far above its own group's reference.  The launch rule gives the
-small shapes here the largest grouping a head_dim has (8 groups at 64, 4 at 128); 24 heads of 1170 rows get two."""
+small shapes here the largest grouping a head_dim has (8 groups at 64, 4 at 128); 24 heads of 1170 rows get two.
+Cross-attention over a prompt that fits into LDS whole (256 tokens at head_dim 128, 512 at 64) runs in a kernel of its
+own (attn_resident.hip) unless a variant is forced: both run here on the same inputs."""
 import pytest
 import torch
 
@@ -17,7 +21,7 @@ def _reference(q, k, v):
     return torch.stack([a @ b for a, b in zip(w, v)]).transpose(0, 1)
 
 
-def _check(heads, head_dim, n_q, n_keys, seed, spoil=None):
+def _check(heads, head_dim, n_q, n_keys, seed, spoil=None, streamed=True):
     g = torch.Generator(device="cuda").manual_seed(seed)
     q, k, v = (torch.empty((n, heads, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
                for n in (n_q, n_keys, n_keys))
@@ -26,7 +30,12 @@ def _check(heads, head_dim, n_q, n_keys, seed, spoil=None):
     prompt = B.Prompt(1, heads, head_dim, n_keys)
     prompt.recache(0, k, v)
     out = torch.full_like(q, 7.0)
-    prompt.cross_attn(0, q, out)
+    if streamed:
+        B.set_attn_variant({n: v for v, n in B.attn_variant_names().items()}[f"d{head_dim}_stream16_qscale"])
+    try:
+        prompt.cross_attn(0, q, out)
+    finally:
+        B.set_attn_variant(0)
     torch.cuda.synchronize()
     prompt.close()
     want = _reference(q, k, v)
@@ -34,13 +43,14 @@ def _check(heads, head_dim, n_q, n_keys, seed, spoil=None):
     return out, want, float(err)
 
 
+@pytest.mark.parametrize("streamed", [True, False])
 @pytest.mark.parametrize("heads, head_dim", [(2, 64), (3, 128)])
 @pytest.mark.parametrize("n_keys", [1, 31, 33, 64, 97, 128, 225, 256, 257, 289, 511, 1000])
 @pytest.mark.parametrize("n_q", [1, 33, 64, 95])
-def test_shares_of_every_length(heads, head_dim, n_q, n_keys):
+def test_shares_of_every_length(heads, head_dim, n_q, n_keys, streamed):
     """bf16 operands and weights: half a unit in the last place (2^-9) on q', on the weights and on the result, in
     quadrature about 2.9e-3; up to 5e-3 where few keys leave nothing to average over."""
-    _, _, err = _check(heads, head_dim, n_q, n_keys, 1000 * n_q + n_keys)
+    _, _, err = _check(heads, head_dim, n_q, n_keys, 1000 * n_q + n_keys, streamed=streamed)
     assert err <= 5e-3
 
 
@@ -50,15 +60,42 @@ def test_two_groups(n_keys):
     assert err <= 5e-3
 
 
+@pytest.mark.parametrize("streamed", [True, False])
 @pytest.mark.parametrize("heads, head_dim, n_q", [(2, 64, 70), (3, 128, 70), (24, 128, 1170)])
-@pytest.mark.parametrize("at", [3, 300, 511])
-def test_a_score_far_above_one_groups_reference(heads, head_dim, n_q, at):
+@pytest.mark.parametrize("at", [3, 200, 300, 511])
+def test_a_score_far_above_one_groups_reference(heads, head_dim, n_q, at, streamed):
     """Key `at` is 40 times query 5: its logit exceeds every other of that row by some 40 sqrt(D), beyond what a fixed
     reference holds, and the whole weight of the row lies in one group."""
     def spoil(q, k):
         k[at] = 40 * q[5]
 
-    out, want, _ = _check(heads, head_dim, n_q, 512, at, spoil)
+    n_keys = 512 if streamed or head_dim == 64 or at > 255 else 256
+    out, want, _ = _check(heads, head_dim, n_q, n_keys, at, spoil, streamed)
     assert bool(torch.isfinite(out).all())
     row = want[5]
     assert float((out[5].double() - row).norm() / row.norm()) <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("heads, head_dim, n_keys", [(12, 128, 200), (300, 64, 33), (7, 64, 512)])
+def test_resident_keys_over_many_rows(heads, head_dim, n_keys):
+    """Several blocks of rows per wave, and more heads than CUs."""
+    _, _, err = _check(heads, head_dim, 9001, n_keys, n_keys, streamed=False)
+    assert err <= 5e-3
+
+
+@pytest.mark.parametrize("head_dim, n_keys", [(128, 256), (64, 400)])
+def test_resident_keys_ignore_a_longer_prompt_before(head_dim, n_keys):
+    """NaN keys and values of an earlier, longer prompt lie behind the last key of this one; in place."""
+    heads, n_q = 3, 100
+    prompt = B.Prompt(1, heads, head_dim, 512)
+    bad = torch.full((512, heads, head_dim), float("nan"), dtype=torch.bfloat16, device="cuda")
+    prompt.recache(0, bad, bad)
+    g = torch.Generator(device="cuda").manual_seed(n_keys)
+    q, k, v = (torch.empty((n, heads, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+               for n in (n_q, n_keys - 7, n_keys - 7))
+    prompt.recache(0, k, v)
+    want = _reference(q, k, v)
+    prompt.cross_attn(0, q, q)
+    torch.cuda.synchronize()
+    prompt.close()
+    assert float((q.double() - want).norm() / want.norm()) <= 5e-3
