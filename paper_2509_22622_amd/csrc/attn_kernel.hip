@@ -336,9 +336,10 @@ bool attn_variant_applies_scale(int v) {
 // groups cost is LDS and L2 traffic: a kblock that goes into LDS serves 256 / G rows, so a step takes longer, the more
 // so the more workgroups run.  A step's length relative to one group's, with n workgroups at work, as measured at
 // 4 to 24 heads and 180 to 1560 rows over 2 to 634 kblocks (us per step with one group: 0.56 at head_dim 128, 0.41
-// at 64):  a_G + n / b_G.  At 1170 rows x 183 kblocks x 12 heads x 128: 114 us with one group, 71 with two, 54 with four.
+// at 64):  a_G + n / b_G.  A workgroup also takes about ten steps' time before its first step and after its last (its
+// arguments, the first loads, the results' way out), which every round of workgroups pays.  At 1170 rows x 183 kblocks x 12 heads x 128: 114 us with one group, 71 with two, 54 with four.
 static int key_groups_log2(const AttnVariant& v, const AttnParams& p) {
-    constexpr int CUS = 256;
+    constexpr int CUS = 256, AROUND = 10;
     struct Step { double a, b; };
     static constexpr Step steps128[4] = {{1.0, 1300}, {1.1, 900}, {1.35, 650}, {0, 1}};
     static constexpr Step steps64[4] = {{1.0, 1300}, {1.05, 1300}, {1.2, 1500}, {1.6, 800}};
@@ -355,11 +356,12 @@ static int key_groups_log2(const AttnVariant& v, const AttnParams& p) {
             work += t * len;
             longest = std::max(longest, len);
         }
-        // equal workgroups run in whole rounds; of unequal ones the last to finish is half a workgroup behind the mean
-        double n_steps = double(longest);
-        if (tiles > CUS) n_steps = p.n_chunks == 1 ? double((tiles + CUS - 1) / CUS) * longest : double(work) / CUS + 0.5 * longest;
         const Step& s = (v.D == 128 ? steps128 : steps64)[lg];
-        const double cost = n_steps * (s.a + double(std::min<int64_t>(tiles, CUS)) / s.b);
+        const double step = s.a + double(std::min<int64_t>(tiles, CUS)) / s.b, one = longest * step + AROUND;
+        // equal workgroups run in whole rounds; of unequal ones the last to finish is half a workgroup behind the mean
+        double cost = one;
+        if (tiles > CUS)
+            cost = p.n_chunks == 1 ? double((tiles + CUS - 1) / CUS) * one : (work * step + double(tiles) * AROUND) / CUS + 0.5 * one;
         if (lg == 0 || cost < best_cost) {
             best = lg;
             best_cost = cost;
@@ -399,7 +401,9 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     int grid = ((total + 7) / 8) * 8;           // the kernels spread their workgroups over the 8 XCDs
     p.n_groups = 0;
     const int groups = p.H * p.n_chunks;
-    if (variant > kNumSimple && p.n_chunks > 1 && groups >= 16 && groups <= MAX_XCD_GROUPS) {   // every kernel but the simple ones reads the placement
+    // (every kernel but the simple ones reads the placement; a launch of one round is better dealt out evenly: whole
+    // groups can give one XCD more tiles than it has CUs)
+    if (variant > kNumSimple && p.n_chunks > 1 && total > 256 && groups >= 16 && groups <= MAX_XCD_GROUPS) {
         // Tiles of different chunks differ in length, and the hardware binds workgroup b to XCD b % 8: hand each
         // XCD whole (head, chunk) groups so that all carry the same number of kblock steps (longest group to the
         // least loaded XCD), and let each start with its longest tiles.
