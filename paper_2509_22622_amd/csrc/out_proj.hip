@@ -18,11 +18,14 @@
 // Formulation, as in the attention kernels: the transposed product y^T = w x^T on 16x16x32 MFMAs.
 //   A: w fragment (n block, k-step), B: x fragment (m block, k-step), same order of the 32 contraction indices in both
 //   C: lane (g, c) register j = y[m0 + c][n0 + 4 g + j]: four neighbouring output features, one 8-byte store.
-// A workgroup of 8 waves (two per SIMD) owns a 256 x 128 tile of y (each wave 64 x 64: 16 accumulator blocks) and
-// walks K in steps of 64 through a ring of three LDS stages filled by direct-to-LDS loads two steps ahead: a step is
-// 48 fragments (16 of w, 32 of x), six loads per wave, and 32 MFMAs per wave; one barrier per step.  Every w fragment
+// A workgroup of 8 waves (two per SIMD) owns a tile of y, 256 x 128 where there are rows enough (each wave 64 x 64: 16
+// accumulator blocks; smaller tiles below, at launch_out_proj), and walks K in steps of 64 through a ring of three LDS
+// stages filled by direct-to-LDS loads two steps ahead: a step is 48 fragments (16 of w, 32 of x), six loads per wave, and
+// 32 MFMAs per wave; one barrier per step (steps of 32 through six stages take the same time).  Every w fragment
 // is read from LDS by four waves, every x fragment by two.
 #include "kernels.h"
+
+#include <algorithm>
 
 namespace ll {
 
@@ -33,14 +36,20 @@ typedef float op_f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned op_u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned op_u32x2 __attribute__((ext_vector_type(2)));
 
-// (steps of 32 through six stages, five ahead, take the same time)
-constexpr int OP_BM = 256, OP_BN = 128, OP_BK = 64, OP_STAGES = 3, OP_AHEAD = OP_STAGES - 1, OP_WAVES = 8;
-constexpr int OP_SUBS = OP_BK / 32;                             // k-steps of 32 per stage
-constexpr int OP_WFRAGS = OP_BN / 16 * OP_SUBS;                 // 1 KB fragments per stage: 16 of w,
-constexpr int OP_FRAGS = OP_WFRAGS + OP_BM / 16 * OP_SUBS;      // then 32 of x
-constexpr int OP_STAGE_BYTES = OP_FRAGS * 1024;
-constexpr int OP_LPW = OP_FRAGS / OP_WAVES;                     // fragments a wave loads per stage
-static_assert(OP_FRAGS % OP_WAVES == 0 && OP_STAGES == OP_AHEAD + 1 && OP_STAGES * OP_STAGE_BYTES <= 160 * 1024, "ring of the output projection");
+constexpr int OP_WAVES = 8;
+// A tile shape: BM x BN outputs per workgroup, WM x WN waves, K in steps of BK through STAGES stages.
+template <int BM_, int BN_, int BK_, int STAGES_, int WM_, int WN_>
+struct OpTile {
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_, WM = WM_, WN = WN_;
+    static constexpr int SUBS = BK / 32;                        // k-steps of 32 per stage
+    static constexpr int WFRAGS = BN / 16 * SUBS;               // 1 KB fragments per stage: of w,
+    static constexpr int FRAGS = WFRAGS + BM / 16 * SUBS;       // then of x
+    static constexpr int STAGE_BYTES = FRAGS * 1024, LDS_BYTES = STAGES * STAGE_BYTES;
+    static constexpr int LPW = FRAGS / OP_WAVES;                // fragments a wave loads per stage
+    static constexpr int AHEAD = STAGES - 1;
+    static constexpr int MB = BM / 16 / WM, NB = BN / 16 / WN;  // 16 x 16 blocks of a wave
+    static_assert(WM * WN == OP_WAVES && FRAGS % OP_WAVES == 0 && LDS_BYTES <= 160 * 1024 && MB >= 1 && NB >= 1, "tile of the output projection");
+};
 
 // s_waitcnt that only waits for vector-memory loads: at most N outstanding
 template <int N>
@@ -48,12 +57,16 @@ __device__ __forceinline__ void op_wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+template <typename Tile>
 __global__ __launch_bounds__(64 * OP_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ll_out_proj_kernel(const OutProjParams p) {
+    constexpr int OP_BM = Tile::BM, OP_BN = Tile::BN, OP_BK = Tile::BK, OP_STAGES = Tile::STAGES, OP_AHEAD = Tile::AHEAD;
+    constexpr int OP_SUBS = Tile::SUBS, OP_WFRAGS = Tile::WFRAGS, OP_STAGE_BYTES = Tile::STAGE_BYTES, OP_LPW = Tile::LPW;
+    constexpr int MB = Tile::MB, NB = Tile::NB;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave & 3, wn = wave >> 2;
+    const int wm = wave % Tile::WM, wn = wave / Tile::WM;
     // Workgroup b runs on XCD b % 8, each with its own L2: every XCD takes one contiguous run of tiles, weight blocks
     // fastest, so that the tiles it has in flight share a few row blocks of x (read once per XCD, then from its L2 for
     // every weight block) and walk the weight together.
@@ -86,11 +99,11 @@ void ll_out_proj_kernel(const OutProjParams p) {
                                              (__attribute__((address_space(3))) void*)(stage + (wave + OP_WAVES * l) * 1024), 16, 0, 0);
     };
 
-    op_f32x4 acc[4][4];                          // [n block][m block]
+    op_f32x4 acc[NB][MB];                        // [n block][m block]
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < NB; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = op_f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < MB; ++b) acc[a][b] = op_f32x4{0.f, 0.f, 0.f, 0.f};
 
 #pragma unroll
     for (int j = 0; j < OP_AHEAD; ++j) issue(j);
@@ -101,32 +114,32 @@ void ll_out_proj_kernel(const OutProjParams p) {
         asm volatile("s_barrier" ::: "memory");
         issue(kt + OP_AHEAD);
         const char* st = lds + (kt % OP_STAGES) * OP_STAGE_BYTES + lane * 16;
-        op_u32x4 wf[OP_SUBS][4], xf[OP_SUBS][4];
+        op_u32x4 wf[OP_SUBS][NB], xf[OP_SUBS][MB];
 #pragma unroll
         for (int sub = 0; sub < OP_SUBS; ++sub) {
 #pragma unroll
-            for (int a = 0; a < 4; ++a) wf[sub][a] = *reinterpret_cast<const op_u32x4*>(st + ((wn * 4 + a) * OP_SUBS + sub) * 1024);
+            for (int a = 0; a < NB; ++a) wf[sub][a] = *reinterpret_cast<const op_u32x4*>(st + ((wn * NB + a) * OP_SUBS + sub) * 1024);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) xf[sub][b] = *reinterpret_cast<const op_u32x4*>(st + (OP_WFRAGS + (wm * 4 + b) * OP_SUBS + sub) * 1024);
+            for (int b = 0; b < MB; ++b) xf[sub][b] = *reinterpret_cast<const op_u32x4*>(st + (OP_WFRAGS + (wm * MB + b) * OP_SUBS + sub) * 1024);
         }
 #pragma unroll
         for (int sub = 0; sub < OP_SUBS; ++sub)
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int a = 0; a < NB; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
+                for (int b = 0; b < MB; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(op_bf16x8, wf[sub][a]),
                                                                         __builtin_bit_cast(op_bf16x8, xf[sub][b]), acc[a][b], 0, 0, 0);
     }
     op_wait_vmcnt<0>();                          // the loads issued past the end have landed before the wave leaves
 
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const int row = m0 + wm * 64 + 16 * b + r;
+    for (int b = 0; b < MB; ++b) {
+        const int row = m0 + (wm * MB + b) * 16 + r;
         if (row >= p.M) continue;
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const int col = n0 + wn * 64 + 16 * a + 4 * g;
+        for (int a = 0; a < NB; ++a) {
+            const int col = n0 + (wn * NB + a) * 16 + 4 * g;
             if (col >= p.N) continue;            // N is a multiple of 16: a group of four is inside or outside
             const op_f32x2 lo = {acc[a][b][0], acc[a][b][1]}, hi = {acc[a][b][2], acc[a][b][3]};
             const op_u32x2 o = {__builtin_bit_cast(unsigned, __builtin_convertvector(lo, op_bf16x2)),
@@ -157,20 +170,47 @@ hipError_t launch_pack_out_weight(const uint16_t* w, uint16_t* w_frag, int N, in
     return hipGetLastError();
 }
 
-hipError_t launch_out_proj(const OutProjParams& p, hipStream_t s) {
-    if (p.M < 1 || p.N < 16 || p.N % 16 != 0 || p.K < OP_BK || p.K % OP_BK != 0) return hipErrorInvalidValue;   // K = H * D, D 64 or 128
-    const int64_t tiles = int64_t((p.M + OP_BM - 1) / OP_BM) * ((p.N + OP_BN - 1) / OP_BN);
+template <typename Tile>
+static hipError_t launch_tile(const OutProjParams& p, hipStream_t s) {
+    const int64_t tiles = int64_t((p.M + Tile::BM - 1) / Tile::BM) * ((p.N + Tile::BN - 1) / Tile::BN);
     if (tiles > 0x7FFFFFFF) return hipErrorInvalidValue;
-    constexpr int lds_bytes = OP_STAGES * OP_STAGE_BYTES;
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ll_out_proj_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ll_out_proj_kernel<Tile>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, Tile::LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL(ll_out_proj_kernel, dim3(unsigned((tiles + 7) / 8 * 8)), dim3(64 * OP_WAVES), lds_bytes, s, p);
+    hipLaunchKernelGGL(ll_out_proj_kernel<Tile>, dim3(unsigned((tiles + 7) / 8 * 8)), dim3(64 * OP_WAVES), Tile::LDS_BYTES, s, p);
     return hipGetLastError();
+}
+
+using OpTile256x128 = OpTile<256, 128, 64, 3, 4, 2>;
+using OpTile128x128 = OpTile<128, 128, 64, 3, 4, 2>;
+using OpTile128x64 = OpTile<128, 64, 64, 5, 4, 2>;
+using OpTile64x64 = OpTile<64, 64, 64, 6, 4, 2>;
+
+// Time of a launch in us as measured (60 to 23400 rows, 128 to 3072 features): rounds of workgroups over the CUs, each a
+// walk over K whose step takes `alone` us with few workgroups on the chip and `more` longer with all CUs at work.
+template <typename Tile>
+static double tile_us(const OutProjParams& p, double alone, double more) {
+    const int64_t tiles = int64_t((p.M + Tile::BM - 1) / Tile::BM) * ((p.N + Tile::BN - 1) / Tile::BN);
+    return double((tiles + 255) / 256) * (p.K / Tile::BK) * (alone + more * double(std::min<int64_t>(tiles, 256)) / 256);
+}
+
+// The largest tile asks least of L2 and is the best one where there are enough of them; a launch of few rows leaves most
+// CUs idle with it while the others walk all of K at 1 us a step.  The sums run over K in the same order in every tile shape:
+// the results do not depend on it.  us with 256 x 128 tiles and with the tile taken, 12 heads x 128: 60 rows 24 -> 8,
+// 300 28 -> 9, 1200 27 -> 14, 2400 29 -> 19, 4680 32 (228 tiles) either way.
+hipError_t launch_out_proj(const OutProjParams& p, hipStream_t s) {
+    if (p.M < 1 || p.N < 16 || p.N % 16 != 0 || p.K < 64 || p.K % 64 != 0) return hipErrorInvalidValue;   // K = H * D, D 64 or 128
+    const double t0 = tile_us<OpTile256x128>(p, 1.03, 0.14), t1 = tile_us<OpTile128x128>(p, 0.62, 0.10);
+    const double t2 = tile_us<OpTile128x64>(p, 0.36, 0.04), t3 = tile_us<OpTile64x64>(p, 0.21, 0.07);
+    const double best = std::min(std::min(t0, t1), std::min(t2, t3));
+    if (best == t0) return launch_tile<OpTile256x128>(p, s);
+    if (best == t1) return launch_tile<OpTile128x128>(p, s);
+    if (best == t2) return launch_tile<OpTile128x64>(p, s);
+    return launch_tile<OpTile64x64>(p, s);
 }
 
 }  // namespace ll

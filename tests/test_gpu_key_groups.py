@@ -99,3 +99,33 @@ def test_resident_keys_ignore_a_longer_prompt_before(head_dim, n_keys):
     torch.cuda.synchronize()
     prompt.close()
     assert float((q.double() - want).norm() / want.norm()) <= 5e-3
+
+
+@pytest.mark.parametrize("heads, head_dim, n_q", [(1, 64, 1), (3, 64, 65), (1, 128, 4160), (12, 128, 63), (12, 128, 700),
+                                                  (12, 128, 2500), (5, 128, 9100), (5, 64, 25000)])
+def test_projection_tiles(heads, head_dim, n_q):
+    """The projection's tile shapes (64 x 64, 128 x 64, 128 x 128, 256 x 128, by rows and features), ragged in both
+    directions: an identity weight returns the attention output bit for bit, a random one the product in 64 bits to
+    one bf16 rounding (2^-9 relative)."""
+    g = torch.Generator(device="cuda").manual_seed(n_q)
+    n = heads * head_dim
+    prompt = B.Prompt(1, heads, head_dim, 64)
+    k, v, q = (torch.empty((m, heads, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for m in (50, 50, n_q))
+    prompt.recache(0, k, v)
+    attn = torch.empty_like(q)
+    prompt.cross_attn(0, q, attn)
+    workspace = torch.empty(prompt.cross_attn_out_workspace_bytes(n_q), dtype=torch.uint8, device="cuda")
+    y = torch.full((n_q, n), 7.0, dtype=torch.bfloat16, device="cuda")
+    eye = torch.eye(n, dtype=torch.bfloat16, device="cuda")
+    w = torch.empty((n, n), dtype=torch.bfloat16, device="cuda").normal_(0, n ** -0.5, generator=g)
+    packed = torch.empty_like(w)
+    for weight in (eye, w):
+        prompt.pack_out_weight(weight, packed)
+        prompt.cross_attn_out(0, q, packed, workspace, y)
+        torch.cuda.synchronize()
+        want = attn.view(n_q, n).double() @ weight.double().T
+        if weight is eye:
+            assert torch.equal(y.view(torch.int16), attn.view(n_q, n).view(torch.int16))
+        else:
+            assert float((y.double() - want).norm() / want.norm()) <= 2.0 ** -9
+    prompt.close()
