@@ -323,7 +323,6 @@ ll_status ll_clip_backward(ll_clip* clip, const void* dout, void* dq, void* dk, 
     if (e == hipSuccess) e = clip_write_pair(c, dO, qrot, rows, clip_u16(c, c->o_cd), c->kb_clip, c->hs_clip, s);   // dO K-style, q'^T
     if (e != hipSuccess) return hip_fail(e, "clip backward preparation kernels launch");
     const int64_t v_off_all = c->kb_all * KBLOCK * c->D, v_off_clip = c->kb_clip * KBLOCK * c->D;
-    const int cols = bwd_tile_cols(c->D);
     // 2. Gq: queries as columns, chunk by chunk over each chunk's key ranges
     const int n_chunks = (n_clip + c->C - 1) / c->C;
     for (int base = 0; base < n_chunks; base += MAX_BWD_GROUPS) {
@@ -336,19 +335,17 @@ ll_status ll_clip_backward(ll_clip* clip, const void* dout, void* dq, void* dk, 
         p.g1 = clip_f32(c, c->o_gq);
         p.H = c->H; p.D = c->D;
         const int m = std::min(MAX_BWD_GROUPS, n_chunks - base);
-        int tiles = 0;
         for (int i = 0; i < m; ++i) {
             const int ci = base + m - 1 - i;
             const int64_t f0 = clip_start + int64_t(ci) * c->C;
             const int n = int(std::min<int64_t>(c->C, clip_start + n_clip - f0));
             const std::vector<SlotRange> ranges = clip_key_ranges(c, f0, n);
             BwdGroup& g = p.group[i];
-            g.c_begin = ci * c->C * c->P; g.c_end = g.c_begin + n * c->P; g.tile_begin = tiles;
+            g.c_begin = ci * c->C * c->P; g.c_end = g.c_begin + n * c->P;
             g.n_ranges = int(ranges.size());
             for (int r = 0; r < g.n_ranges; ++r) { g.rs[r] = int(ranges[r].begin); g.re[r] = int(ranges[r].end); }
-            tiles += (g.c_end - g.c_begin + cols - 1) / cols;
         }
-        p.n_groups = m; p.n_tiles = tiles;
+        p.n_groups = m;
         e = launch_bwd_dq(p, s);
         if (e != hipSuccess) return hip_fail(e, "dQ kernel launch");
     }
@@ -387,13 +384,8 @@ ll_status ll_clip_backward(ll_clip* clip, const void* dout, void* dq, void* dk, 
         // longest streams first
         std::vector<BwdGroup> part(groups.begin() + base, groups.begin() + base + m);
         std::stable_sort(part.begin(), part.end(), [](const BwdGroup& a, const BwdGroup& b) { return a.re[0] - a.rs[0] > b.re[0] - b.rs[0]; });
-        int tiles = 0;
-        for (int i = 0; i < m; ++i) {
-            p.group[i] = part[i];
-            p.group[i].tile_begin = tiles;
-            tiles += (part[i].c_end - part[i].c_begin + cols - 1) / cols;
-        }
-        p.n_groups = m; p.n_tiles = tiles;
+        for (int i = 0; i < m; ++i) p.group[i] = part[i];
+        p.n_groups = m;
         e = launch_bwd_dkv(p, s);
         if (e != hipSuccess) return hip_fail(e, "dK/dV kernel launch");
     }

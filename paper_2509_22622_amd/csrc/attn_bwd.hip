@@ -149,7 +149,7 @@ __device__ inline void bw_load_kstyle_row(const uint16_t* region, int64_t slot, 
 
 // ---------------------------------------------------------------------------------------------------------------
 template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dq_kernel(const BwdParams p) {
+__device__ __forceinline__ void bw_dq(const BwdParams& p) {
     constexpr int KS = D / 16, DB = D / 32;
     constexpr int KB_BYTES = KBLOCK * D * 2;
     constexpr int NREG = 3;                           // streamed regions per block
@@ -198,8 +198,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     auto issue = [&](int kblk, int stage) {
 #pragma unroll
         for (int l = 0; l < LPW; ++l) {
-            static_assert(FPR == NW && LPW == NREG, "wave w loads fragment w of every region");
-            const int region = l, fr = wave_u;
+            static_assert(FPR % NW == 0, "wave w loads fragments w, w + NW, .. of every region");
+            const int region = l / (FPR / NW), fr = wave_u + NW * (l % (FPR / NW));
             char* to = lds + (stage * NREG + region) * KB_BYTES + fr * 1024;
             bw_load_lds16(rsrc[region], to, lane * 16, kblk * KB_BYTES + fr * 1024);
         }
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
 // ---------------------------------------------------------------------------------------------------------------
 template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dkv_kernel(const BwdParams p) {
+__device__ __forceinline__ void bw_dkv(const BwdParams& p) {
     constexpr int KS = D / 16, DB = D / 32;
     constexpr int KB_BYTES = KBLOCK * D * 2;
     constexpr int NREG = 4;
@@ -374,8 +374,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     auto issue = [&](int blk_i, int stage) {
 #pragma unroll
         for (int l = 0; l < LPW; ++l) {
-            static_assert(FPR == NW && LPW == NREG, "wave w loads fragment w of every region");
-            const int region = l, fr = wave_u;
+            static_assert(FPR % NW == 0, "wave w loads fragments w, w + NW, .. of every region");
+            const int region = l / (FPR / NW), fr = wave_u + NW * (l % (FPR / NW));
             char* to = lds + stage * STAGE_BYTES + region * KB_BYTES + fr * 1024;
             bw_load_lds16(rsrc[region], to, lane * 16, blk_i * KB_BYTES + fr * 1024);
         }
@@ -500,6 +500,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
 }
 
+// One workgroup per (head, column tile).  The narrow form (128 columns at head_dim 128 instead of 256) is for launches with
+// too few wide tiles to fill the chip: twice the workgroups of one wave per SIMD instead of two, and a wave alone on its SIMD
+// takes a block in about two thirds of the time.
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dq_kernel(const BwdParams p) { bw_dq<D, NW>(p); }
+template <int D, int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dkv_kernel(const BwdParams p) { bw_dkv<D, NW>(p); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dq_narrow_kernel(const BwdParams p) { bw_dq<128, 4>(p); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dkv_narrow_kernel(const BwdParams p) { bw_dkv<128, 4>(p); }
+
 // ---------------------------------------------------------------------------------------------------------------
 // delta[head][row] = sum_d dO[row][head][d] * O[row][head][d], O being the forward's output before its rounding to
 // bf16; D / 8 lanes per (row, head), 8 features each.
@@ -573,41 +583,49 @@ static hipError_t set_lds(const void* fn, int bytes, bool& done) {
     return e;
 }
 
-// Columns per workgroup: 8 waves (one staged block serves 256 columns) where a kblock splits over 512 threads.
-int bwd_tile_cols(int D) { return D == 128 ? 256 : 128; }
+// Tiles of `cols` columns per workgroup: fills in tile_begin of the groups and n_tiles.
+static int64_t plan_tiles(BwdParams& p, int cols) {
+    p.n_tiles = 0;
+    for (int i = 0; i < p.n_groups; ++i) {
+        p.group[i].tile_begin = p.n_tiles;
+        p.n_tiles += (p.group[i].c_end - p.group[i].c_begin + cols - 1) / cols;
+    }
+    return int64_t(p.n_tiles) * p.H;
+}
+// head_dim 128: narrow tiles where even they fit the 256 CUs in one round (the whole step of a
+// 15-frame clip of 189 tokens x 2 heads 328 -> 250 us with the forward's part, 9 frames of 301 x 3 387 -> 285).
+static bool narrow_tiles(BwdParams& p) { return p.D == 128 && plan_tiles(p, 128) <= 256; }
 
-hipError_t launch_bwd_dq(const BwdParams& p, hipStream_t s) {
-    const int total = p.n_tiles * p.H;
-    if (total <= 0) return hipSuccess;
-    const int grid = ((total + 7) / 8) * 8, lds = BW_DQ_NS * 3 * KBLOCK * p.D * 2;
-    static bool done128 = false, done64 = false;
-    if (p.D == 128) {
-        hipError_t e = set_lds(reinterpret_cast<const void*>(ll_bwd_dq_kernel<128, 8>), lds, done128);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((ll_bwd_dq_kernel<128, 8>), dim3(grid), dim3(512), lds, s, p);
-    } else if (p.D == 64) {
-        hipError_t e = set_lds(reinterpret_cast<const void*>(ll_bwd_dq_kernel<64, 4>), lds, done64);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((ll_bwd_dq_kernel<64, 4>), dim3(grid), dim3(256), lds, s, p);
-    } else return hipErrorInvalidValue;
+template <typename Kernel>
+static hipError_t launch_bwd(Kernel kernel, const BwdParams& p, int waves, int lds, bool& done, hipStream_t s) {
+    hipError_t e = set_lds(reinterpret_cast<const void*>(kernel), lds, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((p.n_tiles * p.H + 7) / 8 * 8), dim3(64 * waves), lds, s, p);
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_dkv(const BwdParams& p, hipStream_t s) {
-    const int total = p.n_tiles * p.H;
-    if (total <= 0) return hipSuccess;
-    const int grid = ((total + 7) / 8) * 8, lds = BW_DKV_NS * (4 * KBLOCK * p.D * 2 + 256);
-    static bool done128 = false, done64 = false;
-    if (p.D == 128) {
-        hipError_t e = set_lds(reinterpret_cast<const void*>(ll_bwd_dkv_kernel<128, 8>), lds, done128);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((ll_bwd_dkv_kernel<128, 8>), dim3(grid), dim3(512), lds, s, p);
-    } else if (p.D == 64) {
-        hipError_t e = set_lds(reinterpret_cast<const void*>(ll_bwd_dkv_kernel<64, 4>), lds, done64);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((ll_bwd_dkv_kernel<64, 4>), dim3(grid), dim3(256), lds, s, p);
-    } else return hipErrorInvalidValue;
-    return hipGetLastError();
+hipError_t launch_bwd_dq(const BwdParams& p_in, hipStream_t s) {
+    BwdParams p = p_in;
+    if (p.D != 128 && p.D != 64) return hipErrorInvalidValue;
+    const bool narrow = narrow_tiles(p);
+    if (plan_tiles(p, p.D == 128 && !narrow ? 256 : 128) <= 0) return hipSuccess;
+    const int lds = BW_DQ_NS * 3 * KBLOCK * p.D * 2;
+    static bool done[3] = {};
+    if (narrow) return launch_bwd(ll_bwd_dq_narrow_kernel, p, 4, lds, done[0], s);
+    if (p.D == 128) return launch_bwd(ll_bwd_dq_kernel<128, 8>, p, 8, lds, done[1], s);
+    return launch_bwd(ll_bwd_dq_kernel<64, 4>, p, 4, lds, done[2], s);
+}
+
+hipError_t launch_bwd_dkv(const BwdParams& p_in, hipStream_t s) {
+    BwdParams p = p_in;
+    if (p.D != 128 && p.D != 64) return hipErrorInvalidValue;
+    const bool narrow = narrow_tiles(p);
+    if (plan_tiles(p, p.D == 128 && !narrow ? 256 : 128) <= 0) return hipSuccess;
+    const int lds = BW_DKV_NS * (4 * KBLOCK * p.D * 2 + 256);
+    static bool done[3] = {};
+    if (narrow) return launch_bwd(ll_bwd_dkv_narrow_kernel, p, 4, lds, done[0], s);
+    if (p.D == 128) return launch_bwd(ll_bwd_dkv_kernel<128, 8>, p, 8, lds, done[1], s);
+    return launch_bwd(ll_bwd_dkv_kernel<64, 4>, p, 4, lds, done[2], s);
 }
 
 hipError_t launch_bwd_delta(const float* out, const uint16_t* dout, float* delta, int rows, int H, int D,

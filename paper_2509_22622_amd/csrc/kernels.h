@@ -173,7 +173,7 @@ struct ReadFrameParams {
 constexpr int MAX_BWD_GROUPS = 32;
 struct BwdGroup {                // column tiles that share one set of streamed rows
     int c_begin, c_end;          // columns: query rows (dQ kernel) or clip-token indices of keys (dK/dV kernel)
-    int tile_begin;              // first tile (bwd_tile_cols columns) of the group in the launch
+    int tile_begin;              // first tile of the group in the launch (filled in by launch_bwd_*)
     int n_ranges;
     int rs[2], re[2];            // streamed rows: key token slots (dQ kernel), query rows (dK/dV kernel: one range)
 };
@@ -189,7 +189,8 @@ struct BwdParams {
     int64_t hc_k1, hc_k2, col_slot0;
     float* g1;                   // fp32 [rows, H, D]: Gq (dQ kernel) or Gk (dK/dV kernel)
     uint16_t* dv;                // dK/dV kernel: bf16 [rows, H, D]
-    int H, D, n_groups, n_tiles;
+    int H, D, n_groups;
+    int n_tiles;                 // filled in by launch_bwd_*
     BwdGroup group[MAX_BWD_GROUPS];
 };
 struct BwdFinishParams {
@@ -200,7 +201,6 @@ struct BwdFinishParams {
     int64_t frame0;              // absolute index of the first frame
     float q_mul, k_mul;          // 1/sqrt(D), ln 2
 };
-int bwd_tile_cols(int D);     // columns per workgroup of the two kernels below
 hipError_t launch_bwd_dq(const BwdParams& p, hipStream_t s);
 hipError_t launch_bwd_dkv(const BwdParams& p, hipStream_t s);
 hipError_t launch_bwd_delta(const float* out32, const uint16_t* dout, float* delta, int rows, int H, int D,

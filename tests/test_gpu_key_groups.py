@@ -129,3 +129,30 @@ def test_projection_tiles(heads, head_dim, n_q):
         else:
             assert float((y.double() - want).norm() / want.norm()) <= 2.0 ** -9
     prompt.close()
+
+
+@pytest.mark.parametrize("heads, grid, n_clip", [(1, (5, 13), 5), (3, (9, 13), 4)])
+def test_narrow_backward_tiles(heads, grid, n_clip):
+    """Small clips at head_dim 128 take backward tiles of 128 columns: key sets and rows that are no multiple of 32 or 128,
+    several chunks, against the gradients in 64 bits.  Five bf16 roundings on a gradient's way (2^-9 / sqrt(3) x 2 each in
+    relative 2-norm): sqrt(5) x 2.26e-3 = 5.0e-3."""
+    D, C, S, W, ctx = 128, 2, 2, 3, 7
+    P = grid[0] * grid[1]
+    g = torch.Generator(device="cuda").manual_seed(heads)
+    make = lambda n: torch.empty((n * P, heads, D), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    q, dout, k, v = make(n_clip), make(n_clip), make(S + W + n_clip), make(S + W + n_clip)
+    clip = B.Clip(heads, D, *grid, C, S, W, n_clip)
+    out, dq, dk, dv = (torch.empty_like(q) for _ in range(4))
+    clip.forward(ctx, W, n_clip, q, k, v, out)
+    clip.backward(dout, dq, dk, dv)
+    torch.cuda.synchronize()
+    clip.close()
+
+    from oracle.clip_backward import ClipOracle
+    from oracle.longlive_oracle import OracleConfig
+    oracle = ClipOracle(OracleConfig(1, heads, D, *grid, C, S, W))
+    host = lambda t: t.double().cpu().numpy()
+    want = (oracle.forward(ctx, W, n_clip, host(q), host(k), host(v)), *oracle.backward(host(dout)))
+    for name, got, ref in zip(("out", "dq", "dk", "dv"), (out, dq, dk, dv), want):
+        ref = torch.from_numpy(ref).cuda()
+        assert float((got.double() - ref).norm() / ref.norm()) <= 5.0e-3, name
