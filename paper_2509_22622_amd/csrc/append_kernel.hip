@@ -49,11 +49,27 @@ __global__ __launch_bounds__(256) void ll_append_kernel(const AppendParams p) {
     const int tid = threadIdx.x;
     const int head = blockIdx.x % p.H;
     const int gseg = blockIdx.x / p.H;
-    // which frame, which segment
-    int fi = 0;
-    while (fi + 1 < p.n_frames && gseg >= p.seg_begin[fi + 1]) ++fi;
-    const int seg = gseg - p.seg_begin[fi];
-    const int64_t slot0 = p.slot[fi];
+    // which frame, which segment: the tables and pointers are fetched in one go (they lie in several cold cache lines)
+    // and searched in registers, instead of one scalar load waiting for another
+    int begin[MAX_APPEND_FRAMES];
+    int64_t slots[MAX_APPEND_FRAMES];
+#pragma unroll
+    for (int i = 0; i < MAX_APPEND_FRAMES; ++i) {
+        begin[i] = p.seg_begin[i];
+        slots[i] = p.slot[i];
+        asm volatile("" ::"s"(begin[i]), "s"(slots[i]));
+    }
+    asm volatile("" ::"s"(p.q), "s"(p.k), "s"(p.v), "s"(p.k_cache), "s"(p.v_cache), "s"(p.head_stride), "s"(p.rope.row_cs), "s"(p.rope.col_cs));
+    int fi = 0, begin_fi = 0;
+    int64_t slot0 = slots[0];
+#pragma unroll
+    for (int i = 1; i < MAX_APPEND_FRAMES; ++i)
+        if (i < p.n_frames && gseg >= begin[i]) {
+            fi = i;
+            begin_fi = begin[i];
+            slot0 = slots[i];
+        }
+    const int seg = gseg - begin_fi;
     const int64_t kb = slot0 / KBLOCK + seg;                       // kblock this segment is in
     const int64_t s_begin = max(slot0, kb * KBLOCK);
     const int64_t s_end = min(slot0 + p.P, (kb + 1) * KBLOCK);
