@@ -134,7 +134,6 @@ struct AttnParams {
     int H, D;
     float scale_log2e;           // factor still to apply to q.k in the log2 domain (1 when q is pre-scaled); only
                                  // the simple kernels and the *_qscale kernels apply it
-    bool keys_reside;            // the one key range may be brought into LDS whole where it fits (attn_resident.hip)
     int n_chunks, n_tiles;       // n_tiles = query tiles over all chunks (filled in by launch_attn)
     // Placement on the 8 XCDs (filled in by launch_attn; workgroup b runs on XCD b % 8).  n_groups == 0: the
     // (head, tile) items are split into 8 contiguous runs.  Otherwise (launches of several chunks, whose tiles
@@ -147,6 +146,7 @@ struct AttnParams {
     int kblock;                  // key slots per kblock: 32 (bf16 cache) or 64 (8-bit cache)
     const double* inv_freq_t;    // frame-axis rotary frequencies [n_t] (used when a chunk has a sink_shift)
     int n_t;
+    bool keys_reside;            // the one key range may be brought into LDS whole where it fits (attn_resident.hip)
     float* lse;                  // *_lse kernels: log2 of each row's sum of 2^score, [H][lse_stride] (null otherwise)
     int64_t lse_stride;
     float* out32;                // *_lse kernels: the output once more in fp32, [rows, H, D] (null: not wanted)
