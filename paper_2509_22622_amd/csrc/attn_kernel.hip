@@ -313,7 +313,6 @@ int attn_variant_default(int D, int kblock) {
     if (kblock == KBLOCK8) return kNumSimple + kNumStreamVariants + (D == 128 ? 1 : 2);
     return first_stream16() + (D == 128 ? 0 : 1);
 }
-int attn_variant_qtile(int v) { return variant(v)->qtile; }
 bool attn_variant_supports(int v, int D, int kblock) { return variant(v) && variant(v)->D == D && variant(v)->kblock == kblock; }
 // only the software-pipelined bf16 kernels take queries turned back for the sink range (AttnChunk::sink_shift)
 bool attn_variant_sink_shift(int v) {

@@ -229,7 +229,6 @@ extern const int kNumStream16Variants;
 int attn_variant_count();
 const char* attn_variant_name(int v);
 int attn_variant_default(int D, int kblock);
-int attn_variant_qtile(int v);                 // query rows per workgroup (of one key group)
 bool attn_variant_supports(int v, int D, int kblock);
 bool attn_variant_sink_shift(int v);          // the variant honours AttnChunk::sink_shift
 int attn_variant_lse(int D);                   // the variant that also writes AttnParams::lse
