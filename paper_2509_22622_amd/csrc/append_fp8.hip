@@ -116,10 +116,8 @@ __global__ __launch_bounds__(256) void ll_append8_kernel(const AppendParams p) {
             if (pi < n_t) w = t_cs[pi];
             const float qr = a8_bf16_to_f32(qv[it][2 * e]), qi = a8_bf16_to_f32(qv[it][2 * e + 1]);
             const float kr = a8_bf16_to_f32(kv[it][2 * e]), ki = a8_bf16_to_f32(kv[it][2 * e + 1]);
-            qo[2 * e] = (qr * w.x - qi * w.y) * p.q_scale;
-            qo[2 * e + 1] = (qr * w.y + qi * w.x) * p.q_scale;
-            ko[2 * e] = (kr * w.x - ki * w.y) * p.k_mul;
-            ko[2 * e + 1] = (kr * w.y + ki * w.x) * p.k_mul;
+            rope_turn_scaled(qr, qi, w, p.q_scale, qo[2 * e], qo[2 * e + 1]);
+            rope_turn_scaled(kr, ki, w, p.k_mul, ko[2 * e], ko[2 * e + 1]);
         }
         const u32x2 q8 = {a8_pack4(qo[0], qo[1], qo[2], qo[3]), a8_pack4(qo[4], qo[5], qo[6], qo[7])};
         const u32x2 k8 = {a8_pack4(ko[0], ko[1], ko[2], ko[3]), a8_pack4(ko[4], ko[5], ko[6], ko[7])};

@@ -142,12 +142,13 @@ __global__ __launch_bounds__(256) void ll_append_kernel(const AppendParams p) {
             if (turn && pi < n_t) w = t_cs[pi];
             const float qr = bf16_to_f32(qv[it][2 * e]), qi = bf16_to_f32(qv[it][2 * e + 1]);
             const float kr = bf16_to_f32(kv[it][2 * e]), ki = bf16_to_f32(kv[it][2 * e + 1]);
-            float q_re, q_im;
+            float q_re, q_im, k_re, k_im;
             rope_turn_scaled(qr, qi, w, p.q_scale, q_re, q_im);
+            rope_turn_key(kr, ki, w, k_re, k_im);
             qo[2 * e] = f32_to_bf16(q_re);
             qo[2 * e + 1] = f32_to_bf16(q_im);
-            ko[2 * e] = f32_to_bf16(kr * w.x - ki * w.y);
-            ko[2 * e + 1] = f32_to_bf16(kr * w.y + ki * w.x);
+            ko[2 * e] = f32_to_bf16(k_re);
+            ko[2 * e + 1] = f32_to_bf16(k_im);
         }
         if (!turn) ko = kv[it];                                    // unchanged bit for bit, signed zeros included
         if (has_q) *reinterpret_cast<u16x8*>(p.q_out + src) = qo;

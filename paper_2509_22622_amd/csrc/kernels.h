@@ -100,13 +100,19 @@ inline void set_frame_rotation(AppendParams& p, const double* inv_freq_t_host) {
         }
 }
 
-// One rotary pair (re, im) turned by w = (cos, sin) and scaled, in fp32.  The cache-write kernel and the attention
-// kernels that turn their queries on load both go through here, with the contraction fixed by hand, so that they
-// produce the same bits.
+// One rotary pair (re, im) turned by w = (cos, sin) and scaled, in fp32.  Every kernel that turns a query or an 8-bit key
+// goes through here, and the bf16 keys through rope_turn_key, with the contraction into fused multiply-adds fixed by hand:
+// left to the compiler it flips with edits elsewhere in the kernel, and some results then round to the neighbouring value.
 __device__ __forceinline__ void rope_turn_scaled(float re, float im, float2 w, float scale, float& o_re, float& o_im) {
     const float t = im * w.y, u = im * w.x;
     o_re = __builtin_fmaf(re, w.x, -t) * scale;
     o_im = __builtin_fmaf(re, w.y, u) * scale;
+}
+// (the other product of the imaginary part is the rounded one here: these are the bits cached keys have always had)
+__device__ __forceinline__ void rope_turn_key(float re, float im, float2 w, float& o_re, float& o_im) {
+    const float t = im * w.y, u = re * w.y;
+    o_re = __builtin_fmaf(re, w.x, -t);
+    o_im = __builtin_fmaf(im, w.x, u);
 }
 
 struct AttnChunk {

@@ -76,6 +76,22 @@ def test_a_score_far_above_one_groups_reference(heads, head_dim, n_q, at, stream
     assert float((out[5].double() - row).norm() / row.norm()) <= 2.0 ** -8
 
 
+@pytest.mark.parametrize("heads, head_dim, n_q, n_keys", [(2, 64, 70, 1000), (3, 128, 70, 1000), (24, 128, 1170, 700)])
+@pytest.mark.parametrize("lo, hi", [(128, 160), (256, 600), (480, 640)])
+def test_keys_without_weight_where_a_share_begins(heads, head_dim, n_q, n_keys, lo, hi):
+    """Keys [lo, hi) score minus infinity (feature 0 of every query is positive, theirs is -inf): a share of the keys may
+    begin with, or consist of, such keys, and the row is the softmax over the others.  Those score 300 to 500 (log2) below
+    zero, so a share that begins with weightless keys cannot fall back to a reference near zero either."""
+    def spoil(q, k):
+        q[..., :2] = 1
+        k[..., 1] = -3000
+        k[lo:hi, :, 0] = float("-inf")
+
+    out, want, err = _check(heads, head_dim, n_q, n_keys, lo, spoil)
+    assert bool(torch.isfinite(out).all())
+    assert err <= 5e-3
+
+
 @pytest.mark.parametrize("heads, head_dim, n_keys", [(12, 128, 200), (300, 64, 33), (7, 64, 512)])
 def test_resident_keys_over_many_rows(heads, head_dim, n_keys):
     """Several blocks of rows per wave, and more heads than CUs."""
