@@ -161,6 +161,10 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     constexpr int LPW = G == 1 ? NF / NW : PERIOD * NF / NW;    // direct-to-LDS loads per wave, per kblock (per period)
     constexpr int PF = RingPlan::AHEAD;
     constexpr int LAND = RingPlan::LANDED;
+    // A share of the keys may begin with a kblock that scores -inf throughout for some query, although the key set does not:
+    // the pass that follows the maximum then has no reference (mref -inf, scores relative to 0) until a live score comes.
+    // (The fixed-reference pass makes NaN of it, which sends the tile there.)
+    constexpr bool NO_REF = TRACK && G > 1;
     static_assert(NF % NW == 0 && (G == 1 || KS % NW == 0), "fragments must split over the waves");
     static_assert(PF >= LAND && PF + 2 <= NS, "ring too short for the prefetch distance");
 
@@ -385,10 +389,11 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     mask_s(sA, S16_LIVE(vb));
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
-        mref[qb] = col_max(max_s(sA, qb));       // a kblock of a range holds a live key: finite
-        negm[qb] = f32x4{-mref[qb], -mref[qb], -mref[qb], -mref[qb]};
+        mref[qb] = col_max(max_s(sA, qb));       // a kblock of a range holds a live key: finite, unless that key scores -inf
+        const float base = NO_REF && mref[qb] == -INFINITY ? 0.f : mref[qb];
+        negm[qb] = f32x4{-base, -base, -base, -base};
 #pragma unroll
-        for (int m = 0; m < 2; ++m) sA[m][qb] -= mref[qb];
+        for (int m = 0; m < 2; ++m) sA[m][qb] -= base;
         mx[qb] = -INFINITY;
         lsum[qb][0] = lsum[qb][1] = 0.f;
     }
@@ -424,9 +429,11 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
                 }                                                                                                   \
             }                                                                                                       \
             if (TRACK) _Pragma("unroll") for (int qb = 0; qb < 2; ++qb) {                                           \
-                const float delta = fmaxf(col_max(mx[qb]), 0.f);                                                    \
-                const float alpha = __builtin_amdgcn_exp2f(-delta);                                                 \
-                mref[qb] += delta;                                                                                  \
+                const float top = col_max(mx[qb]);                                                                  \
+                const bool first = NO_REF && mref[qb] == -INFINITY;      /* no reference yet: nothing to rescale */ \
+                const float delta = first ? (top == -INFINITY ? 0.f : top) : fmaxf(top, 0.f);                       \
+                const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-delta);                                   \
+                mref[qb] = first ? top : mref[qb] + delta;                                                          \
                 lsum[qb][0] *= alpha;                                                                               \
                 lsum[qb][1] *= alpha;                                                                               \
                 _Pragma("unroll") for (int f = 0; f < NV; ++f) st.o[f][qb] *= alpha;                                \
@@ -510,7 +517,8 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
         if (TRACK) {                                                                                                \
             mx[0] = m_run[0];                                                                                       \
             mx[1] = m_run[1];                                                                                       \
-            vote = __any(fmaxf(mx[0], mx[1]) > S16_RESCALE_SLACK);                                                  \
+            vote = __any(fmaxf(mx[0], mx[1]) > S16_RESCALE_SLACK                                                    \
+                         || (NO_REF && ((mref[0] == -INFINITY && mx[0] != -INFINITY) || (mref[1] == -INFINITY && mx[1] != -INFINITY)))); \
         }                                                                                                           \
         if (PERIOD == 1 || BAR == 1 || (BAR == 2 && RingPlan::barrier_after((I) - vb))) {                           \
             if constexpr (G == 1) {                                                                                 \
@@ -702,7 +710,7 @@ __device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnCh
         float m = -INFINITY, l = 0.f;
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + rb][qb][n].x);      // finite: some group has a kblock
+        for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + rb][qb][n].x);      // finite unless every key scores -inf
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             const float2 s = ml[j * NW + rb][qb][n];
