@@ -78,6 +78,7 @@ __global__ __launch_bounds__(RES_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
             }
     };
     fetch(min(lo + wave, n_blocks - 1));
+    __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));                      // vmcnt(0): what this wave brings into LDS has landed
     __syncthreads();
     if (tail < KBLOCK) {                         // slots past the last key may hold anything, even NaN
         uint16_t* v_last = reinterpret_cast<uint16_t*>(lds + (T - 1) * STAGE_BYTES + KB_BYTES);
