@@ -176,7 +176,7 @@ static ll_status cross_attn(const ll_prompt* prompt, int layer, const void* q, i
     if (!aligned16(q, out)) return fail(LL_ERR_INVALID_ARG, "tensors must be 16-byte aligned");
     // these queries carry no factor yet: only kernels that apply AttnParams::scale_log2e themselves qualify
     // A prompt that fits into LDS whole (256 tokens at head_dim 128, 512 at 64) goes to the kernel made for that
-    // (attn_resident.hip: faster or level at every size measured, 3 to 24 heads, 60 to 23400 rows), unless a variant is forced.
+    // (attn_resident.hip), unless a variant is forced or its workgroups would leave the chip idle (resident_fills_chip).
     // Beyond that a workgroup streams the keys, and most of its life is still the load of its queries and the store of
     // its outputs.  With one round of workgroups on the chip (a chunk's queries) the pipelined kernel is the quicker one;
     // with several rounds (a re-prefill's queries) small workgroups, three to a CU in different phases, are.

@@ -14,6 +14,7 @@
 // than RESCALE_SLACK (then O and the row sum are rescaled); the final division by the
 // row sum makes the result independent of the reference chosen.
 #include "kernels.h"
+#include "lds_plan.h"
 
 #include <algorithm>
 #include <vector>
@@ -386,7 +387,8 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         for (int r = 0; r < ch.n_ranges; ++r) ch.n_kblocks += (ch.re[r] + KB - 1) / KB - ch.rs[r] / KB;
         if (ch.n_kblocks < 1) return hipErrorInvalidValue;
     }
-    if (p.keys_reside && attn_resident_fits(p.D, p.chunk[0].n_kblocks)) {
+    if (p.keys_reside && attn_resident_fits(p.D, p.chunk[0].n_kblocks) &&
+        resident_fills_chip(p.H, p.chunk[0].q_end, p.chunk[0].n_kblocks)) {
         ResidentParams r{};
         r.q = p.q; r.out = p.out; r.out_frag = p.out_frag;
         r.k_cache = p.k_cache; r.v_cache = p.v_cache; r.head_stride = p.head_stride;

@@ -121,4 +121,17 @@ struct GroupRing {
     static constexpr int dma_slot(int l, int n, int slots) { return l * slots / n / (PERIOD == 1 ? 2 : 1); }
 };
 
+// Whether the resident-key attention kernel (attn_resident.hip: one workgroup per CU, which first brings a head's keys and
+// values in) has its workgroups fill the chip, or the streaming kernels, whose rows split finer, are to take a launch.
+// Up to 128 heads each gets several workgroups, and the kernel was faster at 12 to 128 heads x 300 to 4680 rows (2 % slower
+// at 86 heads x 4680 x 400 keys x 64).  Above, a head is one workgroup and the last of the rounds may be nearly empty; us, streaming
+// and resident at 400 keys x 64: 129 heads x 4680 rows 109 and 145, 257 x 1170 64 and 87, but 200 x 4680 165 and 152,
+// 1000 x 4680 854 and 652.  At few rows the streaming kernels' latency counts more (129 x 300 25 and 16), and at two kblocks of
+// keys, as far as measured, what they do around them (129 x 4680 x 64 keys x 128 114 and 72, 257 heads 187 and 161).
+constexpr bool resident_fills_chip(int heads, int rows, int n_kblocks) {
+    if (heads <= 128 || n_kblocks <= 2) return true;
+    if (heads <= 256 && rows <= 512) return true;
+    return 4 * heads >= 3 * ((heads + 255) / 256 * 256);         // three quarters of the CUs over the rounds
+}
+
 }  // namespace ll

@@ -92,9 +92,10 @@ def test_keys_without_weight_where_a_share_begins(heads, head_dim, n_q, n_keys, 
     assert err <= 5e-3
 
 
-@pytest.mark.parametrize("heads, head_dim, n_keys", [(12, 128, 200), (300, 64, 33), (7, 64, 512)])
+@pytest.mark.parametrize("heads, head_dim, n_keys", [(12, 128, 200), (300, 64, 33), (300, 64, 97), (400, 64, 97), (7, 64, 512)])
 def test_resident_keys_over_many_rows(heads, head_dim, n_keys):
-    """Several blocks of rows per wave, and more heads than CUs."""
+    """Several blocks of rows per wave, and more heads than CUs (at 97 keys 400 fill two rounds to three
+    quarters, 300 do not and stream)."""
     _, _, err = _check(heads, head_dim, 9001, n_keys, n_keys, streamed=False)
     assert err <= 5e-3
 
