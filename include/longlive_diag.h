@@ -20,6 +20,11 @@ extern "C" {
 ll_status ll_set_attn_variant(int variant);
 const char* ll_attn_variant_name(int variant); /* NULL when `variant` does not exist */
 
+/* Into how many groups (1, 2, 4 or 8) the default bf16 kernels deal the keys of a launch's tiles, for n_chunks chunks of
+ * rows[i] query rows over kblocks[i] blocks of 32 keys each (host arrays).  A chunk in the cache counts as a launch of its
+ * own, with the key set of a full window; a clip or a prompt as the launch it is.  No GPU needed. */
+ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* groups);
+
 /* Diagnostic, not part of the method: the dense bf16 MFMA rate this GPU sustains when every wave issues nothing
  * but 32x32x16 MFMAs (two waves per SIMD, `workgroups` workgroups of 8 waves, iters * 16 MFMAs per wave), and the
  * core clock it settles at while doing so.  random_operands != 0 fills the operand registers with random bf16

@@ -53,6 +53,7 @@ SIGNATURES = {
     "ll_clip_chunk_key_ranges": (_i, [_vp, _i, C.POINTER(_i64), _i, C.POINTER(_i)]),
     "ll_set_attn_variant": (_i, [_i]),
     "ll_attn_variant_name": (C.c_char_p, [_i]),
+    "ll_attn_key_groups": (_i, [_i] * 3 + [C.POINTER(_i)] * 3),
     "ll_probe_mfma_rate": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "ll_probe_mfma_mix": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "ll_status_string": (C.c_char_p, [_i]),
@@ -105,6 +106,14 @@ def cache_bytes(layers, heads, head_dim, tokens_per_frame, sink_frames, window_f
 
 def set_attn_variant(variant: int) -> None:
     _check(lib().ll_set_attn_variant(variant))
+
+
+def attn_key_groups(head_dim, heads, chunks) -> int:
+    """Key groups the default bf16 kernels take for a launch of ``chunks``, (query rows, blocks of 32 keys) each."""
+    rows, kblocks = ((C.c_int * len(chunks))(*x) for x in zip(*chunks))
+    groups = C.c_int()
+    _check(lib().ll_attn_key_groups(head_dim, heads, len(chunks), rows, kblocks, C.byref(groups)))
+    return groups.value
 
 
 def probe_mfma_rate(workgroups: int = 256, iters: int = 20000, random_operands: bool = True):

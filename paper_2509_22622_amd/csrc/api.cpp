@@ -316,7 +316,26 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
     const int variant = raw_q ? attn_variant_qrope(c->D) : pick_variant(c);
     L.variant = variant;
     L.params.clear();
-    for (size_t base = 0; base < work.size(); base += MAX_ATTN_CHUNKS) {
+    auto keys = [&](int i) { int64_t t = 0; for (auto& r : work[i].ranges) t += r.end - r.begin; return t; };
+    // Into how many groups a chunk's keys are dealt is decided for the chunk alone, from its rows and the key set it has
+    // once the window is full: a chunk that is streamed and the same chunk inside a re-prefill then get the same bits.
+    // Chunks of unlike groups (a short one beside full ones) go out in launches of their own.  What that costs is some
+    // of a re-prefill's speed where its larger launch would do with fewer groups; us with groups chosen for the launch and
+    // for the chunk: 15 frames of 390 tokens x 12 x 128 159 and 207, 10 of 135 x 6 x 64 25 and 29, single-frame chunks of
+    // 322 x 22 x 64 67 and 111; over 40 geometries 7 % in the geometric mean, nothing at 1560 tokens in chunks of three.  A
+    // streamed chunk, which is what a video consists of, keeps its best split.
+    std::vector<std::pair<int, int>> order(work.size());              // (key groups, chunk)
+    for (size_t i = 0; i < work.size(); ++i) {
+        const int rows = work[i].q_end - work[i].q_begin;
+        const int kblocks = int((int64_t(c->g.S + c->g.W) * c->g.P + rows + c->kb - 1) / c->kb);
+        order[i] = {attn_key_groups(variant, c->H, 1, &rows, &kblocks), int(i)};
+    }
+    // longest key sets first: they bound the launch
+    std::stable_sort(order.begin(), order.end(), [&](const std::pair<int, int>& a, const std::pair<int, int>& b) {
+        return a.first != b.first ? a.first < b.first : keys(a.second) > keys(b.second);
+    });
+    for (size_t base = 0, end; base < work.size(); base = end) {
+        for (end = base + 1; end < work.size() && end - base < MAX_ATTN_CHUNKS && order[end].first == order[base].first;) ++end;
         AttnParams p{};
         p.out = static_cast<uint16_t*>(out);
         p.kblock = c->kb;
@@ -337,15 +356,11 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
             p.n_h = c->rope.n_h; p.n_w = c->rope.n_w; p.P = c->g.P; p.grid_w = c->grid_w;
             p.q_scale = float(1.4426950408889634 / std::sqrt(double(c->D)));
         }
-        const int m = int(std::min<size_t>(MAX_ATTN_CHUNKS, work.size() - base));
-        // longest key sets first: they bound the launch
-        std::vector<int> order(m);
-        for (int i = 0; i < m; ++i) order[i] = int(base) + i;
-        auto keys = [&](int i) { int64_t t = 0; for (auto& r : work[i].ranges) t += r.end - r.begin; return t; };
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return keys(a) > keys(b); });
+        p.key_groups = order[base].first;
+        const int m = int(end - base);
         p.inv_freq_t = c->rope.inv_freq_t; p.n_t = c->rope.n_t;
         for (int i = 0; i < m; ++i) {
-            ChunkWork w = work[order[i]];
+            ChunkWork w = work[order[base + i].second];
             const int64_t shift = sink_shift_of(c, w.f0);
             if (shift != 0) {
                 // the sink's scores use other queries than the rest: the sink must be a range of its own
@@ -497,8 +512,7 @@ static ll_status recache_prefill(ll_cache* cache, int layer, int include_sink, i
     }
     if (!cache->dev) { L = next; return LL_OK; }
     // rotated queries are staged in `out`; the attention kernel reads and overwrites them in place (bf16: a
-    // wave reads exactly the rows it writes).  E4M3 queries are half as wide as the output rows, so they are
-    // staged in the cache buffer's own area instead.
+    // row is read only in the workgroup that writes it, and before it is written).  E4M3 queries are half as wide as the output rows, so they are staged in the cache buffer's own area instead.
     void* q_stage = cache->fmt ? static_cast<void*>(cache->q8_stage) : out;
     // bf16 cache, default kernel: the attention kernel turns the queries as it loads them, the cache write takes keys
     // and values only and the rotated queries never go through memory

@@ -16,6 +16,16 @@ ll_status ll_set_attn_variant(int variant) {
 }
 const char* ll_attn_variant_name(int variant) { return attn_variant_name(variant); }
 
+ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* groups) {
+    if (!rows || !kblocks || !groups) return fail(LL_ERR_INVALID_ARG, "null pointer");
+    if ((head_dim != 64 && head_dim != 128) || heads < 1 || heads > 1024 || n_chunks < 1 || n_chunks > MAX_ATTN_CHUNKS)
+        return fail(LL_ERR_INVALID_ARG, "head_dim %d, heads %d or n_chunks %d out of range", head_dim, heads, n_chunks);
+    for (int c = 0; c < n_chunks; ++c)
+        if (rows[c] < 1 || kblocks[c] < 1) return fail(LL_ERR_INVALID_ARG, "chunk %d has %d rows and %d kblocks", c, rows[c], kblocks[c]);
+    *groups = attn_key_groups(attn_variant_default(head_dim, KBLOCK), heads, n_chunks, rows, kblocks);
+    return LL_OK;
+}
+
 ll_status ll_probe_mfma_rate(void* dev_scratch, size_t scratch_bytes, int workgroups, int iters, int random_operands,
                              double* tflops, double* clock_ghz, void* stream) {
     return ll_probe_mfma_mix(dev_scratch, scratch_bytes, workgroups, iters, random_operands, 0, 1, tflops, clock_ghz, stream);

@@ -338,7 +338,8 @@ bool attn_variant_applies_scale(int v) {
 // 4 to 24 heads and 180 to 1560 rows over 2 to 634 kblocks (us per step with one group: 0.56 at head_dim 128, 0.41
 // at 64):  a_G + n / b_G.  A workgroup also takes about ten steps' time before its first step and after its last (its
 // arguments, the first loads, the results' way out), which every round of workgroups pays.  At 1170 rows x 183 kblocks x 12 heads x 128: 114 us with one group, 71 with two, 54 with four.
-static int key_groups_log2(const AttnVariant& v, const AttnParams& p) {
+template <typename Rows, typename Kblocks>
+static int key_groups_log2(const AttnVariant& v, int H, int n_chunks, Rows rows, Kblocks kblocks) {
     constexpr int CUS = 256, AROUND = 10;
     struct Step { double a, b; };
     static constexpr Step steps128[4] = {{1.0, 1300}, {1.1, 900}, {1.35, 650}, {0, 1}};
@@ -349,9 +350,9 @@ static int key_groups_log2(const AttnVariant& v, const AttnParams& p) {
         if (lg > 0 && v.grouped[lg - 1] == nullptr) continue;
         const int qtile = v.qtile >> lg;
         int64_t tiles = 0, work = 0, longest = 0;
-        for (int c = 0; c < p.n_chunks; ++c) {
-            const int64_t t = (p.chunk[c].q_end - p.chunk[c].q_begin + qtile - 1) / qtile * int64_t(p.H);
-            const int64_t len = (p.chunk[c].n_kblocks + (1 << lg) - 1) >> lg;
+        for (int c = 0; c < n_chunks; ++c) {
+            const int64_t t = (rows(c) + qtile - 1) / qtile * int64_t(H);
+            const int64_t len = (kblocks(c) + (1 << lg) - 1) >> lg;
             tiles += t;
             work += t * len;
             longest = std::max(longest, len);
@@ -361,7 +362,7 @@ static int key_groups_log2(const AttnVariant& v, const AttnParams& p) {
         // equal workgroups run in whole rounds; of unequal ones the last to finish is half a workgroup behind the mean
         double cost = one;
         if (tiles > CUS)
-            cost = p.n_chunks == 1 ? double((tiles + CUS - 1) / CUS) * one : (work * step + double(tiles) * AROUND) / CUS + 0.5 * one;
+            cost = n_chunks == 1 ? double((tiles + CUS - 1) / CUS) * one : (work * step + double(tiles) * AROUND) / CUS + 0.5 * one;
         // with half the chip at work as it is, a win has to be clear of what the model leaves out (short last tiles are
         // cheaper than whole ones, a round of new workgroups starts cold): 16 frames of 513 tokens x 17 x 128 as a clip
         // were predicted 4 % faster with two groups and ran 11 % slower
@@ -373,6 +374,9 @@ static int key_groups_log2(const AttnVariant& v, const AttnParams& p) {
         }
     }
     return best;
+}
+int attn_key_groups(int variant, int H, int n_chunks, const int* rows, const int* kblocks) {
+    return 1 << key_groups_log2(*ll::variant(variant), H, n_chunks, [&](int c) { return rows[c]; }, [&](int c) { return kblocks[c]; });
 }
 constexpr int GROUPED_LDS_BYTES = 128 * 1024;    // GroupRing: 128 KB / G at most per group; the groups' results fit too
 
@@ -396,7 +400,14 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         r.scale_log2e = p.scale_log2e;
         return launch_attn_resident(r, p.D, s);
     }
-    const int log_g = key_groups_log2(v, p), qtile = v.qtile >> log_g;
+    int log_g = 0;
+    if (p.key_groups == 0)
+        log_g = key_groups_log2(v, p.H, p.n_chunks, [&](int c) { return p.chunk[c].q_end - p.chunk[c].q_begin; },
+                                [&](int c) { return p.chunk[c].n_kblocks; });
+    else
+        while ((1 << log_g) < p.key_groups) ++log_g;
+    if (log_g > 3 || (log_g > 0 && v.grouped[log_g - 1] == nullptr)) return hipErrorInvalidValue;
+    const int qtile = v.qtile >> log_g;
     p.n_tiles = 0;
     for (int c = 0; c < p.n_chunks; ++c) {
         p.chunk[c].tile_begin = p.n_tiles;

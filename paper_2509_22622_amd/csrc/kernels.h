@@ -152,6 +152,7 @@ struct AttnParams {
     int kblock;                  // key slots per kblock: 32 (bf16 cache) or 64 (8-bit cache)
     const double* inv_freq_t;    // frame-axis rotary frequencies [n_t] (used when a chunk has a sink_shift)
     int n_t;
+    int key_groups;              // key groups per tile (AttnVariant::grouped); 0: chosen for the launch (attn_key_groups)
     bool keys_reside;            // the one key range may be brought into LDS whole where it fits (attn_resident.hip)
     float* lse;                  // *_lse kernels: log2 of each row's sum of 2^score, [H][lse_stride] (null otherwise)
     int64_t lse_stride;
@@ -236,6 +237,8 @@ int attn_variant_count();
 const char* attn_variant_name(int v);
 int attn_variant_default(int D, int kblock);
 bool attn_variant_supports(int v, int D, int kblock);
+// the key groups a launch of these chunks takes with the variant: 1, 2, 4 or 8
+int attn_key_groups(int v, int H, int n_chunks, const int* rows, const int* kblocks);
 bool attn_variant_sink_shift(int v);          // the variant honours AttnChunk::sink_shift
 int attn_variant_lse(int D);                   // the variant that also writes AttnParams::lse
 int attn_variant_qscale(int D);                // the variant for queries not yet scaled (honours scale_log2e)

@@ -173,3 +173,27 @@ def test_narrow_backward_tiles(heads, grid, n_clip):
     for name, got, ref in zip(("out", "dq", "dk", "dv"), (out, dq, dk, dv), want):
         ref = torch.from_numpy(ref).cuda()
         assert float((got.double() - ref).norm() / ref.norm()) <= 5.0e-3, name
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, sink, window, n_win", [
+    (12, 128, (15, 26), 3, 3, 9, 12), (12, 64, (16, 19), 2, 2, 4, 6), (21, 128, (6, 19), 1, 2, 5, 6),
+    (16, 64, (10, 16), 3, 3, 6, 9), (10, 64, (17, 23), 3, 2, 5, 7), (12, 128, (19, 33), 2, 2, 6, 8)])
+def test_prefill_equals_streaming_where_a_chunk_takes_key_groups(heads, head_dim, grid, chunk, sink, window, n_win):
+    """Streamed chunk by chunk or rebuilt in one call, a chunk's outputs are the same bits at every size: into how many key
+    groups its tiles are dealt depends on the chunk, not on the launch it is part of."""
+    P, nf = grid[0] * grid[1], sink + n_win
+    g = torch.Generator(device="cuda").manual_seed(P)
+    q, k, v = (torch.empty((nf * P, heads, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(3))
+    streamed, rebuilt = (B.Cache(1, heads, head_dim, *grid, chunk, sink, window) for _ in range(2))
+    want, got = torch.empty_like(q), torch.empty_like(q)
+    starts = [*range(0, sink, chunk), *range(sink, nf, chunk)]
+    assert B.attn_key_groups(head_dim, heads, [(chunk * P, -(-(sink + window + chunk) * P // 32))]) > 1
+    for f0, end in zip(starts, starts[1:] + [nf]):
+        rows = slice(f0 * P, end * P)
+        streamed.chunk_append(0, f0, end - f0, None, k[rows], v[rows], None)
+        streamed.sink_window_attn_unrotated(0, q[rows], want[rows])
+    rebuilt.recache_prefill(0, True, sink, n_win, q, k, v, got)
+    torch.cuda.synchronize()
+    streamed.close()
+    rebuilt.close()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
