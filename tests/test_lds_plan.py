@@ -1,10 +1,12 @@
 """The streaming attention kernel synchronises by hand: LDS fragment reads with counted waits, and a ring of K/V
 stages filled by direct-to-LDS loads with counted waits and one barrier per two kblocks (csrc/lds_plan.h, which the
-kernel compiles in).  Two host programs replay those plans:
+kernel compiles in).  Three host programs replay those plans:
   check_lds_plan.cpp   in-order LDS queue: every wait guarantees its fragment, is no stricter than needed, fits the
                        hardware counter; no fragment register is overwritten before its last use;
   check_ring_plan.cpp  waves under random interleavings, loads landing at random times: no read ever meets a stage
-                       fragment that has not landed or may already be overwritten.
+                       fragment that has not landed or may already be overwritten;
+  check_group_ring.cpp the same for the rings of key groups (GroupRing), with waves that have no rows, groups that have
+                       no keys, and the number of barriers every wave meets.
 The ring checker is also run on copies of the plan with one constant changed, where it must report a violation."""
 import os
 import re
@@ -52,6 +54,27 @@ def test_ring_simulation_catches_a_wrong_plan(tmp_path, old, new):
     shutil.copy(os.path.join(HERE, "check_ring_plan.cpp"), tmp_path / "tests" / "check_ring_plan.cpp")
     run = _build_and_run(tmp_path, tmp_path / "tests" / "check_ring_plan.cpp", "check_wrong")
     assert run.returncode == 1 and re.search(r"reads kblock \d+", run.stdout), run.stdout + run.stderr
+
+
+def test_group_ring_simulation(tmp_path):
+    run = _build_and_run(tmp_path, os.path.join(HERE, "check_group_ring.cpp"), "check_group_ring")
+    assert run.returncode == 0, run.stdout + run.stderr
+    assert "group rings ok" in run.stdout
+
+
+@pytest.mark.parametrize("old, new", [
+    ("DEPTH = 2 * PERIOD;", "DEPTH = PERIOD;"),                   # a half stage loaded while it is read
+    ("return l * slots / n / (PERIOD == 1 ? 2 : 1);", "return l * slots / n + slots / 2;"),   # half of the loads left out
+])
+def test_group_ring_simulation_catches_a_wrong_plan(tmp_path, old, new):
+    text = open(PLAN).read()
+    assert old in text
+    (tmp_path / "paper_2509_22622_amd" / "csrc").mkdir(parents=True)
+    (tmp_path / "tests").mkdir()
+    (tmp_path / "paper_2509_22622_amd" / "csrc" / "lds_plan.h").write_text(text.replace(old, new))
+    shutil.copy(os.path.join(HERE, "check_group_ring.cpp"), tmp_path / "tests" / "check_group_ring.cpp")
+    run = _build_and_run(tmp_path, tmp_path / "tests" / "check_group_ring.cpp", "check_wrong")
+    assert run.returncode == 1 and re.search(r"being read|the fragment holds", run.stdout), run.stdout + run.stderr
 
 
 def test_fp8_lds_plan_replay(tmp_path):
