@@ -90,6 +90,19 @@ def test_clip_forward_and_gradients(heads, head_dim, gh, gw, C, S, W, T, ctx_sta
     run_case(heads, head_dim, gh, gw, C, S, W, T, ctx_start, n_ctx, n_clip)
 
 
+@pytest.mark.parametrize("heads,gh,gw,C,S,W,T,ctx_start,n_ctx,n_clip", [
+    (52, 9, 13, 3, 2, 3, 5, 20, 3, 5),        # tiles of 256 + 95 and 234 columns, in both kernels
+    (86, 5, 13, 2, 1, 3, 7, 0, 0, 6),         # a video's first clip: half of a tile's waves have no columns
+    (70, 7, 9, 1, 0, 2, 5, 0, 2, 5),          # no sink, chunks of one frame of 63 tokens
+])
+def test_wide_backward_tiles(heads, gh, gw, C, S, W, T, ctx_start, n_ctx, n_clip):
+    """Launches of more than 256 tiles of 128 columns take tiles of 256 at head_dim 128 (attn_bwd.hip: narrow_tiles): ragged
+    ones, frames that nothing is aligned with, every element."""
+    tiles = [-(-min(C, n_clip - i) * gh * gw // 128) for i in range(0, n_clip, C)]
+    assert sum(tiles) * heads > 256
+    run_case(heads, 128, gh, gw, C, S, W, T, ctx_start, n_ctx, n_clip, seed=7)
+
+
 def test_gradient_reaches_only_the_keys_a_chunk_sees():
     """A loss on the last chunk only: keys outside its window get exactly zero, its queries alone get dq."""
     gh, gw, C, S, W = 3, 5, 2, 1, 2
@@ -127,7 +140,8 @@ def test_second_step_with_a_shorter_clip_reuses_the_handle():
 
 def test_wan_frame_size():
     """The benchmark model's frame (30 x 52 tokens), head width, chunk, sink and window; two heads and a clip of two
-    chunks keep the oracle's fp64 products to seconds.  Every element of out, dq, dk and dv is compared."""
+    chunks keep the oracle's fp64 products to seconds (and take the backward kernels' narrow tiles; the wide ones have
+    test_wide_backward_tiles and the benchmark's shape).  Every element of out, dq, dk and dv is compared."""
     run_case(2, 128, 30, 52, 3, 3, 9, 6, 60, 9, 6, seed=5)
 
 

@@ -2,14 +2,17 @@
 
 Launches of few rows and heads deal a tile's keys to 2, 4 or 8 groups of the workgroup's waves (attn_stream16.hip);
 the groups' results meet in LDS.  Where that can go wrong: shares of unequal length, fewer kblocks than groups, a last
-kblock of one key, a last tile of one row, a score far above its own group's reference.  The launch rule gives the
-small shapes here the largest grouping a head_dim has (8 groups at 64, 4 at 128); 24 heads of 1170 rows get two.
+kblock of one key, a last tile of one row, a score far above its own group's reference, periods of the groups' rings that
+wrap.  The small shapes here take the largest grouping a head_dim has, 8 groups at 64 and 4 at 128, from five kblocks on,
+and 2 (4 at 64 with three or four) below; every other grouping with long shares has its shapes below, which ask
+attn_key_groups what they get.
 Cross-attention over a prompt that fits into LDS whole (256 tokens at head_dim 128, 512 at 64) runs in a kernel of its
 own (attn_resident.hip) unless a variant is forced: both run here on the same inputs."""
 import pytest
 import torch
 
 from paper_2509_22622_amd import binding as B
+from perf import cases
 
 pytestmark = pytest.mark.gpu
 
@@ -90,6 +93,70 @@ def test_keys_without_weight_where_a_share_begins(heads, head_dim, n_q, n_keys, 
     out, want, err = _check(heads, head_dim, n_q, n_keys, lo, spoil)
     assert bool(torch.isfinite(out).all())
     assert err <= 5e-3
+
+
+LONG_SHARES = [(64, 24, 1560, 1), (64, 24, 1170, 2), (64, 12, 1170, 4), (64, 12, 300, 8),
+               (128, 24, 1560, 1), (128, 24, 1170, 2), (128, 12, 1170, 4)]
+
+
+@pytest.mark.parametrize("head_dim, heads, n_q, groups", LONG_SHARES)
+@pytest.mark.parametrize("n_keys, at", [(300, None), (641, 640), (1000, 700)])
+def test_long_shares(head_dim, heads, n_q, groups, n_keys, at):
+    """Every grouping with shares of several steps, odd and even, unlike ones beside each other; with one score far above
+    the reference of its own share."""
+    def spoil(q, k):
+        if at is not None:
+            k[at] = 40 * q[5]
+
+    assert B.attn_key_groups(head_dim, heads, [(n_q, -(-n_keys // 32))]) == groups
+    out, want, err = _check(heads, head_dim, n_q, n_keys, n_keys, spoil)
+    assert bool(torch.isfinite(out).all())
+    assert err <= 5e-3
+
+
+def _rel(got, want):
+    return float((got.double() - want).norm() / want.norm())
+
+
+@pytest.mark.parametrize("head_dim, heads, grid, groups", [
+    (64, 24, (20, 26), 1), (64, 24, (15, 26), 2), (64, 12, (15, 26), 4), (64, 12, (9, 11), 8),
+    (128, 24, (20, 26), 1), (128, 24, (15, 26), 2), (128, 12, (15, 26), 4)])
+def test_long_shares_in_the_cache(head_dim, heads, grid, groups):
+    """A streamed chunk of every grouping against the pass in 64 bits, to the benchmark's relative tolerance; the kernels
+    that turn the queries themselves give the bits of those that take them turned."""
+    case = {"kind": "stream", "cache": "bf16", "layers": 1, "heads": heads, "head_dim": head_dim, "grid_h": grid[0],
+            "grid_w": grid[1], "chunk": 3, "sink": 3, "window": 6, "frames": 3, "first_frame": 47, "video_chunks": 0, "q_std": 2.0}
+    P = grid[0] * grid[1]
+    assert B.attn_key_groups(head_dim, heads, [(3 * P, -(-12 * P // 32))]) == groups
+    outs = []
+    for form in ("two_call", "unrotated"):
+        state = cases.prepare({**case, "form": form}, 5)
+        outs += cases.run(state)
+        torch.cuda.synchronize()
+        state["cache"].close()
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    assert _rel(outs[0], cases.exact(case, 5)[0]) <= 5e-3 * case["q_std"]
+
+
+@pytest.mark.parametrize("head_dim, heads, grid, clip_frames, groups", [
+    (64, 24, (7, 19), 8, 1), (64, 16, (7, 19), 8, 2), (64, 12, (7, 19), 5, 4), (64, 1, (11, 17), 5, 8),
+    (128, 24, (7, 19), 8, 1), (128, 16, (7, 19), 8, 2), (128, 1, (7, 19), 5, 4)])
+def test_long_shares_in_a_clip(head_dim, heads, grid, clip_frames, groups):
+    """The form that also writes the row sums, of every grouping: output and gradients against 64 bits.  Gradients to the five
+    bf16 roundings on their way (test_narrow_backward_tiles)."""
+    case = {"kind": "clip", "heads": heads, "head_dim": head_dim, "grid_h": grid[0], "grid_w": grid[1], "chunk": 3, "sink": 2,
+            "window": 4, "ctx_start": 20, "n_ctx": 4, "clip_frames": clip_frames, "q_std": 1.0}
+    state = cases.prepare(case, 6)
+    got = cases.run(state)
+    torch.cuda.synchronize()
+    chunks = []
+    for i in range(-(-clip_frames // 3)):
+        kblocks = sum(-(-end // 32) - begin // 32 for begin, end in state["clip"].chunk_key_ranges(i))
+        chunks.append((min(3, clip_frames - 3 * i) * grid[0] * grid[1], kblocks))
+    assert B.attn_key_groups(head_dim, heads, chunks) == groups
+    for name, a, b in zip(("out", "dq", "dk", "dv"), got, cases.exact(case, 6)):
+        assert _rel(a, b) <= 5e-3, name
+    state["clip"].close()
 
 
 @pytest.mark.parametrize("heads, head_dim, n_keys", [(12, 128, 200), (300, 64, 33), (300, 64, 97), (400, 64, 97), (7, 64, 512)])

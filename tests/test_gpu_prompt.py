@@ -203,10 +203,12 @@ def test_wan_shape_full_size(n_q):
 
 @pytest.mark.parametrize("heads,head_dim,n_q,n_t", [
     (12, 128, 11000, 256), (12, 64, 12345, 512), (5, 128, 40000, 768), (12, 128, 11000, 250), (12, 128, 11000, 200),
+    (12, 128, 11000, 300), (12, 64, 12345, 700),
 ])
 def test_many_query_tiles(heads, head_dim, n_q, n_t):
-    """Launches of more than two rounds of query tiles (the small-workgroup kernel): 8, 16, 24 kblocks of keys, a
-    partly dead last kblock, ragged last query tiles, both head sizes.  Every output element against the oracle."""
+    """Launches of more than two rounds of query tiles, in the resident-key kernel up to 256 tokens at head_dim 128 and 512
+    at 64 and in the small-workgroup kernel beyond: 7 to 24 kblocks of keys, a partly dead last kblock, ragged last query
+    tiles, both head sizes in both kernels.  Every output element against the oracle."""
     p = B.Prompt(1, heads, head_dim, 1024)
     k, v = bits((n_t, heads, head_dim), 41, "k"), bits((n_t, heads, head_dim), 41, "v")
     q = bits((n_q, heads, head_dim), 42, "q")
@@ -304,14 +306,15 @@ def test_cross_attn_out_parity(heads, head_dim, n_q, n_t):
 
 
 @pytest.mark.parametrize("heads,head_dim,n_q,n_t", [(3, 128, 300, 50), (5, 64, 77, 50),
-                                                    (12, 128, 11000, 50), (12, 64, 11000, 50),    # many query tiles: the small-workgroup kernel
-                                                    (12, 128, 11000, 256), (12, 64, 11000, 256)])
+                                                    (12, 128, 11000, 50), (12, 64, 11000, 50),    # many query tiles, keys resident
+                                                    (12, 128, 11000, 256), (12, 64, 11000, 256),
+                                                    (12, 128, 11000, 300), (12, 64, 11000, 600)])  # the small-workgroup kernel
 def test_out_projection_exact_cases(heads, head_dim, n_q, n_t):
     """Weights the projection must pass through bit for bit: the identity returns the attention output itself (what
     ll_cross_attn writes: so the hand-over between the two kernels loses and moves nothing), a permutation moves its
     features."""
     n = heads * head_dim
-    p = B.Prompt(1, heads, head_dim, 256)
+    p = B.Prompt(1, heads, head_dim, max(256, n_t))
     k, v, q = bits((n_t, heads, head_dim), 21, "k"), bits((n_t, heads, head_dim), 21, "v"), bits((n_q, heads, head_dim), 22, "q")
     p.recache(0, H.to_dev(k), H.to_dev(v))
     qd = H.to_dev(q)
