@@ -337,7 +337,9 @@ bool attn_variant_applies_scale(int v) {
 // so the more workgroups run.  A step's length relative to one group's, with n workgroups at work, as measured at
 // 4 to 24 heads and 180 to 1560 rows over 2 to 634 kblocks (us per step with one group: 0.56 at head_dim 128, 0.41
 // at 64):  a_G + n / b_G.  A workgroup also takes about ten steps' time before its first step and after its last (its
-// arguments, the first loads, the results' way out), which every round of workgroups pays.  At 1170 rows x 183 kblocks x 12 heads x 128: 114 us with one group, 71 with two, 54 with four.
+// arguments, the first loads, the results' way out), which every round of workgroups pays.  At 1170 rows x 183 kblocks x
+// 12 heads x 128: 114 us with one group, 71 with two, 54 with four.  (A cache asks for each chunk as a launch of its own,
+// api.cpp: build_attn; a clip or a prompt for the launch it makes.)
 template <typename Rows, typename Kblocks>
 static int key_groups_log2(const AttnVariant& v, int H, int n_chunks, Rows rows, Kblocks kblocks) {
     constexpr int CUS = 256, AROUND = 10;
@@ -365,7 +367,7 @@ static int key_groups_log2(const AttnVariant& v, int H, int n_chunks, Rows rows,
             cost = n_chunks == 1 ? double((tiles + CUS - 1) / CUS) * one : (work * step + double(tiles) * AROUND) / CUS + 0.5 * one;
         // with half the chip at work as it is, a win has to be clear of what the model leaves out (short last tiles are
         // cheaper than whole ones, a round of new workgroups starts cold): 16 frames of 513 tokens x 17 x 128 as a clip
-        // were predicted 4 % faster with two groups and ran 11 % slower
+        // were predicted 4 % faster with two groups and ran 11 % slower (the margin is taken from two such clips)
         if (lg == 0 && tiles >= CUS / 2) bar = 0.87;
         if (lg == 0 || cost < bar * best_cost) {
             best = lg;
