@@ -54,6 +54,8 @@ SIGNATURES = {
     "ll_set_attn_variant": (_i, [_i]),
     "ll_attn_variant_name": (C.c_char_p, [_i]),
     "ll_attn_key_groups": (_i, [_i] * 3 + [C.POINTER(_i)] * 3),
+    "ll_attn_split": (_i, [_i] * 4 + [C.POINTER(_i)] * 2),
+    "ll_hold_split_slots": (_i, [_i] * 3),
     "ll_probe_mfma_rate": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "ll_probe_mfma_mix": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "ll_status_string": (C.c_char_p, [_i]),
@@ -114,6 +116,18 @@ def attn_key_groups(head_dim, heads, chunks) -> int:
     groups = C.c_int()
     _check(lib().ll_attn_key_groups(head_dim, heads, len(chunks), rows, kblocks, C.byref(groups)))
     return groups.value
+
+
+def attn_split(head_dim, heads, rows, kblocks):
+    """(key groups, splits) of a streamed chunk with ``kblocks`` blocks of 32 keys in a full window."""
+    groups, splits = C.c_int(), C.c_int()
+    _check(lib().ll_attn_split(head_dim, heads, rows, kblocks, C.byref(groups), C.byref(splits)))
+    return groups.value, splits.value
+
+
+def hold_split_slots(first: int, n: int, hold: bool) -> None:
+    """Take slots for partial results out of use, or give them back (a test instrument; synchronises)."""
+    _check(lib().ll_hold_split_slots(first, n, int(hold)))
 
 
 def probe_mfma_rate(workgroups: int = 256, iters: int = 20000, random_operands: bool = True):

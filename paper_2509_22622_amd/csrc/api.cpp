@@ -312,7 +312,7 @@ static bool can_turn_queries(const ll_cache* c, const std::vector<ChunkWork>& wo
 // raw_q: q holds the queries before the rotary embedding; chunk i's frames are rows work[i].t_row .. of the table the
 // cache write of the same call (or, for a staged chunk, the last ll_chunk_append) left for the layer.
 static ll_status build_attn(const ll_cache* c, int layer, const std::vector<ChunkWork>& work, const void* q, void* out,
-                            AttnLaunches& L, bool raw_q = false) {
+                            AttnLaunches& L, bool raw_q, bool streamed) {
     const int variant = raw_q ? attn_variant_qrope(c->D) : pick_variant(c);
     L.variant = variant;
     L.params.clear();
@@ -324,11 +324,14 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
     // for the chunk: 15 frames of 390 tokens x 12 x 128 159 and 207, 10 of 135 x 6 x 64 25 and 29, single-frame chunks of
     // 322 x 22 x 64 67 and 111; over 40 geometries 7 % in the geometric mean, nothing at 1560 tokens in chunks of three.  A
     // streamed chunk, which is what a video consists of, keeps its best split.
-    std::vector<std::pair<int, int>> order(work.size());              // (key groups, chunk)
+    std::vector<std::pair<int, int>> order(work.size());              // (key groups and splits, chunk)
     for (size_t i = 0; i < work.size(); ++i) {
         const int rows = work[i].q_end - work[i].q_begin;
         const int kblocks = int((int64_t(c->g.S + c->g.W) * c->g.P + rows + c->kb - 1) / c->kb);
-        order[i] = {attn_key_groups(variant, c->H, 1, &rows, &kblocks), int(i)};
+        // (a streamed chunk may also take splits; a re-prefill, whose launch is larger, would pay for them: 16 single-frame
+        // chunks of 190 x 4 x 128 would take 3 times as long, so there a chunk whose tiles split has other roundings)
+        const AttnSplit split = streamed ? attn_split(variant, c->H, rows, kblocks) : AttnSplit{attn_key_groups(variant, c->H, 1, &rows, &kblocks), 1};
+        order[i] = {split.groups * 256 + split.splits, int(i)};
     }
     // longest key sets first: they bound the launch
     std::stable_sort(order.begin(), order.end(), [&](const std::pair<int, int>& a, const std::pair<int, int>& b) {
@@ -356,7 +359,8 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
             p.n_h = c->rope.n_h; p.n_w = c->rope.n_w; p.P = c->g.P; p.grid_w = c->grid_w;
             p.q_scale = float(1.4426950408889634 / std::sqrt(double(c->D)));
         }
-        p.key_groups = order[base].first;
+        p.key_groups = order[base].first / 256;
+        p.splits = order[base].first % 256;
         const int m = int(end - base);
         p.inv_freq_t = c->rope.inv_freq_t; p.n_t = c->rope.n_t;
         for (int i = 0; i < m; ++i) {
@@ -447,7 +451,7 @@ ll_status ll_sink_window_attn(ll_cache* cache, int layer, const void* q_roped, v
     work[0].ranges = live_ranges(cache->g, L);
     work[0].f0 = L.staged_f0;
     AttnLaunches launches;
-    ll_status st = build_attn(cache, layer, work, q_roped, out, launches);
+    ll_status st = build_attn(cache, layer, work, q_roped, out, launches, false, true);
     if (st != LL_OK) return st;
     return launch_built_attn(launches, static_cast<hipStream_t>(stream));
 }
@@ -469,7 +473,7 @@ ll_status ll_sink_window_attn_unrotated(ll_cache* cache, int layer, const void* 
     if (!can_turn_queries(cache, work))
         return fail(LL_ERR_UNSUPPORTED, "unrotated queries need the default kernel and a sink that is not re-indexed for this chunk");
     AttnLaunches launches;
-    ll_status st = build_attn(cache, layer, work, q, out, launches, true);
+    ll_status st = build_attn(cache, layer, work, q, out, launches, true, true);
     if (st != LL_OK) return st;
     return launch_built_attn(launches, static_cast<hipStream_t>(stream));
 }
@@ -526,8 +530,8 @@ static ll_status recache_prefill(ll_cache* cache, int layer, int include_sink, i
         if (st != LL_OK) return st;
     }
     AttnLaunches launches;
-    st = turn_in_attn ? build_attn(cache, layer, work, q, out, launches, true)
-                      : build_attn(cache, layer, work, q_stage, out, launches);
+    st = turn_in_attn ? build_attn(cache, layer, work, q, out, launches, true, false)
+                      : build_attn(cache, layer, work, q_stage, out, launches, false, false);
     if (st != LL_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     std::vector<int64_t> frames;

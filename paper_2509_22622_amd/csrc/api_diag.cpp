@@ -3,6 +3,7 @@
 #include "../../include/longlive_diag.h"
 
 #include "api_common.h"
+#include "split.h"
 
 using namespace ll;
 using namespace ll_api;
@@ -24,6 +25,32 @@ ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* r
         if (rows[c] < 1 || kblocks[c] < 1) return fail(LL_ERR_INVALID_ARG, "chunk %d has %d rows and %d kblocks", c, rows[c], kblocks[c]);
     *groups = attn_key_groups(attn_variant_default(head_dim, KBLOCK), heads, n_chunks, rows, kblocks);
     return LL_OK;
+}
+
+ll_status ll_attn_split(int head_dim, int heads, int rows, int kblocks, int* groups, int* splits) {
+    if (!groups || !splits) return fail(LL_ERR_INVALID_ARG, "null pointer");
+    if ((head_dim != 64 && head_dim != 128) || heads < 1 || heads > 1024 || rows < 1 || kblocks < 1)
+        return fail(LL_ERR_INVALID_ARG, "head_dim %d, heads %d, rows %d or kblocks %d out of range", head_dim, heads, rows, kblocks);
+    const AttnSplit s = attn_split(attn_variant_default(head_dim, KBLOCK), heads, rows, kblocks);
+    *groups = s.groups;
+    *splits = s.splits;
+    return LL_OK;
+}
+
+ll_status ll_hold_split_slots(int first, int n, int hold) {
+    if (first < 0 || n < 1 || first > SPLIT_SLOTS - n) return fail(LL_ERR_INVALID_ARG, "slots [%d, %d + %d) outside [0, %d)", first, first, n, SPLIT_SLOTS);
+    constexpr unsigned long long HELD = 1;       // token 0, which no call has, and one reader, who never comes
+    SplitPool* pool = nullptr;
+    std::vector<unsigned long long> owner(n);
+    hipError_t e = split_pool_address(&pool);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = hipMemcpy(owner.data(), pool->owner + first, n * sizeof(owner[0]), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "reading the slots' owners");
+    for (unsigned long long& o : owner)
+        if (o == (hold ? 0 : HELD)) o = hold ? HELD : 0;
+    e = hipMemcpy(pool->owner + first, owner.data(), n * sizeof(owner[0]), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    return e == hipSuccess ? LL_OK : hip_fail(e, "writing the slots' owners");
 }
 
 ll_status ll_probe_mfma_rate(void* dev_scratch, size_t scratch_bytes, int workgroups, int iters, int random_operands,

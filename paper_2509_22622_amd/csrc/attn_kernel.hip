@@ -15,8 +15,10 @@
 // row sum makes the result independent of the reference chosen.
 #include "kernels.h"
 #include "lds_plan.h"
+#include "split.h"
 
 #include <algorithm>
+#include <atomic>
 #include <vector>
 
 namespace ll {
@@ -380,6 +382,64 @@ static int key_groups_log2(const AttnVariant& v, int H, int n_chunks, Rows rows,
 int attn_key_groups(int variant, int H, int n_chunks, const int* rows, const int* kblocks) {
     return 1 << key_groups_log2(*ll::variant(variant), H, n_chunks, [&](int c) { return rows[c]; }, [&](int c) { return kblocks[c]; });
 }
+
+// The same for one chunk whose tiles may also be dealt to several workgroups, merged by a second launch (split.h).  What a
+// call takes is modelled in us, fitted to 350 timings of 26 shapes (1 to 24 heads, 96 to 4680 rows, 30 to 732 kblocks; 6 %
+// off in the mean; the pair it picks was 1 % slower than the best): a round of workgroups takes its steps, each the longer
+// the more workgroups run (LDS and L2 traffic), and the way in and out; a merge, its launch and the partial results' way
+// through memory.  The groups alone stay as above, and a split has to be 10 % cheaper than they are, 15 %
+// where half the chip is at work without one.  us without and with
+// splits at head_dim 128: 190 rows x 143 kblocks x 4 heads 41 and 20 (4 groups x 12), 720 x 128 x 5 36 and 23 (4 x 4),
+// 1560 x 634 x 12 227 and 172 (1 x 3), 4680 x 732 x 2 162 and 109 (1 x 6); 1170 x 183 x 12 takes none (51, best split 52).
+AttnSplit attn_split(int variant, int H, int rows, int kblocks) {
+    const AttnVariant& v = *ll::variant(variant);
+    const int unsplit = key_groups_log2(v, H, 1, [&](int) { return rows; }, [&](int) { return kblocks; });
+    AttnSplit best{1 << unsplit, 1};
+    if (!v.splits) return best;
+    constexpr int CUS = 256;
+    struct Model { double step[4], busy[4], around, merge, per_split, per_mb; };
+    static constexpr Model models[2] = {{{0.52, 0.63, 0.82, 0}, {0.31, 0.21, 0.14, 0}, 7.1, 3.7, 0.22, 0.25},            // head_dim 128
+                                        {{0.38, 0.41, 0.47, 0.42}, {0.14, 0.10, 0.05, 0.39}, 5.0, 3.7, 0.22, 0.26}};     // 64
+    const Model& m = models[v.D == 128 ? 0 : 1];
+    auto cost = [&](int lg, int splits) {
+        const int64_t n = (int64_t(rows) + (v.qtile >> lg) - 1) / (v.qtile >> lg) * H * splits;
+        const double step = m.step[lg] * (1 + m.busy[lg] * double(std::min<int64_t>(n, CUS)) / CUS);
+        const double round = double((kblocks + (splits << lg) - 1) / (splits << lg)) * step + m.around;
+        return double((n + CUS - 1) / CUS) * round + (splits == 1 ? 0 : m.merge + m.per_split * splits + m.per_mb * 1e-6 * double(n) * (v.qtile >> lg) * v.D * 4);
+    };
+    const int64_t at_work = (int64_t(rows) + (v.qtile >> unsplit) - 1) / (v.qtile >> unsplit) * H;
+    double best_cost = (at_work >= CUS / 2 ? 0.85 : 0.9) * cost(unsplit, 1);
+    for (int lg = 0; lg < 4; ++lg) {
+        if (lg > 0 && v.grouped[lg - 1] == nullptr) continue;
+        const int64_t tiles = (int64_t(rows) + (v.qtile >> lg) - 1) / (v.qtile >> lg) * H;
+        for (int splits = 2; splits <= MAX_SPLITS && tiles * splits <= SPLIT_SLOTS && (splits << lg) <= kblocks; ++splits) {
+            const double c = cost(lg, splits);
+            if (c < best_cost) {
+                best_cost = c;
+                best = {1 << lg, splits};
+            }
+        }
+    }
+    return best;
+}
+static __device__ SplitPool split_pool;
+// its address on the current device (looked up on the first call per device; threads may do that at the same time)
+hipError_t split_pool_address(SplitPool** pool) {
+    constexpr int MAX_DEVICES = 64;
+    static std::atomic<SplitPool*> known[MAX_DEVICES];
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= MAX_DEVICES) return hipErrorInvalidDevice;
+    *pool = known[dev].load(std::memory_order_relaxed);
+    if (*pool) return hipSuccess;
+    void* at = nullptr;
+    e = hipGetSymbolAddress(&at, HIP_SYMBOL(split_pool));
+    if (e != hipSuccess) return e;
+    known[dev].store(*pool = static_cast<SplitPool*>(at), std::memory_order_relaxed);
+    return hipSuccess;
+}
+
 constexpr int GROUPED_LDS_BYTES = 128 * 1024;    // GroupRing: 128 KB / G at most per group; the groups' results fit too
 
 hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
@@ -417,12 +477,25 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     }
     const int total = p.n_tiles * p.H;
     if (total <= 0) return hipSuccess;
-    int grid = ((total + 7) / 8) * 8;           // the kernels spread their workgroups over the 8 XCDs
+    p.splits = std::max(1, p.splits);
+    if (p.splits > MAX_SPLITS || (p.splits > 1 && (!v.splits || int64_t(total) * p.splits > SPLIT_SLOTS))) return hipErrorInvalidValue;
+    p.per_tile = p.splits;
+    p.merge = 0;
+    p.slice_blocks = 16 >> log_g;
+    int grid = ((total * p.splits + 7) / 8) * 8;           // the kernels spread their workgroups over the 8 XCDs
+    if (p.splits > 1) {
+        static std::atomic<unsigned long long> calls{0};
+        p.token = calls.fetch_add(1, std::memory_order_relaxed) % (SPLIT_TOKENS - 1) + 1;
+        hipError_t e = split_pool_address(&p.pool);
+        if (e != hipSuccess) return e;
+        // a workgroup of the merge takes as many of a tile's 16-row blocks as leave about one workgroup per CU
+        while (p.slice_blocks > 1 && int64_t(total) * ((16 >> log_g) / p.slice_blocks) < 200) p.slice_blocks >>= 1;
+    }
     p.n_groups = 0;
     const int groups = p.H * p.n_chunks;
     // (every kernel but the simple ones reads the placement; a launch of one round is better dealt out evenly: whole
     // groups can give one XCD more tiles than it has CUs)
-    if (variant > kNumSimple && p.n_chunks > 1 && total > 256 && groups >= 16 && groups <= MAX_XCD_GROUPS) {
+    if (variant > kNumSimple && p.splits == 1 && p.n_chunks > 1 && total > 256 && groups >= 16 && groups <= MAX_XCD_GROUPS) {
         // Tiles of different chunks differ in length, and the hardware binds workgroup b to XCD b % 8: hand each
         // XCD whole (head, chunk) groups so that all carry the same number of kblock steps (longest group to the
         // least loaded XCD), and let each start with its longest tiles.
@@ -469,6 +542,13 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         attr_set[variant - 1][log_g] = true;
     }
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(v.threads), lds_bytes, s, p);
+    if (p.splits > 1) {
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        p.merge = 1;
+        p.per_tile = (16 >> log_g) / p.slice_blocks;
+        hipLaunchKernelGGL(kernel, dim3((total * p.per_tile + 7) / 8 * 8), dim3(v.threads), lds_bytes, s, p);
+    }
     return hipGetLastError();
 }
 

@@ -36,8 +36,14 @@
 // per step at G = 1, 2, 4 and head_dim 128) and, with all CUs at work, L2 (12.5 TB/s at G = 4).  Measured, us: 270 rows x 43 kblocks x
 // 6 heads x 64: 25 -> 10 (G = 8); 1170 x 183 x 12 x 128: 121 -> 57 (G = 4); 1560 x 634 x 12 x 128: 361 -> 231 (G = 2).  One barrier per step with
 // loads three steps ahead instead of one per two steps and one period ahead was slower (head_dim 64, G = 2: 55 against 48).
+// A streamed chunk may also have its tiles' keys dealt to several workgroups (rule: attn_split in attn_kernel.hip), which need
+// not share one CU's LDS and its 64 bytes a clock from L2 and whose rings can be long again: G * splits shares of a tile's
+// keys, partial results through the slots of split.h, and a second launch of the same kernel that adds them up.  What bounds
+// it then: some 7 us of a workgroup around its steps, the merge's launch, and the partial results' way (0.25 us per MB there
+// and back).  us without and with: 190 rows x 143 kblocks x 4 heads x 128 41 -> 20, 1560 x 634 x 12 x 128 227 -> 172.
 #include "kernels.h"
 #include "lds_plan.h"
+#include "split.h"
 
 namespace ll {
 
@@ -164,7 +170,7 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     // A share of the keys may begin with a kblock that scores -inf throughout for some query, although the key set does not:
     // the pass that follows the maximum then has no reference (mref -inf, scores relative to 0) until a live score comes.
     // (The fixed-reference pass makes NaN of it, which sends the tile there.)
-    constexpr bool NO_REF = TRACK && G > 1;
+    constexpr bool NO_REF = TRACK;
     static_assert(NF % NW == 0 && (G == 1 || KS % NW == 0), "fragments must split over the waves");
     static_assert(PF >= LAND && PF + 2 <= NS, "ring too short for the prefetch distance");
 
@@ -301,7 +307,7 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     // Sink at a fixed rotary distance (see attn_stream.hip): range 0 is the sink, scored with the queries turned back
     // by sink_shift frames on the frame axis; the unturned queries are loaded again in step n0 - 1.
     // (a share that begins behind the sink has nothing to turn)
-    const int sink_shift = G > 1 && vb >= n0 ? 0 : ch.sink_shift;
+    const int sink_shift = vb >= n0 ? 0 : ch.sink_shift;
     if (sink_shift != 0) {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
@@ -656,20 +662,49 @@ __device__ __forceinline__ void s16_group_idle(const AttnParams& p, const AttnCh
     __builtin_amdgcn_s_waitcnt(0);
 }
 
-// One query tile of 256 / G rows, its keys dealt to G groups of 8 / G waves: kblocks [T j / G, T (j + 1) / G) to group j.
+// 16 dq + 4 g + j, j = 0..3, of a row's unnormalised output (with reference m and row sum l) to where the call wants it
+template <int D, bool LSE>
+__device__ __forceinline__ void s16_store_unit(const AttnParams& p, int head, int row, int dq, int g, const f32x4& o, float m, float l) {
+    const float inv = 1.0f / l;
+    const u32x2 w = {s16_pack_bf16(o[0] * inv, o[1] * inv), s16_pack_bf16(o[2] * inv, o[3] * inv)};
+    uint16_t* dst = p.out_frag != nullptr        // uniform
+        ? p.out_frag + op_frag_offset(row, head * (D / 32) + (dq >> 1), g, p.H * (D / 32)) + (dq & 1) * 4
+        : p.out + (int64_t(row) * p.H + head) * D + dq * 16 + g * 4;
+    *reinterpret_cast<u32x2*>(dst) = w;
+    if constexpr (LSE) {
+        if (p.lse != nullptr && dq == 0 && g == 0) p.lse[int64_t(head) * p.lse_stride + row] = m + __builtin_amdgcn_logf(l);
+        if (p.out32 != nullptr) *reinterpret_cast<f32x4*>(p.out32 + (int64_t(row) * p.H + head) * D + dq * 16 + g * 4) = o * inv;
+    }
+}
+
+// Where a workgroup's result goes: as rows [.., row_end) of the output, or (splits > 1) as one of the partial results of a
+// tile whose keys are dealt to several workgroups as well: this one takes share `split` of `splits`.
+struct S16Share {
+    int split, splits, item, readers;            // item: the workgroup's place in the launch; readers: slices of the merge
+};
+
+// One query tile of 256 / G rows from row0 on, its keys dealt to G groups of 8 / G waves: kblocks [T j / G, T (j + 1) / G) to
+// group j (with splits: the split's G of the G * splits shares).
 // Each group's result is relative to its own reference; they meet in LDS (the rings' memory), where every wave adds up
 // its part of the features over the groups: weights 2^(m_j - max m), one division by the weighted sum of the row sums.
 template <int D, bool QSCALE, bool LSE, int SCHED, int G>
-__device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnChunk& ch, int head, int tile, char* lds,
-                                               const float2* shift_cs, float2 (*ml)[2][16]) {
+__device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnChunk& ch, int head, int row0, const S16Share& sh, char* lds,
+                                               const float2* shift_cs, float2 (*ml)[2][16], int& slot_lds) {
     constexpr int NW = 8 / G, UNITS = D / 16 * 2;                // (dq, qb) blocks of a wave's O^T
     static_assert(UNITS % G == 0, "the O^T blocks must split over the groups");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int group = wave / NW, rb = wave % NW;
     const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
-    const int q0 = ch.q_begin + (tile - ch.tile_begin) * (256 / G) + rb * 32;
+    const int q0 = row0 + rb * 32;
     const bool has_rows = q0 < ch.q_end;
-    const int T = ch.n_kblocks, vb = T * group / G, ve = T * (group + 1) / G, n_steps = (T + G - 1) / G;
+    const int T = ch.n_kblocks;
+    int vb = T * group / G, ve = T * (group + 1) / G, n_steps = (T + G - 1) / G;
+    if (sh.splits > 1) {                         // uniform (and three divisions, in front of everything else)
+        const int shares = G * sh.splits, share = G * sh.split + group;
+        vb = T * share / shares;
+        ve = T * (share + 1) / shares;
+        n_steps = (T + shares - 1) / shares;
+    }
     const bool works = has_rows && ve > vb;
     S16State<D> st;
     if (works) s16_segment<D, QSCALE, SCHED, G>(p, ch, head, q0, vb, ve, n_steps, lds, st, shift_cs);
@@ -691,6 +726,7 @@ __device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnCh
         }
     }
     __syncthreads();                             // every group has left its ring
+    if (sh.splits > 1 && threadIdx.x == 0) slot_lds = split_claim(p.pool, sh.item, p.token, sh.readers);
     f32x4* part = reinterpret_cast<f32x4*>(lds);                 // [wave][unit][lane]
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
@@ -703,33 +739,88 @@ __device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnCh
     }
     __syncthreads();
     if (!has_rows) return;
+    // unit group * (UNITS / G) + i of the tile's O^T blocks over all groups, relative to reference m
+    auto add_up = [&](int i, bool may_be_weightless, float& m, float& l, f32x4& o) {
+        const int u = group * (UNITS / G) + i, qb = u & 1;
+        m = -INFINITY;
+        l = 0.f;
+        o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < UNITS / G; ++i) {
-        const int u = group * (UNITS / G) + i, dq = u >> 1, qb = u & 1;
-        const int row = q0 + 16 * qb + n;
-        float m = -INFINITY, l = 0.f;
-        f32x4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + rb][qb][n].x);      // finite unless every key scores -inf
+        for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + rb][qb][n].x);
+        const float base = may_be_weightless && m == -INFINITY ? 0.f : m;
 #pragma unroll
         for (int j = 0; j < G; ++j) {
             const float2 s = ml[j * NW + rb][qb][n];
-            const float a = __builtin_amdgcn_exp2f(s.x - m);
+            const float a = __builtin_amdgcn_exp2f(s.x - base);
             l += s.y * a;
             o += part[((j * NW + rb) * UNITS + u) * 64 + lane] * a;
         }
-        if (row >= ch.q_end) continue;
-        const float inv = 1.0f / l;
-        const u32x2 w = {s16_pack_bf16(o[0] * inv, o[1] * inv), s16_pack_bf16(o[2] * inv, o[3] * inv)};
-        uint16_t* dst = p.out_frag != nullptr        // uniform
-            ? p.out_frag + op_frag_offset(row, head * (D / 32) + (dq >> 1), g, p.H * (D / 32)) + (dq & 1) * 4
-            : p.out + (int64_t(row) * p.H + head) * D + dq * 16 + g * 4;
-        *reinterpret_cast<u32x2*>(dst) = w;
-        if constexpr (LSE) {
-            if (p.lse != nullptr && dq == 0 && g == 0) p.lse[int64_t(head) * p.lse_stride + row] = m + __builtin_amdgcn_logf(l);
-            if (p.out32 != nullptr) *reinterpret_cast<f32x4*>(p.out32 + (int64_t(row) * p.H + head) * D + dq * 16 + g * 4) = o * inv;
+    };
+    float m, l;
+    f32x4 o;
+    if (sh.splits > 1) {                         // uniform.  A share may hold no key with weight, a tile does (or is NaN)
+        const int slot = slot_lds;
+        if (slot < 0) return;                    // the merge does without this workgroup
+#pragma unroll
+        for (int i = 0; i < UNITS / G; ++i) {
+            const int u = group * (UNITS / G) + i, blk = rb * 2 + (u & 1);
+            add_up(i, true, m, l, o);
+            reinterpret_cast<f32x4*>(p.pool->o[slot])[(blk * (D / 16) + (u >> 1)) * 64 + lane] = o;
+            if (u < 2 && g == 0) p.pool->ml[slot][blk * 16 + n] = make_float2(m, l);
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < UNITS / G; ++i) {
+        const int u = group * (UNITS / G) + i, row = q0 + 16 * (u & 1) + n;
+        add_up(i, false, m, l, o);
+        if (row < ch.q_end) s16_store_unit<D, LSE>(p, head, row, u >> 1, g, o, m, l);
+    }
+}
+
+// The partial results of a tile's splits, for the 16-row blocks [first, first + n_blocks) of the tile: the same sum as
+// over key groups.  Bounded by latency and by the partials' way through the last-level cache.  False (for the whole
+// workgroup) if some split found no room for its partial result: nothing is written then.
+template <int D, bool LSE>
+__device__ __forceinline__ bool s16_merge(const AttnParams& p, const AttnChunk& ch, int head, int tile, int splits, int row0, int first,
+                                          int n_blocks, int* slots) {
+    constexpr int DQ = D / 16;
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+    if (tid < splits) slots[tid] = split_find(p.pool, (head * p.splits + tid) * p.n_tiles + tile, p.token);
+    __syncthreads();
+    bool all = true;
+    for (int s = 0; s < splits; ++s) all = all && slots[s] >= 0;
+    if (all) {
+        for (int u = tid >> 6; u < n_blocks * DQ; u += S16_THREADS / 64) {
+            const int blk = first + u / DQ, dq = u % DQ, row = row0 + (blk - first) * 16 + n;
+            float m = -INFINITY, l = 0.f;
+            f32x4 o = {0.f, 0.f, 0.f, 0.f};
+            for (int s = 0; s < splits; s += 4)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m = fmaxf(m, p.pool->ml[slots[min(s + e, splits - 1)]][blk * 16 + n].x);
+            for (int s0 = 0; s0 < splits; s0 += 4) {
+                float2 w[4];
+                f32x4 x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int slot = slots[min(s0 + e, splits - 1)];
+                    w[e] = p.pool->ml[slot][blk * 16 + n];
+                    x[e] = reinterpret_cast<const f32x4*>(p.pool->o[slot])[(blk * DQ + dq) * 64 + lane];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (s0 + e < splits) {
+                        const float a = __builtin_amdgcn_exp2f(w[e].x - m);
+                        l += w[e].y * a;
+                        o += x[e] * a;
+                    }
+            }
+            if (row < ch.q_end) s16_store_unit<D, LSE>(p, head, row, dq, g, o, m, l);
         }
     }
+    __syncthreads();                             // every read of the partial results has returned
+    if (tid < splits && slots[tid] >= 0) split_release(p.pool, slots[tid]);
+    return all;
 }
 
 // ---- one workgroup per (head, query tile): placement on the XCDs as in attn_stream.hip.  G: key groups
@@ -737,21 +828,29 @@ template <int D, bool QSCALE, bool LSE, int SCHED, int G>
 __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_stream16_kernel(const AttnParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ float2 shift_cs[64];
+    __shared__ int slots[MAX_SPLITS];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // The arguments lie in several cache lines; where a launch has one chunk, all that a workgroup needs of them is
     // fetched here in one go instead of one cold scalar load after another.
     AttnChunk ch = p.chunk[0];
     asm volatile("" ::"s"(ch.q_begin), "s"(ch.q_end), "s"(ch.tile_begin), "s"(ch.n_ranges), "s"(ch.rs[0]), "s"(ch.rs[1]), "s"(ch.rs[2]),
                  "s"(ch.re[0]), "s"(ch.re[1]), "s"(ch.re[2]), "s"(ch.n_kblocks), "s"(ch.sink_shift), "s"(ch.t_row));
-    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_frag), "s"(p.t_table), "s"(p.row_cs), "s"(p.col_cs));
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_frag), "s"(p.t_table), "s"(p.row_cs), "s"(p.col_cs), "s"(p.splits), "s"(p.per_tile));
     const int xcd = blockIdx.x & 7;
     int idx = blockIdx.x >> 3, head = -1, tile = 0;
+    S16Share sh = {0, 1, 0, 0};
+    int slice = 0;
     if (p.n_groups == 0) {
-        const int total = p.n_tiles * p.H;
+        const int per_head = p.n_tiles * p.per_tile, total = per_head * p.H;
         const int item = ((xcd * total + 7) >> 3) + idx;
         if (item < (((xcd + 1) * total + 7) >> 3)) {
-            head = item / p.n_tiles;
-            tile = item % p.n_tiles;
+            head = item / per_head;
+            tile = item - head * per_head;
+            if (p.per_tile > 1) {                // a tile's workgroups: splits of its keys (heads, splits, tiles: those of a
+                sh.item = item;                  // split side by side, they share its keys), or slices of the merge
+                slice = sh.split = tile / p.n_tiles;
+                tile -= sh.split * p.n_tiles;
+            }
         }
     } else {
         for (int gi = p.xcd_first[xcd]; gi < p.xcd_first[xcd + 1]; ++gi) {
@@ -771,6 +870,24 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
         ch = p.chunk[ci];
     }
+    int row0 = ch.q_begin + (tile - ch.tile_begin) * (256 / G);
+    if (p.splits > 1) {                          // uniform
+        const int splits = min(p.splits, max(1, ch.n_kblocks / G));              // no more than the chunk has keys for
+        const int slice_rows = 16 * p.slice_blocks, rows = min(256 / G, ch.q_end - row0);
+        if (p.merge) {
+            // where a partial result is missing, the slice is computed here whole, as a tile of its own
+            const int first = slice * p.slice_blocks;
+            row0 += slice * slice_rows;
+            if (slice * slice_rows >= rows) return;
+            if (s16_merge<D, LSE>(p, ch, head, tile, splits, row0, first, min(p.slice_blocks, 16 / G - first), slots)) return;
+            ch.q_end = min(ch.q_end, row0 + slice_rows);
+            sh = {0, 1, 0, 0};
+        } else {
+            if (sh.split >= splits) return;
+            sh.splits = splits;
+            sh.readers = (rows + slice_rows - 1) / slice_rows;
+        }
+    }
     if (ch.sink_shift != 0) {                    // uniform over the workgroup
         if ((int)threadIdx.x < p.n_t) {
             double sn, cs;
@@ -781,30 +898,52 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     }
     if constexpr (G > 1) {
         __shared__ float2 ml[8][2][16];          // (reference, row sum) per wave, query block and column
-        s16_split_tile<D, QSCALE, LSE, SCHED, G>(p, ch, head, tile, lds, shift_cs, ml);
+        s16_split_tile<D, QSCALE, LSE, SCHED, G>(p, ch, head, row0, sh, lds, shift_cs, ml, slots[0]);
         return;
     }
     const int row_block = ((wave & 3) << 1) | (wave >> 2);      // waves w and w + 4 (one SIMD) take neighbouring blocks
-    const int q0 = ch.q_begin + (tile - ch.tile_begin) * 256 + row_block * 32;
+    const int q0 = row0 + row_block * 32;
+    int vb = 0, ve = ch.n_kblocks;
+    if (sh.splits > 1) {                         // uniform
+        vb = ch.n_kblocks * sh.split / sh.splits;
+        ve = ch.n_kblocks * (sh.split + 1) / sh.splits;
+    }
     // wave-uniform: a wave without rows in the chunk's last tile only takes its share of the loads and barriers
     const bool has_rows = q0 < ch.q_end;
     S16State<D> st;
-    if (has_rows) s16_segment<D, QSCALE, SCHED, 1>(p, ch, head, q0, 0, ch.n_kblocks, ch.n_kblocks, lds, st, shift_cs);
-    else s16_segment_loads_only<D>(p, ch, head, 0, ch.n_kblocks, lds);
+    if (has_rows) s16_segment<D, QSCALE, SCHED, 1>(p, ch, head, q0, vb, ve, ve - vb, lds, st, shift_cs);
+    else s16_segment_loads_only<D>(p, ch, head, vb, ve, lds);
     if constexpr ((SCHED & 8) != 0) {
         // the pass above kept its first reference: fine unless some row's sum ran away (a score far above the first
         // kblock's maximum); then the whole workgroup (the waves share the ring and its barriers) takes the tile again
         // with the reference followed.  The barrier inside the vote also ends every wave's reads of the first pass.
         const bool ran_away = has_rows && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
         if (__syncthreads_or(ran_away)) {
-            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1>(p, ch, head, q0, 0, ch.n_kblocks, ch.n_kblocks, lds, st, shift_cs);
-            else s16_segment_loads_only<D>(p, ch, head, 0, ch.n_kblocks, lds);
+            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1>(p, ch, head, q0, vb, ve, ve - vb, lds, st, shift_cs);
+            else s16_segment_loads_only<D>(p, ch, head, vb, ve, lds);
         }
+    }
+    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+    if (sh.splits > 1) {                         // uniform: a partial result
+        if (threadIdx.x == 0) slots[0] = split_claim(p.pool, sh.item, p.token, sh.readers);
+        __syncthreads();
+        const int slot = slots[0];
+        if (slot < 0 || !has_rows) return;       // (the merge does without this workgroup)
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            float l = st.l[qb];
+            l += __shfl_xor(l, 16);
+            l += __shfl_xor(l, 32);
+            const int blk = row_block * 2 + qb;
+            if (g == 0) p.pool->ml[slot][blk * 16 + n] = make_float2(st.m[qb], l);
+#pragma unroll
+            for (int dq = 0; dq < D / 16; ++dq) reinterpret_cast<f32x4*>(p.pool->o[slot])[(blk * (D / 16) + dq) * 64 + lane] = st.o[dq][qb];
+        }
+        return;
     }
     if (!has_rows) return;
 
     // out[row][head][16 dq + 4 g + j] = O^T block (dq, qb) register j, divided by the row sum
-    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
         float l = st.l[qb];
@@ -852,7 +991,7 @@ constexpr int S16_DEFAULT = 9, S16_TRACKED = 1;
 #define S16_ENTRY(name, D, QS, LSE, SCHED)                                                                            \
     {name, D, 256, 8 * 2 * KBLOCK * D * 2, S16_KERNEL(D, QS, LSE, SCHED, 1), S16_THREADS, KBLOCK,                     \
      {S16_KERNEL(D, QS, LSE, SCHED, 2), S16_KERNEL(D, QS, LSE, SCHED, 4),                                             \
-      D == 64 ? S16_KERNEL(D, QS, LSE, SCHED, (D == 64 ? 8 : 4)) : nullptr}}
+      D == 64 ? S16_KERNEL(D, QS, LSE, SCHED, (D == 64 ? 8 : 4)) : nullptr}, true}
 // (the tracked variants are there to be compared with, one key group)
 #define S16_ENTRY_WHOLE(name, D, QS, LSE, SCHED) \
     {name, D, 256, 8 * 2 * KBLOCK * D * 2, S16_KERNEL(D, QS, LSE, SCHED, 1), S16_THREADS, KBLOCK, {}}

@@ -152,7 +152,15 @@ struct AttnParams {
     int kblock;                  // key slots per kblock: 32 (bf16 cache) or 64 (8-bit cache)
     const double* inv_freq_t;    // frame-axis rotary frequencies [n_t] (used when a chunk has a sink_shift)
     int n_t;
-    int key_groups;              // key groups per tile (AttnVariant::grouped); 0: chosen for the launch (attn_key_groups)
+    int key_groups;              // key groups per tile (AttnVariant::grouped); 0: groups and splits chosen for the launch
+    // A tile's keys dealt to `splits` workgroups, whose partial results a second launch of the kernel merges (split.h);
+    // chunks of fewer kblocks take fewer.  The rest is filled in by launch_attn.
+    int splits;
+    int merge;                   // this launch is the merge: a workgroup takes slice_blocks 16-row blocks of a tile
+    int slice_blocks;
+    int per_tile;                // workgroups per tile: splits, or slices of the merge
+    unsigned long long token;
+    struct SplitPool* pool;
     bool keys_reside;            // the one key range may be brought into LDS whole where it fits (attn_resident.hip)
     float* lse;                  // *_lse kernels: log2 of each row's sum of 2^score, [H][lse_stride] (null otherwise)
     int64_t lse_stride;
@@ -224,6 +232,7 @@ struct AttnVariant {
     // The same work with the keys of a tile dealt to G = 2, 4, 8 groups of the workgroup's waves (qtile / G rows per
     // workgroup); null where there is no such kernel.
     void (*grouped[3])(const AttnParams);
+    bool splits;                 // the kernels honour AttnParams::splits
 };
 extern const AttnVariant kStreamVariants[];
 extern const int kNumStreamVariants;
@@ -239,6 +248,9 @@ int attn_variant_default(int D, int kblock);
 bool attn_variant_supports(int v, int D, int kblock);
 // the key groups a launch of these chunks takes with the variant: 1, 2, 4 or 8
 int attn_key_groups(int v, int H, int n_chunks, const int* rows, const int* kblocks);
+// the same for one chunk that may also be dealt to several workgroups per tile
+struct AttnSplit { int groups, splits; };
+AttnSplit attn_split(int v, int H, int rows, int kblocks);
 bool attn_variant_sink_shift(int v);          // the variant honours AttnChunk::sink_shift
 int attn_variant_lse(int D);                   // the variant that also writes AttnParams::lse
 int attn_variant_qscale(int D);                // the variant for queries not yet scaled (honours scale_log2e)

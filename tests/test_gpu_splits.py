@@ -1,0 +1,197 @@
+"""Streamed chunks whose tiles' keys are dealt to several workgroups, merged by a second launch (split.h).
+
+Where that can go wrong: shares of unequal length, warm-up chunks of fewer kblocks than splits, tiles and slices of the merge
+of few rows, a score far above one share's reference, shares without weight, output in place of the queries, a call replayed in
+a HIP graph, calls on several streams over one pool of slots, and workgroups that find no slot.  Every shape asks for what
+it gets.  References are in 64 bits, tolerances those of the unsplit path (bf16 operands, weights and results: up to 5e-3 of the
+2-norm, times the spread of the logits)."""
+import pytest
+import torch
+
+from paper_2509_22622_amd import binding as B
+from perf import cases
+
+pytestmark = pytest.mark.gpu
+
+# heads, head_dim, grid, chunk, sink, window, frames, (groups, splits)
+SHAPES = [
+    (4, 128, (10, 19), 1, 3, 20, 1, (4, 9)),    # three tiles of 64 rows, the last of 62
+    (1, 128, (6, 8), 2, 4, 26, 2, (4, 6)),    # shares of one and two kblocks
+    (5, 128, (12, 20), 3, 2, 14, 3, (4, 4)),
+    (3, 128, (9, 13), 3, 0, 21, 1, (4, 7)),    # a short chunk: 117 of 351 rows
+    (3, 128, (20, 39), 3, 3, 4, 3, (2, 4)),
+    (4, 128, (26, 41), 2, 3, 9, 2, (1, 7)),
+    (3, 64, (5, 19), 2, 3, 50, 2, (8, 7)),
+    (3, 64, (16, 45), 1, 3, 16, 1, (4, 7)),
+    (1, 64, (30, 52), 3, 3, 9, 3, (2, 6)),
+]
+
+
+def _case(heads, head_dim, grid, chunk, sink, window, frames, **kw):
+    return {"kind": "stream", "cache": "bf16", "layers": 1, "heads": heads, "head_dim": head_dim, "grid_h": grid[0],
+            "grid_w": grid[1], "chunk": chunk, "sink": sink, "window": window, "frames": frames, "first_frame": sink + window + 4,
+            "video_chunks": 0, "q_std": 2.0, "form": "two_call", **kw}
+
+
+def _split(heads, head_dim, grid, chunk, sink, window, frames):
+    P = grid[0] * grid[1]
+    return B.attn_split(head_dim, heads, frames * P, -(-(sink + window + frames) * P // 32))
+
+
+def _rel(got, want):
+    return float((got.double() - want).norm() / want.norm())
+
+
+def _bits(t):
+    return t.view(torch.int16)
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_split_tiles(shape):
+    """Both forms of the call give the same bits; so does a second pass, and one that writes over its queries; without free slots
+    (none, or some of a tile's) the merge computes tiles whole."""
+    *geo, split = shape
+    assert _split(*geo) == split
+    case = _case(*geo)
+    want = cases.exact(case, 5)[0]
+    state = cases.prepare({**case, "form": "unrotated"}, 5)
+    unrotated = cases.run(state)[0].clone()
+    torch.cuda.synchronize()
+    state["cache"].close()
+    state = cases.prepare(case, 5)
+    out = cases.run(state)[0]
+    layer, _, _, _, _, q_out, _ = state["passes"][0]
+    assert _rel(out, want) <= 5e-3 * case["q_std"]
+    assert torch.equal(_bits(out), _bits(unrotated))
+    again = torch.full_like(out, 7.0)
+    state["cache"].sink_window_attn(layer, q_out, again)
+    assert torch.equal(_bits(again), _bits(out))
+    for first, n in ((0, 512), (0, 2), (1, 511)):
+        B.hold_split_slots(first, n, True)
+        try:
+            again.fill_(7.0)
+            state["cache"].sink_window_attn(layer, q_out, again)
+            in_place = q_out.clone()
+            state["cache"].sink_window_attn(layer, in_place, in_place)
+        finally:
+            B.hold_split_slots(first, n, False)
+        assert torch.equal(_bits(in_place), _bits(again))
+        assert _rel(again, want) <= 5e-3 * case["q_std"]
+    state["cache"].sink_window_attn(layer, q_out, q_out)
+    assert torch.equal(_bits(q_out), _bits(out))
+    state["cache"].close()
+
+
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[2], SHAPES[5], SHAPES[6]])
+def test_a_video_from_its_first_frame(shape):
+    """Warm-up chunks have fewer kblocks than the full window's splits; with a sink at a fixed rotary distance as well."""
+    *geo, _ = shape
+    for sink_relative in (False, True):
+        case = _case(*geo, video_chunks=1 + -(-(geo[4] + geo[5] + 4) // geo[3]), sink_relative=sink_relative)
+        state = cases.prepare(case, 7)
+        got = cases.run(state)
+        for i, (a, b) in enumerate(zip(got, cases.exact(case, 7))):
+            # (a re-indexed sink's queries are rounded once more)
+            assert _rel(a, b) <= (7e-3 if sink_relative else 5e-3) * case["q_std"], i
+        state["cache"].close()
+
+
+def _cached(cache, P, heads, D):
+    """Rotated keys and values of the live frames, oldest first."""
+    kv = [tuple(torch.empty((P, heads, D), dtype=torch.bfloat16, device="cuda") for _ in range(2)) for _ in cache.live_frames(0)]
+    for f, (k, v) in zip(cache.live_frames(0), kv):
+        cache.read_frame(0, f, k, v)
+    return (torch.cat(x) for x in zip(*kv))
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[4], SHAPES[5], SHAPES[7]])
+@pytest.mark.parametrize("spoil", ["far", "weightless"])
+def test_unlike_shares(shape, spoil):
+    """A key along a query takes that row's whole weight, far above every other share's reference; or the keys of several frames
+    score minus infinity and fill whole shares and the beginnings of others."""
+    heads, D, grid, chunk, sink, window, frames, split = shape
+    P, f0 = grid[0] * grid[1], sink + window + 4
+    g = torch.Generator(device="cuda").manual_seed(P)
+    make = lambda n: torch.empty((n * P, heads, D), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    k, v, kc, vc, q = make(sink + window), make(sink + window), make(frames), make(frames), make(frames)
+    pair = (D - 4 * (D // 6)) // 2 - 1               # the frame axis's slowest pair: a positive angle below pi / 2 at frames 1 .. f0
+    if spoil == "weightless":
+        for x in (k, kc):
+            x[..., 2 * pair:2 * pair + 2] = 0
+        for first, last in ((1, 2), (sink + 1, sink + 4), (sink + window - 1, sink + window)):
+            k[first * P:last * P, :, 2 * pair] = float("-inf")
+    cache = B.Cache(1, heads, D, *grid, chunk, sink, window)
+    cache.recache_prefill(0, True, f0 - window, window, k, k, v, torch.empty_like(k))
+    cache.chunk_append(0, f0, frames, q, kc, vc, torch.empty_like(q))
+    keys, values = _cached(cache, P, heads, D)
+    q = make(frames) * 0.25                           # as the cache write would leave them: scores in the log2 domain
+    if spoil == "far":
+        q[5] = 2 * keys[len(keys) // 2]
+    else:
+        q[..., 2 * pair:2 * pair + 2] = 0.5
+    out = torch.empty_like(q)
+    cache.sink_window_attn(0, q, out)
+    torch.cuda.synchronize()
+    cache.close()
+    want = torch.empty(out.shape, dtype=torch.float64, device="cuda")
+    for h in range(heads):
+        scores = q[:, h].double() @ keys[:, h].double().T.contiguous()
+        assert not bool(scores.isnan().any())
+        want[:, h] = torch.softmax(scores * 0.6931471805599453, 1) @ values[:, h].double()
+    assert bool(torch.isfinite(out).all())
+    assert _rel(out, want) <= 5e-3
+
+
+def test_replays_of_a_captured_call():
+    heads, D, grid, chunk, sink, window, frames, split = SHAPES[2]
+    state = cases.prepare(_case(*SHAPES[2][:-1], form="unrotated"), 9)
+    layer, start, q, k, v, _, out = state["passes"][0]
+    cases.run(state)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cases.run(state)
+    for seed in range(4):
+        fresh = cases.prepare(_case(*SHAPES[2][:-1], form="unrotated"), 20 + seed)
+        want = cases.run(fresh)[0]
+        for mine, theirs in zip((q, k, v), fresh["passes"][0][2:5]):
+            mine.copy_(theirs)
+        cache, same = state["cache"], fresh["cache"]
+        same.sink_window_attn_unrotated(0, q, want)       # the program's own work between replays
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        eager = torch.empty_like(out)
+        cache.sink_window_attn_unrotated(0, q, eager)
+        assert torch.equal(_bits(out), _bits(eager)), seed
+        same.close()
+    state["cache"].close()
+
+
+def test_calls_on_several_streams():
+    """Eight streams over one pool, several of them on one layer: each call's output is that of the call alone, or of its tiles
+    computed whole, and no slot stays taken."""
+    shape = SHAPES[2]
+    state = cases.prepare(_case(*shape[:-1]), 11)
+    want = cases.run(state)[0].clone()
+    cache, q = state["cache"], state["passes"][0][5]
+    B.hold_split_slots(0, 512, True)
+    whole = torch.empty_like(want)
+    cache.sink_window_attn(0, q, whole)
+    B.hold_split_slots(0, 512, False)
+    exact = cases.exact(_case(*shape[:-1]), 11)[0]
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    outs = [[torch.empty_like(want) for _ in range(10)] for _ in streams]
+    torch.cuda.synchronize()
+    for i in range(10):
+        for s, o in zip(streams, outs):
+            with torch.cuda.stream(s):
+                cache.sink_window_attn(0, q, o[i])
+    torch.cuda.synchronize()
+    for o in [x for y in outs for x in y]:
+        assert bool(((_bits(o) == _bits(want)) | (_bits(o) == _bits(whole))).all())
+        assert _rel(o, exact) <= 5e-3 * 2.0
+    again = torch.empty_like(want)
+    cache.sink_window_attn(0, q, again)
+    assert torch.equal(_bits(again), _bits(want))
+    cache.close()
