@@ -76,7 +76,8 @@ ll_status ll_cache_create(int layers, int heads, int head_dim, int tokens_per_fr
  * either kind of handle.  Definition (e4m3 = nearest E4M3 value, ties to even, |x| clamped to 448 first):
  *     K8 = e4m3(K' * 2^-k_exp), V8 = e4m3(V * 2^-v_exp), Q8 = e4m3(q' * log2(e)/sqrt(D) * 2^k_exp),
  *     out = 2^v_exp * sum_j w_j V8_j / sum_j w_j,   w_j = 2^(Q8 . K8_j - max);
- *   the kernel also rounds the weights w_j to E4M3 (relative to a running reference) before the second product.
+ *   the kernel also rounds the weights w_j to E4M3 (relative to a running reference) before the second product, or, where
+ *   a launch of few rows and heads deals a tile's keys to several workgroups, to the sum of two E4M3 numbers.
  *   k_exp, v_exp in [-16, 16]: powers of two (exact to apply) that bring K' and V into E4M3's range; 0 suits
  *   inputs of magnitude up to a few hundred, and a floating point format needs no finer (per-frame) scale.
  *   Differences for the other calls with such a handle:

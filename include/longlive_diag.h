@@ -25,10 +25,11 @@ const char* ll_attn_variant_name(int variant); /* NULL when `variant` does not e
  * own, with the key set of a full window; a clip or a prompt as the launch it is.  No GPU needed. */
 ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* groups);
 
-/* What a streamed chunk of `rows` query rows takes whose key set has `kblocks` blocks of 32 keys once the window is full: its
- * tiles' keys are dealt to `splits` workgroups (1: not split, then groups is ll_attn_key_groups' answer), in each of them to
- * `groups` groups of waves.  No GPU needed. */
-ll_status ll_attn_split(int head_dim, int heads, int rows, int kblocks, int* groups, int* splits);
+/* What a streamed chunk of `rows` query rows takes whose key set has `kblocks` blocks of 32 keys (fp8 != 0, the 8-bit cache: 64)
+ * once the window is full: its tiles' keys are dealt to `splits` workgroups (1: not split), in each of them to `groups`
+ * groups of waves (bf16, not split: ll_attn_key_groups' answer; 8-bit: a tile has 256 / groups rows and its waves all walk
+ * all keys of the split).  No GPU needed. */
+ll_status ll_attn_split(int head_dim, int fp8, int heads, int rows, int kblocks, int* groups, int* splits);
 /* The partial results of split tiles wait for their merge in 512 slots that all calls on a GPU share; a workgroup that finds
  * no slot free leaves its tile to the merge, which then computes it whole.  This call takes the free ones among slots
  * [first, first + n) out of use on the current device (hold != 0), or gives back those it took (hold == 0), so that

@@ -54,7 +54,7 @@ SIGNATURES = {
     "ll_set_attn_variant": (_i, [_i]),
     "ll_attn_variant_name": (C.c_char_p, [_i]),
     "ll_attn_key_groups": (_i, [_i] * 3 + [C.POINTER(_i)] * 3),
-    "ll_attn_split": (_i, [_i] * 4 + [C.POINTER(_i)] * 2),
+    "ll_attn_split": (_i, [_i] * 5 + [C.POINTER(_i)] * 2),
     "ll_hold_split_slots": (_i, [_i] * 3),
     "ll_probe_mfma_rate": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "ll_probe_mfma_mix": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
@@ -118,10 +118,10 @@ def attn_key_groups(head_dim, heads, chunks) -> int:
     return groups.value
 
 
-def attn_split(head_dim, heads, rows, kblocks):
-    """(key groups, splits) of a streamed chunk with ``kblocks`` blocks of 32 keys in a full window."""
+def attn_split(head_dim, heads, rows, kblocks, kv_format="bf16"):
+    """(groups, splits) of a streamed chunk with ``kblocks`` blocks of 32 keys (8-bit cache: 64) in a full window."""
     groups, splits = C.c_int(), C.c_int()
-    _check(lib().ll_attn_split(head_dim, heads, rows, kblocks, C.byref(groups), C.byref(splits)))
+    _check(lib().ll_attn_split(head_dim, int(kv_format == "fp8_e4m3"), heads, rows, kblocks, C.byref(groups), C.byref(splits)))
     return groups.value, splits.value
 
 

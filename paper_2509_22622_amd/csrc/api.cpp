@@ -329,8 +329,10 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
         const int rows = work[i].q_end - work[i].q_begin;
         const int kblocks = int((int64_t(c->g.S + c->g.W) * c->g.P + rows + c->kb - 1) / c->kb);
         // (a streamed chunk may also take splits; a re-prefill, whose launch is larger, would pay for them: 16 single-frame
-        // chunks of 190 x 4 x 128 would take 3 times as long, so there a chunk whose tiles split has other roundings)
-        const AttnSplit split = streamed ? attn_split(variant, c->H, rows, kblocks) : AttnSplit{attn_key_groups(variant, c->H, 1, &rows, &kblocks), 1};
+        // chunks of 190 x 4 x 128 would take 3 times as long, so there a chunk whose tiles split has other roundings.  The
+        // 8-bit cache's re-prefill has tiles and splits chosen for the launch.)
+        const AttnSplit split = streamed ? attn_split(variant, c->H, 1, &rows, &kblocks)
+                                         : AttnSplit{c->fmt ? 0 : attn_key_groups(variant, c->H, 1, &rows, &kblocks), 1};
         order[i] = {split.groups * 256 + split.splits, int(i)};
     }
     // longest key sets first: they bound the launch
@@ -361,6 +363,7 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
         }
         p.key_groups = order[base].first / 256;
         p.splits = order[base].first % 256;
+        p.may_split = true;
         const int m = int(end - base);
         p.inv_freq_t = c->rope.inv_freq_t; p.n_t = c->rope.n_t;
         for (int i = 0; i < m; ++i) {

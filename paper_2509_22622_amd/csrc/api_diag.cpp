@@ -27,11 +27,11 @@ ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* r
     return LL_OK;
 }
 
-ll_status ll_attn_split(int head_dim, int heads, int rows, int kblocks, int* groups, int* splits) {
+ll_status ll_attn_split(int head_dim, int fp8, int heads, int rows, int kblocks, int* groups, int* splits) {
     if (!groups || !splits) return fail(LL_ERR_INVALID_ARG, "null pointer");
     if ((head_dim != 64 && head_dim != 128) || heads < 1 || heads > 1024 || rows < 1 || kblocks < 1)
         return fail(LL_ERR_INVALID_ARG, "head_dim %d, heads %d, rows %d or kblocks %d out of range", head_dim, heads, rows, kblocks);
-    const AttnSplit s = attn_split(attn_variant_default(head_dim, KBLOCK), heads, rows, kblocks);
+    const AttnSplit s = attn_split(attn_variant_default(head_dim, fp8 ? KBLOCK8 : KBLOCK), heads, 1, &rows, &kblocks);
     *groups = s.groups;
     *splits = s.splits;
     return LL_OK;

@@ -18,6 +18,11 @@
 // sums add the fp32 weights before the conversion.  The final division by the row sum removes the reference
 // and the shift; 2^v_exp is applied there.
 //
+// Launches of few rows and heads: a 256-row tile of each head is less than the chip has CUs, and every workgroup walks all keys
+// at the pace of two waves per SIMD (0.8 us a kblock at head_dim 128, exponentials and MFMAs in turn).  They take narrower tiles
+// (0.55 us with one wave per SIMD) and, below that, several workgroups per tile (split.h).  us: 980 rows x 50 kblocks x 2 heads x
+// 128 52 -> 26; 300 x 36 x 24 x 128 42 -> 28; the rule and more figures are at attn_split in attn_kernel.hip.
+//
 // The scaled form of the MFMA is used with both scales 1 (E8M0 code 127).  The compiler may place its result on
 // top of an operand that dies at the instruction, which this multi-pass instruction does not tolerate (wrong
 // numbers, seen on the GPU): f8_mfma keeps both operands alive, together with the result, past the instruction, and
@@ -26,11 +31,13 @@
 // such a register before the counted wait would store stale data.
 #include "kernels.h"
 #include "lds_plan.h"
+#include "split.h"
 
 namespace ll {
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -83,7 +90,7 @@ __device__ __forceinline__ unsigned f8_live_mask(int key0, int rs, int re, int h
 template <int D>
 struct F8State {
     f32x16 o[D / 32];
-    float l;
+    float l, m;                                 // row sum (this lane's half of the keys) and reference
 };
 
 template <int D>
@@ -326,8 +333,13 @@ __device__ __forceinline__ void f8_lds_wait(u32x4& x, u32x4& y) {
 // an octave.  The row sum is then taken from the same 8-bit weights by one more MFMA per kblock whose A operand is all
 // ones, so numerator and denominator agree exactly and the output is a convex combination of the V8 rows; the
 // accumulators hold the raw scores (started from zero), the reference enters through the multiply-add's constant.
-template <int D, bool LOGLIN>
-__device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChunk& ch, int head, int q0, char* lds, F8State<D>& st) {
+//
+// TWO = true carries a weight as the sum of two E4M3 numbers, its nearest and the nearest of what that leaves, each with an
+// MFMA of its own: 7 bits instead of 3.  A weight's rounding depends on the reference, and the shares of a split tile have
+// references of their own; so rounded once, the sum over shares would be as far from the whole tile's as either is from
+// the exact weights (2.6 % of the 2-norm each), though neither is better.  With two terms it is where the exact weights are.
+template <int D, bool LOGLIN, bool TWO, int NW>
+__device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChunk& ch, int head, int q0, int vb, int ve, char* lds, F8State<D>& st) {
     constexpr int DH = D / 64;
     constexpr int DB = D / 32;
     constexpr int NK = 2 * DH;                  // S^T slots
@@ -336,7 +348,6 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
     constexpr int STAGE_BYTES = 2 * KB_BYTES;
     constexpr int NS = RingPlan::STAGES;
     constexpr int NF = STAGE_BYTES / 1024;
-    constexpr int NW = 8;
     constexpr int LPW = NF / NW;
     constexpr int PF = RingPlan::AHEAD;
     constexpr int LAND = RingPlan::LANDED;
@@ -346,7 +357,7 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
     using Plan = Fp8LdsPlan<D>;                 // which buffer a slot's fragment lives in, when it is read, the wait
     constexpr int AH = Plan::AHEAD_SLOTS;
     static_assert(Plan::NK == NK && Plan::NSLOT == NSLOT && Plan::BUFFERS == 4, "plan and kernel disagree on the step's shape");
-    static_assert(NF % NW == 0 && 8 % NK == 0, "step shape");
+    static_assert(NF % NW == 0 && 8 % NK == 0 && NSLOT % LPW == 0 && PF * LPW < 64, "step shape, and loads that vmcnt can count");
     static_assert(PF >= LAND && PF + 2 <= NS, "ring too short for the prefetch distance");
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -364,7 +375,6 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
     const int q_end = ch.q_end;
     const int T = (ke0 - kb0) + (ke1 - kb1) + (ke2 - kb2);
     const int n0 = ke0 - kb0, n01 = n0 + (ke1 - kb1);
-    const int vb = 0, ve = T;
 #define F8_PHYS_KB(v) ((v) + f8_pick((v), n0, n01, kb0, kb1 - n0, kb2 - n01))
 #define F8_LIVE(v) f8_live_mask(F8_PHYS_KB(v) * KBLOCK8, f8_pick((v), n0, n01, rs0, rs1, rs2), f8_pick((v), n0, n01, re0, re1, re2), half)
 
@@ -521,7 +531,7 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
         const unsigned kt_a = lds_a + (((I) + 1) & (NS - 1)) * STAGE_BYTES;            /* K8 of kblock I + 1 */      \
         const unsigned vt_a = lds_a + ((I) & (NS - 1)) * STAGE_BYTES + KB_BYTES;       /* V8 of kblock I     */      \
         const unsigned kn_a = lds_a + (((I) + 2) & (NS - 1)) * STAGE_BYTES;            /* K8 of kblock I + 2 */      \
-        i32x8 pb;                                                                                                   \
+        i32x8 pb, pl;                                                                                               \
         float m_run = -INFINITY;                                                                                    \
         _Pragma("unroll") for (int k = 0; k < NSLOT; ++k) {                                                         \
             if (k == 0) __builtin_amdgcn_s_setprio(1);                                                              \
@@ -540,6 +550,7 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
                     }                                                                                               \
                 }                                                                                                   \
                 st.o[db] = f8_mfma(f8_join(fr[Plan::buffer(k)][0], fr[Plan::buffer(k)][1]), pb, st.o[db]);          \
+                if (TWO) st.o[db] = f8_mfma(f8_join(fr[Plan::buffer(k)][0], fr[Plan::buffer(k)][1]), pl, st.o[db]); \
                 if (LOGLIN && k == NK) lacc = f8_mfma(ones, pb, lacc);     /* row sums of the 8-bit weights */       \
             }                                                                                                       \
             if (k >= DMA_FIRST && (k - DMA_FIRST) % DMA_STEP == 0 && (k - DMA_FIRST) / DMA_STEP < LPW) {            \
@@ -571,6 +582,13 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
                         w = __builtin_amdgcn_cvt_pk_fp8_f32(e2, e3, w, true);                                       \
                         pb[g] = w;                                                                                  \
                         F8_PIN(w);                                                                                  \
+                        if (TWO) {                                                                                  \
+                            const f32x2 r0 = __builtin_amdgcn_cvt_pk_f32_fp8(w, false), r1 = __builtin_amdgcn_cvt_pk_f32_fp8(w, true); \
+                            int x = __builtin_amdgcn_cvt_pk_fp8_f32(e0 - r0[0], e1 - r0[1], 0, false);              \
+                            x = __builtin_amdgcn_cvt_pk_fp8_f32(e2 - r1[0], e3 - r1[1], x, true);                   \
+                            pl[g] = x;                                                                              \
+                            F8_PIN(x);                                                                              \
+                        }                                                                                           \
                         F8_PIN(lsum0);                                                                              \
                         F8_PIN(lsum1);                                                                              \
                     }                                                                                               \
@@ -616,26 +634,26 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
     __builtin_amdgcn_s_waitcnt(0);
     // LOGLIN: the MFMA has summed over both key halves already, and both lanes of a query hold that sum
     st.l = LOGLIN ? 0.5f * lacc[0] : lsum0 + lsum1;
+    st.m = mref;
 }
 
 // A wave without queries in a chunk's short last tile: its share of the loads, waits and barriers only.
-template <int D>
-__device__ __forceinline__ void f8_segment_loads_only(const AttnParams& p, const AttnChunk& ch, int head, char* lds) {
+template <int D, int NW>
+__device__ __forceinline__ void f8_segment_loads_only(const AttnParams& p, const AttnChunk& ch, int head, int vb, int ve, char* lds) {
     constexpr int KB_BYTES = KBLOCK8 * D, STAGE_BYTES = 2 * KB_BYTES;
     constexpr int NF = STAGE_BYTES / 1024;
-    constexpr int NS = RingPlan::STAGES, NW = 8, LPW = NF / NW, PF = RingPlan::AHEAD, LAND = RingPlan::LANDED;
+    constexpr int NS = RingPlan::STAGES, LPW = NF / NW, PF = RingPlan::AHEAD, LAND = RingPlan::LANDED;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n_ranges = ch.n_ranges;
     const int rs0 = ch.rs[0], re0 = ch.re[0];
-    int rs1 = ch.rs[1], re1 = ch.re[1], rs2 = ch.rs[2], re2 = ch.re[2];
+    int rs1 = ch.rs[1], re1 = ch.re[1], rs2 = ch.rs[2];
     if (n_ranges < 2) rs1 = re1 = 0;
-    if (n_ranges < 3) rs2 = re2 = 0;
+    if (n_ranges < 3) rs2 = 0;
     const int kb0 = rs0 / KBLOCK8, ke0 = (re0 + KBLOCK8 - 1) / KBLOCK8;
     const int kb1 = rs1 / KBLOCK8, ke1 = (re1 + KBLOCK8 - 1) / KBLOCK8;
-    const int kb2 = rs2 / KBLOCK8, ke2 = (re2 + KBLOCK8 - 1) / KBLOCK8;
+    const int kb2 = rs2 / KBLOCK8;
     const int n0 = ke0 - kb0, n01 = n0 + (ke1 - kb1);
-    const int vb = 0, ve = n01 + (ke2 - kb2);
     const char* kbase = reinterpret_cast<const char*>(p.k8_cache + head * p.head_stride);
     const char* vbase = reinterpret_cast<const char*>(p.v8_cache + head * p.head_stride);
     const unsigned lane_off = lane * 16;
@@ -686,21 +704,85 @@ __device__ __forceinline__ void f8_store_out(const AttnParams& p, int head, int 
     }
 }
 
-// ---- one workgroup per (head, query tile); placement on the XCDs as in attn_stream.hip
+// The partial results of a tile's splits (split.h), for the 32-row blocks [first, first + n_blocks) of the tile: weights
+// 2^(m_s - max m), one division by the weighted sum of the row sums.  False (for the whole workgroup) if some split found no room
+// for its partial result: nothing is written then.
+template <int D, int NW>
+__device__ __forceinline__ bool f8_merge(const AttnParams& p, const AttnChunk& ch, int head, int tile, int splits, int row0, int first,
+                                         int n_blocks, int* slots) {
+    constexpr int UNITS = D / 8;                 // (db, g) of a row block: four features of a lane's half each
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 31, half = lane >> 5;
+    if (tid < splits) slots[tid] = split_find(p.pool, (head * p.splits + tid) * p.n_tiles + tile, p.token);
+    __syncthreads();
+    bool all = true;
+    for (int s = 0; s < splits; ++s) all = all && slots[s] >= 0;
+    if (all) {
+        for (int u = tid >> 6; u < n_blocks * UNITS; u += NW) {
+            const int blk = first + u / UNITS, dg = u % UNITS, row = row0 + (blk - first) * 32 + col;
+            float m = -INFINITY, l = 0.f;
+            f32x4 o = {0.f, 0.f, 0.f, 0.f};
+            for (int s = 0; s < splits; s += 4)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m = fmaxf(m, p.pool->ml[slots[min(s + e, splits - 1)]][blk * 32 + col].x);
+            for (int s0 = 0; s0 < splits; s0 += 4) {
+                float2 w[4];
+                f32x4 x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int slot = slots[min(s0 + e, splits - 1)];
+                    w[e] = p.pool->ml[slot][blk * 32 + col];
+                    x[e] = reinterpret_cast<const f32x4*>(p.pool->o[slot])[(blk * UNITS + dg) * 64 + lane];
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (s0 + e < splits) {
+                        const float a = __builtin_amdgcn_exp2f(w[e].x - m);
+                        l += w[e].y * a;
+                        o += x[e] * a;
+                    }
+            }
+            if (row < ch.q_end) {
+                const float inv = p.out_scale / l;
+                const u32x2 w = {f8_pack_bf16(o[0] * inv, o[1] * inv), f8_pack_bf16(o[2] * inv, o[3] * inv)};
+                *reinterpret_cast<u32x2*>(p.out + (int64_t(row) * p.H + head) * D + dg * 8 + half * 4) = w;
+            }
+        }
+    }
+    __syncthreads();                             // every read of the partial results has returned
+    if (tid < splits && slots[tid] >= 0) split_release(p.pool, slots[tid]);
+    return all;
+}
+
+// ---- one workgroup per (head, query tile), or several where the tile's keys are split; placement on the XCDs as in attn_stream.hip
 // MODE 0: compiler-scheduled form, 1: explicit pipeline with exact exponentials, 2: explicit pipeline with the
-// log-linear weights
+// log-linear weights, 3: the form of launches with splits (and of their merge): as 1, weights of two terms.
+// Modes 4 and 5 are 1, and 6 is 3, in workgroups of four and two waves with tiles of 128 and 64 rows: where 256-row tiles leave most of
+// the chip idle, a wave that has its SIMD for itself takes a step in two thirds of the time (rule: attn_split in attn_kernel.hip),
+// and every row keeps its bits.
+constexpr int f8_waves(int mode) { return mode == 5 ? 2 : mode == 4 || mode == 6 ? 4 : 8; }
 template <int D, int MODE>
-__global__ __launch_bounds__(F8_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_fp8_kernel(const AttnParams p) {
+__global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_fp8_kernel(const AttnParams p) {
+    constexpr int NW = f8_waves(MODE), ROWS = 32 * NW;
+    constexpr bool SPLIT = MODE == 3 || MODE == 6;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // (the arguments of a launch of one chunk in one go, as in attn_stream16.hip)
+    AttnChunk ch = p.chunk[0];
+    asm volatile("" ::"s"(ch.q_begin), "s"(ch.q_end), "s"(ch.tile_begin), "s"(ch.n_ranges), "s"(ch.rs[0]), "s"(ch.rs[1]), "s"(ch.rs[2]),
+                 "s"(ch.re[0]), "s"(ch.re[1]), "s"(ch.re[2]), "s"(ch.n_kblocks));
+    asm volatile("" ::"s"(p.q8), "s"(p.k8_cache), "s"(p.v8_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_scale));
     const int xcd = blockIdx.x & 7;
-    int idx = blockIdx.x >> 3, head = -1, tile = 0;
+    int idx = blockIdx.x >> 3, head = -1, tile = 0, item = 0, part = 0;      // part: split, or slice of the merge
     if (p.n_groups == 0) {
-        const int total = p.n_tiles * p.H;
-        const int item = ((xcd * total + 7) >> 3) + idx;
+        const int per_head = p.n_tiles * p.per_tile, total = per_head * p.H;
+        item = ((xcd * total + 7) >> 3) + idx;
         if (item < (((xcd + 1) * total + 7) >> 3)) {
-            head = item / p.n_tiles;
-            tile = item % p.n_tiles;
+            head = item / per_head;
+            tile = item - head * per_head;
+            if (SPLIT) {                         // a split's tiles side by side: they share its keys
+                part = tile / p.n_tiles;
+                tile -= part * p.n_tiles;
+            }
         }
     } else {
         for (int g = p.xcd_first[xcd]; g < p.xcd_first[xcd + 1]; ++g) {
@@ -715,25 +797,62 @@ __global__ __launch_bounds__(F8_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         }
     }
     if (head < 0) return;
-    int ci = 0;
-    while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
-    const AttnChunk& ch = p.chunk[ci];
-    const int row_block = ((wave & 3) << 1) | (wave >> 2);        // waves w and w + 4 share a SIMD
-    const int q0 = ch.q_begin + (tile - ch.tile_begin) * 256 + row_block * 32;
-    if (q0 >= ch.q_end) {
-        f8_segment_loads_only<D>(p, ch, head, lds);
-        return;
+    if (p.n_chunks > 1) {
+        int ci = 0;
+        while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
+        ch = p.chunk[ci];
     }
+    int row0 = ch.q_begin + (tile - ch.tile_begin) * ROWS, vb = 0, ve = ch.n_kblocks, readers = 0;
+    if constexpr (SPLIT) {
+        __shared__ int slots[MAX_SPLITS];
+        const int splits = min(p.splits, ch.n_kblocks);          // no more than the chunk has keys for
+        const int slice_rows = 16 * p.slice_blocks, rows = min(ROWS, ch.q_end - row0);
+        if (p.merge) {
+            // where a partial result is missing, the slice is computed here whole, as a tile of its own
+            const int first = part * slice_rows / 32;
+            if (part * slice_rows >= rows) return;
+            row0 += part * slice_rows;
+            if (f8_merge<D, NW>(p, ch, head, tile, splits, row0, first, slice_rows / 32, slots)) return;
+            ch.q_end = min(ch.q_end, row0 + slice_rows);
+        } else {
+            if (part >= splits) return;
+            vb = ch.n_kblocks * part / splits;
+            ve = ch.n_kblocks * (part + 1) / splits;
+            readers = (rows + slice_rows - 1) / slice_rows;
+        }
+    }
+    const int row_block = NW == 8 ? ((wave & 3) << 1) | (wave >> 2) : wave;       // (waves w and w + 4 share a SIMD)
+    const int q0 = row0 + row_block * 32;
+    const bool has_rows = q0 < ch.q_end;
     F8State<D> st;
-    if (MODE == 2) f8_segment_sp<D, true>(p, ch, head, q0, lds, st);
-    else if (MODE == 1) f8_segment_sp<D, false>(p, ch, head, q0, lds, st);
-    else f8_segment<D>(p, ch, head, q0, lds, st);
-    f8_store_out<D>(p, head, q0, ch.q_end, st);
+    if (!has_rows) f8_segment_loads_only<D, NW>(p, ch, head, vb, ve, lds);
+    else if (MODE == 0) f8_segment<D>(p, ch, head, q0, lds, st);
+    else f8_segment_sp<D, MODE == 2, SPLIT, NW>(p, ch, head, q0, vb, ve, lds, st);
+    if constexpr (SPLIT) {
+        __shared__ int slot_lds;
+        if (!p.merge) {                          // uniform: a partial result
+            if (threadIdx.x == 0) slot_lds = split_claim(p.pool, item, p.token, readers);
+            __syncthreads();
+            const int slot = slot_lds;
+            if (slot < 0 || !has_rows) return;   // (the merge does without this workgroup)
+            const int lane = threadIdx.x & 63, col = lane & 31;
+            const float l = st.l + __shfl_xor(st.l, 32);
+            if (lane < 32) p.pool->ml[slot][row_block * 32 + col] = make_float2(st.m, l);
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    reinterpret_cast<f32x4*>(p.pool->o[slot])[(row_block * (D / 8) + db * 4 + g) * 64 + lane] =
+                        f32x4{st.o[db][4 * g], st.o[db][4 * g + 1], st.o[db][4 * g + 2], st.o[db][4 * g + 3]};
+            return;
+        }
+    }
+    if (has_rows) f8_store_out<D>(p, head, q0, ch.q_end, st);
 }
 
 const AttnVariant kFp8Variants[] = {
-    {"d128_fp8", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 1>, F8_THREADS, KBLOCK8},
-    {"d64_fp8", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 1>, F8_THREADS, KBLOCK8},
+    {"d128_fp8", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<128, 4>, ll_attn_fp8_kernel<128, 5>}, ll_attn_fp8_kernel<128, 3>, ll_attn_fp8_kernel<128, 6>},
+    {"d64_fp8", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<64, 4>, ll_attn_fp8_kernel<64, 5>}, ll_attn_fp8_kernel<64, 3>, ll_attn_fp8_kernel<64, 6>},
     {"d128_fp8_simple", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 0>, F8_THREADS, KBLOCK8},
     {"d64_fp8_simple", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 0>, F8_THREADS, KBLOCK8},
     {"d128_fp8_loglin", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 2>, F8_THREADS, KBLOCK8},

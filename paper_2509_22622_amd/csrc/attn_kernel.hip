@@ -345,6 +345,7 @@ bool attn_variant_applies_scale(int v) {
 template <typename Rows, typename Kblocks>
 static int key_groups_log2(const AttnVariant& v, int H, int n_chunks, Rows rows, Kblocks kblocks) {
     constexpr int CUS = 256, AROUND = 10;
+    if (v.kblock == KBLOCK8) return 0;           // (no key groups there)
     struct Step { double a, b; };
     static constexpr Step steps128[4] = {{1.0, 1300}, {1.1, 900}, {1.35, 650}, {0, 1}};
     static constexpr Step steps64[4] = {{1.0, 1300}, {1.05, 1300}, {1.2, 1500}, {1.6, 800}};
@@ -383,36 +384,73 @@ int attn_key_groups(int variant, int H, int n_chunks, const int* rows, const int
     return 1 << key_groups_log2(*ll::variant(variant), H, n_chunks, [&](int c) { return rows[c]; }, [&](int c) { return kblocks[c]; });
 }
 
-// The same for one chunk whose tiles may also be dealt to several workgroups, merged by a second launch (split.h).  What a
-// call takes is modelled in us, fitted to 350 timings of 26 shapes (1 to 24 heads, 96 to 4680 rows, 30 to 732 kblocks; 6 %
-// off in the mean; the pair it picks was 1 % slower than the best): a round of workgroups takes its steps, each the longer
-// the more workgroups run (LDS and L2 traffic), and the way in and out; a merge, its launch and the partial results' way
-// through memory.  The groups alone stay as above, and a split has to be 10 % cheaper than they are, 15 %
-// where half the chip is at work without one.  us without and with
-// splits at head_dim 128: 190 rows x 143 kblocks x 4 heads 41 and 20 (4 groups x 12), 720 x 128 x 5 36 and 23 (4 x 4),
-// 1560 x 634 x 12 227 and 172 (1 x 3), 4680 x 732 x 2 162 and 109 (1 x 6); 1170 x 183 x 12 takes none (51, best split 52).
-AttnSplit attn_split(int variant, int H, int rows, int kblocks) {
+// The same where tiles may also be dealt to several workgroups, merged by a second launch (split.h).  What a launch
+// takes is modelled in us: a round of workgroups takes its steps, each the longer the more workgroups run (LDS and L2
+// traffic), and the way in and out; a merge, its launch and the partial results' way through memory.
+struct SplitModel {
+    struct { double step, busy; } whole[4], split[4];            // by log2 of the groups; 0: no such kernel
+    double around, around_split, merge, per_split, per_mb;       // a round's way in and out, without and with splits
+};
+// bf16 cache: fitted to 350 timings of 26 shapes (1 to 24 heads, 96 to 4680 rows, 30 to 732 kblocks; 6 % off in the mean; the
+// pair it picks was 1 % slower than the best).  The groups alone stay as above, and a split has to be 10 % cheaper than they
+// are, 15 % where half the chip is at work without one.  us without and with splits at head_dim 128: 190 rows x 143 kblocks x 4
+// heads 41 and 20 (4 groups x 12), 720 x 128 x 5 36 and 23 (4 x 4), 1560 x 634 x 12 227 and 172 (1 x 3), 4680 x 732 x 2 162
+// and 109 (1 x 6); 1170 x 183 x 12 takes none (51, best split 52).
+static constexpr SplitModel kSplitModel[2] = {
+    {{{0.52, 0.31}, {0.63, 0.21}, {0.82, 0.14}, {0, 0}}, {{0.52, 0.31}, {0.63, 0.21}, {0.82, 0.14}, {0, 0}}, 7.1, 7.1, 3.7, 0.22, 0.25},
+    {{{0.38, 0.14}, {0.41, 0.10}, {0.47, 0.05}, {0.42, 0.39}}, {{0.38, 0.14}, {0.41, 0.10}, {0.47, 0.05}, {0.42, 0.39}}, 5.0, 5.0, 3.7, 0.22, 0.26}};
+// 8-bit cache: no key groups, but workgroups of half and a quarter of the waves, which keep every row's bits (a wave that
+// has its SIMD for itself takes two thirds of the time), and splits, whose steps take longer (weights of two terms).  430
+// timings of 27 shapes (6 % off in the mean; the pick 2 % slower than the best).  Narrow tiles have to be 5 % cheaper than wide
+// ones, splits 10 %.  us at head_dim 128, 256-row tiles and pick: 980 rows x 50 kblocks of 64 x 2 heads 52 and 26 (128-row tiles, 8
+// splits), 300 x 36 x 24 42 and 28 (64), 1170 x 80 x 16 77 and 54 (128), 4680 x 366 x 2 292 and 109 (256, 6).
+static constexpr SplitModel kSplitModel8[2] = {
+    {{{0.82, 0.0}, {0.545, 0.03}, {0.494, 0.03}, {0, 0}}, {{1.23, 0.15}, {0.864, 0.03}, {0, 0}, {0, 0}}, 9.3, 6.7, 6.3, 0.58, 0.19},
+    {{{0.66, 0.0}, {0.436, 0.05}, {0.373, 0.52}, {0, 0}}, {{1.00, 0.14}, {0.618, 0.46}, {0, 0}, {0, 0}}, 8.7, 3.3, 8.0, 0.26, 0.18}};
+
+AttnSplit attn_split(int variant, int H, int n_chunks, const int* rows, const int* kblocks) {
     const AttnVariant& v = *ll::variant(variant);
-    const int unsplit = key_groups_log2(v, H, 1, [&](int) { return rows; }, [&](int) { return kblocks; });
+    const bool fp8 = v.kblock == KBLOCK8;
+    const int unsplit = key_groups_log2(v, H, n_chunks, [&](int c) { return rows[c]; }, [&](int c) { return kblocks[c]; });
     AttnSplit best{1 << unsplit, 1};
-    if (!v.splits) return best;
+    if (v.split == nullptr) return best;
     constexpr int CUS = 256;
-    struct Model { double step[4], busy[4], around, merge, per_split, per_mb; };
-    static constexpr Model models[2] = {{{0.52, 0.63, 0.82, 0}, {0.31, 0.21, 0.14, 0}, 7.1, 3.7, 0.22, 0.25},            // head_dim 128
-                                        {{0.38, 0.41, 0.47, 0.42}, {0.14, 0.10, 0.05, 0.39}, 5.0, 3.7, 0.22, 0.26}};     // 64
-    const Model& m = models[v.D == 128 ? 0 : 1];
-    auto cost = [&](int lg, int splits) {
-        const int64_t n = (int64_t(rows) + (v.qtile >> lg) - 1) / (v.qtile >> lg) * H * splits;
-        const double step = m.step[lg] * (1 + m.busy[lg] * double(std::min<int64_t>(n, CUS)) / CUS);
-        const double round = double((kblocks + (splits << lg) - 1) / (splits << lg)) * step + m.around;
-        return double((n + CUS - 1) / CUS) * round + (splits == 1 ? 0 : m.merge + m.per_split * splits + m.per_mb * 1e-6 * double(n) * (v.qtile >> lg) * v.D * 4);
+    const SplitModel& m = (fp8 ? kSplitModel8 : kSplitModel)[v.D == 128 ? 0 : 1];
+    int most_kblocks = 0;
+    for (int c = 0; c < n_chunks; ++c) most_kblocks = std::max(most_kblocks, kblocks[c]);
+    auto tiles_of = [&](int lg) {
+        int64_t n = 0;
+        for (int c = 0; c < n_chunks; ++c) n += (int64_t(rows[c]) + (v.qtile >> lg) - 1) / (v.qtile >> lg) * H;
+        return n;
     };
-    const int64_t at_work = (int64_t(rows) + (v.qtile >> unsplit) - 1) / (v.qtile >> unsplit) * H;
-    double best_cost = (at_work >= CUS / 2 ? 0.85 : 0.9) * cost(unsplit, 1);
+    auto cost = [&](int lg, int splits) {
+        const int keys_lg = fp8 ? 0 : lg;                        // groups that share a tile's keys
+        const int64_t slots = fp8 && v.D == 64 && lg > 0 ? 2 * CUS : CUS;          // workgroups the chip holds
+        int64_t n = 0, steps = 0, longest = 0;
+        for (int c = 0; c < n_chunks; ++c) {
+            const int shares = std::min(splits, std::max(1, kblocks[c] >> keys_lg)) << keys_lg;
+            const int64_t t = (int64_t(rows[c]) + (v.qtile >> lg) - 1) / (v.qtile >> lg) * H * (shares >> keys_lg), len = (kblocks[c] + shares - 1) / shares;
+            n += t;
+            steps += t * len;
+            longest = std::max(longest, len);
+        }
+        const auto& k = (splits == 1 ? m.whole : m.split)[lg];
+        const double around = splits == 1 ? m.around : m.around_split;
+        const double step = k.step * (1 + k.busy * double(std::min(n, slots)) / CUS), one = double(longest) * step + around;
+        const double run = n <= slots ? one : n_chunks == 1 ? double((n + slots - 1) / slots) * one : (double(steps) * step + double(n) * around) / double(slots) + 0.5 * one;
+        return run + (splits == 1 ? 0 : m.merge + m.per_split * splits + m.per_mb * 1e-6 * double(n) * (v.qtile >> lg) * v.D * 4);
+    };
+    double best_cost = cost(unsplit, 1), bar = tiles_of(unsplit) >= CUS / 2 && !fp8 ? 0.85 : 0.9;
+    for (int lg = 1; fp8 && lg < 4; ++lg)
+        if (m.whole[lg].step > 0 && cost(lg, 1) < (best.groups == 1 ? 0.95 : 1) * best_cost) {
+            best_cost = cost(lg, 1);
+            best = {1 << lg, 1};
+        }
+    best_cost *= bar;
     for (int lg = 0; lg < 4; ++lg) {
-        if (lg > 0 && v.grouped[lg - 1] == nullptr) continue;
-        const int64_t tiles = (int64_t(rows) + (v.qtile >> lg) - 1) / (v.qtile >> lg) * H;
-        for (int splits = 2; splits <= MAX_SPLITS && tiles * splits <= SPLIT_SLOTS && (splits << lg) <= kblocks; ++splits) {
+        if (m.split[lg].step <= 0) continue;
+        const int64_t tiles = tiles_of(lg);
+        for (int splits = 2; splits <= MAX_SPLITS && tiles * splits <= SPLIT_SLOTS && (fp8 ? splits : splits << lg) <= most_kblocks; ++splits) {
             const double c = cost(lg, splits);
             if (c < best_cost) {
                 best_cost = c;
@@ -430,13 +468,12 @@ hipError_t split_pool_address(SplitPool** pool) {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= MAX_DEVICES) return hipErrorInvalidDevice;
-    *pool = known[dev].load(std::memory_order_relaxed);
-    if (*pool) return hipSuccess;
+    if (dev < MAX_DEVICES && (*pool = known[dev].load(std::memory_order_relaxed)) != nullptr) return hipSuccess;
     void* at = nullptr;
     e = hipGetSymbolAddress(&at, HIP_SYMBOL(split_pool));
     if (e != hipSuccess) return e;
-    known[dev].store(*pool = static_cast<SplitPool*>(at), std::memory_order_relaxed);
+    *pool = static_cast<SplitPool*>(at);
+    if (dev < MAX_DEVICES) known[dev].store(*pool, std::memory_order_relaxed);
     return hipSuccess;
 }
 
@@ -462,12 +499,22 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         r.scale_log2e = p.scale_log2e;
         return launch_attn_resident(r, p.D, s);
     }
+    if (p.key_groups == 0) {
+        int rows[MAX_ATTN_CHUNKS], kblocks[MAX_ATTN_CHUNKS];
+        for (int c = 0; c < p.n_chunks; ++c) {
+            rows[c] = p.chunk[c].q_end - p.chunk[c].q_begin;
+            kblocks[c] = p.chunk[c].n_kblocks;
+        }
+        p.key_groups = attn_key_groups(variant, p.H, p.n_chunks, rows, kblocks);
+        p.splits = 1;
+        if (p.may_split) {
+            const AttnSplit split = attn_split(variant, p.H, p.n_chunks, rows, kblocks);
+            p.key_groups = split.groups;
+            p.splits = split.splits;
+        }
+    }
     int log_g = 0;
-    if (p.key_groups == 0)
-        log_g = key_groups_log2(v, p.H, p.n_chunks, [&](int c) { return p.chunk[c].q_end - p.chunk[c].q_begin; },
-                                [&](int c) { return p.chunk[c].n_kblocks; });
-    else
-        while ((1 << log_g) < p.key_groups) ++log_g;
+    while ((1 << log_g) < p.key_groups) ++log_g;
     if (log_g > 3 || (log_g > 0 && v.grouped[log_g - 1] == nullptr)) return hipErrorInvalidValue;
     const int qtile = v.qtile >> log_g;
     p.n_tiles = 0;
@@ -478,7 +525,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     const int total = p.n_tiles * p.H;
     if (total <= 0) return hipSuccess;
     p.splits = std::max(1, p.splits);
-    if (p.splits > MAX_SPLITS || (p.splits > 1 && (!v.splits || int64_t(total) * p.splits > SPLIT_SLOTS))) return hipErrorInvalidValue;
+    if (p.splits > MAX_SPLITS || (p.splits > 1 && (v.split == nullptr || int64_t(total) * p.splits > SPLIT_SLOTS))) return hipErrorInvalidValue;
     p.per_tile = p.splits;
     p.merge = 0;
     p.slice_blocks = 16 >> log_g;
@@ -489,7 +536,9 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         hipError_t e = split_pool_address(&p.pool);
         if (e != hipSuccess) return e;
         // a workgroup of the merge takes as many of a tile's 16-row blocks as leave about one workgroup per CU
-        while (p.slice_blocks > 1 && int64_t(total) * ((16 >> log_g) / p.slice_blocks) < 200) p.slice_blocks >>= 1;
+        // (of the 8-bit kernel's 32-row blocks, pairs)
+        const int least = p.kblock == KBLOCK8 ? 2 : 1;
+        while (p.slice_blocks > least && int64_t(total) * ((16 >> log_g) / p.slice_blocks) < 200) p.slice_blocks >>= 1;
     }
     p.n_groups = 0;
     const int groups = p.H * p.n_chunks;
@@ -531,23 +580,27 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         p.n_groups = n;
         grid = 8 * most_tiles;
     }
-    static bool attr_set[64][4] = {};
+    static bool attr_set[64][6] = {};
     if (variant > 64) return hipErrorInvalidValue;
-    void (*const kernel)(const AttnParams) = log_g == 0 ? v.kernel : v.grouped[log_g - 1];
-    const int lds_bytes = log_g == 0 ? v.lds_bytes : GROUPED_LDS_BYTES;
-    if (!attr_set[variant - 1][log_g]) {
+    const bool fp8 = v.kblock == KBLOCK8;
+    const int which = p.splits > 1 && (log_g == 0 || fp8) ? 4 + log_g : log_g;
+    void (*const kernel)(const AttnParams) = which == 0 ? v.kernel : which == 4 ? v.split : which == 5 ? v.split_half : v.grouped[log_g - 1];
+    if (which > 5 || kernel == nullptr) return hipErrorInvalidValue;
+    const int lds_bytes = log_g == 0 || fp8 ? v.lds_bytes : GROUPED_LDS_BYTES;
+    const dim3 threads(fp8 ? v.threads >> log_g : v.threads);
+    if (!attr_set[variant - 1][which]) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
         if (e != hipSuccess) return e;
-        attr_set[variant - 1][log_g] = true;
+        attr_set[variant - 1][which] = true;
     }
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(v.threads), lds_bytes, s, p);
+    hipLaunchKernelGGL(kernel, dim3(grid), threads, lds_bytes, s, p);
     if (p.splits > 1) {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         p.merge = 1;
         p.per_tile = (16 >> log_g) / p.slice_blocks;
-        hipLaunchKernelGGL(kernel, dim3((total * p.per_tile + 7) / 8 * 8), dim3(v.threads), lds_bytes, s, p);
+        hipLaunchKernelGGL(kernel, dim3((total * p.per_tile + 7) / 8 * 8), threads, lds_bytes, s, p);
     }
     return hipGetLastError();
 }

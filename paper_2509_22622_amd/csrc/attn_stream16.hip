@@ -991,7 +991,7 @@ constexpr int S16_DEFAULT = 9, S16_TRACKED = 1;
 #define S16_ENTRY(name, D, QS, LSE, SCHED)                                                                            \
     {name, D, 256, 8 * 2 * KBLOCK * D * 2, S16_KERNEL(D, QS, LSE, SCHED, 1), S16_THREADS, KBLOCK,                     \
      {S16_KERNEL(D, QS, LSE, SCHED, 2), S16_KERNEL(D, QS, LSE, SCHED, 4),                                             \
-      D == 64 ? S16_KERNEL(D, QS, LSE, SCHED, (D == 64 ? 8 : 4)) : nullptr}, true}
+      D == 64 ? S16_KERNEL(D, QS, LSE, SCHED, (D == 64 ? 8 : 4)) : nullptr}, S16_KERNEL(D, QS, LSE, SCHED, 1)}
 // (the tracked variants are there to be compared with, one key group)
 #define S16_ENTRY_WHOLE(name, D, QS, LSE, SCHED) \
     {name, D, 256, 8 * 2 * KBLOCK * D * 2, S16_KERNEL(D, QS, LSE, SCHED, 1), S16_THREADS, KBLOCK, {}}

@@ -152,7 +152,8 @@ struct AttnParams {
     int kblock;                  // key slots per kblock: 32 (bf16 cache) or 64 (8-bit cache)
     const double* inv_freq_t;    // frame-axis rotary frequencies [n_t] (used when a chunk has a sink_shift)
     int n_t;
-    int key_groups;              // key groups per tile (AttnVariant::grouped); 0: groups and splits chosen for the launch
+    int key_groups;              // key groups per tile (AttnVariant::grouped); 0: chosen for the launch,
+    bool may_split;              // and splits with them
     // A tile's keys dealt to `splits` workgroups, whose partial results a second launch of the kernel merges (split.h);
     // chunks of fewer kblocks take fewer.  The rest is filled in by launch_attn.
     int splits;
@@ -230,9 +231,12 @@ struct AttnVariant {
     int threads;
     int kblock;                  // 32: bf16 cache, 64: 8-bit cache
     // The same work with the keys of a tile dealt to G = 2, 4, 8 groups of the workgroup's waves (qtile / G rows per
-    // workgroup); null where there is no such kernel.
+    // workgroup); null where there is no such kernel.  8-bit cache: with 1 / G of the waves instead, which all walk all keys.
     void (*grouped[3])(const AttnParams);
-    bool splits;                 // the kernels honour AttnParams::splits
+    // The kernel of launches with AttnParams::splits > 1 and one key group (null: no splits); with more, grouped takes splits
+    // too (8-bit cache: with half the waves split_half does).
+    void (*split)(const AttnParams);
+    void (*split_half)(const AttnParams);
 };
 extern const AttnVariant kStreamVariants[];
 extern const int kNumStreamVariants;
@@ -248,9 +252,9 @@ int attn_variant_default(int D, int kblock);
 bool attn_variant_supports(int v, int D, int kblock);
 // the key groups a launch of these chunks takes with the variant: 1, 2, 4 or 8
 int attn_key_groups(int v, int H, int n_chunks, const int* rows, const int* kblocks);
-// the same for one chunk that may also be dealt to several workgroups per tile
+// the same where tiles may also be dealt to several workgroups: for one streamed chunk, or for a launch of several
 struct AttnSplit { int groups, splits; };
-AttnSplit attn_split(int v, int H, int rows, int kblocks);
+AttnSplit attn_split(int v, int H, int n_chunks, const int* rows, const int* kblocks);
 bool attn_variant_sink_shift(int v);          // the variant honours AttnChunk::sink_shift
 int attn_variant_lse(int D);                   // the variant that also writes AttnParams::lse
 int attn_variant_qscale(int D);                // the variant for queries not yet scaled (honours scale_log2e)

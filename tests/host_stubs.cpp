@@ -8,7 +8,7 @@ int attn_variant_count() { return 4; }
 const char* attn_variant_name(int v) { return v >= 1 && v <= 4 ? "stub" : nullptr; }
 int attn_variant_default(int D, int kblock) { return (kblock == KBLOCK8 ? 2 : 0) + (D == 128 ? 1 : 2); }
 int attn_key_groups(int, int, int, const int*, const int*) { return 1; }
-AttnSplit attn_split(int, int, int, int) { return {1, 1}; }
+AttnSplit attn_split(int, int, int, const int*, const int*) { return {1, 1}; }
 struct SplitPool;
 hipError_t split_pool_address(SplitPool**) { return hipErrorNoDevice; }
 bool attn_variant_supports(int v, int D, int kblock) { return v == attn_variant_default(D, kblock); }

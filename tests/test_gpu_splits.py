@@ -195,3 +195,98 @@ def test_calls_on_several_streams():
     cache.sink_window_attn(0, q, again)
     assert torch.equal(_bits(again), _bits(want))
     cache.close()
+
+
+# the 8-bit cache: heads, head_dim, grid, chunk, sink, window, frames, (groups, splits): 256 / groups rows a tile
+SHAPES8 = [(2, 128, (5, 49), 4, 0, 9, 4, (2, 10)), (4, 128, (10, 19), 1, 3, 20, 1, (2, 9)), (3, 64, (20, 26), 3, 1, 9, 3, (2, 12)),
+           (2, 128, (30, 52), 3, 3, 9, 3, (1, 6)), (2, 64, (9, 39), 4, 0, 21, 3, (2, 15))]
+
+
+def _split8(heads, head_dim, grid, chunk, sink, window, frames):
+    P = grid[0] * grid[1]
+    return B.attn_split(head_dim, heads, frames * P, -(-(sink + window + frames) * P // 64), "fp8_e4m3")
+
+
+def _two_terms(out, want):
+    """Weights rounded once, to 3 mantissa bits, are off by 2.6 % of the 2-norm; the two terms of a split tile's by some 2^-9, beside
+    the rounding of the result (2^-9 / sqrt(3) x 2): 6e-3 is what both can add up to where few keys leave nothing to average."""
+    return _rel(out, want) <= 6e-3
+
+
+@pytest.mark.parametrize("shape", SHAPES8)
+def test_split_tiles_of_the_8_bit_cache(shape):
+    """Against 64 bits with the operands as the cache holds them; again with slots taken; the same video from its first frame."""
+    *geo, split = shape
+    assert _split8(*geo) == split
+    case = _case(*geo, cache="fp8_e4m3")
+    want = cases.exact(case, 5)[0]
+    state = cases.prepare(case, 5)
+    out = cases.run(state)[0]
+    layer, _, _, _, _, q_out, _ = state["passes"][0]
+    assert _two_terms(out, want)
+    again = torch.full_like(out, 7.0)
+    state["cache"].sink_window_attn(layer, q_out, again)
+    assert torch.equal(_bits(again), _bits(out))
+    for first, n in ((0, 512), (0, 2), (1, 511)):
+        B.hold_split_slots(first, n, True)
+        try:
+            again.fill_(7.0)
+            state["cache"].sink_window_attn(layer, q_out, again)
+        finally:
+            B.hold_split_slots(first, n, False)
+        assert _two_terms(again, want)
+    state["cache"].sink_window_attn(layer, q_out, again)
+    assert torch.equal(_bits(again), _bits(out))
+    state["cache"].close()
+    case = _case(*geo[:6], geo[3], cache="fp8_e4m3", video_chunks=1 + -(-(geo[4] + geo[5] + 4) // geo[3]))
+    state = cases.prepare(case, 7)
+    for i, (a, b) in enumerate(zip(cases.run(state), cases.exact(case, 7))):
+        assert _two_terms(a, b), i
+    state["cache"].close()
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, sink, n_win", [(2, 128, (13, 23), 2, 8), (2, 64, (11, 33), 3, 9)])
+def test_split_re_prefill_of_the_8_bit_cache(heads, head_dim, grid, sink, n_win):
+    """Chunks of unlike key sets in one launch with splits."""
+    case = {"kind": "prefill", "cache": "fp8_e4m3", "layers": 1, "heads": heads, "head_dim": head_dim, "grid_h": grid[0],
+            "grid_w": grid[1], "chunk": 3, "sink": sink, "window": 7, "win_start": 20, "n_win": n_win, "q_std": 2.0}
+    state = cases.prepare(case, 3)
+    out = cases.run(state)[0].clone()
+    torch.cuda.synchronize()
+    want = cases.exact(case, 3)[0]
+    assert _two_terms(out, want)
+    for first, n in ((0, 512), (1, 300)):
+        B.hold_split_slots(first, n, True)
+        try:
+            again = cases.run(state)[0]
+        finally:
+            B.hold_split_slots(first, n, False)
+        assert _two_terms(again, want)
+    state["cache"].close()
+
+
+@pytest.mark.parametrize("head_dim, heads, groups, grid, chunk, sink, window, frames", [
+    (128, 16, 2, (15, 26), 3, 2, 8, 3), (128, 24, 4, (10, 10), 3, 2, 20, 3), (128, 1, 4, (8, 9), 4, 0, 18, 3), (64, 6, 4, (9, 15), 2, 2, 6, 2)])
+def test_narrow_tiles_of_the_8_bit_cache(head_dim, heads, groups, grid, chunk, sink, window, frames):
+    """Tiles of 128 and 64 rows give every row the bits it has in a wider one, which a launch of many heads takes."""
+    P, f0 = grid[0] * grid[1], sink + window + 4
+    many = -(-240 // -(-frames * P // 256))
+    assert _split8(heads, head_dim, grid, chunk, sink, window, frames) == (groups, 1)
+    wider = _split8(many, head_dim, grid, chunk, sink, window, frames)
+    assert wider[0] < groups and wider[1] == 1
+    g = torch.Generator(device="cuda").manual_seed(P)
+    make = lambda n: torch.empty((n * P, many, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    past, new = [make(sink + window) for _ in range(2)], [make(frames) for _ in range(3)]
+    outs = []
+    for h in (many, heads):
+        k, v = (x[:, :h].contiguous() for x in past)
+        q, kc, vc = (x[:, :h].contiguous() for x in new)
+        cache = B.Cache(1, h, head_dim, *grid, chunk, sink, window, kv_format="fp8_e4m3")
+        cache.recache_prefill(0, True, f0 - window, window, k, k, v, torch.empty_like(k))
+        q_out, out = torch.empty(q.shape, dtype=torch.uint8, device="cuda"), torch.full_like(q, 7.0)
+        cache.chunk_append(0, f0, frames, q, kc, vc, q_out)
+        cache.sink_window_attn(0, q_out, out)
+        torch.cuda.synchronize()
+        cache.close()
+        outs.append(out)
+    assert torch.equal(_bits(outs[0][:, :heads].contiguous()), _bits(outs[1]))
