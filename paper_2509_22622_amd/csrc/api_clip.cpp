@@ -14,7 +14,7 @@ struct ll_clip {
     int64_t hs_all, hs_clip;            // elements between heads of a fragment region pair
     int64_t row_stride;                 // floats between heads of lse and delta
     // byte offsets into the workspace
-    size_t o_a, o_b, o_cq, o_cd, o_qrot, o_krot, o_lse, o_delta, o_gq, o_gk, o_o32, o_zero, o_freq, o_row, o_col;
+    size_t o_a, o_b, o_cq, o_cd, o_qrot, o_lse, o_delta, o_gq, o_gk, o_o32, o_freq, o_row, o_col;
     RopeTables rope;
     std::vector<double> inv_freq_t;     // host copy of the frame-axis frequencies
     // what the last forward left
@@ -26,7 +26,7 @@ struct ll_clip {
 namespace {
 struct ClipSizes {
     int64_t kb_all, kb_clip, hs_all, hs_clip, row_stride;
-    size_t o_a, o_b, o_cq, o_cd, o_qrot, o_krot, o_lse, o_delta, o_gq, o_gk, o_o32, o_zero, o_freq, o_row, o_col, total;
+    size_t o_a, o_b, o_cq, o_cd, o_qrot, o_lse, o_delta, o_gq, o_gk, o_o32, o_freq, o_row, o_col, total;
 };
 bool clip_shapes_ok(int H, int D, int P, int S, int W, int T, int C) {
     return H >= 1 && H <= 4096 && (D == 64 || D == 128) && P >= 1 && S >= 0 && W >= 0 && T >= 1 && C >= 1 &&
@@ -48,14 +48,12 @@ ClipSizes clip_sizes(int H, int D, int P, int S, int W, int T, int C, int grid_h
     z.o_cq = take(size_t(z.hs_clip) * H * 2);
     z.o_cd = take(size_t(z.hs_clip) * H * 2);
     z.o_qrot = take(size_t(n_clip) * H * D * 2);
-    z.o_krot = take(size_t(n_all) * H * D * 2);
     z.o_lse = take(size_t(z.row_stride) * H * 4);
     z.o_delta = take(size_t(z.row_stride) * H * 4);
     z.o_gq = take(size_t(n_clip) * H * D * 4);
     z.o_gk = take(size_t(n_clip) * H * D * 4);
     z.o_o32 = take(size_t(n_clip) * H * D * 4);
     const int d_hw = 2 * (D / 6), n_t = (D - 2 * d_hw) / 2, n_h = d_hw / 2;
-    z.o_zero = take(size_t(D / 2) * sizeof(double));
     z.o_freq = take(size_t(n_t) * sizeof(double));
     z.o_row = take(size_t(grid_h) * n_h * sizeof(float2));
     z.o_col = take(size_t(grid_w) * n_h * sizeof(float2));
@@ -92,9 +90,9 @@ ll_status ll_clip_create(int heads, int head_dim, int tokens_per_frame, int sink
     c->T = clip_frames; c->C = chunk_frames; c->grid_h = grid_h; c->grid_w = grid_w;
     c->dev = static_cast<char*>(dev_buffer);
     c->kb_all = z.kb_all; c->kb_clip = z.kb_clip; c->hs_all = z.hs_all; c->hs_clip = z.hs_clip; c->row_stride = z.row_stride;
-    c->o_a = z.o_a; c->o_b = z.o_b; c->o_cq = z.o_cq; c->o_cd = z.o_cd; c->o_qrot = z.o_qrot; c->o_krot = z.o_krot;
+    c->o_a = z.o_a; c->o_b = z.o_b; c->o_cq = z.o_cq; c->o_cd = z.o_cd; c->o_qrot = z.o_qrot;
     c->o_lse = z.o_lse; c->o_delta = z.o_delta; c->o_gq = z.o_gq; c->o_gk = z.o_gk; c->o_o32 = z.o_o32;
-    c->o_zero = z.o_zero; c->o_freq = z.o_freq; c->o_row = z.o_row; c->o_col = z.o_col;
+    c->o_freq = z.o_freq; c->o_row = z.o_row; c->o_col = z.o_col;
     const int d_hw = 2 * (head_dim / 6), n_t = (head_dim - 2 * d_hw) / 2, n_h = d_hw / 2;
     c->rope = RopeTables{nullptr, nullptr, nullptr, n_t, n_h, n_h};
     c->inv_freq_t.resize(n_t);
@@ -160,26 +158,6 @@ std::vector<SlotRange> clip_key_ranges(const ll_clip* c, int64_t f0, int n) {
     return r;
 }
 
-// An identity "rotary step" for the cache-write kernel: every pair on the frame axis at frequency zero.
-RopeTables clip_identity_rope(const ll_clip* c) {
-    return RopeTables{reinterpret_cast<const double*>(c->dev + c->o_zero), nullptr, nullptr, c->D / 2, 0, 0};
-}
-
-// Write `rows` rows of (k, v) as one K-style and one V^T-style region from token slot 0 on, unchanged.
-hipError_t clip_write_pair(const ll_clip* c, const uint16_t* k, const uint16_t* v, int64_t rows, uint16_t* region,
-                           int64_t kblocks, int64_t head_stride, hipStream_t s) {
-    AppendParams p{};
-    p.k = k; p.v = v;
-    p.k_cache = region; p.v_cache = region + kblocks * KBLOCK * c->D;
-    p.head_stride = head_stride;
-    p.rope = clip_identity_rope(c);
-    p.identity = 1;
-    p.H = c->H; p.D = c->D; p.P = int(rows); p.grid_w = int(rows);
-    p.n_frames = 1;
-    p.frame[0] = 0; p.slot[0] = 0;
-    p.seg_begin[0] = 0; p.seg_begin[1] = int((rows + KBLOCK - 1) / KBLOCK);
-    return launch_append(p, s);
-}
 }  // namespace
 }  // extern "C++"
 
@@ -204,56 +182,26 @@ ll_status ll_clip_forward(ll_clip* clip, int64_t ctx_start, int n_ctx, int n_cli
     if (!c->dev) { c->have_fwd = true; return LL_OK; }
 
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t frame_elems = int64_t(c->P) * c->H * c->D;
     const int64_t clip_start = ctx_start + n_ctx;
-    const int first_clip = c->n_frames - n_clip;                  // position of the clip's first frame in the list
-    // 1. rotary + cache write of every resident frame into region pair A (K' K-style, V V^T-style); the clip's frames
-    //    also give the rotated, scaled queries
-    for (int base = 0; base < c->n_frames; base += MAX_APPEND_FRAMES) {
-        const int m = std::min(MAX_APPEND_FRAMES, c->n_frames - base);
-        for (int part = 0; part < 2; ++part) {                    // frames without queries, then the clip's
-            const int lo = part == 0 ? base : std::max(base, first_clip);
-            const int hi = part == 0 ? std::min(base + m, first_clip) : base + m;
-            if (lo >= hi) continue;
-            AppendParams p{};
-            p.k = static_cast<const uint16_t*>(k) + lo * frame_elems;
-            p.v = static_cast<const uint16_t*>(v) + lo * frame_elems;
-            if (part == 1) {
-                p.q = static_cast<const uint16_t*>(q) + (lo - first_clip) * frame_elems;
-                p.q_out = clip_u16(c, c->o_qrot) + (lo - first_clip) * frame_elems;
-            }
-            p.q_scale = float(1.4426950408889634 / std::sqrt(double(c->D)));
-            p.k_cache = clip_u16(c, c->o_a); p.v_cache = p.k_cache + c->kb_all * KBLOCK * c->D;
-            p.head_stride = c->hs_all;
-            p.rope = c->rope;
-            p.H = c->H; p.D = c->D; p.P = c->P; p.grid_w = c->grid_w;
-            p.n_frames = hi - lo;
-            p.seg_begin[0] = 0;
-            for (int i = 0; i < hi - lo; ++i) {
-                const int pos = lo + i;
-                p.frame[i] = pos < n_sink_outside ? pos : ctx_start + (pos - n_sink_outside);
-                p.slot[i] = int64_t(pos) * c->P;
-                p.seg_begin[i + 1] = p.seg_begin[i] + int((p.slot[i] % KBLOCK + c->P + KBLOCK - 1) / KBLOCK);
-            }
-            set_frame_rotation(p, c->inv_freq_t.data());
-            hipError_t e = launch_append(p, s);
-            if (e != hipSuccess) return hip_fail(e, "clip cache-write kernel launch");
-        }
-    }
-    // 2. region pair B for the backward pass: V K-style and K'^T V^T-style (K' read back row-major first)
-    const int64_t n_all = int64_t(c->n_frames) * c->P;
+    // 1. every resident frame's keys and values into region pairs A (K' K-style, V V^T-style) and, for the backward pass, B (V K-style,
+    //    K' V^T-style); the clip's queries rotated and scaled
     {
-        ReadFrameParams r{};
-        r.k_cache = clip_u16(c, c->o_a); r.v_cache = r.k_cache + c->kb_all * KBLOCK * c->D;
-        r.head_stride = c->hs_all;
-        r.k_out = clip_u16(c, c->o_krot); r.v_out = nullptr;
-        r.H = c->H; r.D = c->D; r.P = int(n_all); r.slot = 0;
-        hipError_t e = launch_read_frame(r, s);
-        if (e == hipSuccess)
-            e = clip_write_pair(c, static_cast<const uint16_t*>(v), clip_u16(c, c->o_krot), n_all, clip_u16(c, c->o_b), c->kb_all, c->hs_all, s);
-        if (e != hipSuccess) return hip_fail(e, "clip backward-operand kernels launch");
+        ClipLayoutParams p{};
+        p.x = static_cast<const uint16_t*>(k); p.y = static_cast<const uint16_t*>(v);
+        const int64_t v_off = c->kb_all * KBLOCK * c->D;
+        p.x_k = clip_u16(c, c->o_a); p.y_t = p.x_k + v_off;
+        p.y_k = clip_u16(c, c->o_b); p.x_t = p.y_k + v_off;
+        p.head_stride = c->hs_all;
+        p.H = c->H; p.rows = int(int64_t(c->n_frames) * c->P);
+        p.q = static_cast<const uint16_t*>(q); p.q_out = clip_u16(c, c->o_qrot);
+        p.q_row0 = (c->n_frames - n_clip) * c->P;
+        p.q_scale = float(1.4426950408889634 / std::sqrt(double(c->D)));
+        p.rope = c->rope;
+        p.P = c->P; p.grid_w = c->grid_w; p.n_sink_outside = n_sink_outside; p.ctx_start = ctx_start;
+        hipError_t e = launch_clip_layout(p, c->D, s);
+        if (e != hipSuccess) return hip_fail(e, "clip layout kernel launch");
     }
-    // 3. attention of the clip's chunks, each over its own key set, with the row sums kept for the backward pass
+    // 2. attention of the clip's chunks, each over its own key set, with the row sums kept for the backward pass
     const int variant = attn_variant_lse(c->D);
     const int n_chunks = (n_clip + c->C - 1) / c->C;
     for (int base = 0; base < n_chunks; base += MAX_ATTN_CHUNKS) {
@@ -316,13 +264,18 @@ ll_status ll_clip_backward(ll_clip* clip, const void* dout, void* dq, void* dk, 
     const int64_t col_slot0 = int64_t(c->n_frames - n_clip) * c->P;
     const uint16_t* qrot = clip_u16(c, c->o_qrot);
     const uint16_t* dO = static_cast<const uint16_t*>(dout);
+    const int64_t v_off_all = c->kb_all * KBLOCK * c->D, v_off_clip = c->kb_clip * KBLOCK * c->D;
     // 1. delta_i = dO_i . O_i (O as the forward kept it, not rounded to bf16), and the clip's q' and dO as fragment
     //    regions (each both ways round)
-    hipError_t e = launch_bwd_delta(clip_f32(c, c->o_o32), dO, clip_f32(c, c->o_delta), int(rows), c->H, c->D, c->row_stride, s);
-    if (e == hipSuccess) e = clip_write_pair(c, qrot, dO, rows, clip_u16(c, c->o_cq), c->kb_clip, c->hs_clip, s);   // q' K-style, dO^T
-    if (e == hipSuccess) e = clip_write_pair(c, dO, qrot, rows, clip_u16(c, c->o_cd), c->kb_clip, c->hs_clip, s);   // dO K-style, q'^T
-    if (e != hipSuccess) return hip_fail(e, "clip backward preparation kernels launch");
-    const int64_t v_off_all = c->kb_all * KBLOCK * c->D, v_off_clip = c->kb_clip * KBLOCK * c->D;
+    ClipLayoutParams lp{};
+    lp.x = qrot; lp.y = dO;
+    lp.x_k = clip_u16(c, c->o_cq); lp.y_t = lp.x_k + v_off_clip;          // q' K-style, dO^T
+    lp.y_k = clip_u16(c, c->o_cd); lp.x_t = lp.y_k + v_off_clip;          // dO K-style, q'^T
+    lp.head_stride = c->hs_clip;
+    lp.H = c->H; lp.rows = int(rows);
+    lp.out32 = clip_f32(c, c->o_o32); lp.delta = clip_f32(c, c->o_delta); lp.row_stride = c->row_stride;
+    hipError_t e = launch_clip_layout(lp, c->D, s);
+    if (e != hipSuccess) return hip_fail(e, "clip layout kernel launch");
     // 2. Gq: queries as columns, chunk by chunk over each chunk's key ranges
     const int n_chunks = (n_clip + c->C - 1) / c->C;
     for (int base = 0; base < n_chunks; base += MAX_BWD_GROUPS) {

@@ -511,28 +511,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dkv_narrow_kernel(const BwdParams p) { bw_dkv<128, 4>(p); }
 
 // ---------------------------------------------------------------------------------------------------------------
-// delta[head][row] = sum_d dO[row][head][d] * O[row][head][d], O being the forward's output before its rounding to
-// bf16; D / 8 lanes per (row, head), 8 features each.
-template <int D>
-__global__ __launch_bounds__(256) void ll_bwd_delta_kernel(const float* out, const uint16_t* dout, float* delta,
-                                                           int rows, int H, int64_t row_stride) {
-    constexpr int LPR = D / 8;                        // lanes per (row, head)
-    const int64_t idx = (int64_t(blockIdx.x) * 256 + threadIdx.x) / LPR;   // (row, head) pair
-    const int part = threadIdx.x % LPR;
-    const bool on = idx < int64_t(rows) * H;
-    float acc = 0.f;
-    if (on) {
-        const f32x4 a0 = *reinterpret_cast<const f32x4*>(out + idx * D + part * 8);
-        const f32x4 a1 = *reinterpret_cast<const f32x4*>(out + idx * D + part * 8 + 4);
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(dout + idx * D + part * 8);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc += a0[e] * float(b[e]) + a1[e] * float(b[e + 4]);
-    }
-#pragma unroll
-    for (int m = LPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m);
-    if (on && part == 0) delta[(idx % H) * row_stride + idx / H] = acc;
-}
-
 // dq = R^T(Gq) / sqrt(D), dk = R^T(Gk) ln 2: back through the rotary embedding (the rotation by the opposite angle)
 // with the factors the two kernels above left out.  One workgroup per (32 tokens of one frame, head).
 template <int D>
@@ -626,17 +604,6 @@ hipError_t launch_bwd_dkv(const BwdParams& p_in, hipStream_t s) {
     if (narrow) return launch_bwd(ll_bwd_dkv_narrow_kernel, p, 4, lds, done[0], s);
     if (p.D == 128) return launch_bwd(ll_bwd_dkv_kernel<128, 8>, p, 8, lds, done[1], s);
     return launch_bwd(ll_bwd_dkv_kernel<64, 4>, p, 4, lds, done[2], s);
-}
-
-hipError_t launch_bwd_delta(const float* out, const uint16_t* dout, float* delta, int rows, int H, int D,
-                            int64_t row_stride, hipStream_t s) {
-    if (rows <= 0) return hipSuccess;
-    const int64_t threads = int64_t(rows) * H * (D / 8);
-    const unsigned grid = unsigned((threads + 255) / 256);
-    if (D == 128) hipLaunchKernelGGL(ll_bwd_delta_kernel<128>, dim3(grid), dim3(256), 0, s, out, dout, delta, rows, H, row_stride);
-    else if (D == 64) hipLaunchKernelGGL(ll_bwd_delta_kernel<64>, dim3(grid), dim3(256), 0, s, out, dout, delta, rows, H, row_stride);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
 }
 
 hipError_t launch_bwd_finish(const BwdFinishParams& p, hipStream_t s) {

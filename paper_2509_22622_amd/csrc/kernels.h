@@ -217,10 +217,28 @@ struct BwdFinishParams {
     int64_t frame0;              // absolute index of the first frame
     float q_mul, k_mul;          // 1/sqrt(D), ln 2
 };
+// The operands of a training step as MFMA fragments (clip_layout.hip): rows [0, rows) of x and y [rows, H, D], both ways round each.
+struct ClipLayoutParams {
+    const uint16_t* x; const uint16_t* y;
+    uint16_t* x_k; uint16_t* y_k; uint16_t* x_t; uint16_t* y_t;  // K-style and V^T-style regions (head 0)
+    int64_t head_stride;
+    int H, rows;
+    // forward (out32 null): x holds keys before the rotary embedding, and rows from q_row0 on are the clip's, whose queries q
+    // [rows - q_row0, H, D] go to q_out rotated and scaled.  Row r belongs to frame r / P of the list of resident frames: the
+    // first n_sink_outside are the sink's, the others follow ctx_start.
+    const uint16_t* q; uint16_t* q_out;
+    int q_row0;
+    float q_scale;
+    RopeTables rope;
+    int P, grid_w, n_sink_outside;
+    int64_t ctx_start;
+    // backward: x holds q', y dO; delta[head * row_stride + row] = dO . O
+    const float* out32; float* delta;
+    int64_t row_stride;
+};
+hipError_t launch_clip_layout(const ClipLayoutParams& p, int D, hipStream_t s);
 hipError_t launch_bwd_dq(const BwdParams& p, hipStream_t s);
 hipError_t launch_bwd_dkv(const BwdParams& p, hipStream_t s);
-hipError_t launch_bwd_delta(const float* out32, const uint16_t* dout, float* delta, int rows, int H, int D,
-                            int64_t row_stride, hipStream_t s);
 hipError_t launch_bwd_finish(const BwdFinishParams& p, hipStream_t s);
 
 // One attention kernel instantiation.

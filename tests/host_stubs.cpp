@@ -28,7 +28,7 @@ hipError_t launch_out_proj(const OutProjParams&, hipStream_t) { return hipSucces
 hipError_t launch_pack_out_weight(const uint16_t*, uint16_t*, int, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_bwd_dq(const BwdParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_bwd_dkv(const BwdParams&, hipStream_t) { return hipSuccess; }
-hipError_t launch_bwd_delta(const float*, const uint16_t*, float*, int, int, int, int64_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_clip_layout(const ClipLayoutParams&, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_bwd_finish(const BwdFinishParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_probe_mfma(float*, unsigned long long*, int, int, int, int, int, hipStream_t) { return hipSuccess; }
 }  // namespace ll

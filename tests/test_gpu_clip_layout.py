@@ -1,0 +1,37 @@
+"""The operands of a training step laid out in one launch (clip_layout.hip).
+
+Where the layout can go wrong: kblocks of many frames (fewer than 32 tokens a frame), grid rows that wrap once or often inside a
+kblock, a last kblock of few rows, queries that begin inside a kblock, a clip that contains the sink.
+Output and gradients against 64 bits, to the five bf16 roundings on a gradient's way (5.0e-3, twice that
+where a few keys leave nothing to average)."""
+import pytest
+import torch
+
+from paper_2509_22622_amd import binding as B
+from perf import cases
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(tol, heads, head_dim, grid, chunk, sink, window, n_ctx, clip_frames, ctx_start=9):
+    case = {"kind": "clip", "heads": heads, "head_dim": head_dim, "grid_h": grid[0], "grid_w": grid[1], "chunk": chunk, "sink": sink,
+            "window": window, "ctx_start": ctx_start, "n_ctx": n_ctx, "clip_frames": clip_frames, "q_std": 1.0}
+    state = cases.prepare(case, 4)
+    got = [x.clone() for x in cases.run(state)]
+    again = cases.run(state)                         # a used handle
+    torch.cuda.synchronize()
+    for name, a, b, c in zip(("out", "dq", "dk", "dv"), got, cases.exact(case, 4), again):
+        assert float((a.double() - b).norm() / b.norm()) <= tol, name
+        assert torch.equal(a.view(torch.int16), c.view(torch.int16)), name
+    state["clip"].close()
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("grid", [(1, 1), (1, 3), (2, 5), (1, 31), (1, 33), (3, 40), (11, 3), (4, 32)])
+def test_frames_and_grid_rows_inside_a_kblock(head_dim, grid):
+    _check(1e-2, 2, head_dim, grid, 2, 3, 4, 3, 5)
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_no_sink_no_context(head_dim):
+    _check(1e-2, 1, head_dim, (3, 7), 3, 0, 2, 0, 7)
