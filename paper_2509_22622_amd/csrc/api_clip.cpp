@@ -276,71 +276,78 @@ ll_status ll_clip_backward(ll_clip* clip, const void* dout, void* dq, void* dk, 
     lp.out32 = clip_f32(c, c->o_o32); lp.delta = clip_f32(c, c->o_delta); lp.row_stride = c->row_stride;
     hipError_t e = launch_clip_layout(lp, c->D, s);
     if (e != hipSuccess) return hip_fail(e, "clip layout kernel launch");
-    // 2. Gq: queries as columns, chunk by chunk over each chunk's key ranges
+    // 2. Gq: queries as columns, chunk by chunk over each chunk's key ranges, the latest chunks (the longest key sets) first
     const int n_chunks = (n_clip + c->C - 1) / c->C;
-    for (int base = 0; base < n_chunks; base += MAX_BWD_GROUPS) {
-        BwdParams p{};
-        p.q = qrot; p.dout = dO;
-        p.lse = clip_f32(c, c->o_lse); p.delta = clip_f32(c, c->o_delta); p.row_stride = c->row_stride;
-        p.s_k1 = clip_u16(c, c->o_a); p.hs_k1 = c->hs_all;                    // K'   K-style
-        p.s_k2 = clip_u16(c, c->o_b); p.hs_k2 = c->hs_all;                    // V    K-style
-        p.s_t1 = clip_u16(c, c->o_b) + v_off_all; p.hs_t1 = c->hs_all;        // K'^T V^T-style
-        p.g1 = clip_f32(c, c->o_gq);
-        p.H = c->H; p.D = c->D;
-        const int m = std::min(MAX_BWD_GROUPS, n_chunks - base);
-        for (int i = 0; i < m; ++i) {
-            const int ci = base + m - 1 - i;
-            const int64_t f0 = clip_start + int64_t(ci) * c->C;
-            const int n = int(std::min<int64_t>(c->C, clip_start + n_clip - f0));
-            const std::vector<SlotRange> ranges = clip_key_ranges(c, f0, n);
-            BwdGroup& g = p.group[i];
-            g.c_begin = ci * c->C * c->P; g.c_end = g.c_begin + n * c->P;
-            g.n_ranges = int(ranges.size());
-            for (int r = 0; r < g.n_ranges; ++r) { g.rs[r] = int(ranges[r].begin); g.re[r] = int(ranges[r].end); }
-        }
-        p.n_groups = m;
-        e = launch_bwd_dq(p, s);
-        if (e != hipSuccess) return hip_fail(e, "dQ kernel launch");
+    std::vector<BwdGroup> q_groups;
+    for (int ci = n_chunks - 1; ci >= 0; --ci) {
+        const int64_t f0 = clip_start + int64_t(ci) * c->C;
+        const int n = int(std::min<int64_t>(c->C, clip_start + n_clip - f0));
+        const std::vector<SlotRange> ranges = clip_key_ranges(c, f0, n);
+        BwdGroup g{};
+        g.c_begin = ci * c->C * c->P; g.c_end = g.c_begin + n * c->P;
+        g.n_ranges = int(ranges.size());
+        for (int r = 0; r < g.n_ranges; ++r) { g.rs[r] = int(ranges[r].begin); g.re[r] = int(ranges[r].end); }
+        q_groups.push_back(g);
     }
+    BwdParams dq_p{};
+    dq_p.q = qrot; dq_p.dout = dO;
+    dq_p.lse = clip_f32(c, c->o_lse); dq_p.delta = clip_f32(c, c->o_delta); dq_p.row_stride = c->row_stride;
+    dq_p.s_k1 = clip_u16(c, c->o_a); dq_p.hs_k1 = c->hs_all;                    // K'   K-style
+    dq_p.s_k2 = clip_u16(c, c->o_b); dq_p.hs_k2 = c->hs_all;                    // V    K-style
+    dq_p.s_t1 = clip_u16(c, c->o_b) + v_off_all; dq_p.hs_t1 = c->hs_all;        // K'^T V^T-style
+    dq_p.g1 = clip_f32(c, c->o_gq);
+    dq_p.H = c->H; dq_p.D = c->D;
     // 3. Gk and dV: the clip's keys as columns over the query rows of the chunks that see them.  A frame is seen by its
     //    own chunk and by the later chunks that start within W frames after it (a sink frame by all later chunks);
     //    neighbouring frames with the same rows form one group of columns.
-    std::vector<BwdGroup> groups;
+    std::vector<BwdGroup> k_groups;
     for (int gc = 0; gc < n_clip; ++gc) {
         const int64_t gframe = clip_start + gc;
         const int c_first = gc / c->C;
         const int c_last = gframe < c->S ? n_chunks - 1 : std::min(n_chunks - 1, (gc + c->W) / c->C);
         const int rs = c_first * c->C * c->P;
         const int re = int(std::min<int64_t>(n_clip, int64_t(c_last + 1) * c->C) * c->P);
-        if (!groups.empty() && groups.back().rs[0] == rs && groups.back().re[0] == re) {
-            groups.back().c_end += c->P;
+        if (!k_groups.empty() && k_groups.back().rs[0] == rs && k_groups.back().re[0] == re) {
+            k_groups.back().c_end += c->P;
             continue;
         }
         BwdGroup g{};
         g.c_begin = gc * c->P; g.c_end = g.c_begin + c->P;
         g.n_ranges = 1; g.rs[0] = rs; g.re[0] = re;
-        groups.push_back(g);
+        k_groups.push_back(g);
     }
-    for (size_t base = 0; base < groups.size(); base += MAX_BWD_GROUPS) {
-        BwdParams p{};
-        p.lse = clip_f32(c, c->o_lse); p.delta = clip_f32(c, c->o_delta); p.row_stride = c->row_stride;
-        p.s_k1 = clip_u16(c, c->o_cq); p.hs_k1 = c->hs_clip;                  // q'   K-style
-        p.s_k2 = clip_u16(c, c->o_cd); p.hs_k2 = c->hs_clip;                  // dO   K-style
-        p.s_t1 = clip_u16(c, c->o_cq) + v_off_clip; p.hs_t1 = c->hs_clip;     // dO^T V^T-style
-        p.s_t2 = clip_u16(c, c->o_cd) + v_off_clip; p.hs_t2 = c->hs_clip;     // q'^T V^T-style
-        p.c_k1 = clip_u16(c, c->o_a); p.hc_k1 = c->hs_all;                    // K' of the columns
-        p.c_k2 = clip_u16(c, c->o_b); p.hc_k2 = c->hs_all;                    // V  of the columns
-        p.col_slot0 = col_slot0;
-        p.g1 = clip_f32(c, c->o_gk); p.dv = static_cast<uint16_t*>(dv);
-        p.H = c->H; p.D = c->D;
-        const int m = int(std::min<size_t>(MAX_BWD_GROUPS, groups.size() - base));
-        // longest streams first
-        std::vector<BwdGroup> part(groups.begin() + base, groups.begin() + base + m);
-        std::stable_sort(part.begin(), part.end(), [](const BwdGroup& a, const BwdGroup& b) { return a.re[0] - a.rs[0] > b.re[0] - b.rs[0]; });
-        for (int i = 0; i < m; ++i) p.group[i] = part[i];
-        p.n_groups = m;
-        e = launch_bwd_dkv(p, s);
-        if (e != hipSuccess) return hip_fail(e, "dK/dV kernel launch");
+    std::stable_sort(k_groups.begin(), k_groups.end(), [](const BwdGroup& a, const BwdGroup& b) { return a.re[0] - a.rs[0] > b.re[0] - b.rs[0]; });
+    BwdParams dkv_p{};
+    dkv_p.lse = clip_f32(c, c->o_lse); dkv_p.delta = clip_f32(c, c->o_delta); dkv_p.row_stride = c->row_stride;
+    dkv_p.s_k1 = clip_u16(c, c->o_cq); dkv_p.hs_k1 = c->hs_clip;                  // q'   K-style
+    dkv_p.s_k2 = clip_u16(c, c->o_cd); dkv_p.hs_k2 = c->hs_clip;                  // dO   K-style
+    dkv_p.s_t1 = clip_u16(c, c->o_cq) + v_off_clip; dkv_p.hs_t1 = c->hs_clip;     // dO^T V^T-style
+    dkv_p.s_t2 = clip_u16(c, c->o_cd) + v_off_clip; dkv_p.hs_t2 = c->hs_clip;     // q'^T V^T-style
+    dkv_p.c_k1 = clip_u16(c, c->o_a); dkv_p.hc_k1 = c->hs_all;                    // K' of the columns
+    dkv_p.c_k2 = clip_u16(c, c->o_b); dkv_p.hc_k2 = c->hs_all;                    // V  of the columns
+    dkv_p.col_slot0 = col_slot0;
+    dkv_p.g1 = clip_f32(c, c->o_gk); dkv_p.dv = static_cast<uint16_t*>(dv);
+    dkv_p.H = c->H; dkv_p.D = c->D;
+    // groups [from, from + MAX_BWD_GROUPS) of a list; false when there are none left
+    auto take = [](BwdParams& p, const std::vector<BwdGroup>& all, size_t from) {
+        p.n_groups = int(std::min<size_t>(MAX_BWD_GROUPS, all.size() - std::min(from, all.size())));
+        for (int i = 0; i < p.n_groups; ++i) p.group[i] = all[from + i];
+        return p.n_groups > 0;
+    };
+    if (q_groups.size() <= MAX_BWD_GROUPS && k_groups.size() <= MAX_BWD_GROUPS) {
+        take(dq_p, q_groups, 0);
+        take(dkv_p, k_groups, 0);
+        e = launch_bwd_both(dq_p, dkv_p, s);
+        if (e != hipSuccess) return hip_fail(e, "gradient kernel launch");
+    } else {
+        for (size_t base = 0; take(dq_p, q_groups, base); base += MAX_BWD_GROUPS) {
+            e = launch_bwd_dq(dq_p, s);
+            if (e != hipSuccess) return hip_fail(e, "dQ kernel launch");
+        }
+        for (size_t base = 0; take(dkv_p, k_groups, base); base += MAX_BWD_GROUPS) {
+            e = launch_bwd_dkv(dkv_p, s);
+            if (e != hipSuccess) return hip_fail(e, "dK/dV kernel launch");
+        }
     }
     // 4. factors and the turn back through the rotary embedding
     BwdFinishParams f{};

@@ -6,17 +6,20 @@
 //     dV_j = sum_i P_ij dO_i,   dP_ij = dO_i . V_j,   dZ_ij = P_ij (dP_ij - delta_i),   delta_i = dO_i . O_i,
 //     Gq_i = sum_j dZ_ij K'_j,  Gk_j = sum_i dZ_ij q'_i
 // (the factors 1/sqrt(D) and ln 2 and the turn back through the rotary embedding follow in ll_bwd_finish_kernel).
-// Two kernels, both in the forward kernel's formulation: a wave owns 32 columns (queries, or keys), every lane one
+// Two kinds of work, both in the forward kernel's formulation: a wave owns 32 columns (queries, or keys), every lane one
 // column, and the other side streams past in blocks of 32 rows as ready-made MFMA fragments (kernels.h): products
 // that contract over the feature axis take "K-style" fragments as the A operand and the column's own row as B;
 // products that contract over the streamed rows take "V^T-style" fragments as A and the accumulator registers of the
 // step before (P or dZ, rounded to bf16) as B, with no movement between lanes.
-//   ll_bwd_dq_kernel:  columns = queries;  streams K' (K-style), V (K-style), K'^T (V^T-style);   Gq^T += K'^T dZ^T
-//   ll_bwd_dkv_kernel: columns = clip keys; streams q', dO (K-style), dO^T, q'^T (V^T-style);
-//                      dV^T += dO^T P,  Gk^T += q'^T dZ
+//   dQ:    columns = queries;  streams K' (K-style), V (K-style), K'^T (V^T-style);   Gq^T += K'^T dZ^T
+//   dK/dV: columns = clip keys; streams q', dO (K-style), dO^T, q'^T (V^T-style);
+//          dV^T += dO^T P,  Gk^T += q'^T dZ
 // The streamed blocks reach LDS by direct loads into a ring of stages, two blocks ahead; one workgroup of 8 waves
 // (4 at head_dim 64) per 256 (128) columns.
 #include "kernels.h"
+
+#include <algorithm>
+#include <vector>
 
 namespace ll {
 
@@ -149,7 +152,7 @@ __device__ inline void bw_load_kstyle_row(const uint16_t* region, int64_t slot, 
 
 // ---------------------------------------------------------------------------------------------------------------
 template <int D, int NW>
-__device__ __forceinline__ void bw_dq(const BwdParams& p) {
+__device__ __forceinline__ void bw_dq(const BwdParams& p, int head, int tile) {
     constexpr int KS = D / 16, DB = D / 32;
     constexpr int KB_BYTES = KBLOCK * D * 2;
     constexpr int NREG = 3;                           // streamed regions per block
@@ -157,8 +160,6 @@ __device__ __forceinline__ void bw_dq(const BwdParams& p) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
-    int head, tile;
-    if (!bw_item(p.n_tiles, p.H, head, tile)) return;
     int gi = 0;
     while (gi + 1 < p.n_groups && tile >= p.group[gi + 1].tile_begin) ++gi;
     const BwdGroup& g = p.group[gi];
@@ -323,7 +324,7 @@ __device__ __forceinline__ void bw_dq(const BwdParams& p) {
 
 // ---------------------------------------------------------------------------------------------------------------
 template <int D, int NW>
-__device__ __forceinline__ void bw_dkv(const BwdParams& p) {
+__device__ __forceinline__ void bw_dkv(const BwdParams& p, int head, int tile) {
     constexpr int KS = D / 16, DB = D / 32;
     constexpr int KB_BYTES = KBLOCK * D * 2;
     constexpr int NREG = 4;
@@ -331,8 +332,6 @@ __device__ __forceinline__ void bw_dkv(const BwdParams& p) {
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
-    int head, tile;
-    if (!bw_item(p.n_tiles, p.H, head, tile)) return;
     int gi = 0;
     while (gi + 1 < p.n_groups && tile >= p.group[gi + 1].tile_begin) ++gi;
     const BwdGroup& g = p.group[gi];
@@ -500,15 +499,74 @@ __device__ __forceinline__ void bw_dkv(const BwdParams& p) {
     }
 }
 
+// Both gradients in one launch: the two kinds of tiles need nothing of one another, and together they leave one last round of
+// workgroups less than full instead of two (one of six rounds each at 12 heads x 32760 rows), or share the chip where neither
+// kind fills it.  Placement: workgroup b runs on XCD b % 8.  n_units == 0: every XCD gets an equal run of the dK/dV tiles, then
+// one of the dQ tiles.  Otherwise XCD x runs the units xcd_unit[xcd_first[x] .. xcd_first[x + 1]) in that order, a unit being all
+// tiles of one kind, head and group: as much matrix work on every XCD, longest tiles first (place_units).
+template <int D, int NW>
+__device__ __forceinline__ void bw_both(const BwdBothParams& p) {
+    const int xcd = blockIdx.x & 7;
+    int idx = blockIdx.x >> 3, head = -1, tile = 0;
+    bool dq = false;
+    if (p.n_units == 0) {
+        const int kv = p.dkv.n_tiles * p.dkv.H, q = p.dq.n_tiles * p.dq.H;
+        const int kv0 = (xcd * kv + 7) >> 3, kv_n = (((xcd + 1) * kv + 7) >> 3) - kv0;
+        dq = idx >= kv_n;
+        const int item = dq ? ((xcd * q + 7) >> 3) + idx - kv_n : kv0 + idx;
+        if (dq && item >= (((xcd + 1) * q + 7) >> 3)) return;
+        const int n = dq ? p.dq.n_tiles : p.dkv.n_tiles;
+        head = item / n;
+        tile = item - head * n;
+    } else {
+        const int per_head = p.dq.n_groups + p.dkv.n_groups;
+        for (int i = p.xcd_first[xcd]; i < p.xcd_first[xcd + 1]; ++i) {
+            const int unit = p.xcd_unit[i], h = unit / per_head;
+            int g = unit - h * per_head;
+            const bool q = g >= p.dkv.n_groups;
+            if (q) g -= p.dkv.n_groups;
+            const BwdParams& w = q ? p.dq : p.dkv;
+            const int tiles = (g + 1 < w.n_groups ? w.group[g + 1].tile_begin : w.n_tiles) - w.group[g].tile_begin;
+            if (idx < tiles) {
+                head = h;
+                tile = w.group[g].tile_begin + idx;
+                dq = q;
+                break;
+            }
+            idx -= tiles;
+        }
+        if (head < 0) return;
+    }
+    if (dq) bw_dq<D, NW>(p.dq, head, tile);
+    else bw_dkv<D, NW>(p.dkv, head, tile);
+}
+
 // One workgroup per (head, column tile).  The narrow form (128 columns at head_dim 128 instead of 256) is for launches with
 // too few wide tiles to fill the chip: twice the workgroups of one wave per SIMD instead of two, and a wave alone on its SIMD
-// takes a block in about two thirds of the time.
+// takes a block in about two thirds of the time.  One launch for both gradients, or, for clips of more than MAX_BWD_GROUPS groups
+// of columns, launches for one kind each.
+#define BW_KERNEL(NW) __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dq_kernel(const BwdParams p) { bw_dq<D, NW>(p); }
+BW_KERNEL(NW) void ll_bwd_both_kernel(const BwdBothParams p) { bw_both<D, NW>(p); }
 template <int D, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dkv_kernel(const BwdParams p) { bw_dkv<D, NW>(p); }
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dq_narrow_kernel(const BwdParams p) { bw_dq<128, 4>(p); }
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_bwd_dkv_narrow_kernel(const BwdParams p) { bw_dkv<128, 4>(p); }
+BW_KERNEL(NW) void ll_bwd_dq_kernel(const BwdParams p) {
+    int head, tile;
+    if (bw_item(p.n_tiles, p.H, head, tile)) bw_dq<D, NW>(p, head, tile);
+}
+template <int D, int NW>
+BW_KERNEL(NW) void ll_bwd_dkv_kernel(const BwdParams p) {
+    int head, tile;
+    if (bw_item(p.n_tiles, p.H, head, tile)) bw_dkv<D, NW>(p, head, tile);
+}
+BW_KERNEL(4) void ll_bwd_dq_narrow_kernel(const BwdParams p) {
+    int head, tile;
+    if (bw_item(p.n_tiles, p.H, head, tile)) bw_dq<128, 4>(p, head, tile);
+}
+BW_KERNEL(4) void ll_bwd_dkv_narrow_kernel(const BwdParams p) {
+    int head, tile;
+    if (bw_item(p.n_tiles, p.H, head, tile)) bw_dkv<128, 4>(p, head, tile);
+}
+#undef BW_KERNEL
 
 // ---------------------------------------------------------------------------------------------------------------
 // dq = R^T(Gq) / sqrt(D), dk = R^T(Gk) ln 2: back through the rotary embedding (the rotation by the opposite angle)
@@ -574,12 +632,78 @@ static int64_t plan_tiles(BwdParams& p, int cols) {
 // 15-frame clip of 189 tokens x 2 heads 328 -> 250 us with the forward's part, 9 frames of 301 x 3 387 -> 285).
 static bool narrow_tiles(BwdParams& p) { return p.D == 128 && plan_tiles(p, 128) <= 256; }
 
-template <typename Kernel>
-static hipError_t launch_bwd(Kernel kernel, const BwdParams& p, int waves, int lds, bool& done, hipStream_t s) {
+template <typename Kernel, typename Params>
+static hipError_t launch_bwd(Kernel kernel, const Params& p, int grid, int waves, int lds, bool& done, hipStream_t s) {
     hipError_t e = set_lds(reinterpret_cast<const void*>(kernel), lds, done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((p.n_tiles * p.H + 7) / 8 * 8), dim3(64 * waves), lds, s, p);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), lds, s, p);
     return hipGetLastError();
+}
+static int bwd_grid(const BwdParams& p) { return (p.n_tiles * p.H + 7) / 8 * 8; }
+static int dq_lds(int D) { return BW_DQ_NS * 3 * KBLOCK * D * 2; }
+static int dkv_lds(int D) { return BW_DKV_NS * (4 * KBLOCK * D * 2 + 256); }
+
+// Fill in the placement of a launch of both kinds (BwdBothParams): whole (kind, head, group) units, the largest to the least loaded
+// XCD, and within an XCD those of the longest tiles first.  Returns the grid.
+static int place_units(BwdBothParams& p) {
+    struct Unit { int id, tiles, length; };                       // length: MFMAs a wave issues for a tile, over D / 4
+    std::vector<Unit> all;
+    for (int h = 0; h < p.dq.H; ++h)
+        for (int g = 0; g < p.dkv.n_groups + p.dq.n_groups; ++g) {
+            const bool q = g >= p.dkv.n_groups;
+            const BwdParams& w = q ? p.dq : p.dkv;
+            const int i = q ? g - p.dkv.n_groups : g;
+            int blocks = 0;
+            for (int r = 0; r < w.group[i].n_ranges; ++r) blocks += (w.group[i].re[r] + KBLOCK - 1) / KBLOCK - w.group[i].rs[r] / KBLOCK;
+            const int tiles = (i + 1 < w.n_groups ? w.group[i + 1].tile_begin : w.n_tiles) - w.group[i].tile_begin;
+            all.push_back({h * (p.dkv.n_groups + p.dq.n_groups) + g, tiles, blocks * (q ? 3 : 4)});
+        }
+    std::stable_sort(all.begin(), all.end(), [](const Unit& a, const Unit& b) { return int64_t(a.tiles) * a.length > int64_t(b.tiles) * b.length; });
+    std::vector<Unit> per_xcd[8];
+    int64_t load[8] = {};
+    for (const Unit& u : all) {
+        const int x = int(std::min_element(load, load + 8) - load);
+        per_xcd[x].push_back(u);
+        load[x] += int64_t(u.tiles) * u.length;
+    }
+    int n = 0, most = 0;
+    for (int x = 0; x < 8; ++x) {
+        std::stable_sort(per_xcd[x].begin(), per_xcd[x].end(), [](const Unit& a, const Unit& b) { return a.length > b.length; });
+        p.xcd_first[x] = uint16_t(n);
+        int tiles = 0;
+        for (const Unit& u : per_xcd[x]) {
+            p.xcd_unit[n++] = uint16_t(u.id);
+            tiles += u.tiles;
+        }
+        most = std::max(most, tiles);
+    }
+    p.xcd_first[8] = uint16_t(n);
+    p.n_units = n;
+    return 8 * most;
+}
+
+hipError_t launch_bwd_both(const BwdParams& dq, const BwdParams& dkv, hipStream_t s) {
+    BwdBothParams p{};
+    p.dq = dq;
+    p.dkv = dkv;
+    const int D = dq.D;
+    if ((D != 128 && D != 64) || dkv.D != D || dq.H != dkv.H) return hipErrorInvalidValue;
+    // (one round of narrow tiles, of both kinds together)
+    const bool narrow = D == 128 && plan_tiles(p.dq, 128) + plan_tiles(p.dkv, 128) <= 256;
+    const int cols = D == 128 && !narrow ? 256 : 128;
+    const int64_t total = plan_tiles(p.dq, cols) + plan_tiles(p.dkv, cols);
+    if (total <= 0) return hipSuccess;
+    if (total > 0x7FFFFFF) return hipErrorInvalidValue;
+    p.n_units = 0;
+    int grid = bwd_grid(p.dq) + bwd_grid(p.dkv);
+    const int units = dq.H * (dq.n_groups + dkv.n_groups);
+    // (a round holds 256 workgroups, twice as many at head_dim 64; one round is better dealt out evenly)
+    if (total > (D == 128 ? 256 : 512) && units >= 32 && units <= MAX_BWD_UNITS) grid = place_units(p);
+    const int lds = std::max(dq_lds(D), dkv_lds(D));
+    static bool done[3] = {};
+    if (narrow) return launch_bwd(ll_bwd_both_kernel<128, 4>, p, grid, 4, lds, done[0], s);
+    if (D == 128) return launch_bwd(ll_bwd_both_kernel<128, 8>, p, grid, 8, lds, done[1], s);
+    return launch_bwd(ll_bwd_both_kernel<64, 4>, p, grid, 4, lds, done[2], s);
 }
 
 hipError_t launch_bwd_dq(const BwdParams& p_in, hipStream_t s) {
@@ -587,11 +711,11 @@ hipError_t launch_bwd_dq(const BwdParams& p_in, hipStream_t s) {
     if (p.D != 128 && p.D != 64) return hipErrorInvalidValue;
     const bool narrow = narrow_tiles(p);
     if (plan_tiles(p, p.D == 128 && !narrow ? 256 : 128) <= 0) return hipSuccess;
-    const int lds = BW_DQ_NS * 3 * KBLOCK * p.D * 2;
+    const int lds = dq_lds(p.D), grid = bwd_grid(p);
     static bool done[3] = {};
-    if (narrow) return launch_bwd(ll_bwd_dq_narrow_kernel, p, 4, lds, done[0], s);
-    if (p.D == 128) return launch_bwd(ll_bwd_dq_kernel<128, 8>, p, 8, lds, done[1], s);
-    return launch_bwd(ll_bwd_dq_kernel<64, 4>, p, 4, lds, done[2], s);
+    if (narrow) return launch_bwd(ll_bwd_dq_narrow_kernel, p, grid, 4, lds, done[0], s);
+    if (p.D == 128) return launch_bwd(ll_bwd_dq_kernel<128, 8>, p, grid, 8, lds, done[1], s);
+    return launch_bwd(ll_bwd_dq_kernel<64, 4>, p, grid, 4, lds, done[2], s);
 }
 
 hipError_t launch_bwd_dkv(const BwdParams& p_in, hipStream_t s) {
@@ -599,11 +723,11 @@ hipError_t launch_bwd_dkv(const BwdParams& p_in, hipStream_t s) {
     if (p.D != 128 && p.D != 64) return hipErrorInvalidValue;
     const bool narrow = narrow_tiles(p);
     if (plan_tiles(p, p.D == 128 && !narrow ? 256 : 128) <= 0) return hipSuccess;
-    const int lds = BW_DKV_NS * (4 * KBLOCK * p.D * 2 + 256);
+    const int lds = dkv_lds(p.D), grid = bwd_grid(p);
     static bool done[3] = {};
-    if (narrow) return launch_bwd(ll_bwd_dkv_narrow_kernel, p, 4, lds, done[0], s);
-    if (p.D == 128) return launch_bwd(ll_bwd_dkv_kernel<128, 8>, p, 8, lds, done[1], s);
-    return launch_bwd(ll_bwd_dkv_kernel<64, 4>, p, 4, lds, done[2], s);
+    if (narrow) return launch_bwd(ll_bwd_dkv_narrow_kernel, p, grid, 4, lds, done[0], s);
+    if (p.D == 128) return launch_bwd(ll_bwd_dkv_kernel<128, 8>, p, grid, 8, lds, done[1], s);
+    return launch_bwd(ll_bwd_dkv_kernel<64, 4>, p, grid, 4, lds, done[2], s);
 }
 
 hipError_t launch_bwd_finish(const BwdFinishParams& p, hipStream_t s) {

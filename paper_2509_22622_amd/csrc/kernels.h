@@ -209,6 +209,15 @@ struct BwdParams {
     int n_tiles;                 // filled in by launch_bwd_*
     BwdGroup group[MAX_BWD_GROUPS];
 };
+// Both kinds in one launch; the placement on the XCDs is filled in by launch_bwd_both (attn_bwd.hip).
+constexpr int MAX_BWD_UNITS = 640;
+struct BwdBothParams {
+    BwdParams dq, dkv;
+    int n_units;
+    uint16_t xcd_first[9];
+    uint16_t xcd_unit[MAX_BWD_UNITS];            // head * (groups of both kinds) + group, the dK/dV kind's first
+};
+static_assert(sizeof(BwdBothParams) <= 4096, "kernel arguments");
 struct BwdFinishParams {
     const float* gq; const float* gk;                   // [n_frames * P, H, D]
     uint16_t* dq; uint16_t* dk;
@@ -237,6 +246,7 @@ struct ClipLayoutParams {
     int64_t row_stride;
 };
 hipError_t launch_clip_layout(const ClipLayoutParams& p, int D, hipStream_t s);
+hipError_t launch_bwd_both(const BwdParams& dq, const BwdParams& dkv, hipStream_t s);
 hipError_t launch_bwd_dq(const BwdParams& p, hipStream_t s);
 hipError_t launch_bwd_dkv(const BwdParams& p, hipStream_t s);
 hipError_t launch_bwd_finish(const BwdFinishParams& p, hipStream_t s);

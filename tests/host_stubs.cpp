@@ -26,6 +26,7 @@ hipError_t launch_read_frame8(const ReadFrameParams&, hipStream_t) { return hipS
 hipError_t launch_attn(const AttnParams&, int, hipStream_t) { return hipSuccess; }
 hipError_t launch_out_proj(const OutProjParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_pack_out_weight(const uint16_t*, uint16_t*, int, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_bwd_both(const BwdParams&, const BwdParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_bwd_dq(const BwdParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_bwd_dkv(const BwdParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_clip_layout(const ClipLayoutParams&, int, hipStream_t) { return hipSuccess; }

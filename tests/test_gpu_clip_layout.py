@@ -1,8 +1,9 @@
-"""The operands of a training step laid out in one launch (clip_layout.hip).
+"""The operands of a training step laid out in one launch, and its gradients in one launch (clip_layout.hip, attn_bwd.hip).
 
 Where the layout can go wrong: kblocks of many frames (fewer than 32 tokens a frame), grid rows that wrap once or often inside a
-kblock, a last kblock of few rows, queries that begin inside a kblock, a clip that contains the sink.
-Output and gradients against 64 bits, to the five bf16 roundings on a gradient's way (5.0e-3, twice that
+kblock, a last kblock of few rows, queries that begin inside a kblock, a clip that contains the sink.  Where the launch of both
+gradients can: tiles of both kinds on the chip at once, dealt out evenly or placed by work, and clips of more groups of columns
+than one launch holds.  Output and gradients against 64 bits, to the five bf16 roundings on a gradient's way (5.0e-3, twice that
 where a few keys leave nothing to average)."""
 import pytest
 import torch
@@ -35,3 +36,11 @@ def test_frames_and_grid_rows_inside_a_kblock(head_dim, grid):
 @pytest.mark.parametrize("head_dim", [64, 128])
 def test_no_sink_no_context(head_dim):
     _check(1e-2, 1, head_dim, (3, 7), 3, 0, 2, 0, 7)
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, clip_frames", [
+    (3, 128, (3, 5), 1, 40), (2, 64, (2, 9), 1, 33),             # more groups than one launch takes
+    (16, 128, (13, 20), 1, 9), (24, 64, (13, 20), 1, 9),         # several rounds: placed by work
+    (5, 128, (13, 20), 3, 9), (1, 128, (5, 13), 3, 5), (9, 64, (9, 13), 2, 6)])
+def test_both_gradients_in_one_launch(heads, head_dim, grid, chunk, clip_frames):
+    _check(5.0e-3, heads, head_dim, grid, chunk, 2, 4, 4, clip_frames)
