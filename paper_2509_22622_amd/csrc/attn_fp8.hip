@@ -812,7 +812,7 @@ __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_pe
             const int first = part * slice_rows / 32;
             if (part * slice_rows >= rows) return;
             row0 += part * slice_rows;
-            if (f8_merge<D, NW>(p, ch, head, tile, splits, row0, first, slice_rows / 32, slots)) return;
+            if (f8_merge<D, NW>(p, ch, head, tile, splits, row0, first, min(slice_rows / 32, NW - first), slots)) return;
             ch.q_end = min(ch.q_end, row0 + slice_rows);
         } else {
             if (part >= splits) return;

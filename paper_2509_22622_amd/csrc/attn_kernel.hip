@@ -535,10 +535,9 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         p.token = calls.fetch_add(1, std::memory_order_relaxed) % (SPLIT_TOKENS - 1) + 1;
         hipError_t e = split_pool_address(&p.pool);
         if (e != hipSuccess) return e;
-        // a workgroup of the merge takes as many of a tile's 16-row blocks as leave about one workgroup per CU
-        // (of the 8-bit kernel's 32-row blocks, pairs)
-        const int least = p.kblock == KBLOCK8 ? 2 : 1;
-        while (p.slice_blocks > least && int64_t(total) * ((16 >> log_g) / p.slice_blocks) < 200) p.slice_blocks >>= 1;
+        // the merge in one round of workgroups: each takes its part of a tile's 16-row blocks (of the 8-bit kernel's 32-row ones)
+        const int blocks = 16 >> log_g, least = p.kblock == KBLOCK8 ? 2 : 1, slices = std::max(1, std::min(blocks / least, 256 / total));
+        p.slice_blocks = (blocks / least + slices - 1) / slices * least;
     }
     p.n_groups = 0;
     const int groups = p.H * p.n_chunks;
@@ -599,7 +598,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         p.merge = 1;
-        p.per_tile = (16 >> log_g) / p.slice_blocks;
+        p.per_tile = ((16 >> log_g) + p.slice_blocks - 1) / p.slice_blocks;
         hipLaunchKernelGGL(kernel, dim3((total * p.per_tile + 7) / 8 * 8), threads, lds_bytes, s, p);
     }
     return hipGetLastError();
