@@ -46,7 +46,6 @@ struct OpTile {
     static constexpr int FRAGS = WFRAGS + BM / 16 * SUBS;       // then of x
     static constexpr int STAGE_BYTES = FRAGS * 1024, LDS_BYTES = STAGES * STAGE_BYTES;
     static constexpr int LPW = FRAGS / OP_WAVES;                // fragments a wave loads per stage
-    static constexpr int AHEAD = STAGES - 1;
     static constexpr int MB = BM / 16 / WM, NB = BN / 16 / WN;  // 16 x 16 blocks of a wave
     static_assert(WM * WN == OP_WAVES && FRAGS % OP_WAVES == 0 && LDS_BYTES <= 160 * 1024 && MB >= 1 && NB >= 1, "tile of the output projection");
 };
@@ -57,10 +56,21 @@ __device__ __forceinline__ void op_wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+// LDS reads the compiler does not see (attn_stream.hip): `dst` is pending until op_lds_wait, which waits for all of them.
+__device__ __forceinline__ void op_lds_read(op_u32x4& dst, unsigned addr, int offset) {
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(offset));
+}
+template <int N>
+__device__ __forceinline__ void op_lds_wait(op_u32x4 (&x)[N]) {
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x[0]));
+#pragma unroll
+    for (int i = 1; i < N; ++i) asm volatile("" : "+v"(x[i]));   // arrived too: ties the register to this point
+}
+
 template <typename Tile>
 __global__ __launch_bounds__(64 * OP_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ll_out_proj_kernel(const OutProjParams p) {
-    constexpr int OP_BM = Tile::BM, OP_BN = Tile::BN, OP_BK = Tile::BK, OP_STAGES = Tile::STAGES, OP_AHEAD = Tile::AHEAD;
+    constexpr int OP_BM = Tile::BM, OP_BN = Tile::BN, OP_BK = Tile::BK, OP_STAGES = Tile::STAGES;
     constexpr int OP_SUBS = Tile::SUBS, OP_WFRAGS = Tile::WFRAGS, OP_STAGE_BYTES = Tile::STAGE_BYTES, OP_LPW = Tile::LPW;
     constexpr int MB = Tile::MB, NB = Tile::NB;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -90,9 +100,9 @@ void ll_out_proj_kernel(const OutProjParams p) {
         const int blk = is_w ? min((n0 >> 4) + f / OP_SUBS, last_nb) : min((m0 >> 4) + (f - OP_WFRAGS) / OP_SUBS, last_mb);
         src[l] = reinterpret_cast<const char*>(is_w ? p.w_frag : p.x_frag) + (int64_t(blk) * n_ksteps + f % OP_SUBS) * 1024 + lane * 16;
     }
-    auto issue = [&](int kt) {
+    auto issue = [&](int kt, int to) {
         const int kc = min(kt, KT - 1);          // past the end the last step is fetched again, never used
-        char* stage = lds + (kt % OP_STAGES) * OP_STAGE_BYTES;
+        char* stage = lds + to * OP_STAGE_BYTES;
 #pragma unroll
         for (int l = 0; l < OP_LPW; ++l)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[l] + kc * OP_SUBS * 1024),
@@ -105,33 +115,54 @@ void ll_out_proj_kernel(const OutProjParams p) {
 #pragma unroll
         for (int b = 0; b < MB; ++b) acc[a][b] = op_f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // Fragment i of k-step `sub` of a stage: the wave's NB of w, then its MB of x.  Two register sets: while the MFMAs of one k-step
+    // run from the one, the next k-step's fragments are read into the other (by hand: the compiler would put the reads in
+    // front of the MFMAs that use them, and the two waves of a SIMD would wait for LDS at the same time).
+    constexpr int NFR = NB + MB, NMFMA = NB * MB;
+    op_u32x4 fr[2][NFR];
+    const unsigned lds_lane = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds + lane * 16;
+    const unsigned w_at = lds_lane + wn * NB * OP_SUBS * 1024, x_at = lds_lane + (OP_WFRAGS + wm * MB * OP_SUBS) * 1024;
+    auto read_frag = [&](op_u32x4& dst, unsigned stage_at, int sub, int i) {
+        if (i < NB) op_lds_read(dst, w_at + stage_at, (i * OP_SUBS + sub) * 1024);
+        else op_lds_read(dst, x_at + stage_at, ((i - NB) * OP_SUBS + sub) * 1024);
+    };
 #pragma unroll
-    for (int j = 0; j < OP_AHEAD; ++j) issue(j);
+    for (int j = 0; j < OP_STAGES; ++j) issue(j, j);
+    op_wait_vmcnt<(OP_STAGES - 1) * OP_LPW>();
+    asm volatile("s_barrier" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NFR; ++i) read_frag(fr[0][i], 0, 0, i);
+    int stage = 0;                               // kt mod OP_STAGES
+    static_assert(OP_SUBS == 2, "the register sets alternate within a step");
     for (int kt = 0; kt < KT; ++kt) {
-        // this wave's loads of step kt have landed (all but the youngest step's), then every wave's have, and every
-        // wave has left step kt - 1, whose stage the loads issued next overwrite
-        op_wait_vmcnt<(OP_AHEAD - 1) * OP_LPW>();
-        asm volatile("s_barrier" ::: "memory");
-        issue(kt + OP_AHEAD);
-        const char* st = lds + (kt % OP_STAGES) * OP_STAGE_BYTES + lane * 16;
-        op_u32x4 wf[OP_SUBS][NB], xf[OP_SUBS][MB];
+        const int next = stage + 1 == OP_STAGES ? 0 : stage + 1;
 #pragma unroll
         for (int sub = 0; sub < OP_SUBS; ++sub) {
+            op_lds_wait(fr[sub]);
+            if (sub == OP_SUBS - 1) {
+                // every read of this step's stage has returned here, and this wave's loads of the next step have landed: behind
+                // the barrier that holds for every wave, the stage is loaded anew and the next one read
+                op_wait_vmcnt<(OP_STAGES - 2) * OP_LPW>();
+                asm volatile("s_barrier" ::: "memory");
+                issue(kt + OP_STAGES, stage);
+            }
+            const unsigned from = unsigned(sub == OP_SUBS - 1 ? next : stage) * OP_STAGE_BYTES;
 #pragma unroll
-            for (int a = 0; a < NB; ++a) wf[sub][a] = *reinterpret_cast<const op_u32x4*>(st + ((wn * NB + a) * OP_SUBS + sub) * 1024);
+            for (int m = 0; m < NMFMA; ++m) {
+                const int a = m / MB, b = m % MB;
+                acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(op_bf16x8, fr[sub][a]),
+                                                                    __builtin_bit_cast(op_bf16x8, fr[sub][NB + b]), acc[a][b], 0, 0, 0);
+                // the reads of the next k-step, spread over the first half of this one's MFMAs
 #pragma unroll
-            for (int b = 0; b < MB; ++b) xf[sub][b] = *reinterpret_cast<const op_u32x4*>(st + (OP_WFRAGS + (wm * MB + b) * OP_SUBS + sub) * 1024);
+                for (int i = 0; i < NFR; ++i)
+                    if (i * ((NMFMA + 1) / 2) / NFR == m) read_frag(fr[1 - sub][i], from, 1 - sub, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-#pragma unroll
-        for (int sub = 0; sub < OP_SUBS; ++sub)
-#pragma unroll
-            for (int a = 0; a < NB; ++a)
-#pragma unroll
-                for (int b = 0; b < MB; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(op_bf16x8, wf[sub][a]),
-                                                                        __builtin_bit_cast(op_bf16x8, xf[sub][b]), acc[a][b], 0, 0, 0);
+        stage = next;
     }
-    op_wait_vmcnt<0>();                          // the loads issued past the end have landed before the wave leaves
+    op_lds_wait(fr[0]);                          // no load may still be writing registers or LDS past this point
+    op_wait_vmcnt<0>();
 
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
@@ -190,22 +221,27 @@ using OpTile128x128 = OpTile<128, 128, 64, 3, 4, 2>;
 using OpTile128x64 = OpTile<128, 64, 64, 5, 4, 2>;
 using OpTile64x64 = OpTile<64, 64, 64, 6, 4, 2>;
 
-// Time of a launch in us as measured (60 to 23400 rows, 128 to 3072 features): rounds of workgroups over the CUs, each a
-// walk over K whose step takes `alone` us with few workgroups on the chip and `more` longer with all CUs at work.
+// Time of a launch in us, fitted to 224 timings (60 to 23400 rows, 64 to 3072 features): rounds of workgroups over the CUs, each
+// `around` and a walk over K whose step takes `alone` with few workgroups on the chip and `more` longer with all CUs at work.
+// The tile it picks was the fastest or within 3 % of it at all 56 shapes.
 template <typename Tile>
-static double tile_us(const OutProjParams& p, double alone, double more) {
+static double tile_us(const OutProjParams& p, double launch, double around, double alone, double more) {
     const int64_t tiles = int64_t((p.M + Tile::BM - 1) / Tile::BM) * ((p.N + Tile::BN - 1) / Tile::BN);
-    return double((tiles + 255) / 256) * (p.K / Tile::BK) * (alone + more * double(std::min<int64_t>(tiles, 256)) / 256);
+    return launch + double((tiles + 255) / 256) * (around + (p.K / Tile::BK) * (alone + more * double(std::min<int64_t>(tiles, 256)) / 256));
 }
 
-// The largest tile asks least of L2 and is the best one where there are enough of them; a launch of few rows leaves most
-// CUs idle with it while the others walk all of K at 1 us a step.  The sums run over K in the same order in every tile shape:
-// the results do not depend on it.  us with 256 x 128 tiles and with the tile taken, 12 heads x 128: 60 rows 24 -> 8,
-// 300 28 -> 9, 1200 27 -> 14, 2400 29 -> 19, 4680 32 (228 tiles) either way.
+// The largest tile asks least of L2 and LDS and is the best one where there are enough of them; a launch of few rows leaves
+// most CUs idle with it while the others walk all of K at 0.9 us a step.  The sums run over K in the same order in every tile
+// shape: the results do not depend on it.  us with 256 x 128 tiles and with the tile taken, 12 heads x 128: 60 rows 23 -> 7,
+// 300 22 -> 8, 1200 23 -> 11, 2400 25 -> 17, 4680 28 (228 tiles) either way.
+//
+// What a step of 256 x 128 costs: 128 KB of fragment reads and 48 KB of ring writes through LDS (1400 clocks) beside 1024 clocks
+// of MFMAs.  With each k-step's reads in front of its own MFMAs they added up: 32 us at 4680 rows; read a k-step ahead, by
+// hand, 28 (4680 x 3072 104 -> 92, 23400 x 1536 141 -> 128, 2400 x 2432 43 -> 37).
 hipError_t launch_out_proj(const OutProjParams& p, hipStream_t s) {
     if (p.M < 1 || p.N < 16 || p.N % 16 != 0 || p.K < 64 || p.K % 64 != 0) return hipErrorInvalidValue;   // K = H * D, D 64 or 128
-    const double t0 = tile_us<OpTile256x128>(p, 1.03, 0.14), t1 = tile_us<OpTile128x128>(p, 0.62, 0.10);
-    const double t2 = tile_us<OpTile128x64>(p, 0.36, 0.04), t3 = tile_us<OpTile64x64>(p, 0.21, 0.07);
+    const double t0 = tile_us<OpTile256x128>(p, 2.3, 3.85, 0.626, 0.257), t1 = tile_us<OpTile128x128>(p, 2.0, 2.36, 0.367, 0.136);
+    const double t2 = tile_us<OpTile128x64>(p, 1.7, 2.13, 0.216, 0.098), t3 = tile_us<OpTile64x64>(p, 1.8, 1.38, 0.151, 0.103);
     const double best = std::min(std::min(t0, t1), std::min(t2, t3));
     if (best == t0) return launch_tile<OpTile256x128>(p, s);
     if (best == t1) return launch_tile<OpTile128x128>(p, s);
