@@ -358,7 +358,7 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
         if (raw_q) {
             p.t_table = c->t_table + layer * c->t_stride;
             p.row_cs = c->rope.row_cs; p.col_cs = c->rope.col_cs;
-            p.n_h = c->rope.n_h; p.n_w = c->rope.n_w; p.P = c->g.P; p.grid_w = c->grid_w;
+            p.P = c->g.P; p.grid_w = c->grid_w;
             p.q_scale = float(1.4426950408889634 / std::sqrt(double(c->D)));
         }
         p.key_groups = order[base].first / 256;

@@ -272,26 +272,41 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     if constexpr ((SCHED & 16) != 0) {
         // the queries come as the model's projection made them: turn this lane's pairs (3D rotary embedding, the
         // frame axis from the table the cache write left, rows and columns from the cache's tables) and fold in the
-        // softmax scale, with the arithmetic of the cache-write kernel (kernels.h: rope_turn_scaled)
-        const int n_t = p.n_t, n_h = p.n_h;
+        // softmax scale, with the arithmetic of the cache-write kernel (kernels.h: rope_turn_scaled).  The tables are read two
+        // pairs at a time: the lanes' addresses scatter, and one pair each (32 loads a lane at head_dim 128) kept the
+        // address units busy for 2.6 us in front of a workgroup's first step, two 1.3.
+        constexpr int NH = D / 6, NT = D / 2 - 2 * NH;              // rotary pairs of the row (and column) axis, of the frame axis
+        static_assert(NT % 2 == 0, "two neighbouring pairs lie on one axis, but for the last of an odd row axis");
+        typedef float f32x4_8 __attribute__((ext_vector_type(4), aligned(8)));
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             const int rel = min(q0 + 16 * qb + n, q_end - 1) - ch.q_begin;
             const int fi = rel / p.P, tok = rel - fi * p.P;
             const int y = tok / p.grid_w, x = tok - y * p.grid_w;
             const float2* t_cs = p.t_table + (ch.t_row + fi) * MAX_T_PAIRS;
-            const float2* r_cs = p.row_cs + y * n_h - n_t;
-            const float2* c_cs = p.col_cs + x * p.n_w - n_t - n_h;
+            const float2* r_cs = p.row_cs + y * NH - NT;
+            const float2* c_cs = p.col_cs + x * NH - NT - NH;
 #pragma unroll
             for (int s = 0; s < NQ; ++s)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int pi = 16 * s + 4 * g + j;      // rotary pair of features 32 s + 8 g + 2 j, + 1
-                    const float2 w = *(pi < n_t ? t_cs + pi : (pi < n_t + n_h ? r_cs + pi : c_cs + pi));
-                    float re, im;
-                    rope_turn_scaled(float(qf[qb][s][2 * j]), float(qf[qb][s][2 * j + 1]), w, p.q_scale, re, im);
-                    qf[qb][s][2 * j] = __bf16(re);
-                    qf[qb][s][2 * j + 1] = __bf16(im);
+                for (int j = 0; j < 4; j += 2) {
+                    const int pi = 16 * s + 4 * g + j;      // rotary pairs of features 32 s + 8 g + 2 j .. + 3
+                    f32x4 w = *reinterpret_cast<const f32x4_8*>((pi < NT ? t_cs : pi < NT + NH ? r_cs : c_cs) + pi);
+                    constexpr int LAST = NT + NH - 1;       // the row axis's last pair (its row's end is not the table's)
+                    if (LAST % 2 == 0 && LAST / 16 == s && LAST % 4 == j) {
+                        const float2 first = c_cs[LAST + 1];
+                        if (pi == LAST) {
+                            w[2] = first.x;
+                            w[3] = first.y;
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        float re, im;
+                        rope_turn_scaled(float(qf[qb][s][2 * (j + k)]), float(qf[qb][s][2 * (j + k) + 1]), make_float2(w[2 * k], w[2 * k + 1]), p.q_scale, re, im);
+                        qf[qb][s][2 * (j + k)] = __bf16(re);
+                        qf[qb][s][2 * (j + k) + 1] = __bf16(im);
+                    }
                 }
         }
     }

@@ -170,7 +170,7 @@ struct AttnParams {
     // (3D rotary embedding, the same arithmetic as the cache-write kernel) and scales them by q_scale.
     const float2* t_table;       // frame-axis (cos, sin), [frames of the call][MAX_T_PAIRS], written by the cache write
     const float2* row_cs; const float2* col_cs;   // as in RopeTables
-    int n_h, n_w, P, grid_w;
+    int P, grid_w;
     float q_scale;
     uint16_t xcd_first[9];
     uint16_t xcd_group[MAX_XCD_GROUPS];
