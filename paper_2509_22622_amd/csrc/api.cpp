@@ -277,7 +277,7 @@ static ll_status enqueue_append(ll_cache* c, int layer, const int64_t* frames, i
         for (int i = 0; i < m; ++i) {
             p.frame[i] = frames[base + i];
             p.slot[i] = slot_of_frame(c->g, frames[base + i]);
-            const int nseg = int((p.slot[i] % c->kb + c->g.P + c->kb - 1) / c->kb);
+            const int nseg = int((p.slot[i] % KBLOCK + c->g.P + KBLOCK - 1) / KBLOCK);        // 32 slots each, of either cache
             p.seg_begin[i + 1] = p.seg_begin[i] + nseg;
         }
         set_frame_rotation(p, c->inv_freq_t.data());

@@ -8,13 +8,14 @@
 // V8 = e4m3(V * 2^-v_exp), Q8 = e4m3(q' * log2(e)/sqrt(D) * 2^k_exp): the product Q8 . K8 needs no rescaling
 // and 2^v_exp is applied once to the attention output.
 //
-// Work split: one workgroup per (64-slot segment of a frame, head); a segment is the part of one frame that
-// falls into one kblock.  The workgroup builds the segment's share of one K kblock and one V kblock in LDS and
-// stores whole 16-byte units where the segment covers them, single bytes at a frame boundary inside a unit.
-// As in append_kernel.hip a workgroup is a handful of memory round trips long, so its arguments are fetched in one go and
-// every load is issued before the first value is touched; the V image is built two or four features
-// at a time from one LDS read per key and byte permutes.  us, before and after: 64.8 MB (4680 rows x 12 x 128)
-// 20.5 -> 19.9, up to 2392 rows x 5 x 128 11.3 -> 9.6.
+// Work split: one workgroup per (32-slot segment of a frame, head), heads fastest as in append_kernel.hip; a segment is the part
+// of one frame that falls into one half (row block R) of a kblock.  The workgroup builds the segment's share of the half's K
+// and V images in LDS and stores whole 16-byte units where the segment covers them, single bytes at a frame boundary
+// inside a unit.  As in append_kernel.hip a workgroup is a handful of memory round trips long, so its arguments are fetched in
+// one go and every load is issued before the first value is touched; the V image is built two features at a time from
+// one LDS read per key and byte permutes.  Half a kblock and not a whole one: two (head_dim 64: one) items a thread instead of
+// four halve the chain of conversions between the round trips.  us with whole and half kblocks: 4680 rows x 12 x 128 19.4 and
+// 16.7 (64.8 MB: 3.9 TB/s, a copy here takes 13), 2392 rows x 5 x 128 9.4 and 8.5, 598 rows 8.2 and 6.1.
 #include "kernels.h"
 
 namespace ll {
@@ -36,13 +37,15 @@ template <int D>
 __global__ __launch_bounds__(256) void ll_append8_kernel(const AppendParams p) {
     constexpr int CH = D / 8;                 // 8-element chunks per (token, head) row
     constexpr int VROW = D + 16;              // padded LDS row of V bytes
-    constexpr int ITEMS = KBLOCK8 * CH / 256; // (token, chunk) items per thread
+    constexpr int HALF = KBLOCK8 / 2;
+    constexpr int ITEMS = HALF * CH / 256;    // (token, chunk) items per thread
     __shared__ float2 t_cs[64];
-    __shared__ __attribute__((aligned(16))) unsigned char k_img[KBLOCK8 * D];
-    __shared__ __attribute__((aligned(16))) unsigned char v_rows[KBLOCK8 * VROW];
+    __shared__ __attribute__((aligned(16))) unsigned char k_img[HALF * D];
+    __shared__ __attribute__((aligned(16))) unsigned char v_rows[HALF * VROW];
 
     const int tid = threadIdx.x;
-    const int head = blockIdx.y;
+    const int head = blockIdx.x % p.H;
+    const int gseg = blockIdx.x / p.H;
     int begin[MAX_APPEND_FRAMES];
     int64_t slots[MAX_APPEND_FRAMES];
 #pragma unroll
@@ -56,17 +59,17 @@ __global__ __launch_bounds__(256) void ll_append8_kernel(const AppendParams p) {
     int64_t slot0 = slots[0];
 #pragma unroll
     for (int i = 1; i < MAX_APPEND_FRAMES; ++i)
-        if (i < p.n_frames && (int)blockIdx.x >= begin[i]) {
+        if (i < p.n_frames && gseg >= begin[i]) {
             fi = i;
             begin_fi = begin[i];
             slot0 = slots[i];
         }
-    const int seg = blockIdx.x - begin_fi;
-    const int64_t kb = slot0 / KBLOCK8 + seg;                      // kblock this segment is in
-    const int64_t s_begin = max(slot0, kb * KBLOCK8);
-    const int64_t s_end = min(slot0 + p.P, (kb + 1) * KBLOCK8);
-    const int k_lo = int(s_begin - kb * KBLOCK8);                  // slots [k_lo, k_hi) of the kblock
-    const int k_hi = int(s_end - kb * KBLOCK8);
+    const int seg = gseg - begin_fi;
+    const int64_t hb = slot0 / HALF + seg;                         // half kblock this segment is in
+    const int64_t s_begin = max(slot0, hb * HALF);
+    const int64_t s_end = min(slot0 + p.P, (hb + 1) * HALF);
+    const int k_lo = int(s_begin - hb * HALF);                     // slots [k_lo, k_hi) of the half
+    const int k_hi = int(s_end - hb * HALF);
     const int ntok = k_hi - k_lo;
     const int tok0 = int(s_begin - slot0);                         // token inside the frame
     const int n_t = p.rope.n_t, n_h = p.rope.n_h;
@@ -131,43 +134,38 @@ __global__ __launch_bounds__(256) void ll_append8_kernel(const AppendParams p) {
     }
     __syncthreads();
 
-    unsigned char* kdst = p.k8_cache + head * p.head_stride + kb * (KBLOCK8 * D);
-    unsigned char* vdst = p.v8_cache + head * p.head_stride + kb * (KBLOCK8 * D);
-    constexpr int UNITS = KBLOCK8 * D / 16;
-    // K image: unit u = (piece, lane); lane = 32h + r holds key 32R + r of piece (R, dh, c)
-    for (int u = tid; u < UNITS; u += 256) {
-        const int key = 32 * ((u >> 6) / (2 * (D / 64))) + (u & 31);
+    const int R = int(hb & 1);
+    unsigned char* kdst = p.k8_cache + head * p.head_stride + hb * (HALF * D);                    // row block R's pieces side by side
+    unsigned char* vdst = p.v8_cache + head * p.head_stride + (hb >> 1) * (KBLOCK8 * D) + R * 1024;   // piece (db, R) at db * 2 KB
+    // K image: unit u = (piece, lane); lane = 32h + r holds key r of the half
+    for (int u = tid; u < HALF * D / 16; u += 256) {
+        const int key = u & 31;
         if (key >= k_lo && key < k_hi)
             *reinterpret_cast<u32x4*>(kdst + u * 16) = *reinterpret_cast<const u32x4*>(k_img + u * 16);
     }
-    // V image: unit u = (db, R, h, dd); byte 4g + j holds key 32R + 8g + 4h + j at feature 32db + dd.  A thread builds the
-    // units of FPT neighbouring features (so that half of the workgroup's threads take part).
-    constexpr int FPT = D / 32;
-    for (int uq = tid; uq < UNITS / FPT; uq += 256) {
-        const int u = uq * FPT, dd = u & 31, hh = (u >> 5) & 1, Rv = (u >> 6) & 1, db = u >> 7;
+    // V image: unit (db, h, dd); byte 4g + j holds key 8g + 4h + j of the half at feature 32db + dd.  A thread builds the units of
+    // two neighbouring features.
+    constexpr int FPT = 2;
+    for (int uq = tid; uq < HALF * D / 16 / FPT; uq += 256) {
+        const int u = uq * FPT, dd = u & 31, hh = (u >> 5) & 1, db = u >> 6;
         const int d = 32 * db + dd;
-        const int first = 32 * Rv + 4 * hh;                     // keys first + 8g + j
+        const int first = 4 * hh;                               // keys first + 8g + j
+        unsigned char* dst = vdst + db * 2048 + (hh * 32 + dd) * 16;
         u32x4 o[FPT];                                           // [feature][g]
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             unsigned w[4];                                      // one key each, its features (rows outside: not used)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const unsigned char* at = v_rows + (first + 8 * g + j) * VROW + d;
-                w[j] = FPT == 4 ? *reinterpret_cast<const unsigned*>(at) : *reinterpret_cast<const unsigned short*>(at);
+                w[j] = *reinterpret_cast<const unsigned short*>(v_rows + (first + 8 * g + j) * VROW + d);
             }
             const unsigned a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), b = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
             o[0][g] = __builtin_amdgcn_perm(b, a, 0x05040100u);
             o[1][g] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-            if constexpr (FPT == 4) {
-                const unsigned c = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u), e = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
-                o[2][g] = __builtin_amdgcn_perm(e, c, 0x05040100u);
-                o[3][g] = __builtin_amdgcn_perm(e, c, 0x07060302u);
-            }
         }
         if (first >= k_lo && first + 28 <= k_hi) {
 #pragma unroll
-            for (int f = 0; f < FPT; ++f) *reinterpret_cast<u32x4*>(vdst + (u + f) * 16) = o[f];
+            for (int f = 0; f < FPT; ++f) *reinterpret_cast<u32x4*>(dst + f * 16) = o[f];
         } else {
 #pragma unroll
             for (int f = 0; f < FPT; ++f)
@@ -176,7 +174,7 @@ __global__ __launch_bounds__(256) void ll_append8_kernel(const AppendParams p) {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const int kk = first + 8 * g + j;
-                        if (kk >= k_lo && kk < k_hi) vdst[(u + f) * 16 + 4 * g + j] = (unsigned char)(o[f][g] >> (8 * j));
+                        if (kk >= k_lo && kk < k_hi) dst[f * 16 + 4 * g + j] = (unsigned char)(o[f][g] >> (8 * j));
                     }
         }
     }
@@ -186,7 +184,8 @@ hipError_t launch_append8(const AppendParams& p, hipStream_t s) {
     const int nseg = p.seg_begin[p.n_frames];
     if (nseg <= 0) return hipSuccess;
     if (p.n_frames > MAX_APPEND_FRAMES || p.rope.n_t > MAX_T_PAIRS) return hipErrorInvalidValue;
-    dim3 grid(nseg, p.H), block(256);
+    if (int64_t(nseg) * p.H > 0x7FFFFFFF) return hipErrorInvalidValue;
+    dim3 grid(unsigned(nseg) * unsigned(p.H)), block(256);
     if (p.D == 128) hipLaunchKernelGGL(ll_append8_kernel<128>, grid, block, 0, s, p);
     else if (p.D == 64) hipLaunchKernelGGL(ll_append8_kernel<64>, grid, block, 0, s, p);
     else return hipErrorInvalidValue;

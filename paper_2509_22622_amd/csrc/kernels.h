@@ -85,7 +85,7 @@ struct AppendParams {
     // kernels that turn the queries themselves (AttnParams::t_table).
     float2* t_table_out;
     int64_t slot[MAX_APPEND_FRAMES];                            // first token slot
-    int seg_begin[MAX_APPEND_FRAMES + 1];                       // prefix sum of kblock segments (32 or 64 slots)
+    int seg_begin[MAX_APPEND_FRAMES + 1];                       // prefix sum of segments (the part of a frame in 32 slots)
     // 8-bit cache (all null / unused for the bf16 cache): byte pointers, head_stride in bytes
     uint8_t* q8_out; uint8_t* k8_cache; uint8_t* v8_cache;
     float k_mul, v_mul;                                         // 2^-k_exp, 2^-v_exp (q_scale carries 2^k_exp)
