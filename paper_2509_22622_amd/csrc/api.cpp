@@ -341,7 +341,7 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
     });
     for (size_t base = 0, end; base < work.size(); base = end) {
         for (end = base + 1; end < work.size() && end - base < MAX_ATTN_CHUNKS && order[end].first == order[base].first;) ++end;
-        AttnParams p{};
+        AttnParams& p = L.params.emplace_back();
         p.out = static_cast<uint16_t*>(out);
         p.kblock = c->kb;
         if (c->fmt) {
@@ -391,7 +391,6 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
             for (int r = 0; r < ch.n_ranges; ++r) { ch.rs[r] = int(w.ranges[r].begin); ch.re[r] = int(w.ranges[r].end); }
         }
         p.n_chunks = m;
-        L.params.push_back(p);
     }
     return LL_OK;
 }

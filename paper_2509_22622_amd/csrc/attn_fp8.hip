@@ -772,7 +772,7 @@ __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_pe
                  "s"(ch.re[0]), "s"(ch.re[1]), "s"(ch.re[2]), "s"(ch.n_kblocks));
     asm volatile("" ::"s"(p.q8), "s"(p.k8_cache), "s"(p.v8_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_scale));
     const int xcd = blockIdx.x & 7;
-    int idx = blockIdx.x >> 3, head = -1, tile = 0, item = 0, part = 0;      // part: split, or slice of the merge
+    int idx = blockIdx.x >> 3, head = -1, tile = 0, ci = -1, item = 0, part = 0;      // part: split, or slice of the merge
     if (p.n_groups == 0) {
         const int per_head = p.n_tiles * p.per_tile, total = per_head * p.H;
         item = ((xcd * total + 7) >> 3) + idx;
@@ -785,21 +785,12 @@ __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_pe
             }
         }
     } else {
-        for (int g = p.xcd_first[xcd]; g < p.xcd_first[xcd + 1]; ++g) {
-            const int grp = p.xcd_group[g], c = grp % p.n_chunks;
-            const int tiles = (c + 1 < p.n_chunks ? p.chunk[c + 1].tile_begin : p.n_tiles) - p.chunk[c].tile_begin;
-            if (idx < tiles) {
-                head = grp / p.n_chunks;
-                tile = p.chunk[c].tile_begin + idx;
-                break;
-            }
-            idx -= tiles;
-        }
+        if (!attn_placed_tile(p, xcd, idx, head, ci, tile)) head = -1;
     }
     if (head < 0) return;
     if (p.n_chunks > 1) {
-        int ci = 0;
-        while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
+        if (ci < 0)
+            for (ci = 0; ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin;) ++ci;
         ch = p.chunk[ci];
     }
     int row0 = ch.q_begin + (tile - ch.tile_begin) * ROWS, vb = 0, ve = ch.n_kblocks, readers = 0;

@@ -451,6 +451,7 @@ AttnSplit attn_split(int variant, int H, int n_chunks, const int* rows, const in
         if (m.split[lg].step <= 0) continue;
         const int64_t tiles = tiles_of(lg);
         for (int splits = 2; splits <= MAX_SPLITS && tiles * splits <= SPLIT_SLOTS && (fp8 ? splits : splits << lg) <= most_kblocks; ++splits) {
+            if (m.around_split + m.merge + m.per_split * splits >= best_cost) break;         // (no cost of more splits is less)
             const double c = cost(lg, splits);
             if (c < best_cost) {
                 best_cost = c;
@@ -570,14 +571,16 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
             p.xcd_first[x] = uint16_t(n);
             int tiles = 0;
             for (const Group& g : per_xcd[x]) {
-                p.xcd_group[n++] = uint16_t(g.id);
                 tiles += g.tiles;
+                p.xcd_group[n++] = uint32_t(tiles) << 16 | uint32_t(g.id / p.n_chunks) << 8 | uint32_t(g.id % p.n_chunks);
             }
             most_tiles = std::max(most_tiles, tiles);
         }
         p.xcd_first[8] = uint16_t(n);
-        p.n_groups = n;
-        grid = 8 * most_tiles;
+        if (most_tiles < 65536) {                              // (the words' 16 bits)
+            p.n_groups = n;
+            grid = 8 * most_tiles;
+        }
     }
     static bool attr_set[64][6] = {};
     if (variant > 64) return hipErrorInvalidValue;

@@ -504,7 +504,8 @@ __global__ __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2: the workgroups that stream the same
     // head's K/V should share one.
     const int xcd = blockIdx.x & 7;
-    int idx = blockIdx.x >> 3, head = -1, tile = 0;
+    int head = -1, tile = 0, ci = -1;
+    const int idx = blockIdx.x >> 3;
     if (p.n_groups == 0) {                       // one contiguous run of (head, tile) items per XCD
         // Runs of equal length (to within one item): XCD x takes items [ceil(x total / 8), ceil((x + 1) total / 8)).
         // With 12 heads of 19 tiles the cuts fall on a head boundary every second XCD, and the 12 heads make 16
@@ -516,20 +517,11 @@ __global__ __launch_bounds__(SP_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
             tile = item % p.n_tiles;
         }
     } else {                                     // this XCD's list of (head, chunk) groups, longest tiles first
-        for (int g = p.xcd_first[xcd]; g < p.xcd_first[xcd + 1]; ++g) {
-            const int grp = p.xcd_group[g], c = grp % p.n_chunks;
-            const int tiles = (c + 1 < p.n_chunks ? p.chunk[c + 1].tile_begin : p.n_tiles) - p.chunk[c].tile_begin;
-            if (idx < tiles) {
-                head = grp / p.n_chunks;
-                tile = p.chunk[c].tile_begin + idx;
-                break;
-            }
-            idx -= tiles;
-        }
+        if (!attn_placed_tile(p, xcd, idx, head, ci, tile)) head = -1;
     }
     if (head < 0) return;                        // uniform over the workgroup
-    int ci = 0;
-    while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
+    if (ci < 0)
+        for (ci = 0; ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin;) ++ci;
     const AttnChunk& ch = p.chunk[ci];
     if (ch.sink_shift != 0) {                    // uniform over the workgroup
         if ((int)threadIdx.x < p.n_t) {

@@ -852,7 +852,8 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
                  "s"(ch.re[0]), "s"(ch.re[1]), "s"(ch.re[2]), "s"(ch.n_kblocks), "s"(ch.sink_shift), "s"(ch.t_row));
     asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_frag), "s"(p.t_table), "s"(p.row_cs), "s"(p.col_cs), "s"(p.splits), "s"(p.per_tile));
     const int xcd = blockIdx.x & 7;
-    int idx = blockIdx.x >> 3, head = -1, tile = 0;
+    int head = -1, tile = 0, ci = -1;
+    const int idx = blockIdx.x >> 3;
     S16Share sh = {0, 1, 0, 0};
     int slice = 0;
     if (p.n_groups == 0) {
@@ -868,21 +869,12 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
             }
         }
     } else {
-        for (int gi = p.xcd_first[xcd]; gi < p.xcd_first[xcd + 1]; ++gi) {
-            const int grp = p.xcd_group[gi], c = grp % p.n_chunks;
-            const int tiles = (c + 1 < p.n_chunks ? p.chunk[c + 1].tile_begin : p.n_tiles) - p.chunk[c].tile_begin;
-            if (idx < tiles) {
-                head = grp / p.n_chunks;
-                tile = p.chunk[c].tile_begin + idx;
-                break;
-            }
-            idx -= tiles;
-        }
+        if (!attn_placed_tile(p, xcd, idx, head, ci, tile)) head = -1;
     }
     if (head < 0) return;                        // uniform over the workgroup
     if (p.n_chunks > 1) {
-        int ci = 0;
-        while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
+        if (ci < 0)
+            for (ci = 0; ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin;) ++ci;
         ch = p.chunk[ci];
     }
     int row0 = ch.q_begin + (tile - ch.tile_begin) * (256 / G);

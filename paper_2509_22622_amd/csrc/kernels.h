@@ -22,7 +22,7 @@ namespace ll {
 constexpr int KBLOCK = 32;          // key slots per kblock
 constexpr int PAD_KBLOCKS = 8;      // readable padding after the last kblock of a head
 constexpr int MAX_RANGES = 3;
-constexpr int MAX_ATTN_CHUNKS = 16; // query chunks per attention launch
+constexpr int MAX_ATTN_CHUNKS = 24; // query chunks per attention launch
 constexpr int MAX_APPEND_FRAMES = 8;  // frames per cache-write launch (its argument block carries a rotary table per frame)
 constexpr int MAX_CHUNK_FRAMES = 32;  // largest chunk (ll_chunk_append splits longer runs of frames into several launches)
 constexpr int MAX_T_PAIRS = 24;       // frame-axis rotary pairs: 22 at head_dim 128, 12 at 64
@@ -144,7 +144,8 @@ struct AttnParams {
     // Placement on the 8 XCDs (filled in by launch_attn; workgroup b runs on XCD b % 8).  n_groups == 0: the
     // (head, tile) items are split into 8 contiguous runs.  Otherwise (launches of several chunks, whose tiles
     // differ in length) XCD x runs the (head, chunk) groups xcd_group[xcd_first[x] .. xcd_first[x + 1]) in that
-    // order, all tiles of a group on one XCD; group = head * n_chunks + chunk.
+    // order, all tiles of a group on one XCD; a group's word is end << 16 | head << 8 | chunk, end counting the XCD's tiles
+    // up to and with the group's.
     int n_groups;
     // 8-bit cache: E4M3 queries and cache (byte pointers, head_stride in bytes), factor 2^v_exp on the output
     const uint8_t* q8; const uint8_t* k8_cache; const uint8_t* v8_cache;
@@ -173,9 +174,33 @@ struct AttnParams {
     int P, grid_w;
     float q_scale;
     uint16_t xcd_first[9];
-    uint16_t xcd_group[MAX_XCD_GROUPS];
+    uint32_t xcd_group[MAX_XCD_GROUPS];
     AttnChunk chunk[MAX_ATTN_CHUNKS];
 };
+
+// Which group of its XCD's list a workgroup's tile belongs to, found by a wave with one load, an entry a lane, instead of a walk
+// along the groups of three scalar loads each, cold in the first round of workgroups.  us a re-prefill with the walk and so: 7
+// frames of 140 tokens x 16 x 128 in chunks of two 36.6 and 34.4, 7 of 232 x 10 x 64 (two layers) 69.1 and 66.2, 1560 tokens x 12
+// x 128 level.  (The walk along a launch's chunks where nothing is placed stays: over two to four chunks, whose scalar loads
+// share cache lines with the other arguments', it takes 0.3 us less than a vector load.)
+// (idx: the workgroup's number on its XCD; false past the end of the list)
+__device__ __forceinline__ bool attn_placed_tile(const AttnParams& p, int xcd, int idx, int& head, int& chunk, int& tile) {
+    const int lane = threadIdx.x & 63, first = p.xcd_first[xcd], n = p.xcd_first[xcd + 1] - first;
+    int passed = 0;                              // tiles of the groups looked at so far
+    for (int base = 0; base < n; base += 64) {
+        const unsigned word = p.xcd_group[first + min(base + lane, n - 1)];
+        const int k = __builtin_popcountll(__ballot(base + lane < n && idx >= int(word >> 16)));
+        if (k > 0) passed = int(unsigned(__builtin_amdgcn_readlane(int(word), k - 1)) >> 16);
+        if (k < 64 && base + k < n) {
+            const int group = __builtin_amdgcn_readlane(int(word), k);
+            head = (group >> 8) & 255;
+            chunk = group & 255;
+            tile = p.chunk[chunk].tile_begin + idx - passed;
+            return true;
+        }
+    }
+    return false;
+}
 
 struct ReadFrameParams {
     const uint16_t* k_cache; const uint16_t* v_cache; int64_t head_stride;
