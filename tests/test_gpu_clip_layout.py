@@ -44,3 +44,9 @@ def test_no_sink_no_context(head_dim):
     (5, 128, (13, 20), 3, 9), (1, 128, (5, 13), 3, 5), (9, 64, (9, 13), 2, 6)])
 def test_both_gradients_in_one_launch(heads, head_dim, grid, chunk, clip_frames):
     _check(5.0e-3, heads, head_dim, grid, chunk, 2, 4, 4, clip_frames)
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, clip_frames", [
+    (1, 128, (18, 10), 3, 8), (2, 128, (5, 13), 1, 20), (1, 64, (11, 30), 2, 5), (1, 128, (13, 20), 1, 24)])
+def test_a_small_clip_whose_chunks_split(heads, head_dim, grid, chunk, clip_frames):
+    _check(5.0e-3, heads, head_dim, grid, chunk, 3, 5, 5, clip_frames)

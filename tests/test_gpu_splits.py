@@ -290,3 +290,26 @@ def test_narrow_tiles_of_the_8_bit_cache(head_dim, heads, groups, grid, chunk, s
         cache.close()
         outs.append(out)
     assert torch.equal(_bits(outs[0][:, :heads].contiguous()), _bits(outs[1]))
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, sink, n_win", [(1, 128, (6, 42), 3, 2, 5), (3, 128, (10, 19), 1, 3, 20), (1, 64, (30, 52), 3, 3, 9)])
+def test_re_prefill_whose_chunks_all_split(heads, head_dim, grid, chunk, sink, n_win):
+    """Groups and splits chosen for the launch (up to 23 chunks); slots taken: the same within the roundings."""
+    case = {"kind": "prefill", "cache": "bf16", "layers": 1, "heads": heads, "head_dim": head_dim, "grid_h": grid[0], "grid_w": grid[1],
+            "chunk": chunk, "sink": sink, "window": n_win, "win_start": 24, "n_win": n_win, "q_std": 2.0}
+    P = grid[0] * grid[1]
+    assert B.attn_split(head_dim, heads, chunk * P, -(-(sink + n_win + chunk) * P // 32))[1] > 1
+    state = cases.prepare(case, 3)
+    out = cases.run(state)[0].clone()
+    torch.cuda.synchronize()
+    want = cases.exact(case, 3)[0]
+    assert _rel(out, want) <= 1e-2                   # logits of standard deviation 2: twice 5e-3
+    for first, n in ((0, 512), (1, 300)):
+        B.hold_split_slots(first, n, True)
+        try:
+            again = cases.run(state)[0].clone()
+            torch.cuda.synchronize()
+        finally:
+            B.hold_split_slots(first, n, False)
+        assert _rel(again, want) <= 1e-2
+    state["cache"].close()
