@@ -33,8 +33,8 @@ __device__ inline unsigned a8_pack4(float a, float b, float c, float d) {
     return unsigned(w);
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void ll_append8_kernel(const AppendParams p) {
+template <int D, int FRAMES>
+__global__ __launch_bounds__(256) void ll_append8_kernel(const AppendArgs<FRAMES> p) {
     constexpr int CH = D / 8;                 // 8-element chunks per (token, head) row
     constexpr int VROW = D + 16;              // padded LDS row of V bytes
     constexpr int HALF = KBLOCK8 / 2;
@@ -46,10 +46,10 @@ __global__ __launch_bounds__(256) void ll_append8_kernel(const AppendParams p) {
     const int tid = threadIdx.x;
     const int head = blockIdx.x % p.H;
     const int gseg = blockIdx.x / p.H;
-    int begin[MAX_APPEND_FRAMES];
-    int64_t slots[MAX_APPEND_FRAMES];
+    int begin[FRAMES];
+    int64_t slots[FRAMES];
 #pragma unroll
-    for (int i = 0; i < MAX_APPEND_FRAMES; ++i) {
+    for (int i = 0; i < FRAMES; ++i) {
         begin[i] = p.seg_begin[i];
         slots[i] = p.slot[i];
         asm volatile("" ::"s"(begin[i]), "s"(slots[i]));
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256) void ll_append8_kernel(const AppendParams p) {
     int fi = 0, begin_fi = 0;
     int64_t slot0 = slots[0];
 #pragma unroll
-    for (int i = 1; i < MAX_APPEND_FRAMES; ++i)
+    for (int i = 1; i < FRAMES; ++i)
         if (i < p.n_frames && gseg >= begin[i]) {
             fi = i;
             begin_fi = begin[i];
@@ -186,9 +186,16 @@ hipError_t launch_append8(const AppendParams& p, hipStream_t s) {
     if (p.n_frames > MAX_APPEND_FRAMES || p.rope.n_t > MAX_T_PAIRS) return hipErrorInvalidValue;
     if (int64_t(nseg) * p.H > 0x7FFFFFFF) return hipErrorInvalidValue;
     dim3 grid(unsigned(nseg) * unsigned(p.H)), block(256);
-    if (p.D == 128) hipLaunchKernelGGL(ll_append8_kernel<128>, grid, block, 0, s, p);
-    else if (p.D == 64) hipLaunchKernelGGL(ll_append8_kernel<64>, grid, block, 0, s, p);
-    else return hipErrorInvalidValue;
+    if (p.D != 128 && p.D != 64) return hipErrorInvalidValue;
+    if (p.n_frames <= FEW_APPEND_FRAMES) {
+        const auto few = few_frames(p);
+        if (p.D == 128) hipLaunchKernelGGL((ll_append8_kernel<128, FEW_APPEND_FRAMES>), grid, block, 0, s, few);
+        else hipLaunchKernelGGL((ll_append8_kernel<64, FEW_APPEND_FRAMES>), grid, block, 0, s, few);
+    } else {
+        const AppendArgs<MAX_APPEND_FRAMES>& all = p;
+        if (p.D == 128) hipLaunchKernelGGL((ll_append8_kernel<128, MAX_APPEND_FRAMES>), grid, block, 0, s, all);
+        else hipLaunchKernelGGL((ll_append8_kernel<64, MAX_APPEND_FRAMES>), grid, block, 0, s, all);
+    }
     return hipGetLastError();
 }
 

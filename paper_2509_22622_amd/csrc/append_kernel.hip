@@ -37,8 +37,8 @@ __device__ inline unsigned short f32_to_bf16(float f) {
     return __builtin_bit_cast(unsigned, r) & 0xFFFFu;
 }
 
-template <int D>
-__global__ __launch_bounds__(256) void ll_append_kernel(const AppendParams p) {
+template <int D, int FRAMES>
+__global__ __launch_bounds__(256) void ll_append_kernel(const AppendArgs<FRAMES> p) {
     constexpr int CH = D / 8;                 // 16-byte chunks per (token, head) row
     constexpr int VROW = D + 8;               // padded LDS row (elements)
     constexpr int ITEMS = 32 * CH / 256;      // (token, chunk) items per thread
@@ -51,10 +51,10 @@ __global__ __launch_bounds__(256) void ll_append_kernel(const AppendParams p) {
     const int gseg = blockIdx.x / p.H;
     // which frame, which segment: the tables and pointers are fetched in one go (they lie in several cold cache lines)
     // and searched in registers, instead of one scalar load waiting for another
-    int begin[MAX_APPEND_FRAMES];
-    int64_t slots[MAX_APPEND_FRAMES];
+    int begin[FRAMES];
+    int64_t slots[FRAMES];
 #pragma unroll
-    for (int i = 0; i < MAX_APPEND_FRAMES; ++i) {
+    for (int i = 0; i < FRAMES; ++i) {
         begin[i] = p.seg_begin[i];
         slots[i] = p.slot[i];
         asm volatile("" ::"s"(begin[i]), "s"(slots[i]));
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void ll_append_kernel(const AppendParams p) {
     int fi = 0, begin_fi = 0;
     int64_t slot0 = slots[0];
 #pragma unroll
-    for (int i = 1; i < MAX_APPEND_FRAMES; ++i)
+    for (int i = 1; i < FRAMES; ++i)
         if (i < p.n_frames && gseg >= begin[i]) {
             fi = i;
             begin_fi = begin[i];
@@ -202,9 +202,16 @@ hipError_t launch_append(const AppendParams& p, hipStream_t s) {
     if (p.n_frames > MAX_APPEND_FRAMES || (p.identity == 0 && p.rope.n_t > MAX_T_PAIRS)) return hipErrorInvalidValue;
     if (int64_t(nseg) * p.H > 0x7FFFFFFF) return hipErrorInvalidValue;
     dim3 grid(unsigned(nseg) * unsigned(p.H)), block(256);
-    if (p.D == 128) hipLaunchKernelGGL(ll_append_kernel<128>, grid, block, 0, s, p);
-    else if (p.D == 64) hipLaunchKernelGGL(ll_append_kernel<64>, grid, block, 0, s, p);
-    else return hipErrorInvalidValue;
+    if (p.D != 128 && p.D != 64) return hipErrorInvalidValue;
+    if (p.n_frames <= FEW_APPEND_FRAMES) {
+        const auto few = few_frames(p);
+        if (p.D == 128) hipLaunchKernelGGL((ll_append_kernel<128, FEW_APPEND_FRAMES>), grid, block, 0, s, few);
+        else hipLaunchKernelGGL((ll_append_kernel<64, FEW_APPEND_FRAMES>), grid, block, 0, s, few);
+    } else {
+        const AppendArgs<MAX_APPEND_FRAMES>& all = p;
+        if (p.D == 128) hipLaunchKernelGGL((ll_append_kernel<128, MAX_APPEND_FRAMES>), grid, block, 0, s, all);
+        else hipLaunchKernelGGL((ll_append_kernel<64, MAX_APPEND_FRAMES>), grid, block, 0, s, all);
+    }
     return hipGetLastError();
 }
 

@@ -23,7 +23,8 @@ constexpr int KBLOCK = 32;          // key slots per kblock
 constexpr int PAD_KBLOCKS = 8;      // readable padding after the last kblock of a head
 constexpr int MAX_RANGES = 3;
 constexpr int MAX_ATTN_CHUNKS = 24; // query chunks per attention launch
-constexpr int MAX_APPEND_FRAMES = 8;  // frames per cache-write launch (its argument block carries a rotary table per frame)
+constexpr int MAX_APPEND_FRAMES = 16; // frames per cache-write launch (its argument block carries a rotary table per frame)
+constexpr int FEW_APPEND_FRAMES = 8;  // up to here the launch takes the shorter argument block
 constexpr int MAX_CHUNK_FRAMES = 32;  // largest chunk (ll_chunk_append splits longer runs of frames into several launches)
 constexpr int MAX_T_PAIRS = 24;       // frame-axis rotary pairs: 22 at head_dim 128, 12 at 64
 constexpr int MAX_XCD_GROUPS = 256; // (head, chunk) groups an attention launch can place on the XCDs one by one
@@ -66,7 +67,7 @@ struct RopeTables {            // device pointers into the cache buffer's tail
     int n_t, n_h, n_w;
 };
 
-struct AppendParams {
+struct AppendHead {
     const uint16_t* q; const uint16_t* k; const uint16_t* v;   // [n_frames*P, H, D]; q null (bf16 cache only): K, V only
     uint16_t* q_out;                                            // same shape; rotated q times q_scale
     float q_scale;                                              // log2(e) / sqrt(D), folded into q_out
@@ -75,21 +76,40 @@ struct AppendParams {
     RopeTables rope;
     int H, D, P, grid_w;
     int n_frames;
-    int64_t frame[MAX_APPEND_FRAMES];                           // absolute frame index (host side: input of set_frame_rotation)
-    // (cos, sin) of frame * frequency for every frame-axis pair of every frame, computed on the host in double
-    // (set_frame_rotation): the kernels run no trigonometry.  identity != 0: no rotary step at all (every pair
-    // passes unchanged; q, where given, only takes q_scale) - the tables are not read then.
-    float2 t_cs[MAX_APPEND_FRAMES][MAX_T_PAIRS];
+    // no rotary step at all (every pair passes unchanged; q, where given, only takes q_scale): the tables are not read then
     int identity;
     // When set (bf16 cache): t_cs[0 .. n_frames) is also stored there, [n_frames][MAX_T_PAIRS], for the attention
     // kernels that turn the queries themselves (AttnParams::t_table).
     float2* t_table_out;
-    int64_t slot[MAX_APPEND_FRAMES];                            // first token slot
-    int seg_begin[MAX_APPEND_FRAMES + 1];                       // prefix sum of segments (the part of a frame in 32 slots)
     // 8-bit cache (all null / unused for the bf16 cache): byte pointers, head_stride in bytes
     uint8_t* q8_out; uint8_t* k8_cache; uint8_t* v8_cache;
     float k_mul, v_mul;                                         // 2^-k_exp, 2^-v_exp (q_scale carries 2^k_exp)
 };
+// The kernels' arguments for up to N frames.  A re-prefill of 9 to 16 frames is one launch, not two; a chunk's few frames keep
+// the block of 8, 1.6 KB shorter and half the tables for a workgroup to fetch first.  us a call: 10 frames of 299 tokens x 5 x
+// 128 with an 8-bit cache 52.7 -> 46.4, 9 of 126 x 2 x 128 31.0 -> 26.7, three layers' 10 of 132 x 13 x 128 128.5 -> 117.0.
+template <int N>
+struct AppendArgs : AppendHead {
+    // (cos, sin) of frame * frequency for every frame-axis pair of every frame, computed on the host in double
+    // (set_frame_rotation): the kernels run no trigonometry.
+    float2 t_cs[N][MAX_T_PAIRS];
+    int64_t slot[N];                                            // first token slot
+    int seg_begin[N + 1];                                       // prefix sum of segments (the part of a frame in 32 slots)
+};
+struct AppendParams : AppendArgs<MAX_APPEND_FRAMES> {
+    int64_t frame[MAX_APPEND_FRAMES];                           // absolute frame index (input of set_frame_rotation)
+};
+inline AppendArgs<FEW_APPEND_FRAMES> few_frames(const AppendParams& p) {      // p.n_frames <= FEW_APPEND_FRAMES
+    AppendArgs<FEW_APPEND_FRAMES> few;
+    static_cast<AppendHead&>(few) = p;
+    for (int i = 0; i < FEW_APPEND_FRAMES; ++i) {
+        for (int j = 0; j < MAX_T_PAIRS; ++j) few.t_cs[i][j] = p.t_cs[i][j];
+        few.slot[i] = p.slot[i];
+        few.seg_begin[i] = p.seg_begin[i];
+    }
+    few.seg_begin[FEW_APPEND_FRAMES] = p.seg_begin[FEW_APPEND_FRAMES];
+    return few;
+}
 
 // Fill p.t_cs from p.frame[0 .. n_frames) and the host copy of the frame-axis frequencies (p.rope.n_t of them).
 inline void set_frame_rotation(AppendParams& p, const double* inv_freq_t_host) {
