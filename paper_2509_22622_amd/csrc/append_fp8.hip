@@ -15,7 +15,7 @@
 // one go and every load is issued before the first value is touched; the V image is built two features at a time from
 // one LDS read per key and byte permutes.  Half a kblock and not a whole one: two (head_dim 64: one) items a thread instead of
 // four halve the chain of conversions between the round trips.  us with whole and half kblocks: 4680 rows x 12 x 128 19.4 and
-// 16.7 (64.8 MB: 3.9 TB/s, a copy here takes 13), 2392 rows x 5 x 128 9.4 and 8.5, 598 rows 8.2 and 6.1.
+// 16.7 (64.8 MB: 3.9 TB/s, a copy here takes 13), 2392 rows x 5 x 128 9.4 and 8.5, 598 rows 8.2 and 6.1 (all 2990 in one launch now: 10.2).
 #include "kernels.h"
 
 namespace ll {
