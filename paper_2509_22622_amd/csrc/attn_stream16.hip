@@ -883,6 +883,7 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         const int slice_rows = 16 * p.slice_blocks, rows = min(256 / G, ch.q_end - row0);
         if (p.merge) {
             // where a partial result is missing, the slice is computed here whole, as a tile of its own
+            if (splits == 1) return;             // one share: its workgroup has stored the finished rows (maybe over the queries)
             const int first = slice * p.slice_blocks;
             row0 += slice * slice_rows;
             if (slice * slice_rows >= rows) return;

@@ -96,6 +96,42 @@ def test_a_video_from_its_first_frame(shape):
         state["cache"].close()
 
 
+@pytest.mark.parametrize("shape", [SHAPES[0], SHAPES[1], SHAPES[6]])
+def test_first_chunks_written_over_their_queries(shape):
+    """The first chunks have fewer than two kblocks a key group: one share, whose workgroup stores the finished rows.  With the output
+    in place of the queries the merge must not compute them again."""
+    *geo, (groups, _) = shape
+    first = -(-geo[6] * geo[2][0] * geo[2][1] // 32)
+    assert first // groups <= 1
+    case = _case(*geo, video_chunks=1 + -(-(geo[4] + geo[5] + 4) // geo[3]))
+    state = cases.prepare(case, 13)
+    want = cases.run(state)
+    exact = cases.exact(case, 13)
+    cache = state["cache"]
+    cache.reset()
+    for (layer, start, q, k, v, q_out, _), apart, ref in zip(state["passes"], want, exact):
+        cache.chunk_append(layer, start, case["frames"], q, k, v, q_out)
+        cache.sink_window_attn(layer, q_out, q_out)
+        assert torch.equal(_bits(q_out), _bits(apart)), start
+        assert _rel(q_out, ref) <= 5e-3 * case["q_std"], start
+    cache.close()
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, sink, window, n_win", [
+    (2, 128, (14, 14), 1, 3, 8, 6), (1, 128, (8, 19), 1, 2, 16, 8), (1, 128, (4, 19), 2, 4, 24, 22), (1, 128, (6, 42), 3, 2, 5, 5)])
+def test_split_re_prefill_with_a_re_indexed_sink(heads, head_dim, grid, chunk, sink, window, n_win):
+    """The rotated queries wait in `out`; the first chunks have fewer than two kblocks a key group, so their tiles do not split."""
+    P = grid[0] * grid[1]
+    assert B.attn_split(head_dim, heads, chunk * P, -(-(sink + window + chunk) * P // 32))[1] > 1
+    case = {"kind": "prefill", "cache": "bf16", "layers": 1, "heads": heads, "head_dim": head_dim, "grid_h": grid[0], "grid_w": grid[1],
+            "chunk": chunk, "sink": sink, "window": window, "win_start": sink + window + 9, "n_win": n_win, "q_std": 2.0, "sink_relative": True}
+    state = cases.prepare(case, 3)
+    out = cases.run(state)[0]
+    for i, (a, b) in enumerate(zip(out.split(P), cases.exact(case, 3)[0].split(P))):
+        assert _rel(a, b) <= 7e-3 * case["q_std"], i     # a re-indexed sink's queries are rounded once more
+    state["cache"].close()
+
+
 def _cached(cache, P, heads, D):
     """Rotated keys and values of the live frames, oldest first."""
     kv = [tuple(torch.empty((P, heads, D), dtype=torch.bfloat16, device="cuda") for _ in range(2)) for _ in cache.live_frames(0)]
