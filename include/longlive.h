@@ -298,6 +298,7 @@ ll_status ll_clip_chunk_key_ranges(const ll_clip* clip, int chunk, int64_t* rang
 
 /* Backward of the handle's last forward.  dout: device bf16 [n_clip * P, H, D]; dq, dk, dv: device bf16
  * [n_clip * P, H, D], gradients for the clip's own frames (context and sink frames outside the clip are constants).
+ * dout is copied into the handle's buffer before a gradient is written: any one of dq, dk and dv may lie over it.
  * LL_ERR_STATE without a forward pass. */
 ll_status ll_clip_backward(ll_clip* clip, const void* dout, void* dq, void* dk, void* dv, void* stream);
 

@@ -291,7 +291,8 @@ ll_status ll_clip_backward(ll_clip* clip, const void* dout, void* dq, void* dk, 
         q_groups.push_back(g);
     }
     BwdParams dq_p{};
-    dq_p.q = qrot; dq_p.dout = dO;
+    dq_p.q = qrot;
+    dq_p.c_k2 = clip_u16(c, c->o_cd); dq_p.hc_k2 = c->hs_clip;                  // dO of the columns
     dq_p.lse = clip_f32(c, c->o_lse); dq_p.delta = clip_f32(c, c->o_delta); dq_p.row_stride = c->row_stride;
     dq_p.s_k1 = clip_u16(c, c->o_a); dq_p.hs_k1 = c->hs_all;                    // K'   K-style
     dq_p.s_k2 = clip_u16(c, c->o_b); dq_p.hs_k2 = c->hs_all;                    // V    K-style

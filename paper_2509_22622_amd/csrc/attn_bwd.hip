@@ -167,14 +167,10 @@ __device__ __forceinline__ void bw_dq(const BwdParams& p, int head, int tile) {
     const int row = min(q0 + col, g.c_end - 1);
 
     bf16x8 qf[KS], dof[KS];
-    {
-        const int64_t off = (int64_t(row) * p.H + head) * D + half * 8;
+    const int64_t off = (int64_t(row) * p.H + head) * D + half * 8;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            qf[ks] = *reinterpret_cast<const bf16x8*>(p.q + off + ks * 16);
-            dof[ks] = *reinterpret_cast<const bf16x8*>(p.dout + off + ks * 16);
-        }
-    }
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(p.q + off + ks * 16);
+    bw_load_kstyle_row<D>(p.c_k2 + head * p.hc_k2, row, half, dof);
     const float lse = p.lse[int64_t(head) * p.row_stride + row];
     const float delta = p.delta[int64_t(head) * p.row_stride + row];
 

@@ -239,13 +239,14 @@ struct BwdGroup {                // column tiles that share one set of streamed 
     int rs[2], re[2];            // streamed rows: key token slots (dQ kernel), query rows (dK/dV kernel: one range)
 };
 struct BwdParams {
-    const uint16_t* q; const uint16_t* dout;            // dQ kernel: rotated, scaled queries and dO, [rows, H, D]
+    const uint16_t* q;                                  // dQ kernel: rotated, scaled queries, [rows, H, D]
     const float* lse; const float* delta;               // [H][row_stride]
     int64_t row_stride;
     // streamed fragment regions (head 0; element strides between heads): two K-style, two V^T-style
     const uint16_t* s_k1; const uint16_t* s_k2; const uint16_t* s_t1; const uint16_t* s_t2;
     int64_t hs_k1, hs_k2, hs_t1, hs_t2;
-    // dK/dV kernel: K-style regions holding the columns' own K' and V rows, and the token slot of clip token 0
+    // K-style regions holding the columns' own rows: K' and V, and the token slot of clip token 0 (dK/dV kernel); dO in c_k2,
+    // row 0 at slot 0 (dQ kernel: the caller's dO is not read here, dV of the same launch may be written over it)
     const uint16_t* c_k1; const uint16_t* c_k2;
     int64_t hc_k1, hc_k2, col_slot0;
     float* g1;                   // fp32 [rows, H, D]: Gq (dQ kernel) or Gk (dK/dV kernel)

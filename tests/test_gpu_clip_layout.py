@@ -50,3 +50,23 @@ def test_both_gradients_in_one_launch(heads, head_dim, grid, chunk, clip_frames)
     (1, 128, (18, 10), 3, 8), (2, 128, (5, 13), 1, 20), (1, 64, (11, 30), 2, 5), (1, 128, (13, 20), 1, 24)])
 def test_a_small_clip_whose_chunks_split(heads, head_dim, grid, chunk, clip_frames):
     _check(5.0e-3, heads, head_dim, grid, chunk, 3, 5, 5, clip_frames)
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, clip_frames", [
+    (16, 128, (13, 20), 1, 9), (2, 128, (5, 13), 3, 5), (12, 64, (13, 20), 2, 8), (2, 64, (2, 9), 1, 33)])
+def test_gradients_written_over_dout(heads, head_dim, grid, chunk, clip_frames):
+    """Each gradient in place of dout: the bits of tensors apart.  (Both kinds of tiles run in one launch, or, past 32 chunks, in
+    several: none may read dout, which dV is written over.)"""
+    case = {"kind": "clip", "heads": heads, "head_dim": head_dim, "grid_h": grid[0], "grid_w": grid[1], "chunk": chunk, "sink": 2,
+            "window": 4, "ctx_start": 9, "n_ctx": 4, "clip_frames": clip_frames, "q_std": 1.0}
+    state = cases.prepare(case, 6)
+    want = [x.clone() for x in cases.run(state)[1:]]
+    dout = state["in"][3]
+    for i in range(3):
+        got = [torch.full_like(dout, 7.0) for _ in range(3)]
+        got[i] = dout.clone()
+        state["clip"].backward(got[i], *got)
+        torch.cuda.synchronize()
+        for name, a, b in zip(("dq", "dk", "dv"), got, want):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (name, i)
+    state["clip"].close()
