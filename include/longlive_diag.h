@@ -31,10 +31,13 @@ ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* r
  * all keys of the split).  No GPU needed. */
 ll_status ll_attn_split(int head_dim, int fp8, int heads, int rows, int kblocks, int* groups, int* splits);
 /* The partial results of split tiles wait for their merge in 512 slots that all calls on a GPU share; a workgroup that finds
- * no slot free leaves its tile to the merge, which then computes it whole.  This call takes the free ones among slots
- * [first, first + n) out of use on the current device (hold != 0), or gives back those it took (hold == 0), so that
- * this path can be tested.  Waits for the device before and after. */
+ * no slot free leaves its tile to the merge, where one workgroup then computes the tile's shares one after another, with the
+ * same result.  This call takes the free ones among slots [first, first + n) out of use on the current device (hold != 0), or
+ * gives back those it took (hold == 0), so that this path can be tested.  Waits for the device before and after. */
 ll_status ll_hold_split_slots(int first, int n, int hold);
+/* How many of these slots, and of the spaces in which merges compute such tiles, are taken on the current device once it is idle
+ * (waits for it): 0, but for slots held by the call above. */
+ll_status ll_split_slots_taken(int* taken);
 
 /* Diagnostic, not part of the method: the dense bf16 MFMA rate this GPU sustains when every wave issues nothing
  * but 32x32x16 MFMAs (two waves per SIMD, `workgroups` workgroups of 8 waves, iters * 16 MFMAs per wave), and the

@@ -56,6 +56,7 @@ SIGNATURES = {
     "ll_attn_key_groups": (_i, [_i] * 3 + [C.POINTER(_i)] * 3),
     "ll_attn_split": (_i, [_i] * 5 + [C.POINTER(_i)] * 2),
     "ll_hold_split_slots": (_i, [_i] * 3),
+    "ll_split_slots_taken": (_i, [C.POINTER(_i)]),
     "ll_probe_mfma_rate": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "ll_probe_mfma_mix": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "ll_status_string": (C.c_char_p, [_i]),
@@ -128,6 +129,13 @@ def attn_split(head_dim, heads, rows, kblocks, kv_format="bf16"):
 def hold_split_slots(first: int, n: int, hold: bool) -> None:
     """Take slots for partial results out of use, or give them back (a test instrument; synchronises)."""
     _check(lib().ll_hold_split_slots(first, n, int(hold)))
+
+
+def split_slots_taken() -> int:
+    """Places of the pool of partial results that are taken while no call is at work (a test instrument; synchronises)."""
+    taken = C.c_int()
+    _check(lib().ll_split_slots_taken(C.byref(taken)))
+    return taken.value
 
 
 def probe_mfma_rate(workgroups: int = 256, iters: int = 20000, random_operands: bool = True):

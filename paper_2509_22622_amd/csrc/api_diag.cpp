@@ -53,6 +53,18 @@ ll_status ll_hold_split_slots(int first, int n, int hold) {
     return e == hipSuccess ? LL_OK : hip_fail(e, "writing the slots' owners");
 }
 
+ll_status ll_split_slots_taken(int* taken) {
+    if (!taken) return fail(LL_ERR_INVALID_ARG, "null pointer");
+    SplitPool* pool = nullptr;
+    std::vector<unsigned long long> owner(SPLIT_SLOTS + SPLIT_SPACES);
+    hipError_t e = split_pool_address(&pool);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = hipMemcpy(owner.data(), pool->owner, owner.size() * sizeof(owner[0]), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "reading the slots' owners");
+    *taken = int(owner.size() - std::count(owner.begin(), owner.end(), 0ull));
+    return LL_OK;
+}
+
 ll_status ll_probe_mfma_rate(void* dev_scratch, size_t scratch_bytes, int workgroups, int iters, int random_operands,
                              double* tflops, double* clock_ghz, void* stream) {
     return ll_probe_mfma_mix(dev_scratch, scratch_bytes, workgroups, iters, random_operands, 0, 1, tflops, clock_ghz, stream);

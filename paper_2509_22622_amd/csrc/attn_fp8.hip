@@ -704,8 +704,16 @@ __device__ __forceinline__ void f8_store_out(const AttnParams& p, int head, int 
     }
 }
 
-// The partial results of a tile's splits (split.h), for the 32-row blocks [first, first + n_blocks) of the tile: weights
-// 2^(m_s - max m), one division by the weighted sum of the row sums.  False (for the whole workgroup) if some split found no room
+// 8 dg + 4 half + j, j = 0..3, of a row's unnormalised output with row sum l
+template <int D>
+__device__ __forceinline__ void f8_store_unit(const AttnParams& p, int head, int row, int dg, int half, const f32x4& o, float l) {
+    const float inv = p.out_scale / l;
+    const u32x2 w = {f8_pack_bf16(o[0] * inv, o[1] * inv), f8_pack_bf16(o[2] * inv, o[3] * inv)};
+    *reinterpret_cast<u32x2*>(p.out + (int64_t(row) * p.H + head) * D + dg * 8 + half * 4) = w;
+}
+
+// The partial results of a tile's splits (split.h), for the 32-row blocks [first, first + n_blocks) of the tile, added up in
+// order; one division by the row sum.  False (for the whole workgroup, and for all of the tile's) if some split found no room
 // for its partial result: nothing is written then.
 template <int D, int NW>
 __device__ __forceinline__ bool f8_merge(const AttnParams& p, const AttnChunk& ch, int head, int tile, int splits, int row0, int first,
@@ -716,14 +724,12 @@ __device__ __forceinline__ bool f8_merge(const AttnParams& p, const AttnChunk& c
     __syncthreads();
     bool all = true;
     for (int s = 0; s < splits; ++s) all = all && slots[s] >= 0;
+    all = __builtin_amdgcn_readfirstlane(all);
     if (all) {
         for (int u = tid >> 6; u < n_blocks * UNITS; u += NW) {
             const int blk = first + u / UNITS, dg = u % UNITS, row = row0 + (blk - first) * 32 + col;
             float m = -INFINITY, l = 0.f;
             f32x4 o = {0.f, 0.f, 0.f, 0.f};
-            for (int s = 0; s < splits; s += 4)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) m = fmaxf(m, p.pool->ml[slots[min(s + e, splits - 1)]][blk * 32 + col].x);
             for (int s0 = 0; s0 < splits; s0 += 4) {
                 float2 w[4];
                 f32x4 x[4];
@@ -736,21 +742,94 @@ __device__ __forceinline__ bool f8_merge(const AttnParams& p, const AttnChunk& c
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (s0 + e < splits) {
-                        const float a = __builtin_amdgcn_exp2f(w[e].x - m);
-                        l += w[e].y * a;
-                        o += x[e] * a;
+                        float a, b;
+                        split_weights(m, l, w[e].x, w[e].y, a, b);
+                        o = split_add(o, a, x[e], b);
                     }
             }
-            if (row < ch.q_end) {
-                const float inv = p.out_scale / l;
-                const u32x2 w = {f8_pack_bf16(o[0] * inv, o[1] * inv), f8_pack_bf16(o[2] * inv, o[3] * inv)};
-                *reinterpret_cast<u32x2*>(p.out + (int64_t(row) * p.H + head) * D + dg * 8 + half * 4) = w;
-            }
+            if (row < ch.q_end) f8_store_unit<D>(p, head, row, dg, half, o, l);
         }
     }
     __syncthreads();                             // every read of the partial results has returned
     if (tid < splits && slots[tid] >= 0) split_release(p.pool, slots[tid]);
     return all;
+}
+
+// One share of a tile whose keys are split, the workgroup's own or (space >= 0, the merge without some partial result) one
+// of all; true if another one is to follow.
+template <int D, int NW>
+__device__ __forceinline__ bool f8_split_share(const AttnParams& p, char* lds, int* slots, int& share, int& space, float& m_sum, float& l_sum) {
+    constexpr int ROWS = 32 * NW;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    // (the arguments of a launch of one chunk in one go, as in attn_stream16.hip)
+    AttnChunk ch = p.chunk[0];
+    asm volatile("" ::"s"(ch.q_begin), "s"(ch.q_end), "s"(ch.tile_begin), "s"(ch.n_ranges), "s"(ch.rs[0]), "s"(ch.rs[1]), "s"(ch.rs[2]),
+                 "s"(ch.re[0]), "s"(ch.re[1]), "s"(ch.re[2]), "s"(ch.n_kblocks));
+    asm volatile("" ::"s"(p.q8), "s"(p.k8_cache), "s"(p.v8_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_scale));
+    const SplitPlace at_place = split_place(p);
+    const int item = at_place.item, head = at_place.head, part = at_place.part, tile = at_place.tile;      // part: split, or slice of the merge
+    if (item < 0) return false;
+    if (p.n_chunks > 1) {
+        int ci = 0;
+        while (ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin) ++ci;
+        ch = p.chunk[ci];
+    }
+    const int row0 = ch.q_begin + (tile - ch.tile_begin) * ROWS;
+    const int splits = min(p.splits, ch.n_kblocks);              // no more than the chunk has keys for
+    const int slice_rows = 16 * p.slice_blocks, rows = min(ROWS, ch.q_end - row0);
+    if (space < 0) {                                             // uniform, as all of this: the workgroup begins
+        share = part;
+        if (p.merge) {
+            const int first = part * slice_rows / 32;
+            if (part * slice_rows >= rows) return false;
+            if (f8_merge<D, NW>(p, ch, head, tile, splits, row0 + part * slice_rows, first, min(slice_rows / 32, NW - first), slots)) return false;
+            // a partial result is missing: the first slice's workgroup takes the tile's shares one after another
+            if (part > 0) return false;
+            if (threadIdx.x == 0) slots[0] = split_take_space(p.pool, blockIdx.x);
+            __syncthreads();
+            space = __builtin_amdgcn_readfirstlane(slots[0]);
+        } else if (part >= splits) {
+            return false;
+        } else {
+            // a workgroup that finds no slot leaves at once: what it would compute is the merge's then
+            if (threadIdx.x == 0) slots[0] = split_claim(p.pool, item, p.token, (rows + slice_rows - 1) / slice_rows);
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(slots[0]) < 0) return false;
+        }
+    }
+    const int to = space < 0 ? __builtin_amdgcn_readfirstlane(slots[0]) : space;
+    const int row_block = NW == 8 ? ((wave & 3) << 1) | (wave >> 2) : wave;       // (waves w and w + 4 share a SIMD)
+    const int q0 = row0 + row_block * 32;
+    const int vb = ch.n_kblocks * share / splits, ve = ch.n_kblocks * (share + 1) / splits;
+    F8State<D> st;
+    if (q0 < ch.q_end) f8_segment_sp<D, false, true, NW>(p, ch, head, q0, vb, ve, lds, st);
+    else f8_segment_loads_only<D, NW>(p, ch, head, vb, ve, lds);
+    if (q0 < ch.q_end) {
+        const float l = st.l + __shfl_xor(st.l, 32);
+        float a = 0.f, b = 0.f;
+        if (space >= 0) split_weights(m_sum, l_sum, st.m, l, a, b);              // uniform
+        else if (lane < 32) p.pool->ml[to][row_block * 32 + col] = make_float2(st.m, l);
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                f32x4 o = {st.o[db][4 * g], st.o[db][4 * g + 1], st.o[db][4 * g + 2], st.o[db][4 * g + 3]};
+                f32x4* at = reinterpret_cast<f32x4*>(p.pool->o[to]) + (row_block * (D / 8) + db * 4 + g) * 64 + lane;
+                if (space >= 0) {
+                    const f32x4 before = share > 0 ? *at : f32x4{0.f, 0.f, 0.f, 0.f};
+                    o = split_add(before, a, o, b);
+                }
+                if (space < 0 || share + 1 < splits) *at = o;
+                else if (q0 + col < ch.q_end) f8_store_unit<D>(p, head, q0 + col, db * 4 + g, half, o, l_sum);
+                asm volatile("" ::: "memory");                   // one unit's sums in registers at a time
+            }
+    }
+    if (space < 0) return false;
+    __syncthreads();                                             // every read of the sums has returned
+    if (++share < splits) return true;
+    if (threadIdx.x == 0) split_leave_space(p.pool, space);
+    return false;
 }
 
 // ---- one workgroup per (head, query tile), or several where the tile's keys are split; placement on the XCDs as in attn_stream.hip
@@ -763,8 +842,17 @@ constexpr int f8_waves(int mode) { return mode == 5 ? 2 : mode == 4 || mode == 6
 template <int D, int MODE>
 __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_fp8_kernel(const AttnParams p) {
     constexpr int NW = f8_waves(MODE), ROWS = 32 * NW;
-    constexpr bool SPLIT = MODE == 3 || MODE == 6;
     extern __shared__ __attribute__((aligned(16))) char lds[];
+    if constexpr (MODE == 3 || MODE == 6) {
+        __shared__ int slots[MAX_SPLITS];
+        int share = 0, space = -1;
+        float m_sum = -INFINITY, l_sum = 0.f;                    // over the shares
+        while (__builtin_amdgcn_readfirstlane(f8_split_share<D, NW>(attn_params_again(), lds, slots, share, space, m_sum, l_sum))) {
+            share = __builtin_amdgcn_readfirstlane(share);           // (uniform, all of it)
+            space = __builtin_amdgcn_readfirstlane(space);
+        }
+        return;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // (the arguments of a launch of one chunk in one go, as in attn_stream16.hip)
     AttnChunk ch = p.chunk[0];
@@ -772,17 +860,13 @@ __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_pe
                  "s"(ch.re[0]), "s"(ch.re[1]), "s"(ch.re[2]), "s"(ch.n_kblocks));
     asm volatile("" ::"s"(p.q8), "s"(p.k8_cache), "s"(p.v8_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_scale));
     const int xcd = blockIdx.x & 7;
-    int idx = blockIdx.x >> 3, head = -1, tile = 0, ci = -1, item = 0, part = 0;      // part: split, or slice of the merge
+    int idx = blockIdx.x >> 3, head = -1, tile = 0, ci = -1;
     if (p.n_groups == 0) {
-        const int per_head = p.n_tiles * p.per_tile, total = per_head * p.H;
-        item = ((xcd * total + 7) >> 3) + idx;
+        const int total = p.n_tiles * p.H;
+        const int item = ((xcd * total + 7) >> 3) + idx;
         if (item < (((xcd + 1) * total + 7) >> 3)) {
-            head = item / per_head;
-            tile = item - head * per_head;
-            if (SPLIT) {                         // a split's tiles side by side: they share its keys
-                part = tile / p.n_tiles;
-                tile -= part * p.n_tiles;
-            }
+            head = item / p.n_tiles;
+            tile = item % p.n_tiles;
         }
     } else {
         if (!attn_placed_tile(p, xcd, idx, head, ci, tile)) head = -1;
@@ -793,57 +877,20 @@ __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_pe
             for (ci = 0; ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin;) ++ci;
         ch = p.chunk[ci];
     }
-    int row0 = ch.q_begin + (tile - ch.tile_begin) * ROWS, vb = 0, ve = ch.n_kblocks, readers = 0;
-    if constexpr (SPLIT) {
-        __shared__ int slots[MAX_SPLITS];
-        const int splits = min(p.splits, ch.n_kblocks);          // no more than the chunk has keys for
-        const int slice_rows = 16 * p.slice_blocks, rows = min(ROWS, ch.q_end - row0);
-        if (p.merge) {
-            // where a partial result is missing, the slice is computed here whole, as a tile of its own
-            const int first = part * slice_rows / 32;
-            if (part * slice_rows >= rows) return;
-            row0 += part * slice_rows;
-            if (f8_merge<D, NW>(p, ch, head, tile, splits, row0, first, min(slice_rows / 32, NW - first), slots)) return;
-            ch.q_end = min(ch.q_end, row0 + slice_rows);
-        } else {
-            if (part >= splits) return;
-            vb = ch.n_kblocks * part / splits;
-            ve = ch.n_kblocks * (part + 1) / splits;
-            readers = (rows + slice_rows - 1) / slice_rows;
-        }
-    }
+    const int row0 = ch.q_begin + (tile - ch.tile_begin) * ROWS;
     const int row_block = NW == 8 ? ((wave & 3) << 1) | (wave >> 2) : wave;       // (waves w and w + 4 share a SIMD)
     const int q0 = row0 + row_block * 32;
     const bool has_rows = q0 < ch.q_end;
     F8State<D> st;
-    if (!has_rows) f8_segment_loads_only<D, NW>(p, ch, head, vb, ve, lds);
+    if (!has_rows) f8_segment_loads_only<D, NW>(p, ch, head, 0, ch.n_kblocks, lds);
     else if (MODE == 0) f8_segment<D>(p, ch, head, q0, lds, st);
-    else f8_segment_sp<D, MODE == 2, SPLIT, NW>(p, ch, head, q0, vb, ve, lds, st);
-    if constexpr (SPLIT) {
-        __shared__ int slot_lds;
-        if (!p.merge) {                          // uniform: a partial result
-            if (threadIdx.x == 0) slot_lds = split_claim(p.pool, item, p.token, readers);
-            __syncthreads();
-            const int slot = slot_lds;
-            if (slot < 0 || !has_rows) return;   // (the merge does without this workgroup)
-            const int lane = threadIdx.x & 63, col = lane & 31;
-            const float l = st.l + __shfl_xor(st.l, 32);
-            if (lane < 32) p.pool->ml[slot][row_block * 32 + col] = make_float2(st.m, l);
-#pragma unroll
-            for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    reinterpret_cast<f32x4*>(p.pool->o[slot])[(row_block * (D / 8) + db * 4 + g) * 64 + lane] =
-                        f32x4{st.o[db][4 * g], st.o[db][4 * g + 1], st.o[db][4 * g + 2], st.o[db][4 * g + 3]};
-            return;
-        }
-    }
+    else f8_segment_sp<D, MODE == 2, false, NW>(p, ch, head, q0, 0, ch.n_kblocks, lds, st);
     if (has_rows) f8_store_out<D>(p, head, q0, ch.q_end, st);
 }
 
 const AttnVariant kFp8Variants[] = {
-    {"d128_fp8", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<128, 4>, ll_attn_fp8_kernel<128, 5>}, ll_attn_fp8_kernel<128, 3>, ll_attn_fp8_kernel<128, 6>},
-    {"d64_fp8", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<64, 4>, ll_attn_fp8_kernel<64, 5>}, ll_attn_fp8_kernel<64, 3>, ll_attn_fp8_kernel<64, 6>},
+    {"d128_fp8", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<128, 4>, ll_attn_fp8_kernel<128, 5>}, {ll_attn_fp8_kernel<128, 3>, ll_attn_fp8_kernel<128, 6>}, {ll_attn_fp8_kernel<128, 3>, ll_attn_fp8_kernel<128, 6>}},
+    {"d64_fp8", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<64, 4>, ll_attn_fp8_kernel<64, 5>}, {ll_attn_fp8_kernel<64, 3>, ll_attn_fp8_kernel<64, 6>}, {ll_attn_fp8_kernel<64, 3>, ll_attn_fp8_kernel<64, 6>}},
     {"d128_fp8_simple", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 0>, F8_THREADS, KBLOCK8},
     {"d64_fp8_simple", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 0>, F8_THREADS, KBLOCK8},
     {"d128_fp8_loglin", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 2>, F8_THREADS, KBLOCK8},

@@ -413,7 +413,7 @@ AttnSplit attn_split(int variant, int H, int n_chunks, const int* rows, const in
     const bool fp8 = v.kblock == KBLOCK8;
     const int unsplit = key_groups_log2(v, H, n_chunks, [&](int c) { return rows[c]; }, [&](int c) { return kblocks[c]; });
     AttnSplit best{1 << unsplit, 1};
-    if (v.split == nullptr) return best;
+    if (v.split[0] == nullptr) return best;
     constexpr int CUS = 256;
     const SplitModel& m = (fp8 ? kSplitModel8 : kSplitModel)[v.D == 128 ? 0 : 1];
     int most_kblocks = 0;
@@ -516,7 +516,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     }
     int log_g = 0;
     while ((1 << log_g) < p.key_groups) ++log_g;
-    if (log_g > 3 || (log_g > 0 && v.grouped[log_g - 1] == nullptr)) return hipErrorInvalidValue;
+    if (log_g > 3) return hipErrorInvalidValue;
     const int qtile = v.qtile >> log_g;
     p.n_tiles = 0;
     for (int c = 0; c < p.n_chunks; ++c) {
@@ -526,7 +526,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     const int total = p.n_tiles * p.H;
     if (total <= 0) return hipSuccess;
     p.splits = std::max(1, p.splits);
-    if (p.splits > MAX_SPLITS || (p.splits > 1 && (v.split == nullptr || int64_t(total) * p.splits > SPLIT_SLOTS))) return hipErrorInvalidValue;
+    if (p.splits > MAX_SPLITS || (p.splits > 1 && (v.split[log_g] == nullptr || int64_t(total) * p.splits > SPLIT_SLOTS))) return hipErrorInvalidValue;
     p.per_tile = p.splits;
     p.merge = 0;
     p.slice_blocks = 16 >> log_g;
@@ -582,27 +582,33 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
             grid = 8 * most_tiles;
         }
     }
-    static bool attr_set[64][6] = {};
     if (variant > 64) return hipErrorInvalidValue;
     const bool fp8 = v.kblock == KBLOCK8;
-    const int which = p.splits > 1 && (log_g == 0 || fp8) ? 4 + log_g : log_g;
-    void (*const kernel)(const AttnParams) = which == 0 ? v.kernel : which == 4 ? v.split : which == 5 ? v.split_half : v.grouped[log_g - 1];
-    if (which > 5 || kernel == nullptr) return hipErrorInvalidValue;
     const int lds_bytes = log_g == 0 || fp8 ? v.lds_bytes : GROUPED_LDS_BYTES;
     const dim3 threads(fp8 ? v.threads >> log_g : v.threads);
-    if (!attr_set[variant - 1][which]) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    static bool attr_set[64][12] = {};
+    auto prepare = [&](void (*kernel)(const AttnParams), int which) {            // which: one of the variant's kernels
+        if (kernel == nullptr) return hipErrorInvalidValue;
+        if (attr_set[variant - 1][which]) return hipSuccess;
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+        attr_set[variant - 1][which] = e == hipSuccess;
+        return e;
+    };
+    if (p.splits == 1) {
+        void (*const kernel)(const AttnParams) = log_g == 0 ? v.kernel : v.grouped[log_g - 1];
+        const hipError_t e = prepare(kernel, log_g);
         if (e != hipSuccess) return e;
-        attr_set[variant - 1][which] = true;
-    }
-    hipLaunchKernelGGL(kernel, dim3(grid), threads, lds_bytes, s, p);
-    if (p.splits > 1) {
-        hipError_t e = hipGetLastError();
+        hipLaunchKernelGGL(kernel, dim3(grid), threads, lds_bytes, s, p);
+    } else {
+        hipError_t e = prepare(v.split[log_g], 4 + log_g);
+        if (e == hipSuccess) e = prepare(v.merge[log_g], 8 + log_g);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(v.split[log_g], dim3(grid), threads, lds_bytes, s, p);
+        e = hipGetLastError();
         if (e != hipSuccess) return e;
         p.merge = 1;
         p.per_tile = ((16 >> log_g) + p.slice_blocks - 1) / p.slice_blocks;
-        hipLaunchKernelGGL(kernel, dim3((total * p.per_tile + 7) / 8 * 8), threads, lds_bytes, s, p);
+        hipLaunchKernelGGL(v.merge[log_g], dim3((total * p.per_tile + 7) / 8 * 8), threads, lds_bytes, s, p);
     }
     return hipGetLastError();
 }

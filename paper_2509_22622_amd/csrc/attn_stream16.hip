@@ -148,9 +148,20 @@ __device__ __forceinline__ unsigned s16_k_load_offset(int lane) {
 // G: key groups of the workgroup (lds_plan.h: GroupRing).  G == 1: all eight waves walk the chunk's kblocks [vb, ve)
 // through one ring.  G > 1: this wave's group of 8 / G waves walks its own share [vb, ve) through its own ring and runs
 // n_steps >= ve - vb steps, as many as the longest share has (a step past ve has no live key).
-template <int D, bool QSCALE, int SCHED, int G>
-__device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk& ch, int head, int q0, int vb, int ve,
-                                            int n_steps, char* lds, S16State<D>& st, const float2* shift_cs) {
+// `gate` is the barrier behind the first loads; where it says no (to the whole workgroup) nothing is computed: false.
+// (Kernel: keeps what the kernels of this file share apart, which otherwise changes with every user of it: 5 registers more and 1.5 %
+// of the time of the unsplit kernels)
+template <int Kernel>
+struct S16Barrier {
+    static constexpr bool STOPS = false;
+    using Again = S16Barrier;
+    __device__ __forceinline__ bool operator()() const { __builtin_amdgcn_s_barrier(); return true; }
+};
+using S16Unsplit = S16Barrier<0>;
+using S16NextShare = S16Barrier<1>;
+template <int D, bool QSCALE, int SCHED, int G, typename Gate>
+__device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk& ch, int tid, int head, int q0, int vb, int ve,
+                                            int n_steps, char* lds, S16State<D>& st, const float2* shift_cs, Gate gate) {
     using Plan = LdsPlan16<D, (SCHED & 2) != 0>;
     constexpr bool TRACK = !(SCHED & 8);
     constexpr int KS = Plan::KS;                // K fragments per kblock = S^T slots (two MFMAs each)
@@ -174,7 +185,7 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
     static_assert(NF % NW == 0 && (G == 1 || KS % NW == 0), "fragments must split over the waves");
     static_assert(PF >= LAND && PF + 2 <= NS, "ring too short for the prefetch distance");
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int lane = tid & 63;
     const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = wave_wg % NW;              // among the waves that share this ring
     const int n = lane & 15, g = lane >> 4;
@@ -340,12 +351,12 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
                 }
     }
 
-    if constexpr (G == 1) {
-        s16_wait_vmcnt<(PF - LAND) * LPW>();
-        __builtin_amdgcn_s_barrier();
-    } else {
-        s16_wait_vmcnt<0>();
-        if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
+    s16_wait_vmcnt<G == 1 ? (PF - LAND) * LPW : 0>();
+    if constexpr (NW > 1 || Gate::STOPS) {
+        if (!gate()) {
+            __builtin_amdgcn_s_waitcnt(0);
+            return false;
+        }
     }
 
     // dead slots may hold anything, even NaN: zero the V elements of keys outside the range
@@ -579,17 +590,18 @@ __device__ __forceinline__ void s16_segment(const AttnParams& p, const AttnChunk
         st.l[qb] = lsum[qb][0] + lsum[qb][1];
         st.m[qb] = mref[qb];
     }
+    return true;
 }
 
 // A wave without queries (a chunk's short last tile) still owes its workgroup its share of the direct-to-LDS loads,
 // with the same waits and the same number of barriers.
-template <int D>
-__device__ __forceinline__ void s16_segment_loads_only(const AttnParams& p, const AttnChunk& ch, int head, int vb, int ve, char* lds) {
+template <int D, typename Gate>
+__device__ __forceinline__ bool s16_segment_loads_only(const AttnParams& p, const AttnChunk& ch, int tid, int head, int vb, int ve, char* lds, Gate gate) {
     constexpr int KS = D / 16, NV = D / 16;
     constexpr int KB_BYTES = KBLOCK * D * 2, STAGE_BYTES = 2 * KB_BYTES;
     constexpr int NS = RingPlan::STAGES, NW = 8, LPW = (KS + NV) / NW, PF = RingPlan::AHEAD, LAND = RingPlan::LANDED;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n_ranges = ch.n_ranges;
     const int rs0 = ch.rs[0], re0 = ch.re[0];
     int rs1 = ch.rs[1], re1 = ch.re[1], rs2 = ch.rs[2];
@@ -617,7 +629,10 @@ __device__ __forceinline__ void s16_segment_loads_only(const AttnParams& p, cons
 #pragma unroll
     for (int j = 0; j < PF; ++j) issue_loads(min(vb + j, ve - 1), (vb + j) & (NS - 1));
     s16_wait_vmcnt<(PF - LAND) * LPW>();
-    __builtin_amdgcn_s_barrier();
+    if (!gate()) {
+        __builtin_amdgcn_s_waitcnt(0);
+        return false;
+    }
     for (int i = vb; i < ve; ++i) {
         issue_loads(min(i + PF, ve - 1), (i + PF) & (NS - 1));
         if (RingPlan::barrier_after(i - vb)) {
@@ -626,17 +641,21 @@ __device__ __forceinline__ void s16_segment_loads_only(const AttnParams& p, cons
         }
     }
     __builtin_amdgcn_s_waitcnt(0);
+    return true;
 }
 
 // The same for a wave of a key group (G > 1) that has no queries, or whose group has no kblocks (loads nothing then).
-template <int D, int G>
-__device__ __forceinline__ void s16_group_idle(const AttnParams& p, const AttnChunk& ch, int head, int vb, int ve, int n_steps, char* lds) {
+template <int D, int G, typename Gate>
+__device__ __forceinline__ bool s16_group_idle(const AttnParams& p, const AttnChunk& ch, int tid, int head, int vb, int ve, int n_steps, char* lds, Gate gate) {
     using GR = GroupRing<D, G>;
     constexpr int KS = D / 16, NF = 2 * KS, NW = 8 / G, PERIOD = GR::PERIOD, DEPTH = GR::DEPTH, LPW = PERIOD * NF / NW;
     constexpr int KB_BYTES = KBLOCK * D * 2;
-    if constexpr (NW == 1) return;               // a ring of its own: nobody waits for this wave
-    const int lane = threadIdx.x & 63;
-    const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_wg % NW;
+    if constexpr (NW == 1) {                     // a ring of its own: nobody waits for this wave
+        if constexpr (Gate::STOPS) return gate();
+        return true;
+    }
+    const int lane = tid & 63;
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_wg % NW;
     lds += (wave_wg / NW) * GR::BYTES;
     const int n_ranges = ch.n_ranges;
     const int rs0 = ch.rs[0], re0 = ch.re[0];
@@ -667,7 +686,7 @@ __device__ __forceinline__ void s16_group_idle(const AttnParams& p, const AttnCh
     };
     issue_period(0);
     s16_wait_vmcnt<0>();
-    __builtin_amdgcn_s_barrier();
+    if (!gate()) return false;
     for (int r = 0; r + PERIOD <= n_steps; r += PERIOD) {
         issue_period(r + PERIOD);
         s16_wait_vmcnt<0>();
@@ -675,6 +694,7 @@ __device__ __forceinline__ void s16_group_idle(const AttnParams& p, const AttnCh
     }
     if (n_steps % PERIOD != 0) issue_period(n_steps / PERIOD * PERIOD + PERIOD);
     __builtin_amdgcn_s_waitcnt(0);
+    return true;
 }
 
 // 16 dq + 4 g + j, j = 0..3, of a row's unnormalised output (with reference m and row sum l) to where the call wants it
@@ -692,43 +712,36 @@ __device__ __forceinline__ void s16_store_unit(const AttnParams& p, int head, in
     }
 }
 
-// Where a workgroup's result goes: as rows [.., row_end) of the output, or (splits > 1) as one of the partial results of a
-// tile whose keys are dealt to several workgroups as well: this one takes share `split` of `splits`.
-struct S16Share {
-    int split, splits, item, readers;            // item: the workgroup's place in the launch; readers: slices of the merge
-};
-
-// One query tile of 256 / G rows from row0 on, its keys dealt to G groups of 8 / G waves: kblocks [T j / G, T (j + 1) / G) to
-// group j (with splits: the split's G of the G * splits shares).
-// Each group's result is relative to its own reference; they meet in LDS (the rings' memory), where every wave adds up
-// its part of the features over the groups: weights 2^(m_j - max m), one division by the weighted sum of the row sums.
-template <int D, bool QSCALE, bool LSE, int SCHED, int G>
-__device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnChunk& ch, int head, int row0, const S16Share& sh, char* lds,
-                                               const float2* shift_cs, float2 (*ml)[2][16], int& slot_lds) {
+// Share `split` of `splits` of a tile's keys, or (one split) all of them, dealt to G groups of 8 / G waves: kblocks
+// [T j / G, T (j + 1) / G) to group j (with splits: the split's G of the G * splits shares).  Each group's result is relative to
+// its own reference; they meet in LDS (the rings' memory), where s16_add_groups adds up what a wave asks for.  This wave's rows
+// begin at q0.
+template <int D, bool QSCALE, int SCHED, int G, typename Gate>
+__device__ __forceinline__ bool s16_groups(const AttnParams& p, const AttnChunk& ch, int tid, int head, int q0, int split, int splits, char* lds,
+                                           const float2* shift_cs, float2 (*ml)[2][16], Gate gate) {
     constexpr int NW = 8 / G, UNITS = D / 16 * 2;                // (dq, qb) blocks of a wave's O^T
     static_assert(UNITS % G == 0, "the O^T blocks must split over the groups");
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int group = wave / NW, rb = wave % NW;
-    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
-    const int q0 = row0 + rb * 32;
-    const bool has_rows = q0 < ch.q_end;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = wave / NW;
+    const int lane = tid & 63, n = lane & 15, g = lane >> 4;
     const int T = ch.n_kblocks;
     int vb = T * group / G, ve = T * (group + 1) / G, n_steps = (T + G - 1) / G;
-    if (sh.splits > 1) {                         // uniform (and three divisions, in front of everything else)
-        const int shares = G * sh.splits, share = G * sh.split + group;
+    if (splits > 1) {                            // uniform (and three divisions, in front of everything else)
+        const int shares = G * splits, share = G * split + group;
         vb = T * share / shares;
         ve = T * (share + 1) / shares;
         n_steps = (T + shares - 1) / shares;
     }
-    const bool works = has_rows && ve > vb;
+    const bool works = q0 < ch.q_end && ve > vb;
     S16State<D> st;
-    if (works) s16_segment<D, QSCALE, SCHED, G>(p, ch, head, q0, vb, ve, n_steps, lds, st, shift_cs);
-    else s16_group_idle<D, G>(p, ch, head, vb, ve, n_steps, lds);
+    if (!(works ? s16_segment<D, QSCALE, SCHED, G>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate)
+                : s16_group_idle<D, G>(p, ch, tid, head, vb, ve, n_steps, lds, gate)))
+        return false;
     if constexpr ((SCHED & 8) != 0) {
         const bool ran_away = works && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
         if (__syncthreads_or(ran_away)) {
-            if (works) s16_segment<D, QSCALE, SCHED & ~8, G>(p, ch, head, q0, vb, ve, n_steps, lds, st, shift_cs);
-            else s16_group_idle<D, G>(p, ch, head, vb, ve, n_steps, lds);
+            if (works) s16_segment<D, QSCALE, SCHED & ~8, G>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, typename Gate::Again{});
+            else s16_group_idle<D, G>(p, ch, tid, head, vb, ve, n_steps, lds, typename Gate::Again{});
         }
     }
     if (!works) {
@@ -741,7 +754,6 @@ __device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnCh
         }
     }
     __syncthreads();                             // every group has left its ring
-    if (sh.splits > 1 && threadIdx.x == 0) slot_lds = split_claim(p.pool, sh.item, p.token, sh.readers);
     f32x4* part = reinterpret_cast<f32x4*>(lds);                 // [wave][unit][lane]
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
@@ -753,66 +765,83 @@ __device__ __forceinline__ void s16_split_tile(const AttnParams& p, const AttnCh
         for (int dq = 0; dq < D / 16; ++dq) part[(wave * UNITS + dq * 2 + qb) * 64 + lane] = st.o[dq][qb];
     }
     __syncthreads();
-    if (!has_rows) return;
-    // unit group * (UNITS / G) + i of the tile's O^T blocks over all groups, relative to reference m
-    auto add_up = [&](int i, bool may_be_weightless, float& m, float& l, f32x4& o) {
-        const int u = group * (UNITS / G) + i, qb = u & 1;
-        m = -INFINITY;
-        l = 0.f;
-        o = f32x4{0.f, 0.f, 0.f, 0.f};
+    return true;
+}
+
+// Unit u = (dq, qb) of the tile's O^T blocks over all groups, relative to reference m: weights 2^(m_j - max m)
+template <int D, int G>
+__device__ __forceinline__ void s16_add_groups(int tid, const char* lds, const float2 (*ml)[2][16], int u, bool may_be_weightless, float& m, float& l, f32x4& o) {
+    constexpr int NW = 8 / G, UNITS = D / 16 * 2;
+    const int rb = __builtin_amdgcn_readfirstlane(tid >> 6) % NW;
+    const int lane = tid & 63, n = lane & 15, qb = u & 1;
+    const f32x4* part = reinterpret_cast<const f32x4*>(lds);
+    m = -INFINITY;
+    l = 0.f;
+    o = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + rb][qb][n].x);
-        const float base = may_be_weightless && m == -INFINITY ? 0.f : m;
+    for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + rb][qb][n].x);
+    const float base = may_be_weightless && m == -INFINITY ? 0.f : m;
 #pragma unroll
-        for (int j = 0; j < G; ++j) {
-            const float2 s = ml[j * NW + rb][qb][n];
-            const float a = __builtin_amdgcn_exp2f(s.x - base);
-            l += s.y * a;
-            o += part[((j * NW + rb) * UNITS + u) * 64 + lane] * a;
-        }
-    };
-    float m, l;
-    f32x4 o;
-    if (sh.splits > 1) {                         // uniform.  A share may hold no key with weight, a tile does (or is NaN)
-        const int slot = slot_lds;
-        if (slot < 0) return;                    // the merge does without this workgroup
+    for (int j = 0; j < G; ++j) {
+        const float2 s = ml[j * NW + rb][qb][n];
+        const float a = __builtin_amdgcn_exp2f(s.x - base);
+        l = __builtin_fmaf(s.y, a, l);
+        const f32x4 x = part[((j * NW + rb) * UNITS + u) * 64 + lane];
 #pragma unroll
-        for (int i = 0; i < UNITS / G; ++i) {
-            const int u = group * (UNITS / G) + i, blk = rb * 2 + (u & 1);
-            add_up(i, true, m, l, o);
-            reinterpret_cast<f32x4*>(p.pool->o[slot])[(blk * (D / 16) + (u >> 1)) * 64 + lane] = o;
-            if (u < 2 && g == 0) p.pool->ml[slot][blk * 16 + n] = make_float2(m, l);
-        }
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < UNITS / G; ++i) {
-        const int u = group * (UNITS / G) + i, row = q0 + 16 * (u & 1) + n;
-        add_up(i, false, m, l, o);
-        if (row < ch.q_end) s16_store_unit<D, LSE>(p, head, row, u >> 1, g, o, m, l);
+        for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(x[e], a, o[e]);
     }
 }
 
-// The partial results of a tile's splits, for the 16-row blocks [first, first + n_blocks) of the tile: the same sum as
-// over key groups.  Bounded by latency and by the partials' way through the last-level cache.  False (for the whole
-// workgroup) if some split found no room for its partial result: nothing is written then.
+// Kblocks [vb, ve) for the wave's rows from q0 on, all eight waves walking through one ring.
+template <int D, bool QSCALE, int SCHED, typename Gate>
+__device__ __forceinline__ bool s16_whole(const AttnParams& p, const AttnChunk& ch, int tid, int head, int q0, int vb, int ve, char* lds, S16State<D>& st,
+                                          const float2* shift_cs, Gate gate) {
+    // wave-uniform: a wave without rows in the chunk's last tile only takes its share of the loads and barriers
+    const bool has_rows = q0 < ch.q_end;
+    if (!(has_rows ? s16_segment<D, QSCALE, SCHED, 1>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, gate)
+                   : s16_segment_loads_only<D>(p, ch, tid, head, vb, ve, lds, gate)))
+        return false;
+    if constexpr ((SCHED & 8) != 0) {
+        // the pass above kept its first reference: fine unless some row's sum ran away (a score far above the first
+        // kblock's maximum); then the whole workgroup (the waves share the ring and its barriers) takes the tile again
+        // with the reference followed.  The barrier inside the vote also ends every wave's reads of the first pass.
+        const bool ran_away = has_rows && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
+        if (__syncthreads_or(ran_away)) {
+            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, typename Gate::Again{});
+            else s16_segment_loads_only<D>(p, ch, tid, head, vb, ve, lds, typename Gate::Again{});
+        }
+    }
+    return true;
+}
+
+__device__ __forceinline__ void s16_shift_table(const AttnParams& p, const AttnChunk& ch, float2* shift_cs) {
+    if (ch.sink_shift == 0) return;              // uniform over the workgroup
+    if ((int)threadIdx.x < p.n_t) {
+        double sn, cs;
+        sincos(double(ch.sink_shift) * p.inv_freq_t[threadIdx.x], &sn, &cs);
+        shift_cs[threadIdx.x] = make_float2(float(cs), float(sn));
+    }
+    __syncthreads();
+}
+
+// The partial results of a tile's splits, for the 16-row blocks [first, first + n_blocks) of the tile, added up in order.
+// Bounded by latency and by the partials' way through the last-level cache.  False (for the whole workgroup, and for all of
+// the tile's) if some split found no room for its partial result: nothing is written then.
 template <int D, bool LSE>
-__device__ __forceinline__ bool s16_merge(const AttnParams& p, const AttnChunk& ch, int head, int tile, int splits, int row0, int first,
+__device__ __forceinline__ bool s16_merge(const AttnParams& p, const AttnChunk& ch, int tid, int head, int tile, int splits, int row0, int first,
                                           int n_blocks, int* slots) {
     constexpr int DQ = D / 16;
-    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+    const int lane = tid & 63, n = lane & 15, g = lane >> 4;
     if (tid < splits) slots[tid] = split_find(p.pool, (head * p.splits + tid) * p.n_tiles + tile, p.token);
     __syncthreads();
     bool all = true;
     for (int s = 0; s < splits; ++s) all = all && slots[s] >= 0;
+    all = __builtin_amdgcn_readfirstlane(all);
     if (all) {
         for (int u = tid >> 6; u < n_blocks * DQ; u += S16_THREADS / 64) {
             const int blk = first + u / DQ, dq = u % DQ, row = row0 + (blk - first) * 16 + n;
             float m = -INFINITY, l = 0.f;
             f32x4 o = {0.f, 0.f, 0.f, 0.f};
-            for (int s = 0; s < splits; s += 4)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) m = fmaxf(m, p.pool->ml[slots[min(s + e, splits - 1)]][blk * 16 + n].x);
             for (int s0 = 0; s0 < splits; s0 += 4) {
                 float2 w[4];
                 f32x4 x[4];
@@ -825,9 +854,9 @@ __device__ __forceinline__ bool s16_merge(const AttnParams& p, const AttnChunk& 
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (s0 + e < splits) {
-                        const float a = __builtin_amdgcn_exp2f(w[e].x - m);
-                        l += w[e].y * a;
-                        o += x[e] * a;
+                        float a, b;
+                        split_weights(m, l, w[e].x, w[e].y, a, b);
+                        o = split_add(o, a, x[e], b);
                     }
             }
             if (row < ch.q_end) s16_store_unit<D, LSE>(p, head, row, dq, g, o, m, l);
@@ -843,30 +872,23 @@ template <int D, bool QSCALE, bool LSE, int SCHED, int G>
 __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_stream16_kernel(const AttnParams p) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ float2 shift_cs[64];
-    __shared__ int slots[MAX_SPLITS];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, n = lane & 15, g = lane >> 4;
     // The arguments lie in several cache lines; where a launch has one chunk, all that a workgroup needs of them is
     // fetched here in one go instead of one cold scalar load after another.
     AttnChunk ch = p.chunk[0];
     asm volatile("" ::"s"(ch.q_begin), "s"(ch.q_end), "s"(ch.tile_begin), "s"(ch.n_ranges), "s"(ch.rs[0]), "s"(ch.rs[1]), "s"(ch.rs[2]),
                  "s"(ch.re[0]), "s"(ch.re[1]), "s"(ch.re[2]), "s"(ch.n_kblocks), "s"(ch.sink_shift), "s"(ch.t_row));
-    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_frag), "s"(p.t_table), "s"(p.row_cs), "s"(p.col_cs), "s"(p.splits), "s"(p.per_tile));
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.head_stride), "s"(p.out), "s"(p.out_frag), "s"(p.t_table), "s"(p.row_cs), "s"(p.col_cs));
     const int xcd = blockIdx.x & 7;
     int head = -1, tile = 0, ci = -1;
     const int idx = blockIdx.x >> 3;
-    S16Share sh = {0, 1, 0, 0};
-    int slice = 0;
     if (p.n_groups == 0) {
-        const int per_head = p.n_tiles * p.per_tile, total = per_head * p.H;
+        const int total = p.n_tiles * p.H;
         const int item = ((xcd * total + 7) >> 3) + idx;
         if (item < (((xcd + 1) * total + 7) >> 3)) {
-            head = item / per_head;
-            tile = item - head * per_head;
-            if (p.per_tile > 1) {                // a tile's workgroups: splits of its keys (heads, splits, tiles: those of a
-                sh.item = item;                  // split side by side, they share its keys), or slices of the merge
-                slice = sh.split = tile / p.n_tiles;
-                tile -= sh.split * p.n_tiles;
-            }
+            head = item / p.n_tiles;
+            tile = item % p.n_tiles;
         }
     } else {
         if (!attn_placed_tile(p, xcd, idx, head, ci, tile)) head = -1;
@@ -877,79 +899,29 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
             for (ci = 0; ci + 1 < p.n_chunks && tile >= p.chunk[ci + 1].tile_begin;) ++ci;
         ch = p.chunk[ci];
     }
-    int row0 = ch.q_begin + (tile - ch.tile_begin) * (256 / G);
-    if (p.splits > 1) {                          // uniform
-        const int splits = min(p.splits, max(1, ch.n_kblocks / G));              // no more than the chunk has keys for
-        const int slice_rows = 16 * p.slice_blocks, rows = min(256 / G, ch.q_end - row0);
-        if (p.merge) {
-            // where a partial result is missing, the slice is computed here whole, as a tile of its own
-            if (splits == 1) return;             // one share: its workgroup has stored the finished rows (maybe over the queries)
-            const int first = slice * p.slice_blocks;
-            row0 += slice * slice_rows;
-            if (slice * slice_rows >= rows) return;
-            if (s16_merge<D, LSE>(p, ch, head, tile, splits, row0, first, min(p.slice_blocks, 16 / G - first), slots)) return;
-            ch.q_end = min(ch.q_end, row0 + slice_rows);
-            sh = {0, 1, 0, 0};
-        } else {
-            if (sh.split >= splits) return;
-            sh.splits = splits;
-            sh.readers = (rows + slice_rows - 1) / slice_rows;
-        }
-    }
-    if (ch.sink_shift != 0) {                    // uniform over the workgroup
-        if ((int)threadIdx.x < p.n_t) {
-            double sn, cs;
-            sincos(double(ch.sink_shift) * p.inv_freq_t[threadIdx.x], &sn, &cs);
-            shift_cs[threadIdx.x] = make_float2(float(cs), float(sn));
-        }
-        __syncthreads();
-    }
+    const int row0 = ch.q_begin + (tile - ch.tile_begin) * (256 / G);
+    s16_shift_table(p, ch, shift_cs);
     if constexpr (G > 1) {
         __shared__ float2 ml[8][2][16];          // (reference, row sum) per wave, query block and column
-        s16_split_tile<D, QSCALE, LSE, SCHED, G>(p, ch, head, row0, sh, lds, shift_cs, ml, slots[0]);
+        constexpr int NW = 8 / G, PER_WAVE = D / 8 / G;
+        const int q0 = row0 + wave % NW * 32;
+        s16_groups<D, QSCALE, SCHED, G>(p, ch, tid, head, q0, 0, 1, lds, shift_cs, ml, S16Unsplit{});
+        if (q0 >= ch.q_end) return;
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) {
+            const int u = wave / NW * PER_WAVE + i, row = q0 + 16 * (u & 1) + n;
+            float m, l;
+            f32x4 o;
+            s16_add_groups<D, G>(tid, lds, ml, u, false, m, l, o);
+            if (row < ch.q_end) s16_store_unit<D, LSE>(p, head, row, u >> 1, g, o, m, l);
+        }
         return;
     }
     const int row_block = ((wave & 3) << 1) | (wave >> 2);      // waves w and w + 4 (one SIMD) take neighbouring blocks
     const int q0 = row0 + row_block * 32;
-    int vb = 0, ve = ch.n_kblocks;
-    if (sh.splits > 1) {                         // uniform
-        vb = ch.n_kblocks * sh.split / sh.splits;
-        ve = ch.n_kblocks * (sh.split + 1) / sh.splits;
-    }
-    // wave-uniform: a wave without rows in the chunk's last tile only takes its share of the loads and barriers
-    const bool has_rows = q0 < ch.q_end;
     S16State<D> st;
-    if (has_rows) s16_segment<D, QSCALE, SCHED, 1>(p, ch, head, q0, vb, ve, ve - vb, lds, st, shift_cs);
-    else s16_segment_loads_only<D>(p, ch, head, vb, ve, lds);
-    if constexpr ((SCHED & 8) != 0) {
-        // the pass above kept its first reference: fine unless some row's sum ran away (a score far above the first
-        // kblock's maximum); then the whole workgroup (the waves share the ring and its barriers) takes the tile again
-        // with the reference followed.  The barrier inside the vote also ends every wave's reads of the first pass.
-        const bool ran_away = has_rows && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
-        if (__syncthreads_or(ran_away)) {
-            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1>(p, ch, head, q0, vb, ve, ve - vb, lds, st, shift_cs);
-            else s16_segment_loads_only<D>(p, ch, head, vb, ve, lds);
-        }
-    }
-    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
-    if (sh.splits > 1) {                         // uniform: a partial result
-        if (threadIdx.x == 0) slots[0] = split_claim(p.pool, sh.item, p.token, sh.readers);
-        __syncthreads();
-        const int slot = slots[0];
-        if (slot < 0 || !has_rows) return;       // (the merge does without this workgroup)
-#pragma unroll
-        for (int qb = 0; qb < 2; ++qb) {
-            float l = st.l[qb];
-            l += __shfl_xor(l, 16);
-            l += __shfl_xor(l, 32);
-            const int blk = row_block * 2 + qb;
-            if (g == 0) p.pool->ml[slot][blk * 16 + n] = make_float2(st.m[qb], l);
-#pragma unroll
-            for (int dq = 0; dq < D / 16; ++dq) reinterpret_cast<f32x4*>(p.pool->o[slot])[(blk * (D / 16) + dq) * 64 + lane] = st.o[dq][qb];
-        }
-        return;
-    }
-    if (!has_rows) return;
+    s16_whole<D, QSCALE, SCHED>(p, ch, tid, head, q0, 0, ch.n_kblocks, lds, st, shift_cs, S16Unsplit{});
+    if (q0 >= ch.q_end) return;
 
     // out[row][head][16 dq + 4 g + j] = O^T block (dq, qb) register j, divided by the row sum
 #pragma unroll
@@ -991,33 +963,207 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     }
 }
 
+// ---- the launches of tiles whose keys are split: several workgroups per tile, one share of its keys each, and their merge, with
+// the tile's rows in slices
+struct S16SplitTile {
+    SplitPlace at;                               // (part: split, or slice of the merge)
+    AttnChunk ch;
+    int row0, splits, slice_rows, rows;
+};
+template <int G>
+__device__ __forceinline__ S16SplitTile s16_split_tile(const AttnParams& p) {
+    S16SplitTile t;
+    t.ch = p.chunk[0];                           // (in one go, as above)
+    asm volatile("" ::"s"(t.ch.q_begin), "s"(t.ch.q_end), "s"(t.ch.tile_begin), "s"(t.ch.n_ranges), "s"(t.ch.rs[0]), "s"(t.ch.rs[1]), "s"(t.ch.rs[2]),
+                 "s"(t.ch.re[0]), "s"(t.ch.re[1]), "s"(t.ch.re[2]), "s"(t.ch.n_kblocks), "s"(t.ch.sink_shift), "s"(t.ch.t_row));
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.head_stride), "s"(p.out), "s"(p.t_table), "s"(p.row_cs), "s"(p.col_cs), "s"(p.splits), "s"(p.per_tile),
+                 "s"(p.pool), "s"(p.token));
+    t.at = split_place(p);
+    if (p.n_chunks > 1) {
+        int ci = 0;
+        while (ci + 1 < p.n_chunks && t.at.tile >= p.chunk[ci + 1].tile_begin) ++ci;
+        t.ch = p.chunk[ci];
+    }
+    t.row0 = t.ch.q_begin + (t.at.tile - t.ch.tile_begin) * (256 / G);
+    t.splits = min(p.splits, max(1, t.ch.n_kblocks / G));                        // no more than the chunk has keys for
+    t.slice_rows = 16 * p.slice_blocks;
+    t.rows = min(256 / G, t.ch.q_end - t.row0);
+    return t;
+}
+// Share `share` of the tile: false if the gate stopped it, else what the wave's unit i = 0 .. PER_WAVE - 1 is (s16_share_unit).
+template <int D, int SCHED, int G, typename Gate>
+__device__ __forceinline__ bool s16_share(const AttnParams& p, const S16SplitTile& t, int tid, int q0, int share, char* lds, const float2* shift_cs,
+                                          float2 (*ml)[2][16], S16State<D>& st, Gate gate) {
+    if constexpr (G > 1) return s16_groups<D, false, SCHED, G>(p, t.ch, tid, t.at.head, q0, share, t.splits, lds, shift_cs, ml, gate);
+    if (!s16_whole<D, false, SCHED>(p, t.ch, tid, t.at.head, q0, t.ch.n_kblocks * share / t.splits, t.ch.n_kblocks * (share + 1) / t.splits, lds, st, shift_cs, gate))
+        return false;
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        st.l[qb] += __shfl_xor(st.l[qb], 16);
+        st.l[qb] += __shfl_xor(st.l[qb], 32);
+    }
+    return true;
+}
+template <int D, int G>
+__device__ __forceinline__ void s16_share_unit(int tid, const char* lds, const float2 (*ml)[2][16], const S16State<D>& st, int i, int u, float& m, float& l, f32x4& o) {
+    if constexpr (G > 1) {
+        s16_add_groups<D, G>(tid, lds, ml, u, true, m, l, o);    // a share may hold no key with weight, a tile does (or is NaN)
+    } else {
+        m = st.m[i & 1];
+        l = st.l[i & 1];
+        o = st.o[i >> 1][i & 1];
+    }
+}
+template <int G>
+__device__ __forceinline__ int s16_row_block(int wave) { return G > 1 ? wave % (8 / G) : ((wave & 3) << 1) | (wave >> 2); }    // (as in the kernel above)
+
+// One share of a tile whose partial results are not all there, added to the sums in a space of the pool; the last one stores the rows.
+template <int D, bool LSE, int SCHED, int G>
+__device__ __forceinline__ bool s16_next_share(const AttnParams& p, char* lds, const float2* shift_cs, float2 (*ml)[2][16], int space, int share,
+                                               float (&m_sum)[2], float (&l_sum)[2]) {
+    constexpr int DQ = D / 16, NW = 8 / G, PER_WAVE = 2 * DQ / G;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                // (as attn_params_again)
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, n = lane & 15, g = lane >> 4;
+    const S16SplitTile t = s16_split_tile<G>(p);
+    const int row_block = s16_row_block<G>(wave), q0 = t.row0 + row_block * 32, u0 = G > 1 ? wave / NW * PER_WAVE : 0;
+    S16State<D> st;
+    s16_share<D, SCHED, G>(p, t, tid, q0, share, lds, shift_cs, ml, st, S16NextShare{});
+    if (q0 < t.ch.q_end) {
+        float a[2] = {}, b[2] = {};
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) {
+            const int u = u0 + i, dq = u >> 1, row = q0 + 16 * (u & 1) + n;
+            float m, l;
+            f32x4 o;
+            s16_share_unit<D, G>(tid, lds, ml, st, i, u, m, l, o);
+            f32x4* at = reinterpret_cast<f32x4*>(p.pool->o[space]) + ((row_block * 2 + (u & 1)) * DQ + dq) * 64 + lane;
+            if (i < 2) split_weights(m_sum[i], l_sum[i], m, l, a[i], b[i]);
+            const f32x4 before = share > 0 ? *at : f32x4{0.f, 0.f, 0.f, 0.f};
+            o = split_add(before, a[i & 1], o, b[i & 1]);
+            if (share + 1 < t.splits) *at = o;
+            else if (row < t.ch.q_end) s16_store_unit<D, LSE>(p, t.at.head, row, dq, g, o, m_sum[i & 1], l_sum[i & 1]);
+            asm volatile("" ::: "memory");       // one unit's sums in registers at a time
+        }
+    }
+    __syncthreads();                             // the groups' sums have been read, and the sums over shares too
+    return share + 1 < t.splits;
+}
+
+// The gate of a workgroup that needs a slot: it claims one with its first loads, looks at the answer behind them, and leaves if
+// there is none, since what it would compute is the merge's then.  us a call of 1560 rows x 12 x 128, four streams making such
+// calls: 320 where workgroups looked for a slot when they had their result, 209 to 230 so; one stream 167 either way.
+struct S16Claim {
+    static constexpr bool STOPS = true;
+    using Again = S16Barrier<2>;
+    const AttnParams& p;
+    int* slot;
+    int item, readers;                           // readers 0: needs none
+    unsigned long long seen;                     // thread 0: what the claim of the first candidate found
+    __device__ __forceinline__ bool operator()() const {
+        unsigned long long found = seen;
+        asm volatile("" : "+v"(found));          // looked at here: the compiler would compare it, and wait for it, where it was asked for
+        if (threadIdx.x == 0 && readers > 0) *slot = found == 0 ? split_candidate(item, 0) : split_claim(p.pool, item, p.token, readers, 1);
+        __syncthreads();
+        return readers == 0 || __builtin_amdgcn_readfirstlane(*slot) >= 0;
+    }
+};
+template <int D, bool LSE, int SCHED, int G>
+__global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_split16_kernel(const AttnParams p) {
+    constexpr int DQ = D / 16, NW = 8 / G, PER_WAVE = 2 * DQ / G;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ float2 shift_cs[64];
+    __shared__ float2 ml[G > 1 ? 8 : 1][2][16];
+    __shared__ int slot_lds;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, n = lane & 15, g = lane >> 4;
+    const S16SplitTile t = s16_split_tile<G>(p);
+    if (t.at.item < 0 || t.at.part >= t.splits) return;          // uniform, as all of this
+    const int readers = t.splits > 1 ? (t.rows + t.slice_rows - 1) / t.slice_rows : 0;
+    S16Claim claim{p, &slot_lds, t.at.item, readers, 0};
+    if (tid == 0 && readers > 0) claim.seen = split_try(p.pool, t.at.item, 0, p.token, readers);
+    s16_shift_table(p, t.ch, shift_cs);
+    const int row_block = s16_row_block<G>(wave), q0 = t.row0 + row_block * 32, u0 = G > 1 ? wave / NW * PER_WAVE : 0;
+    S16State<D> st;
+    if (!s16_share<D, SCHED, G>(p, t, tid, q0, t.at.part, lds, shift_cs, ml, st, claim) || q0 >= t.ch.q_end) return;
+    float m, l;
+    f32x4 o;
+    if (readers == 0) {                          // (a loop of its own: the units' reads from LDS overlap)
+#pragma unroll
+        for (int i = 0; i < PER_WAVE; ++i) {
+            const int u = u0 + i, row = q0 + 16 * (u & 1) + n;
+            s16_share_unit<D, G>(tid, lds, ml, st, i, u, m, l, o);
+            if (row < t.ch.q_end) s16_store_unit<D, LSE>(p, t.at.head, row, u >> 1, g, o, m, l);
+        }
+        return;
+    }
+    const int slot = __builtin_amdgcn_readfirstlane(slot_lds);
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+        const int u = u0 + i, blk = row_block * 2 + (u & 1);
+        s16_share_unit<D, G>(tid, lds, ml, st, i, u, m, l, o);
+        reinterpret_cast<f32x4*>(p.pool->o[slot])[(blk * DQ + (u >> 1)) * 64 + lane] = o;
+        if (u < 2 && g == 0) p.pool->ml[slot][blk * 16 + n] = make_float2(m, l);
+    }
+}
+
+template <int D, bool LSE, int SCHED, int G>
+__global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_merge16_kernel(const AttnParams p) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ float2 shift_cs[64];
+    __shared__ float2 ml[G > 1 ? 8 : 1][2][16];
+    __shared__ int slots[MAX_SPLITS];
+    const int tid = threadIdx.x;
+    const S16SplitTile t = s16_split_tile<G>(p);
+    const int slice = t.at.part, first = slice * p.slice_blocks;
+    // (one share: its workgroup has stored the finished rows, maybe over the queries)
+    if (t.at.item < 0 || t.splits == 1 || slice * t.slice_rows >= t.rows) return;
+    if (s16_merge<D, LSE>(p, t.ch, tid, t.at.head, t.at.tile, t.splits, t.row0 + slice * t.slice_rows, first, min(p.slice_blocks, 16 / G - first), slots)) return;
+    // a partial result is missing: the first slice's workgroup takes the tile's shares one after another
+    if (slice > 0) return;
+    s16_shift_table(p, t.ch, shift_cs);
+    if (tid == 0) slots[0] = split_take_space(p.pool, blockIdx.x);
+    __syncthreads();
+    const int space = __builtin_amdgcn_readfirstlane(slots[0]);
+    float m_sum[2] = {-INFINITY, -INFINITY}, l_sum[2] = {0.f, 0.f};             // over the shares, by query block
+    int share = 0;
+    while (__builtin_amdgcn_readfirstlane(s16_next_share<D, LSE, SCHED, G>(attn_params_again(), lds, shift_cs, ml, space, share, m_sum, l_sum))) ++share;
+    if (tid == 0) split_leave_space(p.pool, space);
+}
+
 // Default schedule: exponentials of the second query block behind the S^T slots, and the reference kept fixed with
 // the second, maximum-following pass as the fallback (SCHED 9).  The *_tracked variants follow the maximum throughout;
 // the *_qrope variants (SCHED bit 4) take unrotated queries and turn them on load.
 constexpr int S16_DEFAULT = 9, S16_TRACKED = 1;
 #define S16_KERNEL(D, QS, LSE, SCHED, G) ll_attn_stream16_kernel<D, QS, LSE, SCHED, G>
-#define S16_ENTRY(name, D, QS, LSE, SCHED)                                                                            \
+#define S16_BY_GROUPS(kernel, D, LSE, SCHED) \
+    {kernel<D, LSE, SCHED, 1>, kernel<D, LSE, SCHED, 2>, kernel<D, LSE, SCHED, 4>, D == 64 ? kernel<D, LSE, SCHED, (D == 64 ? 8 : 4)> : nullptr}
+#define S16_SPLIT(D, LSE, SCHED) S16_BY_GROUPS(ll_attn_split16_kernel, D, LSE, SCHED), S16_BY_GROUPS(ll_attn_merge16_kernel, D, LSE, SCHED)
+#define S16_ENTRY(name, D, QS, LSE, SCHED, ...)                                                                       \
     {name, D, 256, 8 * 2 * KBLOCK * D * 2, S16_KERNEL(D, QS, LSE, SCHED, 1), S16_THREADS, KBLOCK,                     \
      {S16_KERNEL(D, QS, LSE, SCHED, 2), S16_KERNEL(D, QS, LSE, SCHED, 4),                                             \
-      D == 64 ? S16_KERNEL(D, QS, LSE, SCHED, (D == 64 ? 8 : 4)) : nullptr}, S16_KERNEL(D, QS, LSE, SCHED, 1)}
+      D == 64 ? S16_KERNEL(D, QS, LSE, SCHED, (D == 64 ? 8 : 4)) : nullptr}, __VA_ARGS__}
 // (the tracked variants are there to be compared with, one key group)
 #define S16_ENTRY_WHOLE(name, D, QS, LSE, SCHED) \
     {name, D, 256, 8 * 2 * KBLOCK * D * 2, S16_KERNEL(D, QS, LSE, SCHED, 1), S16_THREADS, KBLOCK, {}}
 const AttnVariant kStream16Variants[] = {
-    S16_ENTRY("d128_stream16", 128, false, false, S16_DEFAULT),
-    S16_ENTRY("d64_stream16", 64, false, false, S16_DEFAULT),
-    S16_ENTRY("d128_stream16_qscale", 128, true, false, S16_DEFAULT),
-    S16_ENTRY("d64_stream16_qscale", 64, true, false, S16_DEFAULT),
-    S16_ENTRY("d128_stream16_lse", 128, false, true, S16_DEFAULT),
-    S16_ENTRY("d64_stream16_lse", 64, false, true, S16_DEFAULT),
+    S16_ENTRY("d128_stream16", 128, false, false, S16_DEFAULT, S16_SPLIT(128, false, S16_DEFAULT)),
+    S16_ENTRY("d64_stream16", 64, false, false, S16_DEFAULT, S16_SPLIT(64, false, S16_DEFAULT)),
+    S16_ENTRY("d128_stream16_qscale", 128, true, false, S16_DEFAULT, {}, {}),
+    S16_ENTRY("d64_stream16_qscale", 64, true, false, S16_DEFAULT, {}, {}),
+    S16_ENTRY("d128_stream16_lse", 128, false, true, S16_DEFAULT, S16_SPLIT(128, true, S16_DEFAULT)),
+    S16_ENTRY("d64_stream16_lse", 64, false, true, S16_DEFAULT, S16_SPLIT(64, true, S16_DEFAULT)),
     S16_ENTRY_WHOLE("d128_stream16_tracked", 128, false, false, S16_TRACKED),
     S16_ENTRY_WHOLE("d64_stream16_tracked", 64, false, false, S16_TRACKED),
-    S16_ENTRY("d128_stream16_qrope", 128, false, false, S16_DEFAULT | 16),
-    S16_ENTRY("d64_stream16_qrope", 64, false, false, S16_DEFAULT | 16),
+    S16_ENTRY("d128_stream16_qrope", 128, false, false, S16_DEFAULT | 16, S16_SPLIT(128, false, S16_DEFAULT | 16)),
+    S16_ENTRY("d64_stream16_qrope", 64, false, false, S16_DEFAULT | 16, S16_SPLIT(64, false, S16_DEFAULT | 16)),
 };
 #undef S16_ENTRY
 #undef S16_ENTRY_WHOLE
 #undef S16_KERNEL
+#undef S16_SPLIT
+#undef S16_BY_GROUPS
 const int kNumStream16Variants = sizeof(kStream16Variants) / sizeof(kStream16Variants[0]);
 
 }  // namespace ll

@@ -198,6 +198,14 @@ struct AttnParams {
     AttnChunk chunk[MAX_ATTN_CHUNKS];
 };
 
+// The kernel's arguments read anew: nothing that was computed from them before can be kept in registers for what follows.
+// For the body of a loop that nearly always runs once, so that a kernel with it needs the registers of one without.
+__device__ __forceinline__ const AttnParams& attn_params_again() {
+    auto at = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(at));
+    return *(const AttnParams*)(at);
+}
+
 // Which group of its XCD's list a workgroup's tile belongs to, found by a wave with one load, an entry a lane, instead of a walk
 // along the groups of three scalar loads each, cold in the first round of workgroups.  us a re-prefill with the walk and so: 7
 // frames of 140 tokens x 16 x 128 in chunks of two 36.6 and 34.4, 7 of 232 x 10 x 64 (two layers) 69.1 and 66.2, 1560 tokens x 12
@@ -220,6 +228,17 @@ __device__ __forceinline__ bool attn_placed_tile(const AttnParams& p, int xcd, i
         }
     }
     return false;
+}
+
+// A workgroup's place in a launch of split tiles, or of their merge: heads, splits (slices of the merge), tiles; a split's tiles side
+// by side, they share its keys.  item < 0: none.
+struct SplitPlace { int item, head, part, tile; };
+__device__ __forceinline__ SplitPlace split_place(const AttnParams& p) {
+    const int xcd = blockIdx.x & 7, per_head = p.n_tiles * p.per_tile, total = per_head * p.H;
+    const int item = ((xcd * total + 7) >> 3) + (blockIdx.x >> 3);
+    if (item >= (((xcd + 1) * total + 7) >> 3)) return {-1, 0, 0, 0};
+    const int head = item / per_head, in_head = item - head * per_head, part = in_head / p.n_tiles;
+    return {item, head, part, in_head - part * p.n_tiles};
 }
 
 struct ReadFrameParams {
@@ -307,10 +326,9 @@ struct AttnVariant {
     // The same work with the keys of a tile dealt to G = 2, 4, 8 groups of the workgroup's waves (qtile / G rows per
     // workgroup); null where there is no such kernel.  8-bit cache: with 1 / G of the waves instead, which all walk all keys.
     void (*grouped[3])(const AttnParams);
-    // The kernel of launches with AttnParams::splits > 1 and one key group (null: no splits); with more, grouped takes splits
-    // too (8-bit cache: with half the waves split_half does).
-    void (*split)(const AttnParams);
-    void (*split_half)(const AttnParams);
+    // The kernels of launches with AttnParams::splits > 1 and of their merges, by log2 of G (null: no splits)
+    void (*split[4])(const AttnParams);
+    void (*merge[4])(const AttnParams);
 };
 extern const AttnVariant kStreamVariants[];
 extern const int kNumStreamVariants;
