@@ -478,6 +478,16 @@ hipError_t split_pool_address(SplitPool** pool) {
     return hipSuccess;
 }
 
+// A call whose splits were launched and whose merge could not be: nobody is to read its partial results.  Gives back the slots
+// that have its token (a word with a token is the call's own) once its stream is through; waits for that, as only this case may.
+static void split_forget(SplitPool* pool, unsigned long long token, hipStream_t s) {
+    unsigned long long owner[SPLIT_SLOTS];
+    const unsigned long long nobody = 0;
+    if (hipStreamSynchronize(s) != hipSuccess || hipMemcpy(owner, pool->owner, sizeof(owner), hipMemcpyDeviceToHost) != hipSuccess) return;
+    for (int i = 0; i < SPLIT_SLOTS; ++i)
+        if (owner[i] >> 24 == token) (void)hipMemcpy(&pool->owner[i], &nobody, sizeof(nobody), hipMemcpyHostToDevice);
+}
+
 constexpr int GROUPED_LDS_BYTES = 128 * 1024;    // GroupRing: 128 KB / G at most per group; the groups' results fit too
 
 hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
@@ -594,23 +604,24 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         attr_set[variant - 1][which] = e == hipSuccess;
         return e;
     };
+    auto launch = [&](void (*kernel)(const AttnParams), int blocks) {
+        void* args[] = {&p};
+        return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(blocks), threads, args, lds_bytes, s);
+    };
     if (p.splits == 1) {
         void (*const kernel)(const AttnParams) = log_g == 0 ? v.kernel : v.grouped[log_g - 1];
         const hipError_t e = prepare(kernel, log_g);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(grid), threads, lds_bytes, s, p);
-    } else {
-        hipError_t e = prepare(v.split[log_g], 4 + log_g);
-        if (e == hipSuccess) e = prepare(v.merge[log_g], 8 + log_g);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(v.split[log_g], dim3(grid), threads, lds_bytes, s, p);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        p.merge = 1;
-        p.per_tile = ((16 >> log_g) + p.slice_blocks - 1) / p.slice_blocks;
-        hipLaunchKernelGGL(v.merge[log_g], dim3((total * p.per_tile + 7) / 8 * 8), threads, lds_bytes, s, p);
+        return e != hipSuccess ? e : launch(kernel, grid);
     }
-    return hipGetLastError();
+    hipError_t e = prepare(v.split[log_g], 4 + log_g);
+    if (e == hipSuccess) e = prepare(v.merge[log_g], 8 + log_g);
+    if (e == hipSuccess) e = launch(v.split[log_g], grid);
+    if (e != hipSuccess) return e;
+    p.merge = 1;
+    p.per_tile = ((16 >> log_g) + p.slice_blocks - 1) / p.slice_blocks;
+    e = launch(v.merge[log_g], (total * p.per_tile + 7) / 8 * 8);
+    if (e != hipSuccess) split_forget(p.pool, p.token, s);
+    return e;
 }
 
 }  // namespace ll
