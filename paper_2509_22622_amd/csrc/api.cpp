@@ -3,6 +3,7 @@
 // the error strings.  The prompt side is in api_prompt.cpp, the train-time rule in api_clip.cpp, the kernel-variant
 // knob and the diagnostic probe (include/longlive_diag.h) in api_diag.cpp.  No device memory is allocated here; everything lives in the buffer
 // the caller handed to ll_cache_create.
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -32,6 +33,7 @@ struct ll_cache {
     std::vector<double> inv_freq_t;   // host copy of the frame-axis frequencies (the device copy is rope.inv_freq_t)
     std::vector<LayerIndex> layer;
     std::vector<int> staged_t_row;    // per layer: row of t_table at which the staged chunk's frames begin
+    mutable std::atomic<uint64_t> last_split;         // variant << 48 | rows << 16 | groups << 8 | splits (streamed_split); 0: none
 };
 
 static thread_local std::string g_err;
@@ -247,41 +249,49 @@ static uint8_t* layer_v8(const ll_cache* c, int layer) {
     return layer_k8(c, layer) + c->kblocks * KBLOCK8 * c->D;
 }
 
-// Enqueue the rotary + cache write of `n` frames whose absolute indices are frames[i];
-// rows of q/k/v are consecutive frames.
+extern "C++" {
+// Enqueue the rotary + cache write of `n` <= N frames whose absolute indices are frames[base + i], rows of q/k/v being the frames
+// from 0 on (base of them in launches before).
+template <int N>
+static hipError_t enqueue_frames(ll_cache* c, int layer, const int64_t* frames, int base, int n, const void* q, const void* k,
+                                 const void* v, void* q_out, hipStream_t s) {
+    const int64_t frame_elems = int64_t(c->g.P) * c->H * c->D;
+    AppendArgs<N> p{};
+    p.q = q ? static_cast<const uint16_t*>(q) + base * frame_elems : nullptr;       // null: keys and values only
+    p.k = static_cast<const uint16_t*>(k) + base * frame_elems;
+    p.v = static_cast<const uint16_t*>(v) + base * frame_elems;
+    p.q_scale = float(1.4426950408889634 / std::sqrt(double(c->D)));
+    if (c->fmt) {
+        p.q8_out = static_cast<uint8_t*>(q_out) + base * frame_elems;
+        p.k8_cache = layer_k8(c, layer); p.v8_cache = layer_v8(c, layer);
+        p.q_scale = std::ldexp(p.q_scale, c->k_exp);
+        p.k_mul = std::ldexp(1.0f, -c->k_exp); p.v_mul = std::ldexp(1.0f, -c->v_exp);
+    } else {
+        p.q_out = q_out ? static_cast<uint16_t*>(q_out) + base * frame_elems : nullptr;
+        p.k_cache = layer_k(c, layer); p.v_cache = layer_v(c, layer);
+        if (base + n <= c->t_stride / MAX_T_PAIRS) p.t_table_out = c->t_table + layer * c->t_stride + base * MAX_T_PAIRS;
+    }
+    p.head_stride = c->head_stride;
+    p.rope = c->rope;
+    p.H = c->H; p.D = c->D; p.P = c->g.P; p.grid_w = c->grid_w;
+    p.n_frames = n;
+    p.seg_begin[0] = 0;
+    for (int i = 0; i < n; ++i) {
+        p.slot[i] = slot_of_frame(c->g, frames[base + i]);
+        const int nseg = int((p.slot[i] % KBLOCK + c->g.P + KBLOCK - 1) / KBLOCK);        // 32 slots each, of either cache
+        p.seg_begin[i + 1] = p.seg_begin[i] + nseg;
+    }
+    set_frame_rotation(p, frames + base, c->inv_freq_t.data());
+    return c->fmt ? launch_append8(p, s) : launch_append(p, s);
+}
+}  // extern "C++"
+// The same for any number of frames; rows of q/k/v are consecutive frames.
 static ll_status enqueue_append(ll_cache* c, int layer, const int64_t* frames, int n, const void* q, const void* k,
                                 const void* v, void* q_out, hipStream_t s) {
-    const int64_t frame_elems = int64_t(c->g.P) * c->H * c->D;
     for (int base = 0; base < n; base += MAX_APPEND_FRAMES) {
-        AppendParams p{};
         const int m = std::min(MAX_APPEND_FRAMES, n - base);
-        p.q = q ? static_cast<const uint16_t*>(q) + base * frame_elems : nullptr;       // null: keys and values only
-        p.k = static_cast<const uint16_t*>(k) + base * frame_elems;
-        p.v = static_cast<const uint16_t*>(v) + base * frame_elems;
-        p.q_scale = float(1.4426950408889634 / std::sqrt(double(c->D)));
-        if (c->fmt) {
-            p.q8_out = static_cast<uint8_t*>(q_out) + base * frame_elems;
-            p.k8_cache = layer_k8(c, layer); p.v8_cache = layer_v8(c, layer);
-            p.q_scale = std::ldexp(p.q_scale, c->k_exp);
-            p.k_mul = std::ldexp(1.0f, -c->k_exp); p.v_mul = std::ldexp(1.0f, -c->v_exp);
-        } else {
-            p.q_out = q_out ? static_cast<uint16_t*>(q_out) + base * frame_elems : nullptr;
-            p.k_cache = layer_k(c, layer); p.v_cache = layer_v(c, layer);
-            if (base + m <= c->t_stride / MAX_T_PAIRS) p.t_table_out = c->t_table + layer * c->t_stride + base * MAX_T_PAIRS;
-        }
-        p.head_stride = c->head_stride;
-        p.rope = c->rope;
-        p.H = c->H; p.D = c->D; p.P = c->g.P; p.grid_w = c->grid_w;
-        p.n_frames = m;
-        p.seg_begin[0] = 0;
-        for (int i = 0; i < m; ++i) {
-            p.frame[i] = frames[base + i];
-            p.slot[i] = slot_of_frame(c->g, frames[base + i]);
-            const int nseg = int((p.slot[i] % KBLOCK + c->g.P + KBLOCK - 1) / KBLOCK);        // 32 slots each, of either cache
-            p.seg_begin[i + 1] = p.seg_begin[i] + nseg;
-        }
-        set_frame_rotation(p, c->inv_freq_t.data());
-        hipError_t e = c->fmt ? launch_append8(p, s) : launch_append(p, s);
+        hipError_t e = m <= FEW_APPEND_FRAMES ? enqueue_frames<FEW_APPEND_FRAMES>(c, layer, frames, base, m, q, k, v, q_out, s)
+                                              : enqueue_frames<MAX_APPEND_FRAMES>(c, layer, frames, base, m, q, k, v, q_out, s);
         if (e != hipSuccess) return hip_fail(e, "append kernel launch");
     }
     return LL_OK;
@@ -309,6 +319,17 @@ struct AttnLaunches { int variant = 0; std::vector<AttnParams> params; };
 // only): bf16 cache, the default kernel, no chunk whose sink is scored with turned-back queries.
 static bool can_turn_queries(const ll_cache* c, const std::vector<ChunkWork>& work);
 
+// Key groups and splits of a streamed chunk of `rows` rows over a full window of `kblocks`.  The answer follows from the rows and
+// the handle's geometry, and a handle keeps the last one: to look for it takes up to 1 us of a call's 8 on the host.
+static AttnSplit streamed_split(const ll_cache* c, int variant, int rows, int kblocks) {
+    const uint64_t key = uint64_t(variant) << 48 | uint64_t(rows) << 16;
+    const uint64_t last = c->last_split.load(std::memory_order_relaxed);
+    if ((last & ~uint64_t(0xFFFF)) == key) return {int(last >> 8 & 0xFF), int(last & 0xFF)};
+    const AttnSplit split = attn_split(variant, c->H, 1, &rows, &kblocks);
+    c->last_split.store(key | uint64_t(split.groups) << 8 | uint64_t(split.splits), std::memory_order_relaxed);
+    return split;
+}
+
 // raw_q: q holds the queries before the rotary embedding; chunk i's frames are rows work[i].t_row .. of the table the
 // cache write of the same call (or, for a staged chunk, the last ll_chunk_append) left for the layer.
 static ll_status build_attn(const ll_cache* c, int layer, const std::vector<ChunkWork>& work, const void* q, void* out,
@@ -335,7 +356,7 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
         // (a streamed chunk may also take splits; a re-prefill, whose launch is larger, would pay for them: 16 single-frame
         // chunks of 190 x 4 x 128 would take 3 times as long, so there a chunk whose tiles split has other roundings.)
         if (rows != rows_before) {                                    // (most of a re-prefill's chunks are alike)
-            const AttnSplit split = attn_split(variant, c->H, 1, &rows, &kblocks);
+            const AttnSplit split = streamed_split(c, variant, rows, kblocks);
             all_split = all_split && split.splits > 1;
             groups_before = streamed ? split.groups * 256 + split.splits : attn_key_groups(variant, c->H, 1, &rows, &kblocks) * 256 + 1;
             rows_before = rows;
@@ -347,7 +368,7 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
     if (!streamed && all_split)
         for (auto& o : order) o.first = 1;
     // longest key sets first: they bound the launch
-    std::stable_sort(order.begin(), order.end(), [&](const std::pair<int, int>& a, const std::pair<int, int>& b) {
+    if (order.size() > 1) std::stable_sort(order.begin(), order.end(), [&](const std::pair<int, int>& a, const std::pair<int, int>& b) {
         return a.first != b.first ? a.first < b.first : keys(a.second) > keys(b.second);
     });
     for (size_t base = 0, end; base < work.size(); base = end) {

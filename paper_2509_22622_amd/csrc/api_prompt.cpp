@@ -93,7 +93,7 @@ ll_status ll_prompt_recache(ll_prompt* prompt, int layer, const void* k, const v
     if (prompt->dev) {
         // The cache-write kernel of ll_chunk_append with one "frame" of n_tokens tokens at slot 0, no queries, and
         // its rotary step switched off: the keys pass unchanged bit for bit.
-        AppendParams p{};
+        FewAppendParams p{};
         p.k = static_cast<const uint16_t*>(k); p.v = static_cast<const uint16_t*>(v);
         p.k_cache = prompt_k(prompt, layer); p.v_cache = prompt_v(prompt, layer);
         p.head_stride = prompt->head_stride;
@@ -101,7 +101,7 @@ ll_status ll_prompt_recache(ll_prompt* prompt, int layer, const void* k, const v
         p.identity = 1;
         p.H = prompt->H; p.D = prompt->D; p.P = n_tokens; p.grid_w = n_tokens;
         p.n_frames = 1;
-        p.frame[0] = 0; p.slot[0] = 0;
+        p.slot[0] = 0;
         p.seg_begin[0] = 0; p.seg_begin[1] = (n_tokens + KBLOCK - 1) / KBLOCK;
         hipError_t e = launch_append(p, static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return hip_fail(e, "prompt cache-write kernel launch");

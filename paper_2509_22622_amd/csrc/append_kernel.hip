@@ -196,24 +196,19 @@ __global__ __launch_bounds__(256) void ll_append_kernel(const AppendArgs<FRAMES>
     }
 }
 
-hipError_t launch_append(const AppendParams& p, hipStream_t s) {
+template <int FRAMES>
+static hipError_t launch(const AppendArgs<FRAMES>& p, hipStream_t s) {
     const int nseg = p.seg_begin[p.n_frames];
     if (nseg <= 0) return hipSuccess;
-    if (p.n_frames > MAX_APPEND_FRAMES || (p.identity == 0 && p.rope.n_t > MAX_T_PAIRS)) return hipErrorInvalidValue;
+    if (p.n_frames > FRAMES || (p.identity == 0 && p.rope.n_t > MAX_T_PAIRS)) return hipErrorInvalidValue;
     if (int64_t(nseg) * p.H > 0x7FFFFFFF) return hipErrorInvalidValue;
-    dim3 grid(unsigned(nseg) * unsigned(p.H)), block(256);
     if (p.D != 128 && p.D != 64) return hipErrorInvalidValue;
-    if (p.n_frames <= FEW_APPEND_FRAMES) {
-        const auto few = few_frames(p);
-        if (p.D == 128) hipLaunchKernelGGL((ll_append_kernel<128, FEW_APPEND_FRAMES>), grid, block, 0, s, few);
-        else hipLaunchKernelGGL((ll_append_kernel<64, FEW_APPEND_FRAMES>), grid, block, 0, s, few);
-    } else {
-        const AppendArgs<MAX_APPEND_FRAMES>& all = p;
-        if (p.D == 128) hipLaunchKernelGGL((ll_append_kernel<128, MAX_APPEND_FRAMES>), grid, block, 0, s, all);
-        else hipLaunchKernelGGL((ll_append_kernel<64, MAX_APPEND_FRAMES>), grid, block, 0, s, all);
-    }
-    return hipGetLastError();
+    void (*const kernel)(const AppendArgs<FRAMES>) = p.D == 128 ? ll_append_kernel<128, FRAMES> : ll_append_kernel<64, FRAMES>;
+    void* args[] = {const_cast<AppendArgs<FRAMES>*>(&p)};        // (not by value: 2 to 3 KB)
+    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(unsigned(nseg) * unsigned(p.H)), dim3(256), args, 0, s);
 }
+hipError_t launch_append(const AppendParams& p, hipStream_t s) { return launch(p, s); }
+hipError_t launch_append(const FewAppendParams& p, hipStream_t s) { return launch(p, s); }
 
 // Copy one frame's K (already rotated) and V out of the cache layout into [P, H, D].
 __global__ __launch_bounds__(256) void ll_read_frame_kernel(const ReadFrameParams p) {

@@ -96,26 +96,15 @@ struct AppendArgs : AppendHead {
     int64_t slot[N];                                            // first token slot
     int seg_begin[N + 1];                                       // prefix sum of segments (the part of a frame in 32 slots)
 };
-struct AppendParams : AppendArgs<MAX_APPEND_FRAMES> {
-    int64_t frame[MAX_APPEND_FRAMES];                           // absolute frame index (input of set_frame_rotation)
-};
-inline AppendArgs<FEW_APPEND_FRAMES> few_frames(const AppendParams& p) {      // p.n_frames <= FEW_APPEND_FRAMES
-    AppendArgs<FEW_APPEND_FRAMES> few;
-    static_cast<AppendHead&>(few) = p;
-    for (int i = 0; i < FEW_APPEND_FRAMES; ++i) {
-        for (int j = 0; j < MAX_T_PAIRS; ++j) few.t_cs[i][j] = p.t_cs[i][j];
-        few.slot[i] = p.slot[i];
-        few.seg_begin[i] = p.seg_begin[i];
-    }
-    few.seg_begin[FEW_APPEND_FRAMES] = p.seg_begin[FEW_APPEND_FRAMES];
-    return few;
-}
+using AppendParams = AppendArgs<MAX_APPEND_FRAMES>;
+using FewAppendParams = AppendArgs<FEW_APPEND_FRAMES>;
 
-// Fill p.t_cs from p.frame[0 .. n_frames) and the host copy of the frame-axis frequencies (p.rope.n_t of them).
-inline void set_frame_rotation(AppendParams& p, const double* inv_freq_t_host) {
+// Fill p.t_cs for frames with absolute indices frames[0 .. n_frames) from the host copy of the frame-axis frequencies (p.rope.n_t).
+template <int N>
+inline void set_frame_rotation(AppendArgs<N>& p, const int64_t* frames, const double* inv_freq_t_host) {
     for (int i = 0; i < p.n_frames; ++i)
         for (int j = 0; j < p.rope.n_t && j < MAX_T_PAIRS; ++j) {
-            const double a = double(p.frame[i]) * inv_freq_t_host[j];
+            const double a = double(frames[i]) * inv_freq_t_host[j];
             p.t_cs[i][j] = make_float2(float(std::cos(a)), float(std::sin(a)));
         }
 }
@@ -382,7 +371,9 @@ bool attn_resident_fits(int D, int n_kblocks);
 hipError_t launch_attn_resident(const ResidentParams& p, int D, hipStream_t s);
 
 hipError_t launch_append(const AppendParams& p, hipStream_t s);
+hipError_t launch_append(const FewAppendParams& p, hipStream_t s);
 hipError_t launch_append8(const AppendParams& p, hipStream_t s);
+hipError_t launch_append8(const FewAppendParams& p, hipStream_t s);
 hipError_t launch_read_frame8(const ReadFrameParams& p, hipStream_t s);
 hipError_t launch_attn(const AttnParams& p, int variant, hipStream_t s);
 hipError_t launch_read_frame(const ReadFrameParams& p, hipStream_t s);

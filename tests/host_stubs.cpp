@@ -20,7 +20,9 @@ int attn_variant_short_keys(int D) { return D == 128 ? 1 : 2; }
 bool attn_variant_applies_scale(int) { return true; }
 bool attn_variant_out_frag(int) { return true; }
 hipError_t launch_append(const AppendParams&, hipStream_t) { return hipSuccess; }
+hipError_t launch_append(const FewAppendParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_append8(const AppendParams&, hipStream_t) { return hipSuccess; }
+hipError_t launch_append8(const FewAppendParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_read_frame(const ReadFrameParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_read_frame8(const ReadFrameParams&, hipStream_t) { return hipSuccess; }
 hipError_t launch_attn(const AttnParams&, int, hipStream_t) { return hipSuccess; }
