@@ -1082,8 +1082,8 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     if (t.at.item < 0 || t.at.part >= t.splits) return;          // uniform, as all of this
     const int readers = t.splits > 1 ? (t.rows + t.slice_rows - 1) / t.slice_rows : 0;
     S16Claim claim{p, &slot_lds, t.at.item, readers, 0};
+    s16_shift_table(p, t.ch, shift_cs);          // (before the claim: its load would wait for that)
     if (tid == 0 && readers > 0) claim.seen = split_try(p.pool, t.at.item, 0, p.token, readers);
-    s16_shift_table(p, t.ch, shift_cs);
     const int row_block = s16_row_block<G>(wave), q0 = t.row0 + row_block * 32, u0 = G > 1 ? wave / NW * PER_WAVE : 0;
     S16State<D> st;
     if (!s16_share<D, SCHED, G>(p, t, tid, q0, t.at.part, lds, shift_cs, ml, st, claim) || q0 >= t.ch.q_end) return;
