@@ -204,8 +204,7 @@ static hipError_t launch(const AppendArgs<FRAMES>& p, hipStream_t s) {
     if (int64_t(nseg) * p.H > 0x7FFFFFFF) return hipErrorInvalidValue;
     if (p.D != 128 && p.D != 64) return hipErrorInvalidValue;
     void (*const kernel)(const AppendArgs<FRAMES>) = p.D == 128 ? ll_append_kernel<128, FRAMES> : ll_append_kernel<64, FRAMES>;
-    void* args[] = {const_cast<AppendArgs<FRAMES>*>(&p)};        // (not by value: 2 to 3 KB)
-    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(unsigned(nseg) * unsigned(p.H)), dim3(256), args, 0, s);
+    return launch_kernel(reinterpret_cast<const void*>(kernel), dim3(unsigned(nseg) * unsigned(p.H)), dim3(256), &p, 0, s);
 }
 hipError_t launch_append(const AppendParams& p, hipStream_t s) { return launch(p, s); }
 hipError_t launch_append(const FewAppendParams& p, hipStream_t s) { return launch(p, s); }

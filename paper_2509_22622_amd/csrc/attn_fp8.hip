@@ -21,7 +21,7 @@
 // Launches of few rows and heads: a 256-row tile of each head is less than the chip has CUs, and every workgroup walks all keys
 // at the pace of two waves per SIMD (0.8 us a kblock at head_dim 128, exponentials and MFMAs in turn).  They take narrower tiles
 // (0.55 us with one wave per SIMD) and, below that, several workgroups per tile (split.h).  us: 980 rows x 50 kblocks x 2 heads x
-// 128 52 -> 26; 300 x 36 x 24 x 128 42 -> 28; the rule and more figures are at attn_split in attn_kernel.hip.
+// 128 50 -> 29; 300 x 36 x 24 x 128 42 -> 28; the rule and more figures are at attn_split in attn_kernel.hip.
 //
 // The scaled form of the MFMA is used with both scales 1 (E8M0 code 127).  The compiler may place its result on
 // top of an operand that dies at the instruction, which this multi-pass instruction does not tolerate (wrong

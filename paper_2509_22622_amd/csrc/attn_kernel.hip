@@ -384,7 +384,7 @@ int attn_key_groups(int variant, int H, int n_chunks, const int* rows, const int
     return 1 << key_groups_log2(*ll::variant(variant), H, n_chunks, [&](int c) { return rows[c]; }, [&](int c) { return kblocks[c]; });
 }
 
-// The same where tiles may also be dealt to several workgroups, merged by a second launch (split.h).  What a launch
+// The same where tiles may also be dealt to several workgroups, merged by a second kernel (split.h).  What a launch
 // takes is modelled in us: a round of workgroups takes its steps, each the longer the more workgroups run (LDS and L2
 // traffic), and the way in and out; a merge, its launch and the partial results' way through memory.
 struct SplitModel {
@@ -394,16 +394,17 @@ struct SplitModel {
 // bf16 cache: fitted to 350 timings of 26 shapes (1 to 24 heads, 96 to 4680 rows, 30 to 732 kblocks; 6 % off in the mean; the
 // pair it picks was 1 % slower than the best).  The groups alone stay as above, and a split has to be 10 % cheaper than they
 // are, 15 % where half the chip is at work without one.  us without and with splits at head_dim 128: 190 rows x 143 kblocks x 4
-// heads 41 and 20 (4 groups x 12), 720 x 128 x 5 36 and 23 (4 x 4), 1560 x 634 x 12 227 and 172 (1 x 3), 4680 x 732 x 2 162
-// and 109 (1 x 6); 1170 x 183 x 12 takes none (51, best split 52).
+// heads 34 and 19 (4 groups x 9), 720 x 143 x 5 40 and 24 (4 x 4), 1560 x 634 x 12 206 and 165 (1 x 3), 4680 x 732 x 2 163
+// and 104 (1 x 6); 1170 x 183 x 12 takes none (50).
 static constexpr SplitModel kSplitModel[2] = {
     {{{0.52, 0.31}, {0.63, 0.21}, {0.82, 0.14}, {0, 0}}, {{0.52, 0.31}, {0.63, 0.21}, {0.82, 0.14}, {0, 0}}, 7.1, 7.1, 3.7, 0.22, 0.25},
     {{{0.38, 0.14}, {0.41, 0.10}, {0.47, 0.05}, {0.42, 0.39}}, {{0.38, 0.14}, {0.41, 0.10}, {0.47, 0.05}, {0.42, 0.39}}, 5.0, 5.0, 3.7, 0.22, 0.26}};
 // 8-bit cache: no key groups, but workgroups of half and a quarter of the waves, which keep every row's bits (a wave that
 // has its SIMD for itself takes two thirds of the time), and splits, whose steps take longer (weights of two terms).  430
-// timings of 27 shapes (6 % off in the mean; the pick 2 % slower than the best).  Narrow tiles have to be 5 % cheaper than wide
-// ones, splits 10 %.  us at head_dim 128, 256-row tiles and pick: 980 rows x 50 kblocks of 64 x 2 heads 52 and 26 (128-row tiles, 8
-// splits), 300 x 36 x 24 42 and 28 (64), 1170 x 80 x 16 77 and 54 (128), 4680 x 366 x 2 292 and 109 (256, 6).
+// timings of 27 shapes (6 % off in the mean; the pick 2 % slower than the best, 4 % over the eleven of
+// profiles/attn_split_times.txt).  Narrow tiles have to be 5 % cheaper than wide ones, splits 10 %.  us at head_dim 128, 256-row
+// tiles and pick: 980 rows x 50 kblocks of 64 x 2 heads 50 and 29 (128-row tiles, 10 splits; 27 with 8), 300 x 22 x 24 30 and 20 (64), 1170 x
+// 80 x 16 74 and 54 (128), 4680 x 366 x 2 285 and 108 (256, 6).
 static constexpr SplitModel kSplitModel8[2] = {
     {{{0.82, 0.0}, {0.545, 0.03}, {0.494, 0.03}, {0, 0}}, {{1.23, 0.15}, {0.864, 0.03}, {0, 0}, {0, 0}}, 9.3, 6.7, 6.3, 0.58, 0.19},
     {{{0.66, 0.0}, {0.436, 0.05}, {0.373, 0.52}, {0, 0}}, {{1.00, 0.14}, {0.618, 0.46}, {0, 0}, {0, 0}}, 8.7, 3.3, 8.0, 0.26, 0.18}};
@@ -605,8 +606,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         return e;
     };
     auto launch = [&](void (*kernel)(const AttnParams), int blocks) {
-        void* args[] = {&p};
-        return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(blocks), threads, args, lds_bytes, s);
+        return launch_kernel(reinterpret_cast<const void*>(kernel), dim3(blocks), threads, &p, lds_bytes, s);
     };
     if (p.splits == 1) {
         void (*const kernel)(const AttnParams) = log_g == 0 ? v.kernel : v.grouped[log_g - 1];

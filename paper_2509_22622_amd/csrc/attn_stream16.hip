@@ -38,9 +38,9 @@
 // loads three steps ahead instead of one per two steps and one period ahead was slower (head_dim 64, G = 2: 55 against 48).
 // A streamed chunk may also have its tiles' keys dealt to several workgroups (rule: attn_split in attn_kernel.hip), which need
 // not share one CU's LDS and its 64 bytes a clock from L2 and whose rings can be long again: G * splits shares of a tile's
-// keys, partial results through the slots of split.h, and a second launch of the same kernel that adds them up.  What bounds
+// keys, partial results through the slots of split.h, and a second kernel that adds them up.  What bounds
 // it then: some 7 us of a workgroup around its steps, the merge's launch, and the partial results' way (0.25 us per MB there
-// and back).  us without and with: 190 rows x 143 kblocks x 4 heads x 128 41 -> 20, 1560 x 634 x 12 x 128 227 -> 172.
+// and back).  us without and with: 190 rows x 143 kblocks x 4 heads x 128 34 -> 19, 1560 x 634 x 12 x 128 206 -> 165.
 #include "kernels.h"
 #include "lds_plan.h"
 #include "split.h"

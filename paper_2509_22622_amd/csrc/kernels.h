@@ -164,7 +164,7 @@ struct AttnParams {
     int n_t;
     int key_groups;              // key groups per tile (AttnVariant::grouped); 0: chosen for the launch,
     bool may_split;              // and splits with them
-    // A tile's keys dealt to `splits` workgroups, whose partial results a second launch of the kernel merges (split.h);
+    // A tile's keys dealt to `splits` workgroups, whose partial results a second kernel merges (split.h);
     // chunks of fewer kblocks take fewer.  The rest is filled in by launch_attn.
     int splits;
     int merge;                   // this launch is the merge: a workgroup takes slice_blocks 16-row blocks of a tile
@@ -370,6 +370,14 @@ struct ResidentParams {
 bool attn_resident_fits(int D, int n_kblocks);
 hipError_t launch_attn_resident(const ResidentParams& p, int D, hipStream_t s);
 
+// A launch with its arguments by pointer (they are 2 to 3 KB).  A failure is the caller's to report: it does not stay behind as the
+// thread's last error, for a later call of somebody else's to find.
+inline hipError_t launch_kernel(const void* kernel, dim3 grid, dim3 block, const void* args, size_t lds_bytes, hipStream_t s) {
+    void* list[] = {const_cast<void*>(args)};
+    const hipError_t e = hipLaunchKernel(kernel, grid, block, list, lds_bytes, s);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
 hipError_t launch_append(const AppendParams& p, hipStream_t s);
 hipError_t launch_append(const FewAppendParams& p, hipStream_t s);
 hipError_t launch_append8(const AppendParams& p, hipStream_t s);

@@ -13,6 +13,7 @@
 static ll::SplitPool* pool;
 static int launches, fail_at, copies;            // fail_at: the launch that fails, counted from 1
 static bool in_attention;
+static hipError_t last_error = hipSuccess;
 
 extern "C" {
 hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStream_t) {
@@ -20,7 +21,9 @@ hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStre
     const ll::AttnParams* p = static_cast<const ll::AttnParams*>(args[0]);
     if (!p->merge)                               // two of the workgroups have claimed their slots
         for (int item : {5, 130}) pool->owner[item] = p->token << 24 | unsigned(item << 8 | 1);
-    return ++launches == fail_at ? hipErrorLaunchFailure : hipSuccess;
+    const hipError_t e = ++launches == fail_at ? hipErrorLaunchFailure : hipSuccess;
+    if (e != hipSuccess) last_error = e;
+    return e;
 }
 hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) {
     auto in_pool = [](const void* at) { return at >= pool && at < pool + 1; };
@@ -32,7 +35,11 @@ hipError_t hipMemcpy(void* dst, const void* src, size_t n, hipMemcpyKind) {
 hipError_t hipMemset(void*, int, size_t) { return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** at, const void*) { *at = pool; return hipSuccess; }
@@ -57,20 +64,23 @@ int main(int, char** argv) {
     CHECK(create(1, 4, 128, 190, 3, 20, 1, 10, 19, 10000.f, device, bytes(1, 4, 128, 190, 3, 20, 1), &cache) == LL_OK);
     for (int f = 0; f < 25; ++f) CHECK(append(cache, 0, f, 1, device, device, device, device, nullptr) == LL_OK);
     in_attention = true;
+    last_error = hipErrorInvalidValue;           // an earlier call's: nothing here is to stumble over it
     const unsigned long long other = 1ull << 50 | 7 << 8 | 2;        // another call's
     pool->owner[6] = other;
     CHECK(attend(cache, 0, device, device, nullptr) == LL_OK);
     CHECK(launches == 2 && copies == 0);
+    last_error = hipSuccess;
     pool->owner[5] = pool->owner[130] = 0;       // (the merge would have)
     launches = 0;
     fail_at = 1;
     CHECK(attend(cache, 0, device, device, nullptr) == LL_ERR_HIP);
     CHECK(launches == 1);                        // no merge without its splits
+    CHECK(last_error == hipSuccess);             // reported, and not left for somebody else's call to find
     pool->owner[5] = pool->owner[130] = 0;
     launches = 0;
     fail_at = 2;
     CHECK(attend(cache, 0, device, device, nullptr) == LL_ERR_HIP);
-    CHECK(launches == 2);
+    CHECK(launches == 2 && last_error == hipSuccess);
     CHECK(pool->owner[5] == 0 && pool->owner[130] == 0 && pool->owner[6] == other);
     std::printf("slots given back\n");
     return 0;

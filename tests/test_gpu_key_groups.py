@@ -246,8 +246,8 @@ def test_narrow_backward_tiles(heads, grid, n_clip):
     (12, 128, (15, 26), 3, 3, 9, 12), (12, 64, (16, 19), 2, 2, 4, 6), (21, 128, (6, 19), 1, 2, 5, 6),
     (16, 64, (10, 16), 3, 3, 6, 9), (10, 64, (17, 23), 3, 2, 5, 7), (12, 128, (19, 33), 2, 2, 6, 8)])
 def test_prefill_equals_streaming_where_a_chunk_takes_key_groups(heads, head_dim, grid, chunk, sink, window, n_win):
-    """Streamed chunk by chunk or rebuilt in one call, a chunk's outputs are the same bits at every size: into how many key
-    groups its tiles are dealt depends on the chunk, not on the launch it is part of."""
+    """Streamed chunk by chunk or rebuilt in one call, the outputs of a chunk whose keys no call deals to several workgroups are the
+    same bits: into how many key groups its tiles are dealt depends on the chunk, not on the launch it is part of."""
     P, nf = grid[0] * grid[1], sink + n_win
     g = torch.Generator(device="cuda").manual_seed(P)
     q, k, v = (torch.empty((nf * P, heads, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(3))
@@ -255,6 +255,8 @@ def test_prefill_equals_streaming_where_a_chunk_takes_key_groups(heads, head_dim
     want, got = torch.empty_like(q), torch.empty_like(q)
     starts = [*range(0, sink, chunk), *range(sink, nf, chunk)]
     assert B.attn_key_groups(head_dim, heads, [(chunk * P, -(-(sink + window + chunk) * P // 32))]) > 1
+    for n in {end - f0 for f0, end in zip(starts, starts[1:] + [nf])}:
+        assert B.attn_split(head_dim, heads, n * P, -(-(sink + window + n) * P // 32))[1] == 1
     for f0, end in zip(starts, starts[1:] + [nf]):
         rows = slice(f0 * P, end * P)
         streamed.chunk_append(0, f0, end - f0, None, k[rows], v[rows], None)

@@ -363,3 +363,27 @@ def test_re_prefill_whose_chunks_all_split(heads, head_dim, grid, chunk, sink, n
             B.hold_split_slots(first, n, False)
         assert torch.equal(_bits(again), _bits(out)), (first, n)
     state["cache"].close()
+
+
+@pytest.mark.parametrize("kv_format, heads, head_dim, grid, chunk, sink, window, n_win", [
+    ("bf16", 4, 128, (10, 19), 1, 3, 20, 12), ("bf16", 3, 64, (16, 45), 1, 3, 16, 6), ("fp8_e4m3", 2, 128, (13, 23), 3, 2, 7, 8)])
+def test_re_prefill_beside_streaming_of_chunks_that_split(kv_format, heads, head_dim, grid, chunk, sink, window, n_win):
+    """Where a streamed chunk's tiles split, the re-prefill's rows have other roundings, and no more than that."""
+    P, nf = grid[0] * grid[1], sink + n_win
+    assert B.attn_split(head_dim, heads, chunk * P, -(-(sink + window + chunk) * P // (32 if kv_format == "bf16" else 64)), kv_format)[1] > 1
+    g = torch.Generator(device="cuda").manual_seed(P)
+    q, k, v = (torch.empty((nf * P, heads, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for _ in range(3))
+    streamed, rebuilt = (B.Cache(1, heads, head_dim, *grid, chunk, sink, window, kv_format=kv_format) for _ in range(2))
+    want, got = torch.empty_like(q), torch.empty_like(q)
+    starts = [*range(0, sink, chunk), *range(sink, nf, chunk)]
+    for f0, end in zip(starts, starts[1:] + [nf]):
+        rows = slice(f0 * P, end * P)
+        q_out = torch.empty(q[rows].shape, dtype=torch.bfloat16 if kv_format == "bf16" else torch.uint8, device="cuda")
+        streamed.chunk_append(0, f0, end - f0, q[rows], k[rows], v[rows], q_out)
+        streamed.sink_window_attn(0, q_out, want[rows])
+    rebuilt.recache_prefill(0, True, sink, n_win, q, k, v, got)
+    torch.cuda.synchronize()
+    streamed.close()
+    rebuilt.close()
+    # twice a path's 5e-3 (bf16), or one path's weights of 3 mantissa bits, 2.6 % of the 2-norm each, and the other's
+    assert _rel(got, want.double()) <= (1e-2 if kv_format == "bf16" else 3e-2)
