@@ -18,7 +18,15 @@
  *     work is enqueued on it and the call returns without synchronising.  Tensors
  *     are borrowed until the stream has passed the call.
  *   - The cache's device buffer is owned by the caller and must outlive the
- *     handle.  The library allocates no device memory.
+ *     handle.  The library allocates no device memory; it holds two static arrays
+ *     on each GPU it is used on, until the process ends: 85 MB (81 MiB) for partial results of
+ *     attention calls of few rows and heads, which deal a tile's keys to several
+ *     workgroups and merge their results in a second kernel, and the 36 MiB of
+ *     ll_recache_prefill_static.  All calls on a GPU, from any stream or thread, eager
+ *     or captured, share the first one; a call that finds no room in it takes longer.
+ *   - Results do not depend on what else the GPU is doing: a call repeated on the
+ *     same data gives the same bits.  (Two replays of one captured call must not overlap
+ *     in time: they write the same output.)
  *   - Host-side bookkeeping changes at call time, so calls for one layer must be
  *     made in program order; layers are independent of each other.
  *   - One handle = one video (batch 1, the paper's interactive setting).
@@ -145,6 +153,9 @@ ll_status ll_sink_window_attn_unrotated(ll_cache* cache, int layer, const void* 
  *   All non-sink frames held before are dropped.  include_sink == 0 keeps the sink K/V
  *   already held (LL_ERR_STATE if the sink is incomplete).  win_start >= S, 0 <= n_win <=
  *   W + C; n_win == 0 (the sink alone, include_sink != 0) requires win_start == S.
+ *   A chunk's rows of out are bit for bit those of the chunk when it is streamed wherever neither call deals a tile's keys to several
+ *   workgroups; where one does (few rows and heads, see ll_attn_split in longlive_diag.h) the two are sums in another order, and
+ *   for an 8-bit cache with weights of one and of two E4M3 terms.
  *   Afterwards the layer is as if those frames had been streamed: the last chunk
  *   is staged and the next ll_chunk_append must start at win_start + n_win (or repeat the
  *   last chunk's start).  Every check is made before anything is enqueued: a refused call leaves
