@@ -34,7 +34,7 @@
 // of its own (lds_plan.h: GroupRing), and the groups' results meet in LDS, so no memory outside the workgroup is
 // needed.  What bounds it: with 256 / G rows per kblock the LDS (fragment reads and ring writes, 144, 160 and 192 KB
 // per step at G = 1, 2, 4 and head_dim 128) and, with all CUs at work, L2 (12.5 TB/s at G = 4).  Measured, us: 270 rows x 43 kblocks x
-// 6 heads x 64: 25 -> 10 (G = 8); 1170 x 183 x 12 x 128: 121 -> 57 (G = 4); 1560 x 634 x 12 x 128: 361 -> 231 (G = 2).  One barrier per step with
+// 6 heads x 64: 25 -> 10 (G = 8); 1170 x 183 x 12 x 128: 121 -> 57 (G = 4; 52 with keys from memory, brought into L2 ahead: S16Touch); 1560 x 634 x 12 x 128: 361 -> 231 (G = 2).  One barrier per step with
 // loads three steps ahead instead of one per two steps and one period ahead was slower (head_dim 64, G = 2: 55 against 48).
 // A streamed chunk may also have its tiles' keys dealt to several workgroups (rule: attn_split in attn_kernel.hip), which need
 // not share one CU's LDS and its 64 bytes a clock from L2 and whose rings can be long again: G * splits shares of a tile's
@@ -159,9 +159,33 @@ struct S16Barrier {
 };
 using S16Unsplit = S16Barrier<0>;
 using S16NextShare = S16Barrier<1>;
+// `touch` (G > 1): the periods whose kblocks this tile brings into L2 (lds_plan.h: GroupRing).
+// Where the key set has S16_TOUCH_BYTES and more: a few layers of it do not fit the 256 MB of the last-level cache, so it comes from
+// memory.  us a call with the keys of many layers in turn, without and with: 1170 rows x 183 kblocks x 12 heads x 128 (36 MB)
+// 70 -> 52, x 293 107 -> 78, 800 x 125 x 16 51 -> 39, 1170 x 183 x 12 x 64 39 -> 33; a key set that is in that cache 50.8 and 49.8.
+// Below, where it may stay there, touching costs up to 3 us of 15 (720 x 113 x 3 x 64).
+constexpr int S16_TOUCH_BYTES = 16 << 20;
+struct S16Touch { int every = 1, first = 1 << 24; };             // (none)
+// The tiles of a head (and split) walk the same keys, more or less in step; those on one XCD take turns.  total: workgroups of a
+// launch that deals them out evenly, this one the idx-th of its XCD; 0 where whole (head, chunk) groups lie on an XCD.
+template <int D, int G>
+__device__ __forceinline__ S16Touch s16_take_turns(const AttnChunk& ch, int heads, int row0, int tile, int idx, int total) {
+    S16Touch t;
+    if (!GroupRing<D, G>::TOUCHES || ch.n_kblocks * heads < S16_TOUCH_BYTES / (4 * KBLOCK * D)) return t;
+    int before = tile - ch.tile_begin, after = (ch.q_end - 1 - row0) / (256 / G);
+    if (total > 0) {
+        const int xcd = blockIdx.x & 7, here = (((xcd + 1) * total + 7) >> 3) - ((xcd * total + 7) >> 3);
+        before = min(before, idx);
+        after = min(after, here - 1 - idx);
+    }
+    const int n = before + 1 + after;
+    t.every = n >= 8 ? 8 : n >= 4 ? 4 : n >= 2 ? 2 : 1;
+    t.first = before & (t.every - 1);
+    return t;
+}
 template <int D, bool QSCALE, int SCHED, int G, typename Gate>
 __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk& ch, int tid, int head, int q0, int vb, int ve,
-                                            int n_steps, char* lds, S16State<D>& st, const float2* shift_cs, Gate gate) {
+                                            int n_steps, char* lds, S16State<D>& st, const float2* shift_cs, Gate gate, S16Touch touch) {
     using Plan = LdsPlan16<D, (SCHED & 2) != 0>;
     constexpr bool TRACK = !(SCHED & 8);
     constexpr int KS = Plan::KS;                // K fragments per kblock = S^T slots (two MFMAs each)
@@ -189,6 +213,7 @@ __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk
     const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave = wave_wg % NW;              // among the waves that share this ring
     const int n = lane & 15, g = lane >> 4;
+    char* const lds_touch = lds + G * GR::BYTES + wave_wg * GR::LDS_TOUCH;
     if (G > 1) lds += (wave_wg / NW) * GR::BYTES;
 
     const int n_ranges = ch.n_ranges;
@@ -238,12 +263,27 @@ __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
                                          (__attribute__((address_space(3))) void*)(dst), 16, 0, 0);
     };
-    // end of a period of a group's ring: what this wave loaded for the next one has landed, and its K fragment reads,
-    // whose stages the loads issued next overwrite, have returned; then every wave's have
+    // the kblocks of the period that begins with step `first`, 128 bytes a lane (past the share's end the last one again)
+    auto touch_period = [&](int first) {
+        const int at = wave * 64 / D, in = (wave * 64 + lane) % D;              // kblock of the period, and 128 bytes of its K and V
+        const char* src = (in < D / 2 ? kbase : vbase) + in % (D / 2) * 128 + int64_t(S16_PHYS_KB(min(vb + first + at, ve - 1))) * KB_BYTES;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
+                                         (__attribute__((address_space(3))) void*)(lds_touch), 4, 0, 0);
+    };
+    int touch_in = touch.first, touch_at = (touch.first + 1 + GR::TOUCH_AHEAD) * PERIOD;        // periods to the next touch; its step
+    // end of a period of a group's ring: what this wave loaded for the next one has landed (but not what it touches now), and
+    // its K fragment reads, whose stages the loads issued next overwrite, have returned; then every wave's have
     auto group_handover = [&](u32x4 (&kf)[KS]) {
 #pragma unroll
         for (int k = 0; k < KS; ++k) s16_lds_wait<0>(kf[k]);
-        s16_wait_vmcnt<0>();
+        if (GR::TOUCHES && --touch_in < 0) {
+            touch_period(touch_at);
+            touch_in += touch.every;
+            touch_at += touch.every * PERIOD;
+            s16_wait_vmcnt<1>();
+        } else {
+            s16_wait_vmcnt<0>();
+        }
         if constexpr (NW > 1) __builtin_amdgcn_s_barrier();
     };
 
@@ -260,6 +300,8 @@ __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk
     } else {
 #pragma unroll
         for (int l = 0; l < LPW; ++l) issue_group(0, l);
+        if constexpr (GR::TOUCHES)
+            for (int t = touch.first; t < GR::TOUCH_AHEAD; t += touch.every) touch_period((t + 1) * PERIOD);
         // the same 16 bytes per lane as the reads of the permuted fragments below, straight from memory
         const unsigned k_lane = (g >> 1) * 1024 + ((g & 1) * 32 + (n & 7) + 16 * (n >> 3)) * 16;
         const char* k0 = kbase + int64_t(S16_PHYS_KB(vb)) * KB_BYTES + k_lane;
@@ -718,7 +760,7 @@ __device__ __forceinline__ void s16_store_unit(const AttnParams& p, int head, in
 // begin at q0.
 template <int D, bool QSCALE, int SCHED, int G, typename Gate>
 __device__ __forceinline__ bool s16_groups(const AttnParams& p, const AttnChunk& ch, int tid, int head, int q0, int split, int splits, char* lds,
-                                           const float2* shift_cs, float2 (*ml)[2][16], Gate gate) {
+                                           const float2* shift_cs, float2 (*ml)[2][16], Gate gate, S16Touch touch) {
     constexpr int NW = 8 / G, UNITS = D / 16 * 2;                // (dq, qb) blocks of a wave's O^T
     static_assert(UNITS % G == 0, "the O^T blocks must split over the groups");
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -734,13 +776,13 @@ __device__ __forceinline__ bool s16_groups(const AttnParams& p, const AttnChunk&
     }
     const bool works = q0 < ch.q_end && ve > vb;
     S16State<D> st;
-    if (!(works ? s16_segment<D, QSCALE, SCHED, G>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate)
+    if (!(works ? s16_segment<D, QSCALE, SCHED, G>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate, touch)
                 : s16_group_idle<D, G>(p, ch, tid, head, vb, ve, n_steps, lds, gate)))
         return false;
     if constexpr ((SCHED & 8) != 0) {
         const bool ran_away = works && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
         if (__syncthreads_or(ran_away)) {
-            if (works) s16_segment<D, QSCALE, SCHED & ~8, G>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, typename Gate::Again{});
+            if (works) s16_segment<D, QSCALE, SCHED & ~8, G>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, typename Gate::Again{}, S16Touch{});
             else s16_group_idle<D, G>(p, ch, tid, head, vb, ve, n_steps, lds, typename Gate::Again{});
         }
     }
@@ -798,7 +840,7 @@ __device__ __forceinline__ bool s16_whole(const AttnParams& p, const AttnChunk& 
                                           const float2* shift_cs, Gate gate) {
     // wave-uniform: a wave without rows in the chunk's last tile only takes its share of the loads and barriers
     const bool has_rows = q0 < ch.q_end;
-    if (!(has_rows ? s16_segment<D, QSCALE, SCHED, 1>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, gate)
+    if (!(has_rows ? s16_segment<D, QSCALE, SCHED, 1>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, gate, S16Touch{})
                    : s16_segment_loads_only<D>(p, ch, tid, head, vb, ve, lds, gate)))
         return false;
     if constexpr ((SCHED & 8) != 0) {
@@ -807,7 +849,7 @@ __device__ __forceinline__ bool s16_whole(const AttnParams& p, const AttnChunk& 
         // with the reference followed.  The barrier inside the vote also ends every wave's reads of the first pass.
         const bool ran_away = has_rows && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
         if (__syncthreads_or(ran_away)) {
-            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, typename Gate::Again{});
+            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, typename Gate::Again{}, S16Touch{});
             else s16_segment_loads_only<D>(p, ch, tid, head, vb, ve, lds, typename Gate::Again{});
         }
     }
@@ -905,7 +947,8 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         __shared__ float2 ml[8][2][16];          // (reference, row sum) per wave, query block and column
         constexpr int NW = 8 / G, PER_WAVE = D / 8 / G;
         const int q0 = row0 + wave % NW * 32;
-        s16_groups<D, QSCALE, SCHED, G>(p, ch, tid, head, q0, 0, 1, lds, shift_cs, ml, S16Unsplit{});
+        const S16Touch touch = s16_take_turns<D, G>(ch, p.H, row0, tile, idx, p.n_groups == 0 ? p.n_tiles * p.H : 0);
+        s16_groups<D, QSCALE, SCHED, G>(p, ch, tid, head, q0, 0, 1, lds, shift_cs, ml, S16Unsplit{}, touch);
         if (q0 >= ch.q_end) return;
 #pragma unroll
         for (int i = 0; i < PER_WAVE; ++i) {
@@ -993,8 +1036,8 @@ __device__ __forceinline__ S16SplitTile s16_split_tile(const AttnParams& p) {
 // Share `share` of the tile: false if the gate stopped it, else what the wave's unit i = 0 .. PER_WAVE - 1 is (s16_share_unit).
 template <int D, int SCHED, int G, typename Gate>
 __device__ __forceinline__ bool s16_share(const AttnParams& p, const S16SplitTile& t, int tid, int q0, int share, char* lds, const float2* shift_cs,
-                                          float2 (*ml)[2][16], S16State<D>& st, Gate gate) {
-    if constexpr (G > 1) return s16_groups<D, false, SCHED, G>(p, t.ch, tid, t.at.head, q0, share, t.splits, lds, shift_cs, ml, gate);
+                                          float2 (*ml)[2][16], S16State<D>& st, Gate gate, S16Touch touch) {
+    if constexpr (G > 1) return s16_groups<D, false, SCHED, G>(p, t.ch, tid, t.at.head, q0, share, t.splits, lds, shift_cs, ml, gate, touch);
     if (!s16_whole<D, false, SCHED>(p, t.ch, tid, t.at.head, q0, t.ch.n_kblocks * share / t.splits, t.ch.n_kblocks * (share + 1) / t.splits, lds, st, shift_cs, gate))
         return false;
 #pragma unroll
@@ -1029,7 +1072,7 @@ __device__ __forceinline__ bool s16_next_share(const AttnParams& p, char* lds, c
     const S16SplitTile t = s16_split_tile<G>(p);
     const int row_block = s16_row_block<G>(wave), q0 = t.row0 + row_block * 32, u0 = G > 1 ? wave / NW * PER_WAVE : 0;
     S16State<D> st;
-    s16_share<D, SCHED, G>(p, t, tid, q0, share, lds, shift_cs, ml, st, S16NextShare{});
+    s16_share<D, SCHED, G>(p, t, tid, q0, share, lds, shift_cs, ml, st, S16NextShare{}, S16Touch{});
     if (q0 < t.ch.q_end) {
         float a[2] = {}, b[2] = {};
 #pragma unroll
@@ -1085,8 +1128,9 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     s16_shift_table(p, t.ch, shift_cs);          // (before the claim: its load would wait for that)
     if (tid == 0 && readers > 0) claim.seen = split_try(p.pool, t.at.item, 0, p.token, readers);
     const int row_block = s16_row_block<G>(wave), q0 = t.row0 + row_block * 32, u0 = G > 1 ? wave / NW * PER_WAVE : 0;
+    const S16Touch touch = s16_take_turns<D, G>(t.ch, p.H, t.row0, t.at.tile, blockIdx.x >> 3, p.n_tiles * p.H * p.splits);
     S16State<D> st;
-    if (!s16_share<D, SCHED, G>(p, t, tid, q0, t.at.part, lds, shift_cs, ml, st, claim) || q0 >= t.ch.q_end) return;
+    if (!s16_share<D, SCHED, G>(p, t, tid, q0, t.at.part, lds, shift_cs, ml, st, claim, touch) || q0 >= t.ch.q_end) return;
     float m, l;
     f32x4 o;
     if (readers == 0) {                          // (a loop of its own: the units' reads from LDS overlap)

@@ -266,3 +266,22 @@ def test_prefill_equals_streaming_where_a_chunk_takes_key_groups(heads, head_dim
     streamed.close()
     rebuilt.close()
     assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("head_dim, heads, n_keys", [(128, 12, 2721), (128, 16, 4000), (64, 12, 5500)])
+@pytest.mark.parametrize("n_q", [33, 130, 400, 1170])
+@pytest.mark.parametrize("at", [None, 2700])
+def test_four_groups_over_many_keys(head_dim, heads, n_keys, n_q, at):
+    """From 16 MB of keys and values on, a head's tiles on one XCD bring kblocks into L2 ahead of their steps by turns: one, two,
+    four or eight of them and more, shares that end within the distance, and the pass that follows the maximum, which does not."""
+    def spoil(q, k):
+        if at is not None:
+            k[at] = 40 * q[5]
+
+    variant = {n: v for v, n in B.attn_variant_names().items()}[f"d{head_dim}_stream16_qscale"]
+    if n_q != 33:                                # (33 rows x 12 x 64 take eight, which leave it)
+        assert B.attn_key_groups(variant, heads, [n_q], [(n_keys + 31) // 32]) in (4, 8)
+    out, want, err = _check(heads, head_dim, n_q, n_keys, n_q, spoil)
+    if at is not None:
+        assert float((out[5].double() - want[5]).norm() / want[5].norm()) <= 2.0 ** -8
+    assert err <= 5e-3
