@@ -47,7 +47,7 @@ struct OpTile {
     static constexpr int STAGE_BYTES = FRAGS * 1024, LDS_BYTES = STAGES * STAGE_BYTES;
     static constexpr int LPW = FRAGS / OP_WAVES;                // fragments a wave loads per stage
     static constexpr int MB = BM / 16 / WM, NB = BN / 16 / WN;  // 16 x 16 blocks of a wave
-    static_assert(WM * WN == OP_WAVES && FRAGS % OP_WAVES == 0 && LDS_BYTES <= 160 * 1024 && MB >= 1 && NB >= 1, "tile of the output projection");
+    static_assert(WM * WN == OP_WAVES && FRAGS % OP_WAVES == 0 && STAGES * LPW < 64 && LDS_BYTES <= 160 * 1024 && MB >= 1 && NB >= 1, "tile of the output projection");
 };
 
 // s_waitcnt that only waits for vector-memory loads: at most N outstanding
@@ -65,6 +65,14 @@ __device__ __forceinline__ void op_lds_wait(op_u32x4 (&x)[N]) {
     asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(x[0]));
 #pragma unroll
     for (int i = 1; i < N; ++i) asm volatile("" : "+v"(x[i]));   // arrived too: ties the register to this point
+}
+
+// The streamed fragments' base and offset stay in scalar registers, as in attn_bwd.hip (offsets are in bounds by construction).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t op_region(const uint16_t* base) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(base), 0, 0x7FFFFFFF, 0x00020000);   // raw buffer of dwords
+}
+__device__ __forceinline__ void op_load_lds16(__amdgpu_buffer_rsrc_t r, char* to, int lane_off, int uniform_off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(to), 16, lane_off, uniform_off, 0, 0);
 }
 
 template <typename Tile>
@@ -91,22 +99,20 @@ void ll_out_proj_kernel(const OutProjParams p) {
 
     // the fragments this wave loads per stage: fragments wave + 8 l of [w: (n block, sub-step) | x: (m block, sub-step)];
     // the two sub-steps of a block are neighbours in memory.  Blocks past the end of a tensor are clamped to its last
-    // block (their products are never stored).
-    const char* src[OP_LPW];
+    // block (their products are never stored).  Base and offset stay in scalar registers (offsets are those within a tile).
+    const __amdgpu_buffer_rsrc_t w_from = op_region(p.w_frag + int64_t(n0 >> 4) * n_ksteps * 512), x_from = op_region(p.x_frag + int64_t(m0 >> 4) * n_ksteps * 512);
+    int src[OP_LPW];
 #pragma unroll
     for (int l = 0; l < OP_LPW; ++l) {
         const int f = wave + OP_WAVES * l;                       // wave-uniform
-        const bool is_w = f < OP_WFRAGS;
-        const int blk = is_w ? min((n0 >> 4) + f / OP_SUBS, last_nb) : min((m0 >> 4) + (f - OP_WFRAGS) / OP_SUBS, last_mb);
-        src[l] = reinterpret_cast<const char*>(is_w ? p.w_frag : p.x_frag) + (int64_t(blk) * n_ksteps + f % OP_SUBS) * 1024 + lane * 16;
+        const int blk = f < OP_WFRAGS ? min(f / OP_SUBS, last_nb - (n0 >> 4)) : min((f - OP_WFRAGS) / OP_SUBS, last_mb - (m0 >> 4));
+        src[l] = (blk * n_ksteps + f % OP_SUBS) * 1024;
     }
-    auto issue = [&](int kt, int to) {
+    static_assert(OP_WFRAGS % OP_WAVES == 0, "a load is of w or of x, whatever the wave");
+    auto issue = [&](int kt, int to, int l) {
         const int kc = min(kt, KT - 1);          // past the end the last step is fetched again, never used
-        char* stage = lds + to * OP_STAGE_BYTES;
-#pragma unroll
-        for (int l = 0; l < OP_LPW; ++l)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[l] + kc * OP_SUBS * 1024),
-                                             (__attribute__((address_space(3))) void*)(stage + (wave + OP_WAVES * l) * 1024), 16, 0, 0);
+        op_load_lds16(OP_WAVES * l < OP_WFRAGS ? w_from : x_from, lds + to * OP_STAGE_BYTES + (wave + OP_WAVES * l) * 1024, lane * 16,
+                      src[l] + kc * OP_SUBS * 1024);
     };
 
     op_f32x4 acc[NB][MB];                        // [n block][m block]
@@ -127,7 +133,9 @@ void ll_out_proj_kernel(const OutProjParams p) {
         else op_lds_read(dst, x_at + stage_at, ((i - NB) * OP_SUBS + sub) * 1024);
     };
 #pragma unroll
-    for (int j = 0; j < OP_STAGES; ++j) issue(j, j);
+    for (int j = 0; j < OP_STAGES; ++j)
+#pragma unroll
+        for (int l = 0; l < OP_LPW; ++l) issue(j, j, l);
     op_wait_vmcnt<(OP_STAGES - 1) * OP_LPW>();
     asm volatile("s_barrier" ::: "memory");
 #pragma unroll
@@ -144,7 +152,6 @@ void ll_out_proj_kernel(const OutProjParams p) {
                 // the barrier that holds for every wave, the stage is loaded anew and the next one read
                 op_wait_vmcnt<(OP_STAGES - 2) * OP_LPW>();
                 asm volatile("s_barrier" ::: "memory");
-                issue(kt + OP_STAGES, stage);
             }
             const unsigned from = unsigned(sub == OP_SUBS - 1 ? next : stage) * OP_STAGE_BYTES;
 #pragma unroll
@@ -156,6 +163,10 @@ void ll_out_proj_kernel(const OutProjParams p) {
 #pragma unroll
                 for (int i = 0; i < NFR; ++i)
                     if (i * ((NMFMA + 1) / 2) / NFR == m) read_frag(fr[1 - sub][i], from, 1 - sub, i);
+                if (sub == OP_SUBS - 1)
+#pragma unroll
+                    for (int l = 0; l < OP_LPW; ++l)
+                        if (l * NMFMA / OP_LPW == m) issue(kt + OP_STAGES, stage, l);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
