@@ -165,8 +165,8 @@ using S16NextShare = S16Barrier<1>;
 // 70 -> 52, x 293 107 -> 78, 800 x 125 x 16 51 -> 39, 1170 x 183 x 12 x 64 39 -> 33; a key set that is in that cache 50.8 and 49.8.
 // Below, where it may stay there, touching costs up to 3 us of 15 (720 x 113 x 3 x 64).
 constexpr int S16_TOUCH_BYTES = 16 << 20;
-struct S16Touch { int every = 1, first = 1 << 24; };             // (none)
-// The tiles of a head (and split) walk the same keys, more or less in step; those on one XCD take turns.  total: workgroups of a
+struct S16Touch { int every = 0, first = 0; };                   // (0: none)
+// The tiles of a head walk the same keys, more or less in step; those on one XCD take turns.  total: workgroups of a
 // launch that deals them out evenly, this one the idx-th of its XCD; 0 where whole (head, chunk) groups lie on an XCD.
 template <int D, int G>
 __device__ __forceinline__ S16Touch s16_take_turns(const AttnChunk& ch, int heads, int row0, int tile, int idx, int total) {
@@ -183,9 +183,10 @@ __device__ __forceinline__ S16Touch s16_take_turns(const AttnChunk& ch, int head
     t.first = before & (t.every - 1);
     return t;
 }
-template <int D, bool QSCALE, int SCHED, int G, typename Gate>
+// (TOUCH: a form of its own, since the code for it costs a call that does not touch 0.4 us of 25)
+template <int D, bool QSCALE, int SCHED, int G, bool TOUCH, typename Gate>
 __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk& ch, int tid, int head, int q0, int vb, int ve,
-                                            int n_steps, char* lds, S16State<D>& st, const float2* shift_cs, Gate gate, S16Touch touch) {
+                                            int n_steps, char* lds, S16State<D>& st, const float2* shift_cs, Gate gate, S16Touch touch = {}) {
     using Plan = LdsPlan16<D, (SCHED & 2) != 0>;
     constexpr bool TRACK = !(SCHED & 8);
     constexpr int KS = Plan::KS;                // K fragments per kblock = S^T slots (two MFMAs each)
@@ -276,7 +277,7 @@ __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk
     auto group_handover = [&](u32x4 (&kf)[KS]) {
 #pragma unroll
         for (int k = 0; k < KS; ++k) s16_lds_wait<0>(kf[k]);
-        if (GR::TOUCHES && --touch_in < 0) {
+        if (TOUCH && --touch_in < 0) {
             touch_period(touch_at);
             touch_in += touch.every;
             touch_at += touch.every * PERIOD;
@@ -300,7 +301,7 @@ __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk
     } else {
 #pragma unroll
         for (int l = 0; l < LPW; ++l) issue_group(0, l);
-        if constexpr (GR::TOUCHES)
+        if constexpr (TOUCH)
             for (int t = touch.first; t < GR::TOUCH_AHEAD; t += touch.every) touch_period((t + 1) * PERIOD);
         // the same 16 bytes per lane as the reads of the permuted fragments below, straight from memory
         const unsigned k_lane = (g >> 1) * 1024 + ((g & 1) * 32 + (n & 7) + 16 * (n >> 3)) * 16;
@@ -776,13 +777,15 @@ __device__ __forceinline__ bool s16_groups(const AttnParams& p, const AttnChunk&
     }
     const bool works = q0 < ch.q_end && ve > vb;
     S16State<D> st;
-    if (!(works ? s16_segment<D, QSCALE, SCHED, G>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate, touch)
+    if (!(works ? (GroupRing<D, G>::TOUCHES && touch.every > 0
+                       ? s16_segment<D, QSCALE, SCHED, G, GroupRing<D, G>::TOUCHES>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate, touch)
+                       : s16_segment<D, QSCALE, SCHED, G, false>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate))
                 : s16_group_idle<D, G>(p, ch, tid, head, vb, ve, n_steps, lds, gate)))
         return false;
     if constexpr ((SCHED & 8) != 0) {
         const bool ran_away = works && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
         if (__syncthreads_or(ran_away)) {
-            if (works) s16_segment<D, QSCALE, SCHED & ~8, G>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, typename Gate::Again{}, S16Touch{});
+            if (works) s16_segment<D, QSCALE, SCHED & ~8, G, false>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, typename Gate::Again{});
             else s16_group_idle<D, G>(p, ch, tid, head, vb, ve, n_steps, lds, typename Gate::Again{});
         }
     }
@@ -840,7 +843,7 @@ __device__ __forceinline__ bool s16_whole(const AttnParams& p, const AttnChunk& 
                                           const float2* shift_cs, Gate gate) {
     // wave-uniform: a wave without rows in the chunk's last tile only takes its share of the loads and barriers
     const bool has_rows = q0 < ch.q_end;
-    if (!(has_rows ? s16_segment<D, QSCALE, SCHED, 1>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, gate, S16Touch{})
+    if (!(has_rows ? s16_segment<D, QSCALE, SCHED, 1, false>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, gate)
                    : s16_segment_loads_only<D>(p, ch, tid, head, vb, ve, lds, gate)))
         return false;
     if constexpr ((SCHED & 8) != 0) {
@@ -849,7 +852,7 @@ __device__ __forceinline__ bool s16_whole(const AttnParams& p, const AttnChunk& 
         // with the reference followed.  The barrier inside the vote also ends every wave's reads of the first pass.
         const bool ran_away = has_rows && !(st.l[0] < S16_FIXED_REF_LIMIT && st.l[1] < S16_FIXED_REF_LIMIT);
         if (__syncthreads_or(ran_away)) {
-            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, typename Gate::Again{}, S16Touch{});
+            if (has_rows) s16_segment<D, QSCALE, SCHED & ~8, 1, false>(p, ch, tid, head, q0, vb, ve, ve - vb, lds, st, shift_cs, typename Gate::Again{});
             else s16_segment_loads_only<D>(p, ch, tid, head, vb, ve, lds, typename Gate::Again{});
         }
     }
@@ -1036,8 +1039,8 @@ __device__ __forceinline__ S16SplitTile s16_split_tile(const AttnParams& p) {
 // Share `share` of the tile: false if the gate stopped it, else what the wave's unit i = 0 .. PER_WAVE - 1 is (s16_share_unit).
 template <int D, int SCHED, int G, typename Gate>
 __device__ __forceinline__ bool s16_share(const AttnParams& p, const S16SplitTile& t, int tid, int q0, int share, char* lds, const float2* shift_cs,
-                                          float2 (*ml)[2][16], S16State<D>& st, Gate gate, S16Touch touch) {
-    if constexpr (G > 1) return s16_groups<D, false, SCHED, G>(p, t.ch, tid, t.at.head, q0, share, t.splits, lds, shift_cs, ml, gate, touch);
+                                          float2 (*ml)[2][16], S16State<D>& st, Gate gate) {
+    if constexpr (G > 1) return s16_groups<D, false, SCHED, G>(p, t.ch, tid, t.at.head, q0, share, t.splits, lds, shift_cs, ml, gate, S16Touch{});
     if (!s16_whole<D, false, SCHED>(p, t.ch, tid, t.at.head, q0, t.ch.n_kblocks * share / t.splits, t.ch.n_kblocks * (share + 1) / t.splits, lds, st, shift_cs, gate))
         return false;
 #pragma unroll
@@ -1072,7 +1075,7 @@ __device__ __forceinline__ bool s16_next_share(const AttnParams& p, char* lds, c
     const S16SplitTile t = s16_split_tile<G>(p);
     const int row_block = s16_row_block<G>(wave), q0 = t.row0 + row_block * 32, u0 = G > 1 ? wave / NW * PER_WAVE : 0;
     S16State<D> st;
-    s16_share<D, SCHED, G>(p, t, tid, q0, share, lds, shift_cs, ml, st, S16NextShare{}, S16Touch{});
+    s16_share<D, SCHED, G>(p, t, tid, q0, share, lds, shift_cs, ml, st, S16NextShare{});
     if (q0 < t.ch.q_end) {
         float a[2] = {}, b[2] = {};
 #pragma unroll
@@ -1128,9 +1131,8 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     s16_shift_table(p, t.ch, shift_cs);          // (before the claim: its load would wait for that)
     if (tid == 0 && readers > 0) claim.seen = split_try(p.pool, t.at.item, 0, p.token, readers);
     const int row_block = s16_row_block<G>(wave), q0 = t.row0 + row_block * 32, u0 = G > 1 ? wave / NW * PER_WAVE : 0;
-    const S16Touch touch = s16_take_turns<D, G>(t.ch, p.H, t.row0, t.at.tile, blockIdx.x >> 3, p.n_tiles * p.H * p.splits);
     S16State<D> st;
-    if (!s16_share<D, SCHED, G>(p, t, tid, q0, t.at.part, lds, shift_cs, ml, st, claim, touch) || q0 >= t.ch.q_end) return;
+    if (!s16_share<D, SCHED, G>(p, t, tid, q0, t.at.part, lds, shift_cs, ml, st, claim) || q0 >= t.ch.q_end) return;
     float m, l;
     f32x4 o;
     if (readers == 0) {                          // (a loop of its own: the units' reads from LDS overlap)
