@@ -351,8 +351,12 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
     for (size_t i = 0; i < work.size(); ++i) {
         const int rows = work[i].q_end - work[i].q_begin;
         order[i] = {1, int(i)};                                       // chosen for the launch
-        if (!streamed && c->fmt) continue;
         const int kblocks = int((int64_t(c->g.S + c->g.W) * c->g.P + rows + c->kb - 1) / c->kb);
+        if (!streamed && c->fmt) {
+            if (rows != rows_before) all_split = all_split && streamed_split(c, variant, rows, kblocks).splits > 1;
+            rows_before = rows;
+            continue;
+        }
         // (a streamed chunk may also take splits; a re-prefill, whose launch is larger, would pay for them: 16 single-frame
         // chunks of 190 x 4 x 128 would take 3 times as long, so there a chunk whose tiles split has other roundings.)
         if (rows != rows_before) {                                    // (most of a re-prefill's chunks are alike)
@@ -364,7 +368,7 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
         order[i].first = groups_before;
     }
     // So a re-prefill all of whose chunks would split has nothing to keep and its groups and splits chosen for the launch (us:
-    // two layers' 5 frames of 252 x 1 x 128 58.7 -> 53.0), as the 8-bit cache's has.
+    // two layers' 5 frames of 252 x 1 x 128 58.7 -> 53.0), as the 8-bit cache's has, whose tiles' keys may then go to key groups too.
     if (!streamed && all_split)
         for (auto& o : order) o.first = 1;
     // longest key sets first: they bound the launch
@@ -396,6 +400,7 @@ static ll_status build_attn(const ll_cache* c, int layer, const std::vector<Chun
         p.key_groups = order[base].first / 256;
         p.splits = order[base].first % 256;
         p.may_split = true;
+        p.may_group8 = c->fmt && !streamed && all_split;
         const int m = int(end - base);
         p.inv_freq_t = c->rope.inv_freq_t; p.n_t = c->rope.n_t;
         for (int i = 0; i < m; ++i) {

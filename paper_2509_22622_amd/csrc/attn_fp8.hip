@@ -68,9 +68,10 @@ __device__ __forceinline__ i32x8 f8_join(const u32x4& lo, const u32x4& hi) {
 __device__ __forceinline__ int f8_pick(int v, int n0, int n01, int a0, int a1, int a2) {
     return v < n0 ? a0 : (v < n01 ? a1 : a2);
 }
-__device__ __forceinline__ int f8_next_edge(int v, int n0, int n01, int T) {
+// (`dead`: first step of a share past its last kblock, 0x7FFFFFFF where there is none)
+__device__ __forceinline__ int f8_next_edge(int v, int n0, int n01, int T, int dead = 0x7FFFFFFF) {
     const int cand[6] = {0, n0 - 1, n0, n01 - 1, n01, T - 1};
-    int best = 0x7FFFFFFF;
+    int best = dead > v ? dead : 0x7FFFFFFF;
 #pragma unroll
     for (int c = 0; c < 6; ++c)
         if (cand[c] > v && cand[c] < best) best = cand[c];
@@ -338,8 +339,12 @@ __device__ __forceinline__ void f8_lds_wait(u32x4& x, u32x4& y) {
 // MFMA of its own: 7 bits instead of 3.  A weight's rounding depends on the reference, and the shares of a split tile have
 // references of their own; so rounded once, the sum over shares would be as far from the whole tile's as either is from
 // the exact weights (2.6 % of the 2-norm each), though neither is better.  With two terms it is where the exact weights are.
-template <int D, bool LOGLIN, bool TWO, int NW>
-__device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChunk& ch, int head, int q0, int vb, int ve, char* lds, F8State<D>& st) {
+//
+// G = 4 deals a tile's keys to four groups of NW waves: this wave's walks its share [vb, ve) through a ring of its own
+// (lds_plan.h: Fp8GroupRing) in n_steps >= ve - vb steps, as many as the longest share has (a step past ve has no live key).
+template <int D, bool LOGLIN, bool TWO, int NW, int G = 1>
+__device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChunk& ch, int head, int q0, int vb, int ve, char* lds, F8State<D>& st,
+                                              int n_steps = 0) {
     constexpr int DH = D / 64;
     constexpr int DB = D / 32;
     constexpr int NK = 2 * DH;                  // S^T slots
@@ -357,11 +362,14 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
     using Plan = Fp8LdsPlan<D>;                 // which buffer a slot's fragment lives in, when it is read, the wait
     constexpr int AH = Plan::AHEAD_SLOTS;
     static_assert(Plan::NK == NK && Plan::NSLOT == NSLOT && Plan::BUFFERS == 4, "plan and kernel disagree on the step's shape");
-    static_assert(NF % NW == 0 && 8 % NK == 0 && NSLOT % LPW == 0 && PF * LPW < 64, "step shape, and loads that vmcnt can count");
+    using GR = Fp8GroupRing<D, G>;
+    static_assert(G == 1 || (!LOGLIN && !TWO && LPW % 2 == 0 && NK >= 2), "key groups");
+    static_assert(NF % NW == 0 && 8 % NK == 0 && (G > 1 || NSLOT % LPW == 0) && (G > 1 || PF * LPW < 64), "step shape, and loads that vmcnt can count");
     static_assert(PF >= LAND && PF + 2 <= NS, "ring too short for the prefetch distance");
 
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_wg % NW;           // (of those that share a ring)
+    if (G > 1) lds += (wave_wg / NW) * GR::BYTES;
     const int col = lane & 31, half = lane >> 5;
 
     const int n_ranges = ch.n_ranges;
@@ -376,7 +384,8 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
     const int T = (ke0 - kb0) + (ke1 - kb1) + (ke2 - kb2);
     const int n0 = ke0 - kb0, n01 = n0 + (ke1 - kb1);
 #define F8_PHYS_KB(v) ((v) + f8_pick((v), n0, n01, kb0, kb1 - n0, kb2 - n01))
-#define F8_LIVE(v) f8_live_mask(F8_PHYS_KB(v) * KBLOCK8, f8_pick((v), n0, n01, rs0, rs1, rs2), f8_pick((v), n0, n01, re0, re1, re2), half)
+    const int v_end = G == 1 ? ve : vb + n_steps, dead = G > 1 && v_end > ve ? ve : 0x7FFFFFFF;
+#define F8_LIVE(v) G > 1 && (v) >= ve ? 0u : f8_live_mask(F8_PHYS_KB(v) * KBLOCK8, f8_pick((v), n0, n01, rs0, rs1, rs2), f8_pick((v), n0, n01, re0, re1, re2), half)
 
     i32x8 qf[DH];
     {
@@ -401,13 +410,36 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
                                          (__attribute__((address_space(3))) void*)(dst), 16, 0, 0);
     };
 
+    // G > 1: load l of those that step `rel` (relative to vb; -1: the prologue) issues, V of the kblock after it, K of the one after that
+    auto issue_group = [&](int rel, int l) {
+        const bool is_k = l < LPW / 2;
+        const int ahead = rel + (is_k ? 2 : 1), v = min(vb + ahead, ve - 1), f = wave + NW * (is_k ? l : l - LPW / 2);
+        const char* src = (is_k ? kbase : vbase) + int64_t(F8_PHYS_KB(v)) * KB_BYTES + f * 1024 + lane_off;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
+                                         (__attribute__((address_space(3))) void*)(lds + ((is_k ? 0 : 2) + (ahead & 1)) * KB_BYTES + f * 1024), 16, 0, 0);
+    };
+
+    if constexpr (G == 1) {
 #pragma unroll
-    for (int j = 0; j < PF; ++j) {
-        const int v = min(vb + j, ve - 1);
+        for (int j = 0; j < PF; ++j) {
+            const int v = min(vb + j, ve - 1);
 #pragma unroll
-        for (int l = 0; l < LPW; ++l) issue_load(F8_PHYS_KB(v), (vb + j) & (NS - 1), l);
+            for (int l = 0; l < LPW; ++l) issue_load(F8_PHYS_KB(v), (vb + j) & (NS - 1), l);
+        }
+    } else {
+        // the tile's first kblock, of which every share takes its first reference, where V of the share's second will be
+#pragma unroll
+        for (int l = 0; l < LPW / 2; ++l) {
+            const int f = wave + NW * l;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kbase + int64_t(F8_PHYS_KB(0)) * KB_BYTES + f * 1024 + lane_off),
+                                             (__attribute__((address_space(3))) void*)(lds + 3 * KB_BYTES + f * 1024), 16, 0, 0);
+        }
+#pragma unroll
+        for (int l = 0; l < LPW / 2; ++l) issue_group(-2, l);
+#pragma unroll
+        for (int l = 0; l < LPW; ++l) issue_group(-1, l);
     }
-    f8_wait_vmcnt<(PF - LAND) * LPW>();
+    f8_wait_vmcnt<G == 1 ? (PF - LAND) * LPW : 0>();
     __builtin_amdgcn_s_barrier();
 
     auto mask_s = [&](f32x16 (&s)[2], unsigned live) {
@@ -443,20 +475,26 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
         for (int db = 0; db < DB; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
-        const char* kt = lds + (vb & (NS - 1)) * STAGE_BYTES + lane_off;
+        auto plain_scores = [&](const char* kt) {
 #pragma unroll
-        for (int R = 0; R < 2; ++R) {
+            for (int R = 0; R < 2; ++R) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sA[R][r] = zero;
+                for (int r = 0; r < 16; ++r) sA[R][r] = zero;
 #pragma unroll
-            for (int dh = 0; dh < DH; ++dh) {
-                const char* kp = kt + ((R * DH + dh) * 2) * 1024;
-                sA[R] = f8_mfma(f8_join(*reinterpret_cast<const u32x4*>(kp), *reinterpret_cast<const u32x4*>(kp + 1024)), qf[dh], sA[R]);
+                for (int dh = 0; dh < DH; ++dh) {
+                    const char* kp = kt + ((R * DH + dh) * 2) * 1024;
+                    sA[R] = f8_mfma(f8_join(*reinterpret_cast<const u32x4*>(kp), *reinterpret_cast<const u32x4*>(kp + 1024)), qf[dh], sA[R]);
+                }
             }
-        }
-        mask_s(sA, F8_LIVE(vb));
+        };
+        plain_scores(lds + (G == 1 ? (vb & (NS - 1)) * STAGE_BYTES : 3 * KB_BYTES) + lane_off);
+        mask_s(sA, F8_LIVE(G == 1 ? vb : 0));
         const float m = max_s(sA);
         mref = fmaxf(m, __shfl_xor(m, 32));
+        if constexpr (G > 1) {
+            plain_scores(lds + lane_off);
+            mask_s(sA, F8_LIVE(vb));
+        }
         if (LOGLIN) {
             bias = 56.0f + 8.0f * (F8_SHIFT - mref);
 #pragma unroll
@@ -471,10 +509,11 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
                 sA[1][r] += F8_SHIFT - mref;
             }
         }
-        mx = -INFINITY;
+        mx = G == 1 ? -INFINITY : max_s(sA);
 #pragma unroll
         for (int j = 0; j < 8; ++j) vmask[j] = 0xFFFFFFFFu;
     }
+    if constexpr (G > 1) __builtin_amdgcn_s_barrier();           // step 0 loads over the keys of kblock vb
     // fragment of slot j of the step whose S^T kblock is stage `ks` and whose O^T kblock is stage `vs`
 #define F8_READ_FRAG(J, KT_A, VT_A)                                                                                 \
     {                                                                                                               \
@@ -486,7 +525,7 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
             f8_lds_read(fr[Plan::buffer(J)][1], (VT_A), (((J) - NK) * 2 + 1) * 1024);                                       \
         }                                                                                                           \
     }
-    {
+    if constexpr (G == 1) {
         const unsigned kt_a = lds_a + ((vb + 1) & (NS - 1)) * STAGE_BYTES;
         const unsigned vt_a = lds_a + (vb & (NS - 1)) * STAGE_BYTES + KB_BYTES;
 #pragma unroll
@@ -500,7 +539,7 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
         if (__builtin_expect(edge || vote, 0)) {                                                                    \
             if (edge) {                                                                                             \
                 const unsigned live = F8_LIVE(I);                                                                   \
-                next_edge = f8_next_edge((I), n0, n01, T);                                                          \
+                next_edge = f8_next_edge((I), n0, n01, T, dead);                                                    \
                 mask_s(S_CUR, live);                                                                                \
                 mx = max_s(S_CUR);                                                                                  \
                 _Pragma("unroll") for (int j = 0; j < 8; ++j) {                                                     \
@@ -528,15 +567,22 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
                 }                                                                                                   \
             }                                                                                                       \
         }                                                                                                           \
-        const unsigned kt_a = lds_a + (((I) + 1) & (NS - 1)) * STAGE_BYTES;            /* K8 of kblock I + 1 */      \
-        const unsigned vt_a = lds_a + ((I) & (NS - 1)) * STAGE_BYTES + KB_BYTES;       /* V8 of kblock I     */      \
+        const unsigned kt_a = lds_a + (G == 1 ? (((I) + 1) & (NS - 1)) * STAGE_BYTES                                \
+                                              : (((I) + 1 - vb) & 1) * KB_BYTES);      /* K8 of kblock I + 1 */      \
+        const unsigned vt_a = lds_a + (G == 1 ? ((I) & (NS - 1)) * STAGE_BYTES + KB_BYTES                           \
+                                              : (2 + (((I) - vb) & 1)) * KB_BYTES);    /* V8 of kblock I     */      \
         const unsigned kn_a = lds_a + (((I) + 2) & (NS - 1)) * STAGE_BYTES;            /* K8 of kblock I + 2 */      \
         i32x8 pb, pl;                                                                                               \
         float m_run = -INFINITY;                                                                                    \
+        if (G > 1) {                             /* (a stage is read behind the barrier that hands it over only) */ \
+            _Pragma("unroll") for (int j = 0; j < AH; ++j) F8_READ_FRAG(j, kt_a, vt_a)                              \
+            __builtin_amdgcn_sched_barrier(0);                                                                      \
+        }                                                                                                           \
         _Pragma("unroll") for (int k = 0; k < NSLOT; ++k) {                                                         \
             if (k == 0) __builtin_amdgcn_s_setprio(1);                                                              \
             if (k == NK) __builtin_amdgcn_s_setprio(0);                                                             \
-            f8_lds_wait<Plan::wait()>(fr[Plan::buffer(k)][0], fr[Plan::buffer(k)][1]);                                                             \
+            if (G > 1 && k == NSLOT - 1) f8_lds_wait<0>(fr[Plan::buffer(k)][0], fr[Plan::buffer(k)][1]);            \
+            else f8_lds_wait<Plan::wait()>(fr[Plan::buffer(k)][0], fr[Plan::buffer(k)][1]);                         \
             if (k < NK) {                                                                                           \
                 const int R = k / DH, dh = k % DH;                                                                  \
                 S_NEXT[R] = f8_mfma(f8_join(fr[Plan::buffer(k)][0], fr[Plan::buffer(k)][1]), qf[dh],                \
@@ -553,13 +599,16 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
                 if (TWO) st.o[db] = f8_mfma(f8_join(fr[Plan::buffer(k)][0], fr[Plan::buffer(k)][1]), pl, st.o[db]); \
                 if (LOGLIN && k == NK) lacc = f8_mfma(ones, pb, lacc);     /* row sums of the 8-bit weights */       \
             }                                                                                                       \
-            if (k >= DMA_FIRST && (k - DMA_FIRST) % DMA_STEP == 0 && (k - DMA_FIRST) / DMA_STEP < LPW) {            \
+            if (G > 1) {                                                                                            \
+                _Pragma("unroll") for (int l = 0; l < LPW; ++l)                                                     \
+                    if (GR::dma_slot(l, LPW, NSLOT) == k) issue_group((I) - vb, l);                                 \
+            } else if (k >= DMA_FIRST && (k - DMA_FIRST) % DMA_STEP == 0 && (k - DMA_FIRST) / DMA_STEP < LPW) {            \
                 const int v = min((I) + PF, ve - 1);                                                                \
                 issue_load(F8_PHYS_KB(v), ((I) + PF) & (NS - 1), (k - DMA_FIRST) / DMA_STEP);                       \
             }                                                                                                       \
             /* the fragment of the slot after next (the first two slots of the next step read kblock I + 2) */      \
             if (k + AH < NSLOT) F8_READ_FRAG(k + AH, kt_a, vt_a)                                                    \
-            else F8_READ_FRAG(k + AH - NSLOT, kn_a, vt_a)                                                           \
+            else if (G == 1) F8_READ_FRAG(k + AH - NSLOT, kn_a, vt_a)                                               \
             if (k < NK) {                                                                                           \
                 _Pragma("unroll") for (int g = k * QPS; g < (k + 1) * QPS; ++g) {                                   \
                     const int R = g / 4, r = 4 * (g % 4);                                                           \
@@ -604,23 +653,23 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
         if (EDGE && edge) {                                                                                         \
             _Pragma("unroll") for (int j = 0; j < 8; ++j) vmask[j] = 0xFFFFFFFFu;                                   \
         }                                                                                                           \
-        if (BAR == 1 || (BAR == 2 && RingPlan::barrier_after((I) - vb))) {                                          \
-            f8_wait_vmcnt<(PF - LAND) * LPW>();                                                                     \
+        if (G > 1 || BAR == 1 || (BAR == 2 && RingPlan::barrier_after((I) - vb))) {                                 \
+            f8_wait_vmcnt<G == 1 ? (PF - LAND) * LPW : 0>();                                                                     \
             __builtin_amdgcn_s_barrier();                                                                           \
         }                                                                                                           \
     }
 
-    int next_edge = f8_next_edge(vb - 1, n0, n01, T);
-    bool vote = false;
+    int next_edge = f8_next_edge(vb - 1, n0, n01, T, dead);
+    bool vote = G > 1 && __any(mx > F8_SHIFT + F8_SLACK);
     int i = vb;
-    while (i < ve) {
-        while (i < ve && (((i - vb) & 1) || i + 1 >= ve || i == next_edge || i + 1 == next_edge)) {
+    while (i < v_end) {
+        while (i < v_end && (((i - vb) & 1) || i + 1 >= v_end || i == next_edge || i + 1 == next_edge)) {
             F8_STEP(i, sA, sB, 1, 2)
 #pragma unroll
             for (int R = 0; R < 2; ++R) sA[R] = sB[R];
             ++i;
         }
-        for (int n = (min(ve, next_edge) - i) >> 1; n > 0; --n) {
+        for (int n = (min(v_end, next_edge) - i) >> 1; n > 0; --n) {
             F8_STEP(i, sA, sB, 0, 0)
             F8_STEP(i + 1, sB, sA, 0, 1)
             i += 2;
@@ -683,6 +732,53 @@ __device__ __forceinline__ void f8_segment_loads_only(const AttnParams& p, const
     __builtin_amdgcn_s_waitcnt(0);
 }
 
+// The same for a wave of a key group that has no queries, or whose group has no kblocks (loads nothing then).
+template <int D, int NW, int G>
+__device__ __forceinline__ void f8_group_idle(const AttnParams& p, const AttnChunk& ch, int head, int vb, int ve, int n_steps, char* lds) {
+    using GR = Fp8GroupRing<D, G>;
+    constexpr int KB_BYTES = KBLOCK8 * D, PIECES = KB_BYTES / 1024 / NW;          // of a kblock's keys, a wave
+    const int lane = threadIdx.x & 63;
+    const int wave_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_wg % NW;
+    lds += (wave_wg / NW) * GR::BYTES;
+    const int n_ranges = ch.n_ranges;
+    const int rs0 = ch.rs[0], re0 = ch.re[0];
+    int rs1 = ch.rs[1], re1 = ch.re[1], rs2 = ch.rs[2];
+    if (n_ranges < 2) rs1 = re1 = 0;
+    if (n_ranges < 3) rs2 = 0;
+    const int kb0 = rs0 / KBLOCK8, ke0 = (re0 + KBLOCK8 - 1) / KBLOCK8;
+    const int kb1 = rs1 / KBLOCK8, ke1 = (re1 + KBLOCK8 - 1) / KBLOCK8;
+    const int kb2 = rs2 / KBLOCK8;
+    const int n0 = ke0 - kb0, n01 = n0 + (ke1 - kb1);
+    const char* kbase = reinterpret_cast<const char*>(p.k8_cache + head * p.head_stride);
+    const char* vbase = reinterpret_cast<const char*>(p.v8_cache + head * p.head_stride);
+    const unsigned lane_off = lane * 16;
+    auto issue = [&](int rel, bool is_k) {
+        if (ve <= vb) return;
+        const int ahead = rel + (is_k ? 2 : 1), v = min(vb + ahead, ve - 1), kb = v + f8_pick(v, n0, n01, kb0, kb1 - n0, kb2 - n01);
+#pragma unroll
+        for (int l = 0; l < PIECES; ++l) {
+            const int f = wave + NW * l;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((is_k ? kbase : vbase) + int64_t(kb) * KB_BYTES + f * 1024 + lane_off),
+                                             (__attribute__((address_space(3))) void*)(lds + ((is_k ? 0 : 2) + (ahead & 1)) * KB_BYTES + f * 1024), 16, 0, 0);
+        }
+    };
+    if (ve > vb)
+#pragma unroll
+        for (int l = 0; l < PIECES; ++l) {
+            const int f = wave + NW * l;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kbase + int64_t(f8_pick(0, n0, n01, kb0, kb1 - n0, kb2 - n01)) * KB_BYTES + f * 1024 + lane_off),
+                                             (__attribute__((address_space(3))) void*)(lds + 3 * KB_BYTES + f * 1024), 16, 0, 0);
+        }
+    issue(-2, true);
+    for (int rel = -1; rel < n_steps; ++rel) {
+        issue(rel, true);
+        issue(rel, false);
+        f8_wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+        if (rel < 0) __builtin_amdgcn_s_barrier();               // (as behind the prologue's scores)
+    }
+}
+
 // out[row][head][32*db + 8*g + 4*half + i] = O^T register 4*g + i, times 2^v_exp, divided by the row sum
 template <int D>
 __device__ __forceinline__ void f8_store_out(const AttnParams& p, int head, int q0, int q_end, const F8State<D>& st) {
@@ -710,6 +806,64 @@ __device__ __forceinline__ void f8_store_unit(const AttnParams& p, int head, int
     const float inv = p.out_scale / l;
     const u32x2 w = {f8_pack_bf16(o[0] * inv, o[1] * inv), f8_pack_bf16(o[2] * inv, o[3] * inv)};
     *reinterpret_cast<u32x2*>(p.out + (int64_t(row) * p.H + head) * D + dg * 8 + half * 4) = w;
+}
+
+// All keys of a tile, dealt to G groups of NW waves: kblocks [T j / G, T (j + 1) / G) to group j, whose results, each relative to
+// its own reference, meet in LDS (the rings' memory).  Weights are rounded once, as a whole tile's are; every share begins with the
+// reference that the whole tile would begin with, so its weights are those of the whole tile, bit for bit, unless a score rises far
+// above it (error against 64 bits 0.0256 of the 2-norm, 0.0257 for whole tiles; 0.0103 and 0.0154 at logits of standard deviation 3).
+template <int D, int NW, int G>
+__device__ __forceinline__ void f8_groups(const AttnParams& p, const AttnChunk& ch, int head, int row0, char* lds, float2 (*ml)[32]) {
+    constexpr int UNITS = D / 8, PER_WAVE = UNITS / G;           // (db, g) of a row block: four features of a lane's half each
+    static_assert(UNITS % G == 0 && NW * G == 8, "the units must split over the groups");
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), group = wave / NW;
+    const int lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+    const int T = ch.n_kblocks, vb = T * group / G, ve = T * (group + 1) / G, n_steps = (T + G - 1) / G;
+    const int q0 = row0 + wave % NW * 32;
+    F8State<D> st;
+    if (q0 < ch.q_end && ve > vb) {
+        f8_segment_sp<D, false, false, NW, G>(p, ch, head, q0, vb, ve, lds, st, n_steps);
+    } else {
+        f8_group_idle<D, NW, G>(p, ch, head, vb, ve, n_steps, lds);
+        st.l = 0.f;
+        st.m = -INFINITY;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) st.o[db][r] = 0.f;
+    }
+    __syncthreads();                             // every group has left its ring
+    f32x4* part = reinterpret_cast<f32x4*>(lds);                 // [wave][unit][lane]
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            part[(wave * UNITS + db * 4 + g) * 64 + lane] = f32x4{st.o[db][4 * g], st.o[db][4 * g + 1], st.o[db][4 * g + 2], st.o[db][4 * g + 3]};
+    const float l_own = st.l + __shfl_xor(st.l, 32);
+    if (lane < 32) ml[wave][col] = make_float2(st.m, l_own);
+    __syncthreads();
+    if (q0 >= ch.q_end) return;
+    float m = -INFINITY, l = 0.f, a[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + wave % NW][col].x);     // (the first share has a kblock of the tile's: finite)
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+        const float2 s = ml[j * NW + wave % NW][col];
+        a[j] = __builtin_amdgcn_exp2f(s.x - m);
+        l = __builtin_fmaf(s.y, a[j], l);
+    }
+#pragma unroll
+    for (int i = 0; i < PER_WAVE; ++i) {
+        const int u = group * PER_WAVE + i;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const f32x4 x = part[((j * NW + wave % NW) * UNITS + u) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(x[e], a[j], o[e]);
+        }
+        if (q0 + col < ch.q_end) f8_store_unit<D>(p, head, q0 + col, u, half, o, l);
+    }
 }
 
 // The partial results of a tile's splits (split.h), for the 32-row blocks [first, first + n_blocks) of the tile, added up in
@@ -838,10 +992,13 @@ __device__ __forceinline__ bool f8_split_share(const AttnParams& p, char* lds, i
 // Modes 4 and 5 are 1, and 6 is 3, in workgroups of four and two waves with tiles of 128 and 64 rows: where 256-row tiles leave most of
 // the chip idle, a wave that has its SIMD for itself takes a step in two thirds of the time (rule: attn_split in attn_kernel.hip),
 // and every row keeps its bits.
+// Mode 7: tiles of 64 rows, their keys dealt to four groups of two waves (re-prefills in one round of workgroups; rule:
+// takes_group8 in attn_kernel.hip).  Mode 5 leaves half of a CU's SIMDs idle and the others to one wave each; us: 2990 rows in four
+// chunks over 10 to 47 kblocks x 5 heads x 128 38 -> 27.  What bounds it: 64 KB a step from L2 to each CU, and 10 us around the steps.
 constexpr int f8_waves(int mode) { return mode == 5 ? 2 : mode == 4 || mode == 6 ? 4 : 8; }
 template <int D, int MODE>
 __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void ll_attn_fp8_kernel(const AttnParams p) {
-    constexpr int NW = f8_waves(MODE), ROWS = 32 * NW;
+    constexpr int NW = f8_waves(MODE), ROWS = MODE == 7 ? 64 : 32 * NW;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     if constexpr (MODE == 3 || MODE == 6) {
         __shared__ int slots[MAX_SPLITS];
@@ -878,6 +1035,11 @@ __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_pe
         ch = p.chunk[ci];
     }
     const int row0 = ch.q_begin + (tile - ch.tile_begin) * ROWS;
+    if constexpr (MODE == 7) {
+        __shared__ float2 ml[8][32];             // (reference, row sum) per wave and column
+        f8_groups<D, 2, 4>(p, ch, head, row0, lds, ml);
+        return;
+    }
     const int row_block = NW == 8 ? ((wave & 3) << 1) | (wave >> 2) : wave;       // (waves w and w + 4 share a SIMD)
     const int q0 = row0 + row_block * 32;
     const bool has_rows = q0 < ch.q_end;
@@ -889,8 +1051,8 @@ __global__ __launch_bounds__(f8_waves(MODE) * 64) __attribute__((amdgpu_waves_pe
 }
 
 const AttnVariant kFp8Variants[] = {
-    {"d128_fp8", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<128, 4>, ll_attn_fp8_kernel<128, 5>}, {ll_attn_fp8_kernel<128, 3>, ll_attn_fp8_kernel<128, 6>}, {ll_attn_fp8_kernel<128, 3>, ll_attn_fp8_kernel<128, 6>}},
-    {"d64_fp8", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<64, 4>, ll_attn_fp8_kernel<64, 5>}, {ll_attn_fp8_kernel<64, 3>, ll_attn_fp8_kernel<64, 6>}, {ll_attn_fp8_kernel<64, 3>, ll_attn_fp8_kernel<64, 6>}},
+    {"d128_fp8", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<128, 4>, ll_attn_fp8_kernel<128, 5>, ll_attn_fp8_kernel<128, 7>}, {ll_attn_fp8_kernel<128, 3>, ll_attn_fp8_kernel<128, 6>}, {ll_attn_fp8_kernel<128, 3>, ll_attn_fp8_kernel<128, 6>}},
+    {"d64_fp8", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 1>, F8_THREADS, KBLOCK8, {ll_attn_fp8_kernel<64, 4>, ll_attn_fp8_kernel<64, 5>, ll_attn_fp8_kernel<64, 7>}, {ll_attn_fp8_kernel<64, 3>, ll_attn_fp8_kernel<64, 6>}, {ll_attn_fp8_kernel<64, 3>, ll_attn_fp8_kernel<64, 6>}},
     {"d128_fp8_simple", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 0>, F8_THREADS, KBLOCK8},
     {"d64_fp8_simple", 64, 256, 8 * 2 * KBLOCK8 * 64, ll_attn_fp8_kernel<64, 0>, F8_THREADS, KBLOCK8},
     {"d128_fp8_loglin", 128, 256, 8 * 2 * KBLOCK8 * 128, ll_attn_fp8_kernel<128, 2>, F8_THREADS, KBLOCK8},

@@ -462,6 +462,23 @@ AttnSplit attn_split(int variant, int H, int n_chunks, const int* rows, const in
     }
     return best;
 }
+// Whether a launch of the 8-bit cache that takes no splits has its tiles in 64 rows and their keys dealt to four groups of two waves
+// (attn_fp8.hip) instead of the narrow tiles that attn_split picks.  In one round of workgroups the longest share is a quarter of the
+// longest key set, at two waves per SIMD instead of one; us a layer of a re-prefill, cache write included, without and with:
+// 10 frames of 299 tokens x 5 heads x 128 (250 tiles) 46.3 -> 35.2, x 64 40 -> 27, 13 of 190 x 4 x 128 38 -> 30, 10 of 96 x 3 x 128 23.5 ->
+// 22.5.  More tiles than CUs walk as many steps either way and read more of L2 (300 tiles 49 and 49, 450 52 and 56, 1200 96 and
+// 116), and six kblocks leave a share little to walk (17.6 and 18.7).  In long key sets most rows' references move on the way, and a share
+// does not know of those before it: its weights, no further from the exact ones, are rounded otherwise than the whole tile's (outputs
+// 1.8 % of the 2-norm apart at 47 kblocks, 3.0 % at 131, two separate roundings 3.7 %), so those keep their tiles.
+static bool takes_group8(int H, int n_chunks, const int* rows, const int* kblocks) {
+    int64_t tiles = 0;
+    int longest = 0;
+    for (int c = 0; c < n_chunks; ++c) {
+        tiles += int64_t(rows[c] + 63) / 64 * H;
+        longest = std::max(longest, kblocks[c]);
+    }
+    return tiles <= 256 && longest >= 7 && longest <= 64;
+}
 static __device__ SplitPool split_pool;
 // its address on the current device (looked up on the first call per device; threads may do that at the same time)
 hipError_t split_pool_address(SplitPool** pool) {
@@ -523,12 +540,14 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
             const AttnSplit split = attn_split(variant, p.H, p.n_chunks, rows, kblocks);
             p.key_groups = split.groups;
             p.splits = split.splits;
+            if (p.may_group8 && split.splits == 1 && takes_group8(p.H, p.n_chunks, rows, kblocks)) p.key_groups = 8;
         }
     }
     int log_g = 0;
     while ((1 << log_g) < p.key_groups) ++log_g;
     if (log_g > 3) return hipErrorInvalidValue;
-    const int qtile = v.qtile >> log_g;
+    const bool fp8 = v.kblock == KBLOCK8;
+    const int qtile = v.qtile >> (fp8 ? std::min(log_g, 2) : log_g);             // (8 there: 64 rows, four key groups)
     p.n_tiles = 0;
     for (int c = 0; c < p.n_chunks; ++c) {
         p.chunk[c].tile_begin = p.n_tiles;
@@ -594,9 +613,8 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
         }
     }
     if (variant > 64) return hipErrorInvalidValue;
-    const bool fp8 = v.kblock == KBLOCK8;
     const int lds_bytes = log_g == 0 || fp8 ? v.lds_bytes : GROUPED_LDS_BYTES;
-    const dim3 threads(fp8 ? v.threads >> log_g : v.threads);
+    const dim3 threads(fp8 && log_g < 3 ? v.threads >> log_g : v.threads);
     static bool attr_set[64][12] = {};
     auto prepare = [&](void (*kernel)(const AttnParams), int which) {            // which: one of the variant's kernels
         if (kernel == nullptr) return hipErrorInvalidValue;

@@ -90,6 +90,17 @@ struct Fp8LdsPlan {
     static_assert(AHEAD_SLOTS < BUFFERS, "a fragment would be read into a buffer still in use");
 };
 
+// The rings of a workgroup of the 8-bit kernel whose waves are dealt into G key groups (attn_fp8.hip, G = 4): a group's walk their
+// share of the kblocks through two half stages of keys and two of values.  The step for kblock i reads V of i and K of i + 1 and
+// issues the loads of V of i + 1 and K of i + 2, over the half stages that the step before has read; behind it a wave waits for
+// all it has issued and meets the others at a barrier.  Nothing is read ahead across that.
+template <int D, int G>
+struct Fp8GroupRing {
+    static constexpr int BYTES = 4 * 64 * D;
+    static_assert(G * BYTES <= 128 * 1024, "the rings of a workgroup");
+    static constexpr int dma_slot(int l, int n, int slots) { return l * slots / n / 2; }         // in the step's first half
+};
+
 // The ring of K/V stages in LDS and its hand-over between the waves of a workgroup.
 //   Kblock v lives in stage v % STAGES.  The prologue issues the loads of the first AHEAD kblocks; step i issues
 //   those of kblock i + AHEAD, and reads kblock i (V^T) and kblock i + 2 (K for the scores of the step after next;

@@ -24,6 +24,7 @@ from paper_2509_22622_amd import binding as B
 from paper_2509_22622_amd import synth
 
 import gpu_harness as H
+from perf import cases
 from test_gpu_parity import HEADS6, MID128, NOSINK, ODD128, ODD64, WIDE, _random_workload
 
 pytestmark = pytest.mark.gpu
@@ -423,3 +424,34 @@ def test_thirty_layer_loop_fp8():
     torch.cuda.synchronize()
     assert cache.buffer.numel() == nbytes
     cache.close()
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, sink, window, n_win", [
+    (5, 128, (13, 23), 3, 2, 7, 8),       # 250 tiles of 64 rows, ragged
+    (4, 128, (10, 19), 1, 3, 9, 10),      # single-frame chunks of two to 39 kblocks
+    (3, 128, (1, 97), 1, 1, 16, 12),      # two kblocks at first: groups without keys; one row in a second 32-row block
+    (1, 128, (5, 10), 1, 1, 40, 30),      # one kblock at first; two launches
+    (5, 64, (13, 23), 3, 2, 7, 8),
+    (1, 64, (5, 13), 1, 1, 30, 20),       # tiles of one row
+    (4, 64, (13, 15), 2, 3, 9, 10)])
+@pytest.mark.parametrize("q_std", [1.0, 6.0])
+def test_re_prefill_in_key_groups(heads, head_dim, grid, chunk, sink, window, n_win, q_std):
+    """Re-prefills whose chunks would all split when streamed and which fit the chip in one round of 64-row tiles: a tile's keys
+    are dealt to four groups of its waves.  Unequal and empty shares, waves without rows, references far apart (q_std 6)."""
+    P = grid[0] * grid[1]
+    split = lambda frames: B.attn_split(head_dim, heads, frames * P, -(-(sink + window + frames) * P // 64), "fp8_e4m3")[1]
+    lengths = {min(chunk, end - f) for lo, end in ((0, sink), (sink, sink + n_win)) for f in range(lo, end, chunk)}
+    tiles = sum(-(-min(chunk, end - f) * P // 64) * heads for lo, end in ((0, sink), (sink, sink + n_win)) for f in range(lo, end, chunk))
+    assert tiles <= 256 and all(split(n) > 1 for n in lengths)
+    case = {"kind": "prefill", "cache": "fp8_e4m3", "layers": 1, "heads": heads, "head_dim": head_dim, "grid_h": grid[0],
+            "grid_w": grid[1], "chunk": chunk, "sink": sink, "window": window, "win_start": sink + 20, "n_win": n_win, "q_std": q_std}
+    state = cases.prepare(case, 3)
+    out = cases.run(state)[0].clone()
+    torch.cuda.synchronize()
+    want = cases.exact(case, 3)[0]
+    err = (out.double() - want).abs()
+    # one weight's rounding at most 2^-4, and 2.6 % rms over independent values; logits of standard deviation 6 leave nothing to average
+    assert bool(torch.isfinite(out).all()) and float(err.norm() / want.norm()) <= (REL_L2_TOL_FP8 if q_std == 1.0 else 2.0 ** -4)
+    again = cases.run(state)[0]
+    assert torch.equal(again.view(torch.int16), out.view(torch.int16))
+    state["cache"].close()
