@@ -8,9 +8,11 @@
 // other.  Here a workgroup brings the keys and values of one head into LDS once and its eight waves then go through
 // their rows on their own: blocks of 32 rows, no barrier, no ring, the next block's queries on their way while this
 // block is computed, and the waves of a CU in different phases.  Measured against the streaming kernels, us:
-// 226 tokens x 23400 rows x 12 x 128 75 -> 55 (16 tokens, all memory: 47 -> 36, 4.0 TB/s), x 24 heads 137 -> 101;
+// 226 tokens x 23400 rows x 12 x 128 75 -> 48 (16 tokens, all memory: 47 -> 36, 4.0 TB/s), x 24 heads 137 -> 101;
 // 1200 rows x 77 tokens x 24 x 64 10 -> 7.  Rows that went to memory in the lanes' own order (64-byte loads, 32-byte stores) took
-// 46 us at 16 tokens; fragments read a phase ahead of their MFMAs spill and are no faster.
+// 46 us at 16 tokens.  With the fragments' reads left to the compiler, which put each in front of its MFMAs
+// (no room for more beside the next queries), the matrix work of 226 tokens did not hide under the memory's: 51 us; 20000 rows x 400 x
+// 12 x 64 39.5 -> 36.5, 9000 x 500 x 6 x 64 16.4 -> 14.7.
 #include "kernels.h"
 
 #include <algorithm>
@@ -31,6 +33,15 @@ constexpr float RES_SLACK = 6.0f;                // log2 units: weights stay bel
 __device__ __forceinline__ unsigned res_pack_bf16(float a, float b) {
     f32x2 v = {a, b};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+
+// LDS reads the compiler does not see (attn_stream.hip): `dst` is pending until res_lds_wait<N>(dst) with N reads issued after it
+__device__ __forceinline__ void res_lds_read(u32x4& dst, unsigned addr, int offset) {
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(offset));
+}
+template <int N>
+__device__ __forceinline__ void res_lds_wait(u32x4& x) {
+    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N));
 }
 
 // FRAG: the output goes out in the output projection's fragment order (AttnParams::out_frag)
@@ -112,9 +123,10 @@ __global__ __launch_bounds__(RES_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         fetch(min(b + RES_WAVES, n_blocks - 1));
 
         f32x4 o[NV][2];
-        float lsum[2] = {0.f, 0.f}, mref[2] = {0.f, 0.f};        // row sums, references (log2 domain)
+        float lsum[2], mref[2];                  // row sums, references (log2 domain)
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
+            lsum[qb] = 0.f;
 #pragma unroll
             for (int f = 0; f < NV; ++f) o[f][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
@@ -129,65 +141,124 @@ __global__ __launch_bounds__(RES_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
                 }
             }
         };
-        // kblock kb, whose scores are `cur`; those of kb + 1 go to `nxt` under its vector work
-        f32x4 cur[2][2], nxt[2][2] = {};
-        scores(0, cur);
-        for (int kb = 0; kb < T; ++kb) {
-            if (kb + 1 < T) scores(kb + 1, nxt);
-            if (kb == T - 1 && tail < KBLOCK) {  // register j of group m is key 8 g + 4 m + j
-#pragma unroll
-                for (int m = 0; m < 2; ++m)
-#pragma unroll
-                    for (int qb = 0; qb < 2; ++qb) {
-                        const f32x4 x = cur[m][qb];
-                        const int left = tail - 8 * g - 4 * m;
-                        cur[m][qb] = f32x4{left > 0 ? x[0] : -INFINITY, left > 1 ? x[1] : -INFINITY,
-                                           left > 2 ? x[2] : -INFINITY, left > 3 ? x[3] : -INFINITY};
-                    }
-            }
-            float mx[2];
-#pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
-                mx[qb] = fmaxf(fmaxf(cur[0][qb][0], cur[0][qb][1]), cur[0][qb][2]);
-                mx[qb] = fmaxf(fmaxf(mx[qb], cur[0][qb][3]), cur[1][qb][0]);
-                mx[qb] = fmaxf(fmaxf(mx[qb], cur[1][qb][1]), cur[1][qb][2]);
-                mx[qb] = fmaxf(mx[qb], cur[1][qb][3]);
-            }
-            if (kb == 0 || __any(mx[0] * c > mref[0] + RES_SLACK || mx[1] * c > mref[1] + RES_SLACK)) {
-#pragma unroll
-                for (int qb = 0; qb < 2; ++qb) {
-                    const float top = col_max(mx[qb]) * c;       // the first kblock holds a live key: finite there
-                    const float m = kb == 0 ? top : fmaxf(mref[qb], top);
-                    const float alpha = kb == 0 ? 0.f : __builtin_amdgcn_exp2f(mref[qb] - m);
-                    mref[qb] = m;
-                    lsum[qb] *= alpha;
-                    if (kb != 0)
-#pragma unroll
-                        for (int f = 0; f < NV; ++f) o[f][qb] *= alpha;
-                }
-            }
-            u32x4 pb[2];
-#pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[w >> 1][qb][2 * (w & 1)], c, -mref[qb]));
-                    const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[w >> 1][qb][2 * (w & 1) + 1], c, -mref[qb]));
-                    lsum[qb] += e0;
-                    lsum[qb] += e1;
-                    pb[qb][w] = res_pack_bf16(e0, e1);
-                }
-#pragma unroll
-            for (int f = 0; f < NV; ++f) {
-                const bf16x8 a = frag(kb, 1, f);
-#pragma unroll
-                for (int qb = 0; qb < 2; ++qb)
-                    o[f][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, pb[qb]), o[f][qb], 0, 0, 0);
-            }
+        auto mask_tail = [&](f32x4 (&s)[2][2]) {                  // register j of group m is key 8 g + 4 m + j
 #pragma unroll
             for (int m = 0; m < 2; ++m)
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb) cur[m][qb] = nxt[m][qb];
+                for (int qb = 0; qb < 2; ++qb) {
+                    const f32x4 x = s[m][qb];
+                    const int left = tail - 8 * g - 4 * m;
+                    s[m][qb] = f32x4{left > 0 ? x[0] : -INFINITY, left > 1 ? x[1] : -INFINITY,
+                                     left > 2 ? x[2] : -INFINITY, left > 3 ? x[3] : -INFINITY};
+                }
+        };
+        auto max_s = [&](const f32x4 (&s)[2][2], int qb) {
+            float m = fmaxf(fmaxf(s[0][qb][0], s[0][qb][1]), s[0][qb][2]);
+            m = fmaxf(fmaxf(m, s[0][qb][3]), s[1][qb][0]);
+            m = fmaxf(fmaxf(m, s[1][qb][1]), s[1][qb][2]);
+            return fmaxf(m, s[1][qb][3]);
+        };
+        auto weights = [&](const f32x4 (&s)[2][2], int qb, int w, u32x4 (&pb)[2]) {
+            const float e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[w >> 1][qb][2 * (w & 1)], c, -mref[qb]));
+            const float e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[w >> 1][qb][2 * (w & 1) + 1], c, -mref[qb]));
+            lsum[qb] += e0;
+            lsum[qb] += e1;
+            pb[qb][w] = res_pack_bf16(e0, e1);
+        };
+
+        // A kblock is KS + NV fragments, two MFMAs each: those of keys kb + 1, with the weights of kb behind them, then those of
+        // values kb, with the maximum over the new scores.  The fragments are read by hand, AHEAD before their MFMAs, into a
+        // ring of four buffers.
+        f32x4 sA[2][2], sB[2][2];
+        scores(0, sA);
+        if (T == 1 && tail < KBLOCK) mask_tail(sA);
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) mref[qb] = col_max(max_s(sA, qb)) * c;     // the first kblock holds a live key: finite
+        float mx[2];                             // largest score of the kblock to come among this lane's keys
+        // (before that kblock's weights: the reference follows where a score exceeds it by far)
+        auto follow = [&]() {
+            if (__any(mx[0] * c > mref[0] + RES_SLACK || mx[1] * c > mref[1] + RES_SLACK)) {
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) {
+                    const float m = fmaxf(mref[qb], col_max(mx[qb]) * c);
+                    const float alpha = __builtin_amdgcn_exp2f(mref[qb] - m);
+                    mref[qb] = m;
+                    lsum[qb] *= alpha;
+#pragma unroll
+                    for (int f = 0; f < NV; ++f) o[f][qb] *= alpha;
+                }
+            }
+        };
+        constexpr int AHEAD = 3, RING = 4, NFR = KS + NV;
+        u32x4 fr[RING];
+        u32x4 pb[2];
+        // fragment j of kblock kb's NFR, from NFR on those of the next one; `at`: this lane's place in kblock kb
+        auto read = [&](int j, unsigned at) {
+            const int next = j / NFR, f = j % NFR < KS ? j % NFR : j % NFR - KS;
+            res_lds_read(fr[j % RING], at + (next + (j % NFR < KS ? 1 : 0)) * STAGE_BYTES, (j % NFR < KS ? 0 : KB_BYTES) + (f >> 1) * 2048 + (f & 1) * 256);
+        };
+        static_assert(NFR % RING == 0 && STAGE_BYTES + KB_BYTES < 65536, "a fragment's buffer does not depend on the kblock");
+        unsigned at = (unsigned)(size_t)(__attribute__((address_space(3))) const char*)lane_lds;
+        auto step = [&](f32x4 (&cur)[2][2], f32x4 (&nxt)[2][2]) {
+#pragma unroll
+            for (int j = 0; j < NFR; ++j) {
+                read(j + AHEAD, at);
+                res_lds_wait<AHEAD>(fr[j % RING]);
+                const bf16x8 a = __builtin_bit_cast(bf16x8, fr[j % RING]);
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) {
+                    if (j < KS) nxt[j & 1][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[qb][j >> 1], j < 2 ? f32x4{0.f, 0.f, 0.f, 0.f} : nxt[j & 1][qb], 0, 0, 0);
+                    else o[j - KS][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, pb[qb]), o[j - KS][qb], 0, 0, 0);
+                }
+                if (j < KS) {
+#pragma unroll
+                    for (int w = j * 8 / KS; w < (j + 1) * 8 / KS; ++w) weights(cur, w / 4, w % 4, pb);
+                } else if (j >= NFR - 2) {
+                    mx[j - (NFR - 2)] = max_s(nxt, j - (NFR - 2));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            at += STAGE_BYTES;
+        };
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");        // nothing else is counted from here on
+        __builtin_amdgcn_sched_barrier(0);
+        if (T > 1) {
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) read(j, at);
+            step(sA, sB);
+            int kb = 1;
+            for (; kb + 2 < T; kb += 2) {        // (the two score sets swap roles)
+                follow();
+                step(sB, sA);
+                follow();
+                step(sA, sB);
+            }
+            if (kb + 1 < T) {
+                follow();
+                step(sB, sA);
+            } else {
+#pragma unroll
+                for (int m = 0; m < 2; ++m)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb) sA[m][qb] = sB[m][qb];
+            }
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) res_lds_wait<0>(fr[j]);               // (read for a kblock past the last: not used)
+            if (tail < KBLOCK) {
+                mask_tail(sA);
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) mx[qb] = max_s(sA, qb);
+            }
+            follow();
+        }
+#pragma unroll
+        for (int w = 0; w < 8; ++w) weights(sA, w / 4, w % 4, pb);
+#pragma unroll
+        for (int f = 0; f < NV; ++f) {
+            const bf16x8 a = frag(T - 1, 1, f);
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+                o[f][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, pb[qb]), o[f][qb], 0, 0, 0);
         }
 
         // the next block's queries are waited for before the stores are issued: one counter counts both, in order

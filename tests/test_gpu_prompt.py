@@ -368,3 +368,28 @@ def test_cross_attn_out_benchmark_shape():
     want = cross_attention_out(bf16_bits_to_f64(q), bf16_bits_to_f64(k), bf16_bits_to_f64(v), bf16_bits_to_f64(w))
     assert_parity_projection(H.to_bits(y), want, v, "benchmark shape")
     p.close()
+
+
+@pytest.mark.parametrize("heads, head_dim, n_q, n_tok", [(2, 128, 70, 32), (2, 128, 300, 65), (3, 128, 1000, 97), (2, 128, 33, 256),
+                                                          (2, 64, 100, 64), (3, 64, 1000, 290), (2, 64, 65, 512)])
+@pytest.mark.parametrize("at", ["first", "last", "none"])
+def test_resident_kernel_keeps_or_follows_its_reference(heads, head_dim, n_q, n_tok, at):
+    """One, two, three and more kblocks (their two score sets swap roles), ragged ones; a score some 40 sqrt(D) above the first
+    kblock's, which the reference has to follow, in the first and the last kblock."""
+    g = torch.Generator(device="cuda").manual_seed(n_q + n_tok)
+    q, k, v = (torch.empty((n, heads, head_dim), dtype=torch.bfloat16, device="cuda").normal_(generator=g) for n in (n_q, n_tok, n_tok))
+    if at != "none":
+        k[0 if at == "first" else n_tok - 1] = 40 * q[5]
+    prompt = B.Prompt(1, heads, head_dim, 512)
+    prompt.recache(0, k, v)
+    out = torch.full_like(q, 7.0)
+    prompt.cross_attn(0, q, out)
+    torch.cuda.synchronize()
+    prompt.close()
+    qd, kd, vd = (x.double().transpose(0, 1) for x in (q, k, v))
+    w = torch.softmax(torch.stack([a @ b.T.contiguous() for a, b in zip(qd, kd)]) * head_dim ** -0.5, -1)
+    want = torch.stack([a @ b for a, b in zip(w, vd)]).transpose(0, 1)
+    assert bool(torch.isfinite(out).all())
+    assert float((out.double() - want).norm() / want.norm()) <= 5e-3
+    if at != "none":                              # the whole weight of row 5 lies on that key
+        assert float((out[5].double() - want[5]).norm() / want[5].norm()) <= 2.0 ** -8
