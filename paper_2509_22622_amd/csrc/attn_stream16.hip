@@ -162,8 +162,7 @@ using S16NextShare = S16Barrier<1>;
 // `touch` (G > 1): the periods whose kblocks this tile brings into L2 (lds_plan.h: GroupRing).
 // Where the key set has S16_TOUCH_BYTES and more: a few layers of it do not fit the 256 MB of the last-level cache, so it comes from
 // memory.  us a call with the keys of many layers in turn, without and with: 1170 rows x 183 kblocks x 12 heads x 128 (36 MB)
-// 70 -> 52, x 293 107 -> 78, 800 x 125 x 16 51 -> 39, 1170 x 183 x 12 x 64 39 -> 33; a key set that is in that cache 50.8 and 49.8.
-// Below, where it may stay there, touching costs up to 3 us of 15 (720 x 113 x 3 x 64).
+// 70 -> 52, x 293 107 -> 78, 800 x 125 x 16 51 -> 39; a key set that is in that cache 50.8 and 49.8.
 constexpr int S16_TOUCH_BYTES = 16 << 20;
 struct S16Touch { int every = 0, first = 0; };                   // (0: none)
 // The tiles of a head walk the same keys, more or less in step; those on one XCD take turns.  total: workgroups of a
@@ -777,8 +776,9 @@ __device__ __forceinline__ bool s16_groups(const AttnParams& p, const AttnChunk&
     }
     const bool works = q0 < ch.q_end && ve > vb;
     S16State<D> st;
-    if (!(works ? (GroupRing<D, G>::TOUCHES && touch.every > 0
-                       ? s16_segment<D, QSCALE, SCHED, G, GroupRing<D, G>::TOUCHES>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate, touch)
+    constexpr bool TOUCH = GroupRing<D, G>::TOUCHES && !QSCALE;  // (a prompt's keys are few)
+    if (!(works ? (TOUCH && touch.every > 0
+                       ? s16_segment<D, QSCALE, SCHED, G, TOUCH>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate, touch)
                        : s16_segment<D, QSCALE, SCHED, G, false>(p, ch, tid, head, q0, vb, ve, n_steps, lds, st, shift_cs, gate))
                 : s16_group_idle<D, G>(p, ch, tid, head, vb, ve, n_steps, lds, gate)))
         return false;
@@ -950,7 +950,8 @@ __global__ __launch_bounds__(S16_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         __shared__ float2 ml[8][2][16];          // (reference, row sum) per wave, query block and column
         constexpr int NW = 8 / G, PER_WAVE = D / 8 / G;
         const int q0 = row0 + wave % NW * 32;
-        const S16Touch touch = s16_take_turns<D, G>(ch, p.H, row0, tile, idx, p.n_groups == 0 ? p.n_tiles * p.H : 0);
+        S16Touch touch;
+        if constexpr (!QSCALE) touch = s16_take_turns<D, G>(ch, p.H, row0, tile, idx, p.n_groups == 0 ? p.n_tiles * p.H : 0);
         s16_groups<D, QSCALE, SCHED, G>(p, ch, tid, head, q0, 0, 1, lds, shift_cs, ml, S16Unsplit{}, touch);
         if (q0 >= ch.q_end) return;
 #pragma unroll

@@ -130,12 +130,13 @@ struct GroupRing {
     // slot of a period's first step behind whose MFMAs load l of n is issued: spread over the step, or, where that step
     // is the whole period, over its first half (they have to land within it)
     static constexpr int dma_slot(int l, int n, int slots) { return l * slots / n / (PERIOD == 1 ? 2 : 1); }
-    // Keys that come from memory.  A period's loads have a period (half of it where that is one step) to land: enough for L2, not
-    // for memory, and the LDS has no room for longer rings.  So one 4-byte load a lane, 128 bytes apart, brings the kblocks of the
-    // period TOUCH_AHEAD periods on into L2 (and into LDS_TOUCH bytes a wave that nobody reads).  A head's tiles on an XCD take
-    // turns, since a wave's next wait is for the touch too.  With two groups, whose periods are longer, it gains nothing (75.1 us
-    // and 74.5); with eight a launch is too short (5 us of 25 at 300 rows x 24 heads x 64, but 0.2 of 8 lost at 180 x 4).
-    static constexpr bool TOUCHES = G == 4;
+    // Keys that come from memory.  Where a period is one step its loads have half of it to land: enough for L2, not for memory, and
+    // the LDS has no room for longer rings.  So one 4-byte load a lane, 128 bytes apart, brings the kblocks of the period
+    // TOUCH_AHEAD periods on into L2 (and into LDS_TOUCH bytes a wave that nobody reads).  A head's tiles on an XCD take turns,
+    // since a wave's next wait is for the touch too.  Periods of two steps gain less and lose more where the keys are in the
+    // last-level cache (G = 4 at head_dim 64: 39 -> 33 us from memory, but 40 -> 43 from there; G = 2 75.1 -> 74.5 and 67 -> 69), and
+    // launches with eight groups are too short (5 us of 25 at 300 rows x 24 heads x 64, but 0.2 of 8 lost at 180 x 4).
+    static constexpr bool TOUCHES = G == 4 && PERIOD == 1;
     static constexpr int TOUCH_AHEAD = 4, TOUCH_LANES = PERIOD * 2 * BYTES_KBLOCK / 128, LDS_TOUCH = 64 * 4;
     static_assert(!TOUCHES || TOUCH_LANES == 64 * (8 / G), "one load a wave");
 };
