@@ -211,7 +211,7 @@ ll_status ll_clip_forward(ll_clip* clip, int64_t ctx_start, int n_ctx, int n_cli
         p.head_stride = c->hs_all;
         p.H = c->H; p.D = c->D; p.kblock = KBLOCK;
         p.scale_log2e = 1.0f;
-        p.may_split = true;
+        p.may_split = p.may_split_tail = true;
         p.lse = clip_f32(c, c->o_lse); p.lse_stride = c->row_stride;
         p.out32 = clip_f32(c, c->o_o32);
         const int m = std::min(MAX_ATTN_CHUNKS, n_chunks - base);

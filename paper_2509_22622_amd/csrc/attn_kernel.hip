@@ -479,6 +479,37 @@ static bool takes_group8(int H, int n_chunks, const int* rows, const int* kblock
     }
     return tiles <= 256 && longest >= 7 && longest <= 64;
 }
+// A launch of whole-key tiles of one length that fills some rounds of workgroups and a small part of one more: the tiles per head to
+// take out of it and how many splits a launch of their own deals their keys to (0 tiles: none).  What that last round takes with
+// and without, by the model above; it has to save 15 us.  us a clip's forward pass
+// (layout included): 21 frames of 1560 tokens x 12 heads x 128 (1596 tiles, 60 of them in a seventh round) 4085 -> 3637, 21 of 390 x 8
+// (280) 290 -> 218, 18 of 600 x 6 (270) 337 -> 244, 15 of 1560 x 4 (380) 1044 -> 886, 20 of 200 x 15 (300) 143 -> 125.
+// (equal key sets that begin at other places of their first kblocks differ by one or two)
+static bool same_length(int a, int b) { return std::abs(a - b) <= 2 && std::min(a, b) >= 16; }
+struct AttnTail { int tiles, splits; };
+static AttnTail attn_tail(const AttnVariant& v, int H, int n_chunks, const int* rows, const int* kblocks) {
+    constexpr int CUS = 256;
+    int tiles = 0;
+    for (int c = 0; c < n_chunks; ++c) {
+        if (!same_length(kblocks[c], kblocks[0])) return {0, 1};
+        tiles += (rows[c] + v.qtile - 1) / v.qtile;
+    }
+    const int full = tiles * H / CUS * CUS, per_head = (tiles * H - full + H - 1) / H, n = per_head * H;
+    if (v.split[0] == nullptr || full == 0 || per_head == 0 || per_head >= tiles) return {0, 1};
+    const SplitModel& m = kSplitModel[v.D == 128 ? 0 : 1];
+    auto steps = [&](int workgroups, int length) { return length * m.split[0].step * (1 + m.split[0].busy * double(workgroups) / CUS) + m.around_split; };
+    AttnTail best{0, 1};
+    double most = 15;
+    for (int splits = 2; splits <= MAX_SPLITS && n * splits <= CUS && splits <= kblocks[0]; ++splits) {
+        const double saved = steps(n, kblocks[0]) - steps(n * splits, (kblocks[0] + splits - 1) / splits) -
+                             (m.merge + m.per_split * splits + m.per_mb * 1e-6 * double(n) * splits * v.qtile * v.D * 4);
+        if (saved > most) {
+            most = saved;
+            best = {per_head, splits};
+        }
+    }
+    return best;
+}
 static __device__ SplitPool split_pool;
 // its address on the current device (looked up on the first call per device; threads may do that at the same time)
 hipError_t split_pool_address(SplitPool** pool) {
@@ -540,6 +571,27 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
             const AttnSplit split = attn_split(variant, p.H, p.n_chunks, rows, kblocks);
             p.key_groups = split.groups;
             p.splits = split.splits;
+            const AttnTail tail = p.may_split_tail && split.groups == 1 && split.splits == 1 ? attn_tail(v, p.H, p.n_chunks, rows, kblocks) : AttnTail{0, 1};
+            if (tail.tiles > 0) {                // the last tiles of the last chunks in a launch of their own
+                AttnParams t = p, rest = p;
+                t.key_groups = rest.key_groups = 1;
+                t.splits = tail.splits;
+                rest.splits = 1;
+                t.n_chunks = 0;
+                for (int left = tail.tiles; left > 0;) {
+                    AttnChunk& last = rest.chunk[rest.n_chunks - 1];
+                    AttnChunk& moved = t.chunk[t.n_chunks++] = last;
+                    const int tiles = (last.q_end - last.q_begin + v.qtile - 1) / v.qtile;
+                    if (tiles <= left) {
+                        --rest.n_chunks;
+                    } else {
+                        moved.q_begin = last.q_end = last.q_begin + (tiles - left) * v.qtile;
+                    }
+                    left -= tiles;
+                }
+                const hipError_t e = launch_attn(rest, variant, s);
+                return e != hipSuccess ? e : launch_attn(t, variant, s);
+            }
             if (p.may_group8 && split.splits == 1 && takes_group8(p.H, p.n_chunks, rows, kblocks)) p.key_groups = 8;
         }
     }
@@ -572,9 +624,11 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     }
     p.n_groups = 0;
     const int groups = p.H * p.n_chunks;
-    // (every kernel but the simple ones reads the placement; a launch of one round is better dealt out evenly: whole
-    // groups can give one XCD more tiles than it has CUs)
-    if (variant > kNumSimple && p.splits == 1 && p.n_chunks > 1 && total > 256 && groups >= 16 && groups <= MAX_XCD_GROUPS) {
+    // (every kernel but the simple ones reads the placement; a launch of one round, or of tiles of one length, is better dealt out
+    // evenly: whole groups can give one XCD more tiles than the others; 500 tiles of a clip of 15 x 390 rows x 20 x 64 283 us -> 208)
+    bool one_length = true;
+    for (int c = 1; c < p.n_chunks; ++c) one_length = one_length && same_length(p.chunk[c].n_kblocks, p.chunk[0].n_kblocks);
+    if (variant > kNumSimple && p.splits == 1 && p.n_chunks > 1 && !one_length && total > 256 && groups >= 16 && groups <= MAX_XCD_GROUPS) {
         // Tiles of different chunks differ in length, and the hardware binds workgroup b to XCD b % 8: hand each
         // XCD whole (head, chunk) groups so that all carry the same number of kblock steps (longest group to the
         // least loaded XCD), and let each start with its longest tiles.

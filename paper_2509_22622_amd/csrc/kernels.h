@@ -165,6 +165,7 @@ struct AttnParams {
     int key_groups;              // key groups per tile (AttnVariant::grouped); 0: chosen for the launch,
     bool may_split;              // and splits with them
     bool may_group8;             // 8-bit cache: and tiles of 64 rows in four key groups
+    bool may_split_tail;         // and splits for the tiles of the last round alone (queries rotated already, whole chunks or not)
     // A tile's keys dealt to `splits` workgroups, whose partial results a second kernel merges (split.h);
     // chunks of fewer kblocks take fewer.  The rest is filled in by launch_attn.
     int splits;

@@ -387,3 +387,34 @@ def test_re_prefill_beside_streaming_of_chunks_that_split(kv_format, heads, head
     rebuilt.close()
     # twice a path's 5e-3 (bf16), or one path's weights of 3 mantissa bits, 2.6 % of the 2-norm each, and the other's
     assert _rel(got, want.double()) <= (1e-2 if kv_format == "bf16" else 3e-2)
+
+
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, clip_frames", [
+    (8, 128, (15, 26), 3, 21),       # 280 tiles: the last three of every head's last chunk
+    (15, 128, (10, 20), 1, 20),      # 300 tiles, one a chunk: three whole chunks
+    (9, 128, (15, 26), 2, 15),       # 270 tiles, a last chunk of two: that one and a tile of the next
+    (15, 64, (15, 26), 3, 21)])      # 525 tiles, one a head
+def test_clip_whose_last_round_is_split(heads, head_dim, grid, chunk, clip_frames):
+    """The tiles of a clip's forward pass that do not fill a round of workgroups have their keys dealt to several: output and, by
+    way of the row sums, gradients against 64 bits (test_gpu_clip.py: 5e-3 each); with slots taken the same bits."""
+    case = {"kind": "clip", "heads": heads, "head_dim": head_dim, "grid_h": grid[0], "grid_w": grid[1], "chunk": chunk, "sink": 3,
+            "window": 9, "ctx_start": 40, "n_ctx": 9, "clip_frames": clip_frames, "q_std": 1.0}
+    rows = grid[0] * grid[1]
+    tiles = sum(-(-min(chunk, clip_frames - f) * rows // 256) for f in range(0, clip_frames, chunk)) * heads
+    assert tiles > 256 and 0 < tiles % 256 <= 64
+    state = cases.prepare(case, 3)
+    got = [x.clone() for x in cases.run(state)]
+    torch.cuda.synchronize()
+    for a, b in zip(got, cases.exact(case, 3)):
+        assert _rel(a, b) <= 5e-3
+    for first, n in ((0, 512), (1, 300)):
+        B.hold_split_slots(first, n, True)
+        try:
+            again = [x.clone() for x in cases.run(state)]
+            torch.cuda.synchronize()
+        finally:
+            B.hold_split_slots(first, n, False)
+        for a, b in zip(again, got):
+            assert torch.equal(_bits(a), _bits(b)), (first, n)
+    assert B.split_slots_taken() == 0
+    state["clip"].close()
