@@ -20,8 +20,8 @@
  *   - The cache's device buffer is owned by the caller and must outlive the
  *     handle.  The library allocates no device memory; it holds two static arrays
  *     on each GPU it is used on, until the process ends: 85 MB (81 MiB) for partial results of
- *     attention calls of few rows and heads, which deal a tile's keys to several
- *     workgroups and merge their results in a second kernel, and the 36 MiB of
+ *     attention calls of few rows and heads, and of the last tiles of a clip's forward pass, which deal a tile's keys
+ *     to several workgroups and merge their results in a second kernel, and the 36 MiB of
  *     ll_recache_prefill_static.  All calls on a GPU, from any stream or thread, eager
  *     or captured, share the first one; a call that finds no room in it takes longer.
  *   - Results do not depend on what else the GPU is doing: a call repeated on the

@@ -19,7 +19,7 @@
 // and the shift; 2^v_exp is applied there.
 //
 // Launches of few rows and heads: a 256-row tile of each head is less than the chip has CUs, and every workgroup walks all keys
-// at the pace of two waves per SIMD (0.8 us a kblock at head_dim 128, exponentials and MFMAs in turn).  They take narrower tiles
+// at the pace of two waves per SIMD (0.8 us a kblock at head_dim 128).  They take narrower tiles
 // (0.55 us with one wave per SIMD) and, below that, several workgroups per tile (split.h).  us: 980 rows x 50 kblocks x 2 heads x
 // 128 50 -> 29; 300 x 36 x 24 x 128 42 -> 28; the rule and more figures are at attn_split in attn_kernel.hip.
 //
@@ -326,8 +326,8 @@ __device__ __forceinline__ void f8_lds_wait(u32x4& x, u32x4& y) {
 // through the general form of the step one at a time, all others in aligned pairs through a form with no
 // masking logic.
 //
-// LOGLIN = true is a cheaper way to the weights (the exponentials bound the exact form: 16 cycles each on the vector
-// pipe).  An E4M3 code read as an integer is nearly linear in the logarithm of its value (8 codes per octave), so the
+// LOGLIN = true is a cheaper way to the weights (the exponentials are the largest part of the exact form's vector
+// work, 8.6 clocks each).  An E4M3 code read as an integer is nearly linear in the logarithm of its value (8 codes per octave), so the
 // code of 2^x is taken as round(8 x + 56) (56 = the code of 1.0) with one multiply-add and one v_cvt_pk_u8_f32 per
 // score (which also clamps at 0 and inserts the byte into the operand word): the weight is 2^x times a factor between
 // 0.96 and 1.02 (after the common factor has cancelled in the normalisation), on top of a rounding to an eighth of

@@ -592,7 +592,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
                 const hipError_t e = launch_attn(rest, variant, s);
                 return e != hipSuccess ? e : launch_attn(t, variant, s);
             }
-            if (p.may_group8 && split.splits == 1 && takes_group8(p.H, p.n_chunks, rows, kblocks)) p.key_groups = 8;
+            if (p.may_group8 && v.grouped[2] != nullptr && split.splits == 1 && takes_group8(p.H, p.n_chunks, rows, kblocks)) p.key_groups = 8;
         }
     }
     int log_g = 0;
