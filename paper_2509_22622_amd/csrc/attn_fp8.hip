@@ -513,7 +513,9 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
 #pragma unroll
         for (int j = 0; j < 8; ++j) vmask[j] = 0xFFFFFFFFu;
     }
-    if constexpr (G > 1) __builtin_amdgcn_s_barrier();           // step 0 loads over the keys of kblock vb
+    // step 0 loads over the keys read above: every wave's reads have returned (and stay in front of the barrier, which the
+    // builtin does not promise)
+    if constexpr (G > 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     // fragment of slot j of the step whose S^T kblock is stage `ks` and whose O^T kblock is stage `vs`
 #define F8_READ_FRAG(J, KT_A, VT_A)                                                                                 \
     {                                                                                                               \

@@ -28,3 +28,9 @@ def test_bf16_split_kernels_do_not_spill():
     """The merges' too, with their loop over a tile's shares."""
     ours = {k: v for k, v in _spills("attn_stream16.hip").items() if "ll_attn_split16_kernel" in k or "ll_attn_merge16_kernel" in k}
     assert len(ours) == 42 and all(v == 0 for v in ours.values()), f"spills: {ours}"
+
+
+def test_key_group_kernels_do_not_spill():
+    """The 8-bit kernels whose tiles' keys are dealt to groups of waves."""
+    ours = {k: v for k, v in _spills("attn_fp8.hip").items() if "ll_attn_fp8_kernel" in k and "ELi7E" in k}
+    assert len(ours) == 2 and all(v == 0 for v in ours.values()), f"spills: {ours}"
