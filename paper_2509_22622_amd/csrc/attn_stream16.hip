@@ -277,10 +277,11 @@ __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk
 #pragma unroll
         for (int k = 0; k < KS; ++k) s16_lds_wait<0>(kf[k]);
         if (TOUCH && --touch_in < 0) {
-            touch_period(touch_at);
+            asm volatile("" ::: "memory");       // the touch is the last load in front of the wait that leaves one out: not even
+            touch_period(touch_at);              // the compiler may move another between them
             touch_in += touch.every;
             touch_at += touch.every * PERIOD;
-            s16_wait_vmcnt<1>();
+            asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
         } else {
             s16_wait_vmcnt<0>();
         }
