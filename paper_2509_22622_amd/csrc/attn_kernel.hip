@@ -538,6 +538,7 @@ static void split_forget(SplitPool* pool, unsigned long long token, hipStream_t 
 }
 
 constexpr int GROUPED_LDS_BYTES = 130 * 1024;    // GroupRing: 128 KB / G at most per group (the groups' results fit too), and what is touched
+static_assert(4 * GroupRing<128, 4>::BYTES + 8 * GroupRing<128, 4>::LDS_TOUCH <= GROUPED_LDS_BYTES, "rings and what is touched");
 
 hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     if (!attn_variant_supports(variant, p_in.D, p_in.kblock)) return hipErrorInvalidValue;

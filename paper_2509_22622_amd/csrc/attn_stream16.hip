@@ -159,7 +159,7 @@ struct S16Barrier {
 };
 using S16Unsplit = S16Barrier<0>;
 using S16NextShare = S16Barrier<1>;
-// `touch` (G > 1): the periods whose kblocks this tile brings into L2 (lds_plan.h: GroupRing).
+// `touch` (GroupRing::TOUCHES in lds_plan.h): the periods whose kblocks this tile brings into L2.
 // Where the key set has S16_TOUCH_BYTES and more: a few layers of it do not fit the 256 MB of the last-level cache, so it comes from
 // memory.  us a call with the keys of many layers in turn, without and with: 1170 rows x 183 kblocks x 12 heads x 128 (36 MB)
 // 70 -> 52, x 293 107 -> 78, 800 x 125 x 16 51 -> 39; a key set that is in that cache 50.8 and 49.8.
@@ -263,10 +263,11 @@ __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
                                          (__attribute__((address_space(3))) void*)(dst), 16, 0, 0);
     };
-    // the kblocks of the period that begins with step `first`, 128 bytes a lane (past the share's end the last one again)
+    // the kblock of the period that begins with step `first` (a period is one step where anything is touched), 128 bytes a lane (past
+    // the share's end the last one again)
     auto touch_period = [&](int first) {
-        const int at = wave * 64 / D, in = (wave * 64 + lane) % D;              // kblock of the period, and 128 bytes of its K and V
-        const char* src = (in < D / 2 ? kbase : vbase) + in % (D / 2) * 128 + int64_t(S16_PHYS_KB(min(vb + first + at, ve - 1))) * KB_BYTES;
+        const int in = wave * 64 + lane;         // of a kblock's K and V
+        const char* src = (in < D / 2 ? kbase : vbase) + in % (D / 2) * 128 + int64_t(S16_PHYS_KB(min(vb + first, ve - 1))) * KB_BYTES;
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
                                          (__attribute__((address_space(3))) void*)(lds_touch), 4, 0, 0);
     };
@@ -281,7 +282,7 @@ __device__ __forceinline__ bool s16_segment(const AttnParams& p, const AttnChunk
             touch_period(touch_at);              // the compiler may move another between them
             touch_in += touch.every;
             touch_at += touch.every * PERIOD;
-            asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(GR::TOUCH_LOADS) : "memory");
         } else {
             s16_wait_vmcnt<0>();
         }

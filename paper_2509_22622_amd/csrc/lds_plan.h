@@ -137,7 +137,8 @@ struct GroupRing {
     // last-level cache (G = 4 at head_dim 64: 39 -> 33 us from memory, but 40 -> 43 from there; G = 2 75.1 -> 74.5 and 67 -> 69), and
     // launches with eight groups are too short (5 us of 25 at 300 rows x 24 heads x 64, but 0.2 of 8 lost at 180 x 4).
     static constexpr bool TOUCHES = G == 4 && PERIOD == 1;
-    static constexpr int TOUCH_AHEAD = 4, TOUCH_LANES = PERIOD * 2 * BYTES_KBLOCK / 128, LDS_TOUCH = 64 * 4;
+    // TOUCH_LOADS of a wave, its last in front of a hand-over, may still be in flight behind it.
+    static constexpr int TOUCH_AHEAD = 4, TOUCH_LOADS = 1, TOUCH_LANES = PERIOD * 2 * BYTES_KBLOCK / 128, LDS_TOUCH = 64 * 4;
     static_assert(!TOUCHES || TOUCH_LANES == 64 * (8 / G), "one load a wave");
 };
 

@@ -3,7 +3,9 @@
 // loads, LDS reads, waits and barriers under random interleavings; loads land at random later times unless a wait
 // forces them.  Violations: a read of a fragment that has not landed or holds another kblock, a load issued to a fragment
 // that some wave still has a read of in flight, waves that leave with unequal numbers of barriers behind them (the
-// barrier is the workgroup's: all groups run the same number of steps).  Exit status 0 = no violation in any run.
+// barrier is the workgroup's: all groups run the same number of steps).  Waves that bring kblocks into L2 ahead (GroupRing::TOUCHES)
+// issue such a load, which nobody reads, in front of some hand-overs, whose wait leaves it in flight.  Exit status 0 = no violation
+// in any run.
 #include <cstdio>
 #include <cstdlib>
 #include <initializer_list>
@@ -11,7 +13,7 @@
 
 #include "../paper_2509_22622_amd/csrc/lds_plan.h"
 
-enum Kind { LOAD, WAIT_LOADS, BARRIER, READ, READ_DONE };
+enum Kind { LOAD, TOUCH, WAIT_LOADS, WAIT_BUT_TOUCH, BARRIER, READ, READ_DONE };
 struct Op { Kind kind; int is_v, rel, frag; };           // rel: kblock relative to the share's first
 
 // what one wave of a group issues
@@ -22,19 +24,27 @@ struct Program {
     static constexpr int KS = Plan::KS, NV = Plan::NV, NF = KS + NV, NW = 8 / G, LPW = Ring::PERIOD * NF / NW;
     std::vector<Op> ops;
     int wave, share;                                     // among the waves of the ring; kblocks of the share
+    int every = 0, touch_in = 0;                         // S16Touch: one touch every so many periods (0: none); periods to the next
 
     void load(int first, int l) {                        // as issue_group: V of the period's kblocks, K two kblocks on
         const int j = NW * l / NF, part = NW * l % NF;
         const int is_v = part >= KS;
         ops.push_back({LOAD, is_v, first + j + (is_v ? 0 : 2), (is_v ? part - KS : part) + wave});
     }
-    void handover() {
-        ops.push_back({WAIT_LOADS, 0, 0, 0});
+    void handover(bool touches) {
+        if (touches && every > 0 && --touch_in < 0) {
+            ops.push_back({TOUCH, 0, 0, 0});
+            touch_in += every;
+            ops.push_back({WAIT_BUT_TOUCH, 0, 0, 0});
+        } else {
+            ops.push_back({WAIT_LOADS, 0, 0, 0});
+        }
         if (NW > 1) ops.push_back({BARRIER, 0, 0, 0});
     }
     void works(int n_steps) {
         for (int l = 0; l < LPW; ++l) load(0, l);
-        handover();
+        for (int t = touch_in; every > 0 && t < Ring::TOUCH_AHEAD; t += every) ops.push_back({TOUCH, 0, 0, 0});
+        handover(false);
         std::vector<int> k_pending(KS, -1);              // K reads in flight from the step before: their kblock
         for (int r = 0; r < n_steps; ++r) {
             for (int slot = 0; slot < NF; ++slot) {
@@ -60,7 +70,7 @@ struct Program {
                     ops.push_back({READ_DONE, 0, k_pending[f], f});
                     k_pending[f] = -1;
                 }
-                handover();
+                handover(true);
             }
         }
     }
@@ -69,7 +79,7 @@ struct Program {
         for (int r = -Ring::PERIOD; r + Ring::PERIOD <= n_steps; r += Ring::PERIOD) {
             if (share > 0)
                 for (int l = 0; l < LPW; ++l) load(r + Ring::PERIOD, l);
-            handover();
+            handover(false);
         }
         if (n_steps % Ring::PERIOD != 0 && share > 0)
             for (int l = 0; l < LPW; ++l) load(n_steps / Ring::PERIOD * Ring::PERIOD + Ring::PERIOD, l);
@@ -78,18 +88,21 @@ struct Program {
 
 struct Fragment { int kblock = -1, owner = -1, seq = -1, readers = 0; };
 
-// T kblocks; the first `with_rows` of a group's waves have query rows
+// T kblocks; the first `with_rows` of a group's waves have query rows, which touch every `every` periods from the `first` on
 template <int D, int G>
-static int simulate(int T, int with_rows, unsigned seed) {
+static int simulate(int T, int with_rows, unsigned seed, int every, int first) {
     using P = Program<D, G>;
     constexpr int DEPTH = P::Ring::DEPTH;
     std::srand(seed);
+    const int lag = seed % 2 ? 4 : 256;                  // how late loads land that nothing waits for
     const int n_steps = (T + G - 1) / G;
     std::vector<P> prog(8);
     int barriers[8];
     for (int w = 0; w < 8; ++w) {
         const int group = w / P::NW;
         prog[w].wave = w % P::NW;
+        prog[w].every = every;
+        prog[w].touch_in = first;
         prog[w].share = T * (group + 1) / G - T * group / G;
         if (prog[w].share > 0 && prog[w].wave < with_rows) prog[w].works(n_steps);
         else prog[w].idles(n_steps);
@@ -122,13 +135,15 @@ static int simulate(int T, int with_rows, unsigned seed) {
         const int w = std::rand() % 8, group = w / P::NW;
         if (pc[w] >= prog[w].ops.size() || waiting[w]) continue;
         for (int o = 0; o < 8; ++o)
-            if (landed[o] < issued[o] && std::rand() % 4 == 0) ++landed[o];
+            if (landed[o] < issued[o] && std::rand() % lag == 0) ++landed[o];
         const Op op = prog[w].ops[pc[w]];
         Fragment& f = at(group, op);
         const int kblock = op.rel < prog[w].share - 1 ? op.rel : prog[w].share - 1;      // past the end the last one again
         const char* what = op.is_v ? "V" : "K";
         if (op.kind == BARRIER) { waiting[w] = 1; continue; }
+        if (op.kind == TOUCH) ++issued[w];
         if (op.kind == WAIT_LOADS) landed[w] = issued[w];
+        if (op.kind == WAIT_BUT_TOUCH && landed[w] < issued[w] - P::Ring::TOUCH_LOADS) landed[w] = issued[w] - P::Ring::TOUCH_LOADS;
         if (op.kind == LOAD) {
             if (f.readers > 0) {
                 std::printf("D %d G %d T %d: wave %d loads %s %d over a fragment being read\n", D, G, T, w, what, op.rel);
@@ -154,8 +169,11 @@ template <int D, int G>
 static int check() {
     for (int T : {1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 64, 83})
         for (int with_rows = 1; with_rows <= 8 / G; ++with_rows)
-            for (unsigned seed = 1; seed <= 25; ++seed)
-                if (simulate<D, G>(T, with_rows, seed * 7919u + T)) return 1;
+            for (unsigned seed = 1; seed <= 25; ++seed) {
+                if (simulate<D, G>(T, with_rows, seed * 7919u + T, 0, 0)) return 1;
+                for (int every = 1; every <= 8 && ll::GroupRing<D, G>::TOUCHES; every *= 2)
+                    if (simulate<D, G>(T, with_rows, seed * 7919u + T, every, int(seed) % every)) return 1;
+            }
     return 0;
 }
 

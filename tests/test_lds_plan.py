@@ -65,6 +65,7 @@ def test_group_ring_simulation(tmp_path):
 @pytest.mark.parametrize("old, new", [
     ("DEPTH = 2 * PERIOD;", "DEPTH = PERIOD;"),                   # a half stage loaded while it is read
     ("return l * slots / n / (PERIOD == 1 ? 2 : 1);", "return l * slots / n + slots / 2;"),   # half of the loads left out
+    ("TOUCH_LOADS = 1", "TOUCH_LOADS = 2"),                       # a hand-over that leaves out more than the touch
 ])
 def test_group_ring_simulation_catches_a_wrong_plan(tmp_path, old, new):
     text = open(PLAN).read()
