@@ -413,10 +413,10 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
     // G > 1: load l of those that step `rel` (relative to vb; -1: the prologue) issues, V of the kblock after it, K of the one after that
     auto issue_group = [&](int rel, int l) {
         const bool is_k = l < LPW / 2;
-        const int ahead = rel + (is_k ? 2 : 1), v = min(vb + ahead, ve - 1), f = wave + NW * (is_k ? l : l - LPW / 2);
+        const int ahead = rel + (is_k ? GR::K_AHEAD : GR::V_AHEAD), v = min(vb + ahead, ve - 1), f = wave + NW * (is_k ? l : l - LPW / 2);
         const char* src = (is_k ? kbase : vbase) + int64_t(F8_PHYS_KB(v)) * KB_BYTES + f * 1024 + lane_off;
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src),
-                                         (__attribute__((address_space(3))) void*)(lds + ((is_k ? 0 : 2) + (ahead & 1)) * KB_BYTES + f * 1024), 16, 0, 0);
+                                         (__attribute__((address_space(3))) void*)(lds + (is_k ? GR::k_half(ahead) : GR::v_half(ahead)) * KB_BYTES + f * 1024), 16, 0, 0);
     };
 
     if constexpr (G == 1) {
@@ -432,10 +432,10 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
         for (int l = 0; l < LPW / 2; ++l) {
             const int f = wave + NW * l;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kbase + int64_t(F8_PHYS_KB(0)) * KB_BYTES + f * 1024 + lane_off),
-                                             (__attribute__((address_space(3))) void*)(lds + 3 * KB_BYTES + f * 1024), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(lds + GR::FIRST_HALF * KB_BYTES + f * 1024), 16, 0, 0);
         }
 #pragma unroll
-        for (int l = 0; l < LPW / 2; ++l) issue_group(-2, l);
+        for (int l = 0; l < LPW / 2; ++l) issue_group(-GR::K_AHEAD, l);
 #pragma unroll
         for (int l = 0; l < LPW; ++l) issue_group(-1, l);
     }
@@ -487,12 +487,12 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
                 }
             }
         };
-        plain_scores(lds + (G == 1 ? (vb & (NS - 1)) * STAGE_BYTES : 3 * KB_BYTES) + lane_off);
+        plain_scores(lds + (G == 1 ? (vb & (NS - 1)) * STAGE_BYTES : GR::FIRST_HALF * KB_BYTES) + lane_off);
         mask_s(sA, F8_LIVE(G == 1 ? vb : 0));
         const float m = max_s(sA);
         mref = fmaxf(m, __shfl_xor(m, 32));
         if constexpr (G > 1) {
-            plain_scores(lds + lane_off);
+            plain_scores(lds + GR::k_half(0) * KB_BYTES + lane_off);
             mask_s(sA, F8_LIVE(vb));
         }
         if (LOGLIN) {
@@ -570,9 +570,9 @@ __device__ __forceinline__ void f8_segment_sp(const AttnParams& p, const AttnChu
             }                                                                                                       \
         }                                                                                                           \
         const unsigned kt_a = lds_a + (G == 1 ? (((I) + 1) & (NS - 1)) * STAGE_BYTES                                \
-                                              : (((I) + 1 - vb) & 1) * KB_BYTES);      /* K8 of kblock I + 1 */      \
+                                              : GR::k_half((I) + 1 - vb) * KB_BYTES);  /* K8 of kblock I + 1 */      \
         const unsigned vt_a = lds_a + (G == 1 ? ((I) & (NS - 1)) * STAGE_BYTES + KB_BYTES                           \
-                                              : (2 + (((I) - vb) & 1)) * KB_BYTES);    /* V8 of kblock I     */      \
+                                              : GR::v_half((I) - vb) * KB_BYTES);      /* V8 of kblock I     */      \
         const unsigned kn_a = lds_a + (((I) + 2) & (NS - 1)) * STAGE_BYTES;            /* K8 of kblock I + 2 */      \
         i32x8 pb, pl;                                                                                               \
         float m_run = -INFINITY;                                                                                    \
@@ -756,12 +756,12 @@ __device__ __forceinline__ void f8_group_idle(const AttnParams& p, const AttnChu
     const unsigned lane_off = lane * 16;
     auto issue = [&](int rel, bool is_k) {
         if (ve <= vb) return;
-        const int ahead = rel + (is_k ? 2 : 1), v = min(vb + ahead, ve - 1), kb = v + f8_pick(v, n0, n01, kb0, kb1 - n0, kb2 - n01);
+        const int ahead = rel + (is_k ? GR::K_AHEAD : GR::V_AHEAD), v = min(vb + ahead, ve - 1), kb = v + f8_pick(v, n0, n01, kb0, kb1 - n0, kb2 - n01);
 #pragma unroll
         for (int l = 0; l < PIECES; ++l) {
             const int f = wave + NW * l;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((is_k ? kbase : vbase) + int64_t(kb) * KB_BYTES + f * 1024 + lane_off),
-                                             (__attribute__((address_space(3))) void*)(lds + ((is_k ? 0 : 2) + (ahead & 1)) * KB_BYTES + f * 1024), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(lds + (is_k ? GR::k_half(ahead) : GR::v_half(ahead)) * KB_BYTES + f * 1024), 16, 0, 0);
         }
     };
     if (ve > vb)
@@ -769,9 +769,9 @@ __device__ __forceinline__ void f8_group_idle(const AttnParams& p, const AttnChu
         for (int l = 0; l < PIECES; ++l) {
             const int f = wave + NW * l;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(kbase + int64_t(f8_pick(0, n0, n01, kb0, kb1 - n0, kb2 - n01)) * KB_BYTES + f * 1024 + lane_off),
-                                             (__attribute__((address_space(3))) void*)(lds + 3 * KB_BYTES + f * 1024), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(lds + GR::FIRST_HALF * KB_BYTES + f * 1024), 16, 0, 0);
         }
-    issue(-2, true);
+    issue(-GR::K_AHEAD, true);
     for (int rel = -1; rel < n_steps; ++rel) {
         issue(rel, true);
         issue(rel, false);
@@ -847,7 +847,7 @@ __device__ __forceinline__ void f8_groups(const AttnParams& p, const AttnChunk& 
     if (q0 >= ch.q_end) return;
     float m = -INFINITY, l = 0.f, a[G];
 #pragma unroll
-    for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + wave % NW][col].x);     // (the first share has a kblock of the tile's: finite)
+    for (int j = 0; j < G; ++j) m = fmaxf(m, ml[j * NW + wave % NW][col].x);     // (the last share always has a kblock: finite)
 #pragma unroll
     for (int j = 0; j < G; ++j) {
         const float2 s = ml[j * NW + wave % NW][col];

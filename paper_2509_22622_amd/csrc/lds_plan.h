@@ -93,11 +93,17 @@ struct Fp8LdsPlan {
 // The rings of a workgroup of the 8-bit kernel whose waves are dealt into G key groups (attn_fp8.hip, G = 4): a group's walk their
 // share of the kblocks through two half stages of keys and two of values.  The step for kblock i reads V of i and K of i + 1 and
 // issues the loads of V of i + 1 and K of i + 2, over the half stages that the step before has read; behind it a wave waits for
-// all it has issued and meets the others at a barrier.  Nothing is read ahead across that.
+// all it has issued and meets the others at a barrier.  Nothing is read ahead across that.  The prologue loads K of a share's first two
+// kblocks and V of the first, and the keys of the tile's first kblock to where V of the share's second will be; it reads those and the
+// share's first keys between two barriers.
 template <int D, int G>
 struct Fp8GroupRing {
-    static constexpr int BYTES = 4 * 64 * D;
+    static constexpr int KB_BYTES = 64 * D, BYTES = 4 * KB_BYTES;
     static_assert(G * BYTES <= 128 * 1024, "the rings of a workgroup");
+    static constexpr int K_AHEAD = 2, V_AHEAD = 1;               // kblocks from a step to those it loads
+    static constexpr int k_half(int rel) { return rel & 1; }     // half stage of a share's rel-th kblock
+    static constexpr int v_half(int rel) { return 2 + (rel & 1); }
+    static constexpr int FIRST_HALF = v_half(1);
     static constexpr int dma_slot(int l, int n, int slots) { return l * slots / n / 2; }         // in the step's first half
 };
 
