@@ -30,6 +30,14 @@ ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* r
  * groups of waves (bf16, not split: ll_attn_key_groups' answer; 8-bit: a tile has 256 / groups rows and its waves all walk
  * all keys of the split).  No GPU needed. */
 ll_status ll_attn_split(int head_dim, int fp8, int heads, int rows, int kblocks, int* groups, int* splits);
+/* What one launch of n_chunks chunks (24 at most) of rows[i] query rows over kblocks[i] blocks of keys takes (host arrays).  No GPU
+ * needed.
+ *   ll_attn_key_groups_fp8: a launch of a re-prefill of an 8-bit cache (blocks of 64 keys), all of whose chunks would have splits
+ *     when streamed (ll_attn_split): 4 where its tiles have 64 rows and their keys dealt to four groups of waves, else 1.
+ *   ll_attn_clip_tail: a clip's forward pass (blocks of 32 keys; the latest chunk is the first): how many tiles per head, from the
+ *     end of the list, go out in a launch of their own with their keys dealt to `splits` workgroups; 0 and 1 where none do. */
+ll_status ll_attn_key_groups_fp8(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* groups);
+ll_status ll_attn_clip_tail(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* tiles, int* splits);
 /* The partial results of split tiles wait for their merge in 512 slots that all calls on a GPU share; a workgroup that finds
  * no slot free leaves its tile to the merge, where one workgroup then computes the tile's shares one after another, with the
  * same result.  This call takes the free ones among slots [first, first + n) out of use on the current device (hold != 0), or

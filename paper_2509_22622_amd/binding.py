@@ -55,6 +55,8 @@ SIGNATURES = {
     "ll_attn_variant_name": (C.c_char_p, [_i]),
     "ll_attn_key_groups": (_i, [_i] * 3 + [C.POINTER(_i)] * 3),
     "ll_attn_split": (_i, [_i] * 5 + [C.POINTER(_i)] * 2),
+    "ll_attn_key_groups_fp8": (_i, [_i] * 3 + [C.POINTER(_i)] * 3),
+    "ll_attn_clip_tail": (_i, [_i] * 3 + [C.POINTER(_i)] * 4),
     "ll_hold_split_slots": (_i, [_i] * 3),
     "ll_split_slots_taken": (_i, [C.POINTER(_i)]),
     "ll_probe_mfma_rate": (_i, [C.c_void_p, C.c_size_t, _i, _i, _i, C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
@@ -124,6 +126,24 @@ def attn_split(head_dim, heads, rows, kblocks, kv_format="bf16"):
     groups, splits = C.c_int(), C.c_int()
     _check(lib().ll_attn_split(head_dim, int(kv_format == "fp8_e4m3"), heads, rows, kblocks, C.byref(groups), C.byref(splits)))
     return groups.value, splits.value
+
+
+def attn_key_groups_fp8(head_dim, heads, chunks) -> int:
+    """4 where a re-prefill launch of an 8-bit cache deals its tiles' keys to groups of waves, else 1; ``chunks``: (query rows,
+    blocks of 64 keys) each, all of which would split when streamed."""
+    rows, kblocks = ((C.c_int * len(chunks))(*x) for x in zip(*chunks))
+    groups = C.c_int()
+    _check(lib().ll_attn_key_groups_fp8(head_dim, heads, len(chunks), rows, kblocks, C.byref(groups)))
+    return groups.value
+
+
+def attn_clip_tail(head_dim, heads, chunks):
+    """(tiles per head, splits) of the last round that a clip's forward pass launches by itself; ``chunks``: (query rows, blocks of
+    32 keys) each, the latest first."""
+    rows, kblocks = ((C.c_int * len(chunks))(*x) for x in zip(*chunks))
+    tiles, splits = C.c_int(), C.c_int()
+    _check(lib().ll_attn_clip_tail(head_dim, heads, len(chunks), rows, kblocks, C.byref(tiles), C.byref(splits)))
+    return tiles.value, splits.value
 
 
 def hold_split_slots(first: int, n: int, hold: bool) -> None:

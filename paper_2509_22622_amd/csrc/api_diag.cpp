@@ -17,12 +17,22 @@ ll_status ll_set_attn_variant(int variant) {
 }
 const char* ll_attn_variant_name(int variant) { return attn_variant_name(variant); }
 
-ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* groups) {
-    if (!rows || !kblocks || !groups) return fail(LL_ERR_INVALID_ARG, "null pointer");
+extern "C++" {
+namespace {
+ll_status check_launch(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks) {
     if ((head_dim != 64 && head_dim != 128) || heads < 1 || heads > 1024 || n_chunks < 1 || n_chunks > MAX_ATTN_CHUNKS)
         return fail(LL_ERR_INVALID_ARG, "head_dim %d, heads %d or n_chunks %d out of range", head_dim, heads, n_chunks);
     for (int c = 0; c < n_chunks; ++c)
         if (rows[c] < 1 || kblocks[c] < 1) return fail(LL_ERR_INVALID_ARG, "chunk %d has %d rows and %d kblocks", c, rows[c], kblocks[c]);
+    return LL_OK;
+}
+}  // namespace
+}  // extern "C++"
+
+ll_status ll_attn_key_groups(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* groups) {
+    if (!rows || !kblocks || !groups) return fail(LL_ERR_INVALID_ARG, "null pointer");
+    const ll_status bad = check_launch(head_dim, heads, n_chunks, rows, kblocks);
+    if (bad != LL_OK) return bad;
     *groups = attn_key_groups(attn_variant_default(head_dim, KBLOCK), heads, n_chunks, rows, kblocks);
     return LL_OK;
 }
@@ -34,6 +44,26 @@ ll_status ll_attn_split(int head_dim, int fp8, int heads, int rows, int kblocks,
     const AttnSplit s = attn_split(attn_variant_default(head_dim, fp8 ? KBLOCK8 : KBLOCK), heads, 1, &rows, &kblocks);
     *groups = s.groups;
     *splits = s.splits;
+    return LL_OK;
+}
+
+ll_status ll_attn_key_groups_fp8(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* groups) {
+    if (!rows || !kblocks || !groups) return fail(LL_ERR_INVALID_ARG, "null pointer");
+    const ll_status bad = check_launch(head_dim, heads, n_chunks, rows, kblocks);
+    if (bad != LL_OK) return bad;
+    const int variant = attn_variant_default(head_dim, KBLOCK8);
+    *groups = attn_takes_group8(variant, attn_split(variant, heads, n_chunks, rows, kblocks), heads, n_chunks, rows, kblocks) ? 4 : 1;
+    return LL_OK;
+}
+
+ll_status ll_attn_clip_tail(int head_dim, int heads, int n_chunks, const int* rows, const int* kblocks, int* tiles, int* splits) {
+    if (!rows || !kblocks || !tiles || !splits) return fail(LL_ERR_INVALID_ARG, "null pointer");
+    const ll_status bad = check_launch(head_dim, heads, n_chunks, rows, kblocks);
+    if (bad != LL_OK) return bad;
+    const int variant = attn_variant_lse(head_dim);
+    const AttnTail t = attn_tail(variant, attn_split(variant, heads, n_chunks, rows, kblocks), heads, n_chunks, rows, kblocks);
+    *tiles = t.tiles;
+    *splits = t.splits;
     return LL_OK;
 }
 

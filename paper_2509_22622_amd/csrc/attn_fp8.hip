@@ -995,7 +995,7 @@ __device__ __forceinline__ bool f8_split_share(const AttnParams& p, char* lds, i
 // the chip idle, a wave that has its SIMD for itself takes a step in two thirds of the time (rule: attn_split in attn_kernel.hip),
 // and every row keeps its bits.
 // Mode 7: tiles of 64 rows, their keys dealt to four groups of two waves (re-prefills in one round of workgroups; rule:
-// takes_group8 in attn_kernel.hip).  Mode 5 leaves half of a CU's SIMDs idle and the others to one wave each; us: 2990 rows in four
+// attn_takes_group8 in attn_kernel.hip).  Mode 5 leaves half of a CU's SIMDs idle and the others to one wave each; us: 2990 rows in four
 // chunks over 10 to 47 kblocks x 5 heads x 128 38 -> 27.  What bounds it: 64 KB a step from L2 to each CU, and 10 us around the steps.
 constexpr int f8_waves(int mode) { return mode == 5 ? 2 : mode == 4 || mode == 6 ? 4 : 8; }
 template <int D, int MODE>

@@ -462,15 +462,16 @@ AttnSplit attn_split(int variant, int H, int n_chunks, const int* rows, const in
     }
     return best;
 }
-// Whether a launch of the 8-bit cache that takes no splits has its tiles in 64 rows and their keys dealt to four groups of two waves
-// (attn_fp8.hip) instead of the narrow tiles that attn_split picks.  In one round of workgroups the longest share is a quarter of the
+// Whether a re-prefill launch of the 8-bit cache that takes no splits has its tiles in 64 rows and their keys dealt to four groups of
+// two waves (attn_fp8.hip) instead of the narrow tiles that attn_split picks.  In one round of workgroups the longest share is a quarter of the
 // longest key set, at two waves per SIMD instead of one; us a layer of a re-prefill, cache write included, without and with:
 // 10 frames of 299 tokens x 5 heads x 128 (250 tiles) 46.3 -> 35.2, x 64 40 -> 27, 13 of 190 x 4 x 128 38 -> 30, 10 of 96 x 3 x 128 23.5 ->
 // 22.5.  More tiles than CUs walk as many steps either way and read more of L2 (300 tiles 49 and 49, 450 52 and 56, 1200 96 and
 // 116), and six kblocks leave a share little to walk (17.6 and 18.7).  In long key sets most rows' references move on the way, and a share
 // does not know of those before it: its weights, no further from the exact ones, are rounded otherwise than the whole tile's (outputs
 // 1.8 % of the 2-norm apart at 47 kblocks, 3.0 % at 131, two separate roundings 3.7 %), so those keep their tiles.
-static bool takes_group8(int H, int n_chunks, const int* rows, const int* kblocks) {
+bool attn_takes_group8(int variant, AttnSplit split, int H, int n_chunks, const int* rows, const int* kblocks) {
+    if (split.splits > 1 || ll::variant(variant)->grouped[2] == nullptr) return false;
     int64_t tiles = 0;
     int longest = 0;
     for (int c = 0; c < n_chunks; ++c) {
@@ -484,11 +485,14 @@ static bool takes_group8(int H, int n_chunks, const int* rows, const int* kblock
 // and without, by the model above; it has to save 15 us.  us a clip's forward pass
 // (layout included): 21 frames of 1560 tokens x 12 heads x 128 (1596 tiles, 60 of them in a seventh round) 4085 -> 3637, 21 of 390 x 8
 // (280) 290 -> 218, 18 of 600 x 6 (270) 337 -> 244, 15 of 1560 x 4 (380) 1044 -> 886, 20 of 200 x 15 (300) 143 -> 125.
+// Only where all chunks are alike: a clip whose last chunk is shorter keeps the one launch (20 frames of 1560 x 12 x 128 in chunks of three
+// take 3994 us, 21 take 3672).
 // (equal key sets that begin at other places of their first kblocks differ by one or two)
 static bool same_length(int a, int b) { return std::abs(a - b) <= 2 && std::min(a, b) >= 16; }
-struct AttnTail { int tiles, splits; };
-static AttnTail attn_tail(const AttnVariant& v, int H, int n_chunks, const int* rows, const int* kblocks) {
+AttnTail attn_tail(int variant, AttnSplit split, int H, int n_chunks, const int* rows, const int* kblocks) {
+    const AttnVariant& v = *ll::variant(variant);
     constexpr int CUS = 256;
+    if (split.groups > 1 || split.splits > 1) return {0, 1};
     int tiles = 0;
     for (int c = 0; c < n_chunks; ++c) {
         if (!same_length(kblocks[c], kblocks[0])) return {0, 1};
@@ -572,7 +576,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
             const AttnSplit split = attn_split(variant, p.H, p.n_chunks, rows, kblocks);
             p.key_groups = split.groups;
             p.splits = split.splits;
-            const AttnTail tail = p.may_split_tail && split.groups == 1 && split.splits == 1 ? attn_tail(v, p.H, p.n_chunks, rows, kblocks) : AttnTail{0, 1};
+            const AttnTail tail = p.may_split_tail ? attn_tail(variant, split, p.H, p.n_chunks, rows, kblocks) : AttnTail{0, 1};
             if (tail.tiles > 0) {                // the last tiles of the last chunks in a launch of their own
                 AttnParams t = p, rest = p;
                 t.key_groups = rest.key_groups = 1;
@@ -593,7 +597,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
                 const hipError_t e = launch_attn(rest, variant, s);
                 return e != hipSuccess ? e : launch_attn(t, variant, s);
             }
-            if (p.may_group8 && v.grouped[2] != nullptr && split.splits == 1 && takes_group8(p.H, p.n_chunks, rows, kblocks)) p.key_groups = 8;
+            if (p.may_group8 && attn_takes_group8(variant, split, p.H, p.n_chunks, rows, kblocks)) p.key_groups = 8;
         }
     }
     int log_g = 0;

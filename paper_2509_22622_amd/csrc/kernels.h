@@ -315,7 +315,8 @@ struct AttnVariant {
     int threads;
     int kblock;                  // 32: bf16 cache, 64: 8-bit cache
     // The same work with the keys of a tile dealt to G = 2, 4, 8 groups of the workgroup's waves (qtile / G rows per
-    // workgroup); null where there is no such kernel.  8-bit cache: with 1 / G of the waves instead, which all walk all keys.
+    // workgroup); null where there is no such kernel.  8-bit cache: the first two have 1 / G of the waves instead, which all
+    // walk all keys; the third 64 rows, whose keys are dealt to four groups of two waves.
     void (*grouped[3])(const AttnParams);
     // The kernels of launches with AttnParams::splits > 1 and of their merges, by log2 of G (null: no splits)
     void (*split[4])(const AttnParams);
@@ -338,6 +339,11 @@ int attn_key_groups(int v, int H, int n_chunks, const int* rows, const int* kblo
 // the same where tiles may also be dealt to several workgroups: for one streamed chunk, or for a launch of several
 struct AttnSplit { int groups, splits; };
 AttnSplit attn_split(int v, int H, int n_chunks, const int* rows, const int* kblocks);
+// where that is `split`: whether an 8-bit re-prefill's tiles go to four key groups, and how many tiles a head of a clip's forward
+// pass go out in a launch of their own, with how many splits (0 and 1: none)
+bool attn_takes_group8(int v, AttnSplit split, int H, int n_chunks, const int* rows, const int* kblocks);
+struct AttnTail { int tiles, splits; };
+AttnTail attn_tail(int v, AttnSplit split, int H, int n_chunks, const int* rows, const int* kblocks);
 bool attn_variant_sink_shift(int v);          // the variant honours AttnChunk::sink_shift
 int attn_variant_lse(int D);                   // the variant that also writes AttnParams::lse
 int attn_variant_qscale(int D);                // the variant for queries not yet scaled (honours scale_log2e)

@@ -9,6 +9,8 @@ const char* attn_variant_name(int v) { return v >= 1 && v <= 4 ? "stub" : nullpt
 int attn_variant_default(int D, int kblock) { return (kblock == KBLOCK8 ? 2 : 0) + (D == 128 ? 1 : 2); }
 int attn_key_groups(int, int, int, const int*, const int*) { return 1; }
 AttnSplit attn_split(int, int, int, const int*, const int*) { return {1, 1}; }
+bool attn_takes_group8(int, AttnSplit, int, int, const int*, const int*) { return false; }
+AttnTail attn_tail(int, AttnSplit, int, int, const int*, const int*) { return {0, 1}; }
 struct SplitPool;
 hipError_t split_pool_address(SplitPool**) { return hipErrorNoDevice; }
 bool attn_variant_supports(int v, int D, int kblock) { return v == attn_variant_default(D, kblock); }

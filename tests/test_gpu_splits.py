@@ -389,19 +389,23 @@ def test_re_prefill_beside_streaming_of_chunks_that_split(kv_format, heads, head
     assert _rel(got, want.double()) <= (1e-2 if kv_format == "bf16" else 3e-2)
 
 
-@pytest.mark.parametrize("heads, head_dim, grid, chunk, clip_frames", [
-    (8, 128, (15, 26), 3, 21),       # 280 tiles: the last three of every head's last chunk
-    (15, 128, (10, 20), 1, 20),      # 300 tiles, one a chunk: three whole chunks
-    (9, 128, (15, 26), 2, 15),       # 270 tiles, a last chunk of two: that one and a tile of the next
-    (15, 64, (15, 26), 3, 21)])      # 525 tiles, one a head
-def test_clip_whose_last_round_is_split(heads, head_dim, grid, chunk, clip_frames):
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, clip_frames, tail", [
+    (8, 128, (15, 26), 3, 21, (3, 10)),       # 280 tiles: three of the five of every head's first chunk
+    (15, 128, (10, 20), 1, 20, (3, 5)),       # 300 tiles, one a chunk: the first three chunks
+    (5, 128, (15, 26), 2, 28, (5, 8)),        # 280 tiles, four a chunk: the first chunk and a tile of the next
+    (9, 128, (15, 26), 2, 15, (0, 1)),        # 270 tiles, but the last chunk is a frame shorter: one launch
+    (15, 64, (15, 26), 3, 21, (1, 11))])      # 525 tiles, one a head
+def test_clip_whose_last_round_is_split(heads, head_dim, grid, chunk, clip_frames, tail):
     """The tiles of a clip's forward pass that do not fill a round of workgroups have their keys dealt to several: output and, by
     way of the row sums, gradients against 64 bits (test_gpu_clip.py: 5e-3 each); with slots taken the same bits."""
     case = {"kind": "clip", "heads": heads, "head_dim": head_dim, "grid_h": grid[0], "grid_w": grid[1], "chunk": chunk, "sink": 3,
             "window": 9, "ctx_start": 40, "n_ctx": 9, "clip_frames": clip_frames, "q_std": 1.0}
-    rows = grid[0] * grid[1]
-    tiles = sum(-(-min(chunk, clip_frames - f) * rows // 256) for f in range(0, clip_frames, chunk)) * heads
-    assert tiles > 256 and 0 < tiles % 256 <= 64
+    rows, n_chunks = grid[0] * grid[1], -(-clip_frames // chunk)
+    index = B.Clip(heads, head_dim, *grid, chunk, 3, 9, clip_frames, device=None)
+    index.forward(40, 9, clip_frames)
+    kblocks = [sum(-(-end // 32) - begin // 32 for begin, end in index.chunk_key_ranges(c)) for c in range(n_chunks)]
+    assert n_chunks <= 24 and B.attn_clip_tail(head_dim, heads, [(min(chunk, clip_frames - c * chunk) * rows, kblocks[c])
+                                                                 for c in reversed(range(n_chunks))]) == tail
     state = cases.prepare(case, 3)
     got = [x.clone() for x in cases.run(state)]
     torch.cuda.synchronize()
