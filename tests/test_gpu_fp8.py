@@ -426,23 +426,27 @@ def test_thirty_layer_loop_fp8():
     cache.close()
 
 
-@pytest.mark.parametrize("heads, head_dim, grid, chunk, sink, window, n_win", [
-    (5, 128, (13, 23), 3, 2, 7, 8),       # 250 tiles of 64 rows, ragged
-    (4, 128, (10, 19), 1, 3, 9, 10),      # single-frame chunks of two to 39 kblocks
-    (3, 128, (1, 97), 1, 1, 16, 12),      # two kblocks at first: groups without keys; one row in a second 32-row block
-    (1, 128, (5, 10), 1, 1, 40, 30),      # one kblock at first; two launches
-    (5, 64, (13, 23), 3, 2, 7, 8),
-    (1, 64, (5, 13), 1, 1, 30, 20),       # tiles of one row
-    (4, 64, (13, 15), 2, 3, 9, 10)])
+@pytest.mark.parametrize("heads, head_dim, grid, chunk, sink, window, n_win, groups", [
+    (5, 128, (13, 23), 3, 2, 7, 8, [4]),       # 250 tiles of 64 rows, ragged
+    (4, 128, (10, 19), 1, 3, 9, 10, [4]),      # single-frame chunks of three to 39 kblocks
+    (3, 128, (1, 97), 1, 1, 16, 12, [4]),      # two kblocks at first: groups without keys; one row in a second 32-row block
+    (1, 128, (5, 10), 1, 1, 40, 20, [4]),      # one kblock at first: three groups without keys
+    (1, 128, (5, 10), 1, 1, 40, 30, [4, 1]),   # two launches, the second of six kblocks and less, which is not dealt out
+    (5, 64, (13, 23), 3, 2, 7, 8, [4]),
+    (1, 64, (5, 13), 1, 1, 30, 20, [4]),       # tiles of one row
+    (1, 64, (5, 12), 1, 1, 30, 20, [4]),       # one kblock at first
+    (4, 64, (13, 15), 2, 3, 9, 10, [4])])
 @pytest.mark.parametrize("q_std", [1.0, 6.0])
-def test_re_prefill_in_key_groups(heads, head_dim, grid, chunk, sink, window, n_win, q_std):
+def test_re_prefill_in_key_groups(heads, head_dim, grid, chunk, sink, window, n_win, groups, q_std):
     """Re-prefills whose chunks would all split when streamed and which fit the chip in one round of 64-row tiles: a tile's keys
     are dealt to four groups of its waves.  Unequal and empty shares, waves without rows, references far apart (q_std 6)."""
     P = grid[0] * grid[1]
     split = lambda frames: B.attn_split(head_dim, heads, frames * P, -(-(sink + window + frames) * P // 64), "fp8_e4m3")[1]
-    lengths = {min(chunk, end - f) for lo, end in ((0, sink), (sink, sink + n_win)) for f in range(lo, end, chunk)}
-    tiles = sum(-(-min(chunk, end - f) * P // 64) * heads for lo, end in ((0, sink), (sink, sink + n_win)) for f in range(lo, end, chunk))
-    assert tiles <= 256 and all(split(n) > 1 for n in lengths)
+    chunks = [(min(chunk, end - f), min(f, sink) + min(chunk, end - f) + min(max(f - sink, 0), window))          # frames, those they see
+              for lo, end in ((0, sink), (sink, sink + n_win)) for f in range(lo, end, chunk)]
+    work = sorted(((n * P, -(-seen * P // 64)) for n, seen in chunks), key=lambda c: -c[1])                      # the longest key sets first
+    assert all(split(n) > 1 for n, _ in chunks)
+    assert [B.attn_key_groups_fp8(head_dim, heads, work[i:i + 24]) for i in range(0, len(work), 24)] == groups   # a launch holds 24 chunks
     case = {"kind": "prefill", "cache": "fp8_e4m3", "layers": 1, "heads": heads, "head_dim": head_dim, "grid_h": grid[0],
             "grid_w": grid[1], "chunk": chunk, "sink": sink, "window": window, "win_start": sink + 20, "n_win": n_win, "q_std": q_std}
     state = cases.prepare(case, 3)
@@ -450,8 +454,10 @@ def test_re_prefill_in_key_groups(heads, head_dim, grid, chunk, sink, window, n_
     torch.cuda.synchronize()
     want = cases.exact(case, 3)[0]
     err = (out.double() - want).abs()
-    # one weight's rounding at most 2^-4, and 2.6 % rms over independent values; logits of standard deviation 6 leave nothing to average
-    assert bool(torch.isfinite(out).all()) and float(err.norm() / want.norm()) <= (REL_L2_TOL_FP8 if q_std == 1.0 else 2.0 ** -4)
+    # A weight's rounding, 2.6 % rms for values spread evenly over their binades, is independent from key to key, and so are the
+    # values: it comes through to the output, less of it where few keys hold the weight, since the row sum has it too (one key: none).
+    # No more than whole tiles gave over such shapes: 2.3 to 2.7 % at logits of standard deviation 1, 0.8 to 1.2 % at 6.
+    assert bool(torch.isfinite(out).all()) and float(err.norm() / want.norm()) <= (3e-2 if q_std == 1.0 else 1.2e-2)
     again = cases.run(state)[0]
     assert torch.equal(again.view(torch.int16), out.view(torch.int16))
     state["cache"].close()
