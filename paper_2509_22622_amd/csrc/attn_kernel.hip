@@ -483,10 +483,10 @@ bool attn_takes_group8(int variant, AttnSplit split, int H, int n_chunks, const 
 // A launch of whole-key tiles of one length that fills some rounds of workgroups and a small part of one more: the tiles per head to
 // take out of it and how many splits a launch of their own deals their keys to (0 tiles: none).  What that last round takes with
 // and without, by the model above; it has to save 15 us.  us a clip's forward pass
-// (layout included): 21 frames of 1560 tokens x 12 heads x 128 (1596 tiles, 60 of them in a seventh round) 4085 -> 3637, 21 of 390 x 8
-// (280) 290 -> 218, 18 of 600 x 6 (270) 337 -> 244, 15 of 1560 x 4 (380) 1044 -> 886, 20 of 200 x 15 (300) 143 -> 125.
+// (layout included): 21 frames of 1560 tokens x 12 heads x 128 (1596 tiles, 60 of them in a seventh round) 3996 -> 3517, 21 of 390 x 8
+// (280) 289 -> 219, 18 of 600 x 6 (270) 407 -> 294, 15 of 1560 x 4 (380) 996 -> 873, 20 of 200 x 15 (300) 163 -> 147.
 // Only where all chunks are alike: a clip whose last chunk is shorter keeps the one launch (20 frames of 1560 x 12 x 128 in chunks of three
-// take 3994 us, 21 take 3672).
+// take 3750 to 3950 us).
 // (equal key sets that begin at other places of their first kblocks differ by one or two)
 static bool same_length(int a, int b) { return std::abs(a - b) <= 2 && std::min(a, b) >= 16; }
 AttnTail attn_tail(int variant, AttnSplit split, int H, int n_chunks, const int* rows, const int* kblocks) {
@@ -630,7 +630,7 @@ hipError_t launch_attn(const AttnParams& p_in, int variant, hipStream_t s) {
     p.n_groups = 0;
     const int groups = p.H * p.n_chunks;
     // (every kernel but the simple ones reads the placement; a launch of one round, or of tiles of one length, is better dealt out
-    // evenly: whole groups can give one XCD more tiles than the others; 500 tiles of a clip of 15 x 390 rows x 20 x 64 283 us -> 208)
+    // evenly: whole groups can give one XCD more tiles than the others; 500 tiles of a clip of 15 x 390 rows x 20 x 64 289 us -> 222)
     bool one_length = true;
     for (int c = 1; c < p.n_chunks; ++c) one_length = one_length && same_length(p.chunk[c].n_kblocks, p.chunk[0].n_kblocks);
     if (variant > kNumSimple && p.splits == 1 && p.n_chunks > 1 && !one_length && total > 256 && groups >= 16 && groups <= MAX_XCD_GROUPS) {

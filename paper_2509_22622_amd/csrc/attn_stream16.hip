@@ -162,7 +162,7 @@ using S16NextShare = S16Barrier<1>;
 // `touch` (GroupRing::TOUCHES in lds_plan.h): the periods whose kblocks this tile brings into L2.
 // Where the key set has S16_TOUCH_BYTES and more: a few layers of it do not fit the 256 MB of the last-level cache, so it comes from
 // memory.  us a call with the keys of many layers in turn, without and with: 1170 rows x 183 kblocks x 12 heads x 128 (36 MB)
-// 70 -> 52, x 293 107 -> 78, 800 x 125 x 16 51 -> 39; a key set that is in that cache 50.8 and 49.8.
+// 70 -> 52, x 293 107 -> 78, 800 x 125 x 16 51 -> 39; a key set that is in that cache (four layers' just written) 50.8 and 49.8.
 constexpr int S16_TOUCH_BYTES = 16 << 20;
 struct S16Touch { int every = 0, first = 0; };                   // (0: none)
 // The tiles of a head walk the same keys, more or less in step; those on one XCD take turns.  total: workgroups of a

@@ -249,9 +249,9 @@ static double tile_us(const OutProjParams& p, double launch, double around, doub
 // What a step of 256 x 128 costs: 128 KB of fragment reads and 48 KB of ring writes through LDS (1400 clocks) beside 1024 clocks
 // of MFMAs.  With each k-step's reads in front of its own MFMAs they added up: 32 us at 4680 rows; read a k-step ahead, by
 // hand, 28 (4680 x 3072 104 -> 92, 23400 x 1536 141 -> 128, 2400 x 2432 43 -> 37).
-// With the loads dealt out between the MFMAs instead of six in a row behind the barrier: 4680 x 3072 with the attention in front of it
-// 106 -> 100.6, 9000 x 1536 64.3 -> 62.1.  What bounds it now is L2: 228 tiles x 24 steps x 48 KB at 12.8 TB/s; four waves of 128 x 64,
-// which read two thirds as much of LDS, take the same time.
+// With the loads dealt out between the MFMAs instead of six in a row behind the barrier, with the attention in front of it: 4680 x 3072
+// 128.7 -> 125.6, 4680 x 1536 35.5 -> 34.5 (16 tokens) and 47.2 -> 46.5 (512).  What bounds it now is L2: 228 tiles x 24 steps x 48 KB at
+// 12.8 TB/s while the steps run, 10.9 over a call; four waves of 128 x 64, which read two thirds as much of LDS, take the same time.
 hipError_t launch_out_proj(const OutProjParams& p, hipStream_t s) {
     if (p.M < 1 || p.N < 16 || p.N % 16 != 0 || p.K < 64 || p.K % 64 != 0) return hipErrorInvalidValue;   // K = H * D, D 64 or 128
     const double t0 = tile_us<OpTile256x128>(p, 2.3, 3.85, 0.626, 0.257), t1 = tile_us<OpTile128x128>(p, 2.0, 2.36, 0.367, 0.136);
