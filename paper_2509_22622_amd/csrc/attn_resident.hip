@@ -11,8 +11,8 @@
 // 226 tokens x 23400 rows x 12 x 128 75 -> 55 (16 tokens, all memory: 47 -> 36, 4.0 TB/s), x 24 heads 137 -> 101;
 // 1200 rows x 77 tokens x 24 x 64 10 -> 7.  Rows that went to memory in the lanes' own order (64-byte loads, 32-byte stores) took
 // 46 us at 16 tokens.  The fragments' reads were then left to the compiler, which put each in front of its MFMAs
-// (no room for more beside the next queries), and the matrix work did not hide under the memory's; by hand, in turn on one box (where
-// boxes differ by 8 %): 226 tokens x 23400 x 12 x 128 48.0 -> 47.1, 20000 x 400 x 12 x 64 39.6 -> 37.8, 9000 x 500 x 6 x 64 15.4 -> 14.8.
+// (no room for more beside the next queries), and the matrix work did not hide under the memory's; by hand, in turn on one card (they
+// differ by 8 %): 226 tokens x 23400 x 12 x 128 48.0 -> 47.1, 20000 x 400 x 12 x 64 39.6 -> 37.8, 9000 x 500 x 6 x 64 15.4 -> 14.8.
 #include "kernels.h"
 
 #include <algorithm>

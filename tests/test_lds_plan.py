@@ -8,7 +8,7 @@ kernels compile in).  Host programs replay those plans:
   check_group_ring.cpp the same for the rings of key groups (GroupRing), with waves that have no rows, groups that have
                        no keys, and the number of barriers every wave meets;
   check_fp8_group_ring.cpp that of the 8-bit kernel's key groups (Fp8GroupRing), prologue and all.
-The ring checkers are also run on copies of the plan with one constant changed, where they must report a violation."""
+The ring simulations are also run on copies of the plan with one constant changed, where they must report a violation."""
 import os
 import re
 import shutil
